@@ -4,7 +4,8 @@
 // read once and written once (8 bytes per element per peer) although each output has three inputs.
 // Low precision: one workgroup owns one chunk of all k peers.  The per-peer difference is
 // quantised, the public copies xhat are advanced and the three-neighbour mix is formed while x and
-// the new xhat of every peer are still in registers: 17 bytes per element per peer, one pass.
+// the new xhat of every peer are still in registers: 17 bytes per element per peer, one pass, for any
+// number of peers and any chunk length.
 #include "launchers.hpp"
 #include "minmax_device.hpp"
 
@@ -67,8 +68,12 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 // Workgroup = one chunk of all K peers; wave w holds rows [w*RPW, (w+1)*RPW) of every peer.
 // Peers are processed in order; peer p's output is formed as soon as the new public copies of
 // p-1, p, p+1 exist, so only a short window of peers is live in registers at any time.
+// Bound by the memory system's rate for 5 K interleaved streams.  Unrolled over the peers (the compiler moves the
+// next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows: 108 VGPRs, no spill at 1024 threads.
+// 16 peers x 25.6 M elements, C = 8192: 1.33 ms (5.28 TB/s); encode per peer + a mixing pass over the public copies,
+// 25 bytes per element per peer, took 1.81 ms.
 template <int K, int RPW>
-__global__ void __launch_bounds__(64 * ((16 + RPW - 1) / RPW))
+__global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n,
               uint32_t chunk, float third)
 {
@@ -139,11 +144,113 @@ k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable code
     if (K > 1) finalize(0);
 }
 
-// ------------------------------------------------------------------------------------------ LP, two-pass fallback
-// Pass 1 (per peer): d = x - xhat; codes, minmax = Q(d); xhat <- xhat + decode.
+// ------------------------------------------------------------------------------------------ LP, any number of peers
+// One peer's rows of a chunk: x and the public copy, as they are before the round.
+template <int RPW>
+__device__ __forceinline__ void lp_load(const float* x_c, const float* hat_c, int len, int wave, int lane, f4 (&x)[RPW], f4 (&h)[RPW])
+{
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const int off = static_cast<int>(wave * RPW + r) * kRow;
+        const int remain = len - off;
+        x[r] = f4{0.f, 0.f, 0.f, 0.f};
+        h[r] = f4{0.f, 0.f, 0.f, 0.f};
+        if (remain > 0) {
+            x[r] = load_row(x_c + off, lane, remain, 0.0f);
+            h[r] = load_row(hat_c + off, lane, remain, 0.0f);
+        }
+    }
+}
+
+// Publish Q(x - h) of the rows just loaded and advance the public copy.  On return h = the new public copy (also
+// stored), x = x - h, what the peer adds to the mix.  One barrier.
+template <int RPW>
+__device__ __forceinline__ void lp_publish(f4 (&x)[RPW], f4 (&h)[RPW], float* hat_c, uint8_t* codes_c, float* minmax_c, int len,
+                                           int wave, int lane, int nwaves, float* s_red)
+{
+    f4 d[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) d[r] = sub4(x[r], h[r]);
+    minmax_encode_chunk<RPW, false, false, true>(d, len, wave, lane, nwaves, nullptr, codes_c, minmax_c, nullptr, s_red);
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const int off = static_cast<int>(wave * RPW + r) * kRow;
+        const int remain = len - off;
+        h[r] = add4(h[r], d[r]);
+        x[r] = sub4(x[r], h[r]);
+        if (remain > 0) store_row(hat_c + off, lane, remain, h[r]);
+    }
+}
+
+template <int RPW>
+__device__ __forceinline__ void copy_rows(f4 (&to)[RPW], const f4 (&from)[RPW])
+{
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) to[r] = from[r];
+}
+
+template <int RPW>
+__device__ __forceinline__ void ring_mix(const f4 (&left)[RPW], const f4 (&mid)[RPW], const f4 (&right)[RPW], const f4 (&own)[RPW],
+                                         float third, float* out_c, int len, int wave, int lane)
+{
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const int off = static_cast<int>(wave * RPW + r) * kRow;
+        const int remain = len - off;
+        const f4 s = add4(add4(left[r], mid[r]), right[r]);
+        if (remain > 0) store_row(out_c + off, lane, remain, add4(mul4(s, third), own[r]));
+    }
+}
+
+// The same with the peers in a loop, for what the unrolled kernel cannot hold: the first peer's new copy is not kept
+// for the wrap-around but read again at the end (12 bytes per element of a round, mostly from cache), which keeps four
+// rows per wave within 128 VGPRs.  8 peers x 25.6 M elements, C = 16384: 0.71 ms against 0.98 ms in two passes.  Up to
+// 32 rows it is 1-10 % slower than the unrolled kernel (8 peers x 109 M: 3.03 against 2.84 ms).  Requesting the next
+// peer's rows ahead was slower in every launch of more than one workgroup per CU.
 template <int RPW>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_lp_encode(const float* __restrict__ x, float* __restrict__ xhat, size_t n, uint32_t chunk,
+k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
+                  uint32_t chunk, float third)
+{
+    __shared__ float s_red[2][2 * kMaxWaves];
+    const size_t c = blockIdx.x;
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+    auto x_of = [&](int i) { return static_cast<const float*>(xin.p[i]) + base; };
+    auto hat_of = [&](int i) { return static_cast<float*>(xhat.p[i]) + base; };
+    auto out_of = [&](int i) { return static_cast<float*>(xout.p[i]) + base; };
+
+    f4 left[RPW], mid[RPW], own[RPW];   // public copies of peers i - 2 and i - 1, and what the latter adds to its mix
+    f4 x[RPW], h[RPW];
+    for (int i = 0; i < k; ++i) {
+        lp_load<RPW>(x_of(i), hat_of(i), len, wave, lane, x, h);
+        lp_publish<RPW>(x, h, hat_of(i), static_cast<uint8_t*>(codes.p[i]) + base, static_cast<float*>(minmax.p[i]) + 2 * c, len,
+                        wave, lane, nwaves, s_red[i & 1]);
+        if (i >= 2) ring_mix<RPW>(left, mid, h, own, third, out_of(i - 1), len, wave, lane);
+        copy_rows<RPW>(left, mid);
+        copy_rows<RPW>(mid, h);
+        copy_rows<RPW>(own, x);
+    }
+    // the wrap-around: peers k - 1 and 0 need the new copies of peers 0 and 1 again, which this lane has stored
+    if (k == 1) {
+        ring_mix<RPW>(mid, mid, mid, own, third, out_of(0), len, wave, lane);
+        return;
+    }
+    f4 right[RPW];
+    lp_load<RPW>(x_of(0), hat_of(0), len, wave, lane, x, h);
+    lp_load<RPW>(hat_of(1), hat_of(1), len, wave, lane, right, right);
+    ring_mix<RPW>(left, mid, h, own, third, out_of(k - 1), len, wave, lane);
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) x[r] = sub4(x[r], h[r]);
+    ring_mix<RPW>(mid, h, right, x, third, out_of(0), len, wave, lane);
+}
+
+// ------------------------------------------------------------------------------------------ LP, one peer
+// d = x - xhat; codes, minmax = Q(d); xhat <- xhat + decode.
+template <int RPW>
+__global__ void __launch_bounds__(wg_threads_max(RPW))
+k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, uint32_t chunk,
             uint8_t* __restrict__ codes, float* __restrict__ minmax)
 {
     __shared__ float s_red[2 * kMaxWaves];
@@ -151,48 +258,9 @@ k_lp_encode(const float* __restrict__ x, float* __restrict__ xhat, size_t n, uin
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-    f4 h[RPW], d[RPW];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-        const int off = static_cast<int>(wave * RPW + r) * kRow;
-        const int remain = len - off;
-        h[r] = f4{0.f, 0.f, 0.f, 0.f};
-        d[r] = h[r];
-        if (remain > 0) {
-            h[r] = load_row(xhat + base + off, lane, remain, 0.0f);
-            d[r] = sub4(load_row(x + base + off, lane, remain, 0.0f), h[r]);
-        }
-    }
-    minmax_encode_chunk<RPW, false, false, true>(d, len, wave, lane, nwaves, nullptr, codes + base,
-                                                 minmax + 2 * c, nullptr, s_red);
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-        const int off = static_cast<int>(wave * RPW + r) * kRow;
-        const int remain = len - off;
-        if (remain > 0) store_row(xhat + base + off, lane, remain, add4(h[r], d[r]));
-    }
-}
-
-// Pass 2: x_out[i] = ((xhat[i-1] + xhat[i]) + xhat[i+1]) * third + (x[i] - xhat[i]), rolling over peers.
-__global__ void __launch_bounds__(kWave * kRowWaves)
-k_lp_mix(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, int k, size_t n, float third)
-{
-    const size_t row = static_cast<size_t>(blockIdx.x) * kRowWaves + wave_index();
-    const int lane = threadIdx.x & 63;
-    const size_t e0 = row * kRow;
-    if (e0 >= n) return;
-    const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
-    const f4 first = load_row(static_cast<const float*>(xhat.p[0]) + e0, lane, remain, 0.0f);
-    f4 prev = load_row(static_cast<const float*>(xhat.p[k - 1]) + e0, lane, remain, 0.0f);
-    f4 cur = first;
-    for (int i = 0; i < k; ++i) {
-        const f4 next = (i + 1 < k) ? load_row(static_cast<const float*>(xhat.p[i + 1]) + e0, lane, remain, 0.0f) : first;
-        const f4 xi = load_row(static_cast<const float*>(xin.p[i]) + e0, lane, remain, 0.0f);
-        const f4 s = add4(add4(prev, cur), next);
-        store_row(static_cast<float*>(xout.p[i]) + e0, lane, remain, add4(mul4(s, third), sub4(xi, cur)));
-        prev = cur;
-        cur = next;
-    }
+    f4 x[RPW], h[RPW];
+    lp_load<RPW>(x_in + base, xhat + base, len, wave, lane, x, h);
+    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red);
 }
 
 // ------------------------------------------------------------------------------------------ host
@@ -250,27 +318,20 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
     const float third = 1.0f / 3.0f;
     const size_t nc = num_chunks(n, chunk);
     const int rows = static_cast<int>(chunk / kRow);
-    if (k <= 8 && rows <= 16) {
-        dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + BAGUA_RPW_LP - 1) / BAGUA_RPW_LP));
-        const uint32_t ch = static_cast<uint32_t>(chunk);
+    const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
+    dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
+    const uint32_t ch = static_cast<uint32_t>(chunk);
+    if (rpw == BAGUA_RPW_LP) {   // at most kMaxWaves waves of that many rows
         switch (k) {
-#define BAGUA_LP_CASE(K) case K: launch_lp_k<K>(in, out, hat, cd, mm, n, ch, third, grid, block, stream); break;
+#define BAGUA_LP_CASE(K) case K: launch_lp_k<K>(in, out, hat, cd, mm, n, ch, third, grid, block, stream); return launch_status();
             BAGUA_LP_CASE(1) BAGUA_LP_CASE(2) BAGUA_LP_CASE(3) BAGUA_LP_CASE(4) BAGUA_LP_CASE(5) BAGUA_LP_CASE(6)
-            BAGUA_LP_CASE(7) BAGUA_LP_CASE(8)
+            BAGUA_LP_CASE(7) BAGUA_LP_CASE(8) BAGUA_LP_CASE(9) BAGUA_LP_CASE(10) BAGUA_LP_CASE(11) BAGUA_LP_CASE(12)
+            BAGUA_LP_CASE(13) BAGUA_LP_CASE(14) BAGUA_LP_CASE(15) BAGUA_LP_CASE(16)
 #undef BAGUA_LP_CASE
         }
-        return launch_status();
     }
-    // larger k or chunk: the chunk of all peers does not fit one workgroup's registers
-    const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
-    dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
-    for (int i = 0; i < k; ++i) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, stream, x_in[i], xhat[i], n,
-                                                   static_cast<uint32_t>(chunk), codes[i], minmax[i]))
-    }
-    const size_t nrows = (n + kRow - 1) / kRow;
-    hipLaunchKernelGGL(k_lp_mix, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves)), dim3(kWave * kRowWaves), 0, stream, in, out, hat, k, n,
-                       third);
+    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
+                                               third))
     return launch_status();
 }
 
@@ -437,20 +498,23 @@ extern "C" int bagua_centralized_avg_fp(const float* const* x, int k, size_t n, 
 // D_LP_S with one chosen peer per worker (Sections 3.2 and 3.4): every worker publishes Q(x - xhat),
 // all holders advance xhat, then x_out[i] = (xhat[i] + xhat[peer[i]]) * 0.5 + (x[i] - xhat[i]).
 // A matched pair is one fused job: a workgroup owns one chunk of both partners, so x and xhat of
-// each are read once and out, xhat, codes written once (17 bytes per element per peer).  Any other
-// peer map takes two passes: k_lp_encode per worker, then a mix over the advanced public copies.
+// each are read once and out, xhat, codes written once (17 bytes per element per peer).  A worker
+// that is its own peer (the odd one out of a random matching) is a job with one side.  Only a worker
+// whose peer chose somebody else takes two passes: k_lp_encode, then a mix over the advanced public copies.
 namespace bagua {
 
 struct PeerLpJobs {
-    const float* x[2][BAGUA_MAX_WORKERS / 2];
-    float* out[2][BAGUA_MAX_WORKERS / 2];
-    float* hat[2][BAGUA_MAX_WORKERS / 2];
-    uint8_t* codes[2][BAGUA_MAX_WORKERS / 2];
-    float* minmax[2][BAGUA_MAX_WORKERS / 2];
+    const float* x[2][BAGUA_MAX_WORKERS];   // side 1 is unused where a worker is its own peer
+    float* out[2][BAGUA_MAX_WORKERS];
+    float* hat[2][BAGUA_MAX_WORKERS];
+    uint8_t* codes[2][BAGUA_MAX_WORKERS];
+    float* minmax[2][BAGUA_MAX_WORKERS];
 };
 
-template <int RPW>
-__global__ void __launch_bounds__(64 * ((16 + RPW - 1) / RPW))
+// Job after job over blockIdx.y, so that only one pair's ten streams are interleaved.  7 workers x 25.6 M elements
+// (three pairs and a single), C = 4096: 0.53 ms; encode + mix in two passes 0.83 ms.
+template <int RPW, bool PAIR>
+__global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)   // two rows per wave fit 64 VGPRs: full occupancy
 k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
@@ -461,47 +525,24 @@ k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk)
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
     f4 h[2][RPW], own[2][RPW];
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd) {
-        const float* __restrict__ xp = jobs.x[sd][job];
-        float* __restrict__ hp = jobs.hat[sd][job];
-        f4 x[RPW], d[RPW];
-        float mn, mx;
-#pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-            const int off = static_cast<int>(wave * RPW + r) * kRow;
-            const int remain = len - off;
-            x[r] = f4{0.f, 0.f, 0.f, 0.f};
-            h[sd][r] = x[r];
-            if (remain > 0) {
-                x[r] = load_row(xp + base + off, lane, remain, 0.0f);
-                h[sd][r] = load_row(hp + base + off, lane, remain, 0.0f);
-            }
-            d[r] = sub4(x[r], h[sd][r]);
-        }
-        chunk_minmax_partial<RPW>(d, len, wave, lane, nwaves, s_red[sd], mn, mx);
-        if (nwaves > 1) __syncthreads();
-        chunk_minmax_finish(nwaves, s_red[sd], mn, mx);
-        minmax_quantise_chunk<RPW, false, false, true>(d, mn, mx, len, wave, lane, nullptr, jobs.codes[sd][job] + base,
-                                                       jobs.minmax[sd][job] + 2 * c, nullptr);
+    auto publish = [&](int sd) {
+        lp_load<RPW>(jobs.x[sd][job] + base, jobs.hat[sd][job] + base, len, wave, lane, own[sd], h[sd]);
+        lp_publish<RPW>(own[sd], h[sd], jobs.hat[sd][job] + base, jobs.codes[sd][job] + base, jobs.minmax[sd][job] + 2 * c, len,
+                        wave, lane, nwaves, s_red[sd]);
+    };
+    auto mix = [&](int sd, int second) {   // the sum of a pair is the same one for both sides
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
             const int off = static_cast<int>(wave * RPW + r) * kRow;
             const int remain = len - off;
-            h[sd][r] = add4(h[sd][r], d[r]);
-            own[sd][r] = sub4(x[r], h[sd][r]);
-            if (remain > 0) store_row(hp + base + off, lane, remain, h[sd][r]);
+            const f4 avg = mul4(add4(h[0][r], h[second][r]), 0.5f);
+            if (remain > 0) store_row(jobs.out[sd][job] + base + off, lane, remain, add4(avg, own[sd][r]));
         }
-    }
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-        const int off = static_cast<int>(wave * RPW + r) * kRow;
-        const int remain = len - off;
-        if (remain <= 0) continue;
-        const f4 avg = mul4(add4(h[0][r], h[1][r]), 0.5f);
-        store_row(jobs.out[0][job] + base + off, lane, remain, add4(avg, own[0][r]));
-        store_row(jobs.out[1][job] + base + off, lane, remain, add4(avg, own[1][r]));
-    }
+    };
+    publish(0);
+    if (PAIR) publish(1);
+    mix(0, PAIR ? 1 : 0);
+    if (PAIR) mix(1, 1);
 }
 
 // Second pass of the general case: worker i = blockIdx.y reads the advanced xhat of itself and of its peer.
@@ -562,42 +603,45 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
     const int rows = static_cast<int>(chunk / kRow);
     const uint32_t ch = static_cast<uint32_t>(chunk);
 
-    bool matching = true;  // every worker is in a pair with a distinct partner
-    for (int i = 0; i < k; ++i) matching = matching && peer[i] != i && peer[peer[i]] == i;
-    if (matching && rows <= 16) {
-        PeerLpJobs jobs{};
-        int nj = 0;
-        for (int i = 0; i < k; ++i) {
-            const int p = peer[i];
-            if (p < i) continue;
-            const int side[2] = {i, p};
-            for (int sd = 0; sd < 2; ++sd) {
-                jobs.x[sd][nj] = x_in[side[sd]];
-                jobs.out[sd][nj] = x_out[side[sd]];
-                jobs.hat[sd][nj] = xhat[side[sd]];
-                jobs.codes[sd][nj] = codes[side[sd]];
-                jobs.minmax[sd][nj] = minmax[side[sd]];
-            }
-            ++nj;
-        }
-        dim3 grid(static_cast<unsigned>(nc), nj), block(64 * ((rows + BAGUA_RPW_LP - 1) / BAGUA_RPW_LP));
-        hipLaunchKernelGGL((k_peer_avg_lp<BAGUA_RPW_LP>), grid, block, 0, s, jobs, n, ch);
-        return launch_status();
-    }
-    const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
+    const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
-    for (int i = 0; i < k; ++i) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, s, x_in[i], xhat[i], n, ch,
-                                                   codes[i], minmax[i]))
-    }
+    // matched pairs and workers that are their own peer: one pass
+    PeerLpJobs pairs{}, singles{};
     PeerMixJobs mix{};
+    int npairs = 0, nsingles = 0, nmix = 0;
     for (int i = 0; i < k; ++i) {
-        mix.x[i] = x_in[i];
-        mix.hat_own[i] = xhat[i];
-        mix.hat_peer[i] = xhat[peer[i]];
-        mix.out[i] = x_out[i];
+        const int p = peer[i];
+        if (peer[p] != i) {                             // chosen by nobody it chose: two passes
+            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, s, x_in[i], xhat[i], n, ch, codes[i],
+                                                       minmax[i]))
+            mix.x[nmix] = x_in[i];
+            mix.hat_own[nmix] = xhat[i];
+            mix.hat_peer[nmix] = xhat[p];
+            mix.out[nmix] = x_out[i];
+            ++nmix;
+        } else if (p >= i) {
+            PeerLpJobs& jobs = p == i ? singles : pairs;
+            const int j = p == i ? nsingles++ : npairs++;
+            const int side[2] = {i, p};
+            for (int sd = 0; sd < (p == i ? 1 : 2); ++sd) {
+                jobs.x[sd][j] = x_in[side[sd]];
+                jobs.out[sd][j] = x_out[side[sd]];
+                jobs.hat[sd][j] = xhat[side[sd]];
+                jobs.codes[sd][j] = codes[side[sd]];
+                jobs.minmax[sd][j] = minmax[side[sd]];
+            }
+        }
     }
-    hipLaunchKernelGGL(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), k), dim3(kWave * kRowWaves), 0, s, mix, n);
+    if (npairs) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, 0, s, pairs, n, ch))
+    }
+    if (nsingles) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch))
+    }
+    if (nmix) {                                         // all public copies are advanced by now
+        hipLaunchKernelGGL(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), nmix),
+                           dim3(kWave * kRowWaves), 0, s, mix, n);
+    }
     return launch_status();
 }
 

@@ -76,8 +76,8 @@ def _matching(r, k):
                                     (1, [0]), (4, [0, 0, 0, 0]), (5, [1, 2, 3, 4, 0]), (7, [1, 0, 2, 4, 3, 6, 5])])
 def test_peer_avg_lp(bg, oracle, n, chunk, k, peer):
     """D_LP_S with chosen peers: codes, (min,max), the advanced xhat and the outputs equal the oracle's, bit for
-    bit, over two rounds (the second starts from the first's xhat).  Matchings with chunk <= 4096 run the fused
-    pair kernel; every other case the two-pass path."""
+    bit, over two rounds (the second starts from the first's xhat).  Matched pairs and workers
+    that are their own peer run the fused kernel, the others two passes."""
     r = np.random.default_rng(n + 7 * k + chunk)
     if peer == "matching":
         peer = _matching(r, k)
@@ -103,3 +103,9 @@ def test_peer_avg_lp(bg, oracle, n, chunk, k, peer):
             assert np.array_equal(og[i].cpu().numpy().view(np.uint32), want[i].view(np.uint32)), tag
             assert np.array_equal(xg[i].cpu().numpy(), xs[i]), tag
         xs = [(w - np.float32(0.01) * (r.standard_normal(n) * 1e-2).astype(np.float32)).astype(np.float32) for w in want]
+
+
+@pytest.mark.parametrize("n,chunk", [(1, 256), (4096 * 2 + 1027, 4096), (8192 + 300, 8192), (16384 * 2 + 5, 16384)])
+@pytest.mark.parametrize("k,peer", [(6, [1, 0, 0, 3, 4, 2]), (3, [0, 1, 2]), (4, [2, 0, 0, 3])])
+def test_peer_avg_lp_fused_and_two_pass_jobs_in_one_call(bg, oracle, n, chunk, k, peer):
+    test_peer_avg_lp(bg, oracle, n, chunk, k, peer)
