@@ -384,8 +384,9 @@ int bagua_momentum_sign_compress_ef(const float* g, const float* m, float beta1,
  *   residual / server_residual / out_fp32   either NULL (none for any bucket) or an array with B non-NULL entries
  *   codes_in, meta_in (server step)   host[B*k], bucket-major: entry b*k + j is worker j's buffer for bucket b
  *   workspace   device, >= bagua_batch_workspace_bytes(B, k) bytes (k = 0 for the calls without workers),
- *               16-byte aligned; holds the bucket table, written by small launches on `stream` before the main
- *               launch (no host-to-device copy, no synchronisation; the host arrays may be reused on return).
+ *               16-byte aligned; holds the bucket table where it does not fit the launch's kernel arguments (480
+ *               8-byte words), written by small launches on `stream` before the main launch (no host-to-device copy,
+ *               no synchronisation; the host arrays may be reused on return).
  *               It must stay untouched until the call's work on `stream` has finished.
  * Alignment, aliasing and error rules as for the unbatched calls, applied over all buckets of the call.
  * bagua_bucket_flatten_batched_run launches the copy of B planned buckets (plans[b] from bagua_flatten_plan with

@@ -111,9 +111,8 @@ extern "C" int bagua_decompress_reduce_recompress_batched(int codec, const void*
     if (!rl.disjoint()) return BAGUA_ERR_INVALID_ARG;
     if (total > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), s) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
-    if (minmax) return launch_drr_minmax_batched(workspace, B, k, total, chunk, ef, with_out, s);
-    return launch_drr_sign_batched(workspace, B, k, total, chunk, ef, with_out, s);
+    if (minmax) return launch_drr_minmax_batched(table, workspace, B, k, chunk, ef, with_out, s);
+    return launch_drr_sign_batched(table, workspace, B, k, chunk, ef, with_out, s);
 }
 
 extern "C" int bagua_decompress(int codec, const void* codes, const float* meta, size_t n, size_t chunk, float* out,

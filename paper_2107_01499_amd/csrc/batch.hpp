@@ -3,9 +3,9 @@
 //
 // A batched entry point writes a table into the caller's workspace and launches the ordinary chunk kernel over the
 // concatenation of all buckets' chunks; a workgroup finds its bucket from the buckets' first unit indices through a
-// small lookup table (two or three dependent uniform loads, served by the scalar cache).  The table travels to
-// the device as kernel arguments of small upload launches: no host-to-device copy, no synchronisation, and the host
-// arrays may be reused as soon as the call returns.
+// small lookup table (two or three dependent uniform loads, served by the scalar cache).  A table that fits the kernel
+// arguments (kInlineWords) travels with the launch itself, a larger one as kernel arguments of small upload launches in
+// front of it: no host-to-device copy, no synchronisation, and the host arrays may be reused as soon as the call returns.
 //
 // Table layout (8-byte words):  first_unit[0..B]  (first_unit[B] = units in the launch), padded to 16 bytes, then B
 // entries of `entry_words` words each (layout per entry point, see the kernels), then a unit -> bucket lookup table of
@@ -24,9 +24,10 @@ struct BatchView {
     uint32_t B;
     uint32_t entry_words;
     uint32_t shift;
+    __host__ __device__ __forceinline__ BatchView view() const { return *this; }
 };
 
-inline size_t batch_first_words(size_t B) { return (B + 1 + 1) & ~static_cast<size_t>(1); }  // 16-byte multiple
+__host__ __device__ constexpr size_t batch_first_words(size_t B) { return (B + 1 + 1) & ~static_cast<size_t>(1); }  // 16-byte multiple
 // Entries of the unit -> bucket lookup table: a power of two, about four per bucket, 16..1024.
 inline size_t batch_lut_entries(size_t B)
 {
@@ -72,6 +73,24 @@ inline void batch_fill_lut(uint64_t* table, size_t B, size_t entry_words)
     }
 }
 
+// A whole table as a kernel argument: an upload launch in front of the call takes 1.4-5 us and a gap.  8 workers x 5
+// buckets of 25.6 M elements in all (17 batched calls): 856 -> 826 us; 4 workers x 5 buckets of 1 M: 99 -> 69 us.  The
+// limit keeps the launch below the 4 KiB of kernel arguments: 58 buckets of a compression, 21 of a server step with
+// eight workers.  The kernels read it through the scalar cache as they read a table in memory.
+constexpr int kInlineWords = 480;
+struct BatchInline {
+    uint64_t w[kInlineWords];
+    uint32_t B;
+    uint32_t entry_words;
+    uint32_t shift;
+    __host__ __device__ __forceinline__ BatchView view() const
+    {
+        const uint64_t* entries = w + batch_first_words(B);
+        return BatchView{w, entries, reinterpret_cast<const uint32_t*>(entries + static_cast<size_t>(B) * entry_words), B,
+                         entry_words, shift};
+    }
+};
+
 // A device pointer read from the table.  The table holds integers; the cast goes through the global address space so
 // that accesses through the result compile to global memory instructions.  Without it the compiler has to assume a
 // generic ("flat") pointer: flat loads and stores count against both wait counters, cannot be kept in flight past LDS
@@ -104,6 +123,27 @@ __global__ void k_upload_words(UploadBlob blob, uint32_t words, uint64_t* __rest
 
 // Enqueues the launches that write `words` 8-byte words from host memory to device memory at dst.
 int batch_upload(const uint64_t* host, size_t words, uint64_t* dst, hipStream_t stream);
+
+// Hands the table to `launch`, which takes a BatchInline or a BatchView (of the workspace, once uploaded).
+template <typename LAUNCH>
+int batch_launch(const std::vector<uint64_t>& table, size_t B, size_t entry_words, void* workspace, hipStream_t stream,
+                 const LAUNCH& launch)
+{
+    const BatchView bv = batch_view(workspace, B, entry_words, table[B]);
+    if (table.size() <= kInlineWords) {
+        BatchInline t;
+        std::copy(table.begin(), table.end(), t.w);
+        std::fill(t.w + table.size(), t.w + kInlineWords, 0);
+        t.B = bv.B;
+        t.entry_words = bv.entry_words;
+        t.shift = bv.shift;
+        launch(t);
+    } else {
+        if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), stream) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
+        launch(bv);
+    }
+    return launch_status();
+}
 
 // Aliasing rule of a batched call: as RangeCheck, for any number of ranges.
 struct RangeList {

@@ -102,10 +102,12 @@ k_flatten(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile
 }
 
 // Batched: entry = [planned workspace, T, bucket, bucket_numel]; unit = tile.
+template <typename TABLE>
 __global__ void __launch_bounds__(kWave)
-k_flatten_batched(BatchView bv)
+k_flatten_batched(TABLE table)
 {
     const uint32_t unit = blockIdx.x / kTileWaves;
+    const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, unit);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     const size_t T = e[1];
@@ -359,7 +361,7 @@ extern "C" int bagua_bucket_flatten_batched_run(const void* const* plans, const 
     if (!plans || !T || !bucket || !bucket_numel || !workspace || B == 0 || B > 0xffffffffu) return BAGUA_ERR_INVALID_ARG;
     if (workspace_bytes < bagua_batch_workspace_bytes(B, 0)) return BAGUA_ERR_INVALID_ARG;
     if (!aligned16(workspace)) return BAGUA_ERR_ALIGNMENT;
-    const size_t ew = batch_entry_words_for(0);
+    const size_t ew = 4;   // <= batch_entry_words_for(0)
     std::vector<uint64_t> table(batch_table_words(B, ew), 0);
     uint64_t* entries = table.data() + batch_first_words(B);
     RangeList rl;
@@ -384,10 +386,10 @@ extern "C" int bagua_bucket_flatten_batched_run(const void* const* plans, const 
     if (!rl.disjoint()) return BAGUA_ERR_INVALID_ARG;
     if (total > kMaxGrid / kTileWaves) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), s) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_flatten_batched, dim3(static_cast<unsigned>(total * kTileWaves)), dim3(kWave), 0, s,
-                       batch_view(workspace, B, ew, total));
-    return launch_status();
+    return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
+        hipLaunchKernelGGL(k_flatten_batched<std::decay_t<decltype(tab)>>, dim3(static_cast<unsigned>(total * kTileWaves)), dim3(kWave),
+                           0, s, tab);
+    });
 }
 
 extern "C" int bagua_decompress_unflatten(int codec, const void* codes, const float* meta, size_t n, size_t chunk,

@@ -61,11 +61,12 @@ k_compress_minmax(const float* __restrict__ x, float* __restrict__ residual, siz
 }
 
 // Batched: entry = [x, residual, codes, minmax, n]; unit = chunk.
-template <int RPW, bool EF>
+template <int RPW, bool EF, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_compress_minmax_batched(BatchView bv, uint32_t chunk, int pace)
+k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace)
 {
     __shared__ float s_red[2 * kMaxWaves];
+    const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     compress_minmax_chunk<RPW, EF>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
@@ -191,12 +192,13 @@ k_drr_minmax(PtrTable codes_in, PtrTable meta_in, int k, float inv_k, float* __r
                                    blockIdx.x, s_red, s_mn, s_step);
 }
 
-template <int RPW, bool EF, bool OUT>
+template <int RPW, bool EF, bool OUT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_drr_minmax_batched(BatchView bv, int k, float inv_k, uint32_t chunk)
+k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk)
 {
     __shared__ float s_red[2 * kMaxWaves];
     __shared__ float s_mn[BAGUA_MAX_WORKERS], s_step[BAGUA_MAX_WORKERS];
+    const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     drr_minmax_chunk<RPW, EF, OUT>(DrrEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
@@ -268,24 +270,25 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
     return launch_status();
 }
 
-int launch_drr_minmax_batched(const void* workspace, size_t B, int k, size_t total_chunks, size_t chunk, bool ef,
+int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspace, size_t B, int k, size_t chunk, bool ef,
                               bool with_out, hipStream_t stream)
 {
-    const BatchView bv = batch_view(workspace, B, 5 + 2 * static_cast<size_t>(k), total_chunks);
     const int rows = static_cast<int>(chunk / kRow);
     const int rpw = pick_rpw(rows, BAGUA_RPW_DRR);
-    dim3 grid(static_cast<unsigned>(total_chunks)), block(64 * ((rows + rpw - 1) / rpw));
+    dim3 grid(static_cast<unsigned>(table[B])), block(64 * ((rows + rpw - 1) / rpw));
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
-#define BAGUA_DRR(EFv, OUTv)                                                                                       \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv>), grid, block, 0, stream, bv, \
+    return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
+        using TABLE = std::decay_t<decltype(tab)>;
+#define BAGUA_DRR(EFv, OUTv)                                                                                               \
+    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, TABLE>), grid, block, 0, stream, tab, \
                                                k, inv_k, ch))
-    if (ef && with_out) { BAGUA_DRR(true, true) }
-    else if (ef) { BAGUA_DRR(true, false) }
-    else if (with_out) { BAGUA_DRR(false, true) }
-    else { BAGUA_DRR(false, false) }
+        if (ef && with_out) { BAGUA_DRR(true, true) }
+        else if (ef) { BAGUA_DRR(true, false) }
+        else if (with_out) { BAGUA_DRR(false, true) }
+        else { BAGUA_DRR(false, false) }
 #undef BAGUA_DRR
-    return launch_status();
+    });
 }
 
 int launch_decompress_minmax(const uint8_t* codes, const float* minmax, size_t n, size_t chunk, float* out,
@@ -326,7 +329,7 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
     if (workspace_bytes < bagua_batch_workspace_bytes(B, 0)) return BAGUA_ERR_INVALID_ARG;
     if (!aligned16(workspace)) return BAGUA_ERR_ALIGNMENT;
     const bool ef = residual != nullptr;
-    const size_t ew = batch_entry_words_for(0);
+    const size_t ew = 5;   // <= batch_entry_words_for(0)
     std::vector<uint64_t> table(batch_table_words(B, ew), 0);
     uint64_t* entries = table.data() + batch_first_words(B);
     RangeList rl;
@@ -355,16 +358,16 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
     if (!rl.disjoint()) return BAGUA_ERR_INVALID_ARG;
     if (total > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), s) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
-    const BatchView bv = batch_view(workspace, B, ew, total);
     const int rows = static_cast<int>(chunk / kRow);
     const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
     dim3 grid(static_cast<unsigned>(total)), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
-    if (ef) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, true>), grid, block, 0, s, bv, ch, pace_for(total * chunk)))
-    } else {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, false>), grid, block, 0, s, bv, ch, pace_for(total * chunk)))
-    }
-    return launch_status();
+    return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
+        using TABLE = std::decay_t<decltype(tab)>;
+        if (ef) {
+            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, true, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk)))
+        } else {
+            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, false, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk)))
+        }
+    });
 }

@@ -79,11 +79,12 @@ k_sign_compress(const float* __restrict__ x, float* __restrict__ residual, size_
 }
 
 // Batched: entry = [x, residual, bits, scale, n]; unit = chunk.
-template <int RPW, bool EF>
+template <int RPW, bool EF, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_sign_compress_batched(BatchView bv, uint32_t chunk, int pace)
+k_sign_compress_batched(TABLE table, uint32_t chunk, int pace)
 {
     extern __shared__ float s_q[];
+    const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     sign_compress_chunk<RPW, EF, false>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
@@ -286,11 +287,12 @@ k_drr_sign(PtrTable bits_in, PtrTable scale_in, int k, float inv_k, float* __res
                                  blockIdx.x, s_q);
 }
 
-template <int RPW, bool EF, bool OUT>
+template <int RPW, bool EF, bool OUT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_drr_sign_batched(BatchView bv, int k, float inv_k, uint32_t chunk)
+k_drr_sign_batched(TABLE table, int k, float inv_k, uint32_t chunk)
 {
     extern __shared__ float s_q[];
+    const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     drr_sign_chunk<RPW, EF, OUT>(SignEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
@@ -375,23 +377,24 @@ int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, in
     return launch_status();
 }
 
-int launch_drr_sign_batched(const void* workspace, size_t B, int k, size_t total_chunks, size_t chunk, bool ef,
+int launch_drr_sign_batched(const std::vector<uint64_t>& table, void* workspace, size_t B, int k, size_t chunk, bool ef,
                             bool with_out, hipStream_t stream)
 {
-    const BatchView bv = batch_view(workspace, B, 5 + 2 * static_cast<size_t>(k), total_chunks);
     SignGeometry g = sign_geometry(chunk, chunk, BAGUA_RPW_DRR_SIGN, false);
-    g.grid = dim3(static_cast<unsigned>(total_chunks));
+    g.grid = dim3(static_cast<unsigned>(table[B]));
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
-#define BAGUA_DRR(EFv, OUTv)                                                                                           \
-    BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_drr_sign_batched<RPW, EFv, OUTv>), g.grid, g.block, g.lds, stream, \
-                                                 bv, k, inv_k, ch))
-    if (ef && with_out) { BAGUA_DRR(true, true) }
-    else if (ef) { BAGUA_DRR(true, false) }
-    else if (with_out) { BAGUA_DRR(false, true) }
-    else { BAGUA_DRR(false, false) }
+    return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
+        using TABLE = std::decay_t<decltype(tab)>;
+#define BAGUA_DRR(EFv, OUTv)                                                                                       \
+    BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_drr_sign_batched<RPW, EFv, OUTv, TABLE>), g.grid, g.block, g.lds, stream, \
+                                                 tab, k, inv_k, ch))
+        if (ef && with_out) { BAGUA_DRR(true, true) }
+        else if (ef) { BAGUA_DRR(true, false) }
+        else if (with_out) { BAGUA_DRR(false, true) }
+        else { BAGUA_DRR(false, false) }
 #undef BAGUA_DRR
-    return launch_status();
+    });
 }
 
 int launch_decompress_sign(const uint32_t* bits, const float* scale, size_t n, size_t chunk, float* out,
@@ -459,7 +462,7 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
     if (workspace_bytes < bagua_batch_workspace_bytes(B, 0)) return BAGUA_ERR_INVALID_ARG;
     if (!aligned16(workspace)) return BAGUA_ERR_ALIGNMENT;
     const bool ef = residual != nullptr;
-    const size_t ew = batch_entry_words_for(0);
+    const size_t ew = 5;   // <= batch_entry_words_for(0)
     std::vector<uint64_t> table(batch_table_words(B, ew), 0);
     uint64_t* entries = table.data() + batch_first_words(B);
     RangeList rl;
@@ -488,15 +491,15 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
     if (!rl.disjoint()) return BAGUA_ERR_INVALID_ARG;
     if (total > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), s) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
-    const BatchView bv = batch_view(workspace, B, ew, total);
     SignGeometry g = sign_geometry(chunk, chunk, BAGUA_RPW_SIGN, false);
     g.grid = dim3(static_cast<unsigned>(total));
     const uint32_t ch = static_cast<uint32_t>(chunk);
-    if (ef) {
-        BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, true>), g.grid, g.block, g.lds, s, bv, ch, pace_for(total * chunk)))
-    } else {
-        BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, false>), g.grid, g.block, g.lds, s, bv, ch, pace_for(total * chunk)))
-    }
-    return launch_status();
+    return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
+        using TABLE = std::decay_t<decltype(tab)>;
+        if (ef) {
+            BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, true, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk)))
+        } else {
+            BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, false, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk)))
+        }
+    });
 }

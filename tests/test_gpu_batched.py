@@ -267,3 +267,29 @@ def test_batched_validation(bg):
     assert lib.bagua_sign_compress_ef_batched(one(A), None, n0, 1, 256, one(Bp), one(Cc), W, wsb, None) == INVALID
     assert lib.bagua_decompress_reduce_recompress_batched(7, one(A), one(Bp), 1, None, n1, 1, 256, one(Cc), one(D), None, W,
                                                           bg.bagua_batch_workspace_bytes(1, 1), None) == INVALID
+
+
+# The last bucket counts whose tables travel as a kernel argument (480 words) and the first that are uploaded.
+@pytest.mark.parametrize("step,B", [("minmax", 58), ("minmax", 59), ("sign", 58), ("sign", 59), ("drr_minmax", 35), ("drr_minmax", 36),
+                                    ("drr_sign", 35), ("drr_sign", 36), ("flatten", 64), ("flatten", 65)])
+def test_table_as_argument_and_uploaded(bg, oracle, monkeypatch, step, B):
+    monkeypatch.setitem(globals(), "NS", [1 + (37 * b * b) % 9001 for b in range(B)])
+    if step == "minmax":
+        test_compress_minmax_batched(bg, oracle, 4096, True)
+    elif step == "sign":
+        test_sign_compress_batched(bg, oracle, 2048, True)
+    elif step == "drr_minmax":
+        test_drr_minmax_batched(bg, oracle, 2, True, True)
+    elif step == "drr_sign":
+        test_drr_sign_batched(bg, oracle, 2, True, True)
+    else:
+        srcs = [vals(n, b) for b, n in enumerate(NS)]
+        gs = [dev(s) for s in srcs]
+        plans = [torch.empty(bg.bagua_flatten_workspace_bytes(1, n + 3), dtype=torch.uint8, device="cuda") for n in NS]
+        for g, n, ws in zip(gs, NS, plans):
+            bg.bagua_flatten_plan([g], [0], n + 3, ws)
+        out = [torch.full((n + 3,), float("nan"), device="cuda") for n in NS]
+        bg.bagua_bucket_flatten_batched_run(plans, [1] * B, out, ws_for(bg, B))
+        torch.cuda.synchronize()
+        for b in range(B):
+            same(host(out[b]), oracle.bucket_flatten([srcs[b]], [0], NS[b] + 3), "bucket %d" % b)
