@@ -100,7 +100,7 @@ constexpr int wg_threads_max(int rpw)
 {
     return kWave * (((64 + rpw - 1) / rpw) < kMaxWaves ? ((64 + rpw - 1) / rpw) : kMaxWaves);
 }
-static_assert(wg_threads_max(1) <= 1024 && wg_threads_max(2) <= 1024 && wg_threads_max(8) == 512, "launch bound");
+static_assert(wg_threads_max(1) <= 1024 && wg_threads_max(2) <= 1024 && 4 * kMaxWaves >= 64, "four rows per wave hold any chunk");
 
 struct PtrTable {
     const void* p[BAGUA_MAX_WORKERS];
@@ -125,6 +125,29 @@ __device__ __forceinline__ int wave_index()
     return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
 }
 
+// Worker-side launches short enough that a wave's latency shows: with the tail tests folded away (row_remain<true>) all
+// loads of a wave are in flight together; with them the compiler waits for one row before it requests the next, which
+// in a long launch is the better pattern (see pace_loads).  Measured with the tests kept and folded away: a momentum +
+// sign compression round of 8 workers x 6.5 M elements 197 -> 183 us; 4 workers, MinMax: 6.5 M 106 -> 103 us, 25.6 M
+// 347 -> 343 us, 50 M 672 -> 679 us, 100 M 1306 -> 1322 us, sign codec 300 M 4138 -> 4337 us.  A batched launch, whose
+// waves first look up their bucket, gains up to twice that size (60 M in 9 buckets 697 -> 682 us, sign 604 -> 590 us;
+// 120 M +-1 %).
+inline bool short_launch(size_t elements_per_launch, bool batched = false)
+{
+    return elements_per_launch < (static_cast<size_t>(1) << (batched ? 26 : 25));
+}
+
+// f(0), ..., f(N - 1) written out.  A loop over the rows of a wave would do, but where N = 1 the compiler moves a store
+// out of the one-trip loop before it unrolls it, and the store loses its nontemporal hint (-12 % at 100 M elements).
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(const F& f)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(f);
+        f(N - 1);
+    }
+}
+
 // ---------------------------------------------------------------- wave-level reductions
 __device__ __forceinline__ float wave_min(float v)
 {
@@ -147,6 +170,18 @@ __device__ __forceinline__ float wave_butterfly_sum(float v)
 }
 
 // ---------------------------------------------------------------- row accessors with ragged tails
+// Valid elements of a chunk from element `off` on.  FULL: every row of every wave of the workgroup is complete, and the
+// constant lets all tail tests fold away.
+template <bool FULL>
+__device__ __forceinline__ int row_remain(int len, int off)
+{
+    return FULL ? kRow : len - off;
+}
+template <int RPW>
+__device__ __forceinline__ bool chunk_full(int len, int nwaves)
+{
+    return len == RPW * kRow * nwaves;
+}
 // `remain` = number of valid elements counted from the start of the row (wave-uniform, may be <= 0
 // for an absent row or >= 256 for a full one).  Absent elements read as `fill`.
 __device__ __forceinline__ f4 load_row(const float* __restrict__ row, int lane, int remain, float fill)
@@ -254,7 +289,7 @@ struct RangeCheck {
 inline int pick_rpw(int rows, int preferred)
 {
     int rpw = preferred;
-    while (rpw < 8 && (rows + rpw - 1) / rpw > kMaxWaves) rpw *= 2;
+    while (rpw < 4 && (rows + rpw - 1) / rpw > kMaxWaves) rpw *= 2;
     return rpw;
 }
 
@@ -268,12 +303,11 @@ inline int pick_rpw_worker(int rows, int preferred)
     return pick_rpw(rows, (preferred == 2 && rows >= 6 && rows <= 8) ? 1 : preferred);
 }
 
-// Expands `stmt` with a constexpr RPW equal to the runtime value rpw (2, 4 or 8).
+// Expands `stmt` with a constexpr RPW equal to the runtime value rpw (2 or 4; chunks have at most 64 rows).
 #define BAGUA_DISPATCH_RPW(rpw, stmt)                    \
     switch (rpw) {                                        \
         case 2: { constexpr int RPW = 2; stmt; } break;  \
-        case 4: { constexpr int RPW = 4; stmt; } break;  \
-        default: { constexpr int RPW = 8; stmt; } break; \
+        default: { constexpr int RPW = 4; stmt; } break; \
     }
 
 // The same for the worker-side kernels, which also come with one row per wave.
@@ -281,9 +315,13 @@ inline int pick_rpw_worker(int rows, int preferred)
     switch (rpw) {                                        \
         case 1: { constexpr int RPW = 1; stmt; } break;  \
         case 2: { constexpr int RPW = 2; stmt; } break;  \
-        case 4: { constexpr int RPW = 4; stmt; } break;  \
-        default: { constexpr int RPW = 8; stmt; } break; \
+        default: { constexpr int RPW = 4; stmt; } break; \
     }
+
+// Expands `stmt` with a constexpr SHORT equal to the runtime value is_short (see short_launch).
+#define BAGUA_DISPATCH_SHORT(is_short, stmt)            \
+    if (is_short) { constexpr bool SHORT = true; stmt; } \
+    else { constexpr bool SHORT = false; stmt; }
 
 inline int launch_status()
 {

@@ -14,32 +14,28 @@ namespace bagua {
 // ------------------------------------------------------------------------------------------
 // Worker side: v = x (+ residual); codes = Q(v); residual <- v - decode.
 // One workgroup per chunk, block = 64 * ceil(rows / RPW); c = index of the chunk in its bucket.
-template <int RPW, bool EF>
-__device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
-                                                      uint32_t chunk, uint8_t* __restrict__ codes,
-                                                      float* __restrict__ minmax, size_t c, float* s_red, int pace)
+template <int RPW, bool EF, bool FULL>
+__device__ __forceinline__ void compress_minmax_rows(const float* __restrict__ x, float* __restrict__ residual, int len,
+                                                     uint8_t* __restrict__ codes, float* __restrict__ minmax_c, float* s_red, int pace)
 {
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-
     f4 v[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
+        const int remain = row_remain<FULL>(len, off);
         v[i] = f4{0.f, 0.f, 0.f, 0.f};
-        if (remain > 0) v[i] = load_row(x + base + off, lane, remain, 0.0f);
-        if (pace) pace_loads();
+        if (remain > 0) v[i] = load_row(x + off, lane, remain, 0.0f);
+        if (!FULL && pace) pace_loads();
     }
     if (EF) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int off = static_cast<int>(wave * RPW + i) * kRow;
-            const int remain = len - off;
+            const int remain = row_remain<FULL>(len, off);
             if (remain > 0) {
-                const f4 d = load_row(residual + base + off, lane, remain, 0.0f);
-                if (pace) pace_loads();
+                const f4 d = load_row(residual + off, lane, remain, 0.0f);
+                if (!FULL && pace) pace_loads();
                 v[i].x = v[i].x + d.x;
                 v[i].y = v[i].y + d.y;
                 v[i].z = v[i].z + d.z;
@@ -47,21 +43,33 @@ __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ 
             }
         }
     }
-    minmax_encode_chunk<RPW, EF, false>(v, len, wave, lane, nwaves, EF ? residual + base : nullptr,
-                                        codes + base, minmax + 2 * c, nullptr, s_red);
+    minmax_encode_chunk<RPW, EF, false, false, FULL>(v, len, wave, lane, nwaves, residual, codes, minmax_c, nullptr, s_red);
 }
 
-template <int RPW, bool EF>
+template <int RPW, bool EF, bool SHORT>
+__device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
+                                                      uint32_t chunk, uint8_t* __restrict__ codes,
+                                                      float* __restrict__ minmax, size_t c, float* s_red, int pace)
+{
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    float* res_c = EF ? residual + base : nullptr;
+    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
+        compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0);
+    else compress_minmax_rows<RPW, EF, false>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, pace);
+}
+
+template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_minmax(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
                   uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    compress_minmax_chunk<RPW, EF>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace);
+    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace);
 }
 
 // Batched: entry = [x, residual, codes, minmax, n]; unit = chunk.
-template <int RPW, bool EF, typename TABLE>
+template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace)
 {
@@ -69,7 +77,7 @@ k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace)
     const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
-    compress_minmax_chunk<RPW, EF>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
+    compress_minmax_chunk<RPW, EF, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                    table_ptr<uint8_t>(e[2]), table_ptr<float>(e[3]),
                                    blockIdx.x - bv.first_unit[b], s_red, pace);
 }
@@ -237,11 +245,11 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_compress_minmax<RPW, true>), grid, block, 0, stream, x,
-                                                          residual, n, ch, codes, minmax, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_compress_minmax<RPW, false>), grid, block, 0, stream, x,
-                                                          residual, n, ch, codes, minmax, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n))))
     }
     return launch_status();
 }
@@ -365,9 +373,11 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, true, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk)))
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk))))
         } else {
-            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_minmax_batched<RPW, false, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk)))
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk))))
         }
     });
 }

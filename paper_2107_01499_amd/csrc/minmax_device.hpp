@@ -10,14 +10,14 @@ namespace bagua {
 // caller can put the statistics of several chunks behind one barrier.
 // Phase 1: this wave's (min, max) over its valid elements (`len` = valid elements of the chunk; rows
 // beyond it are ignored); with several waves the pair is also parked in s_red (2*kMaxWaves floats).
-template <int RPW>
+template <int RPW, bool FULL = false>
 __device__ __forceinline__ void chunk_minmax_partial(const f4 (&v)[RPW], int len, int wave, int lane, int nwaves,
                                                      float* s_red, float& mn_out, float& mx_out)
 {
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
-        const int remain = len - static_cast<int>(wave * RPW + i) * kRow;
+        const int remain = row_remain<FULL>(len, static_cast<int>(wave * RPW + i) * kRow);
         if (remain >= kRow) {
             mn = fminf(fminf(mn, v[i].x), fminf(v[i].y, fminf(v[i].z, v[i].w)));
             mx = fmaxf(fmaxf(mx, v[i].x), fmaxf(v[i].y, fmaxf(v[i].z, v[i].w)));
@@ -50,11 +50,11 @@ __device__ __forceinline__ void chunk_minmax_finish(int nwaves, const float* s_r
     mn = mn + 0.0f;
     mx = mx + 0.0f;
 }
-template <int RPW>
+template <int RPW, bool FULL>
 __device__ __forceinline__ void chunk_minmax(const f4 (&v)[RPW], int len, int wave, int lane, int nwaves,
                                              float* s_red, float& mn_out, float& mx_out)
 {
-    chunk_minmax_partial<RPW>(v, len, wave, lane, nwaves, s_red, mn_out, mx_out);
+    chunk_minmax_partial<RPW, FULL>(v, len, wave, lane, nwaves, s_red, mn_out, mx_out);
     if (nwaves > 1) __syncthreads();
     chunk_minmax_finish(nwaves, s_red, mn_out, mx_out);
 }
@@ -81,7 +81,7 @@ __device__ __forceinline__ uint32_t pack_codes(float q0, float q1, float q2, flo
     return w;
 }
 
-template <int RPW, bool EF, bool OUT, bool DEQ_BACK>
+template <int RPW, bool EF, bool OUT, bool DEQ_BACK, bool FULL = false>
 __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, float mx, int len, int wave, int lane,
                                                       float* __restrict__ residual, uint8_t* __restrict__ codes,
                                                       float* __restrict__ minmax_c, float* __restrict__ out);
@@ -89,20 +89,20 @@ __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, fl
 // Encode the chunk held in v: writes codes, (min,max), and optionally the updated residual
 // (v - decode) and the decoded values.  Pointers are already offset to the start of the chunk.
 // If DEQ_BACK, v is overwritten with the decoded values (used by the decentralised LP kernel).
-template <int RPW, bool EF, bool OUT, bool DEQ_BACK = false>
+template <int RPW, bool EF, bool OUT, bool DEQ_BACK = false, bool FULL = false>
 __device__ __forceinline__ void minmax_encode_chunk(f4 (&v)[RPW], int len, int wave, int lane, int nwaves,
                                                     float* __restrict__ residual, uint8_t* __restrict__ codes,
                                                     float* __restrict__ minmax_c, float* __restrict__ out,
                                                     float* s_red)
 {
     float mn, mx;
-    chunk_minmax<RPW>(v, len, wave, lane, nwaves, s_red, mn, mx);
-    minmax_quantise_chunk<RPW, EF, OUT, DEQ_BACK>(v, mn, mx, len, wave, lane, residual, codes, minmax_c, out);
+    chunk_minmax<RPW, FULL>(v, len, wave, lane, nwaves, s_red, mn, mx);
+    minmax_quantise_chunk<RPW, EF, OUT, DEQ_BACK, FULL>(v, mn, mx, len, wave, lane, residual, codes, minmax_c, out);
 }
 
 // Quantise the chunk held in v given its canonical (min, max): writes codes, (min,max), and optionally the
 // updated residual (v - decode) and the decoded values; if DEQ_BACK, v is overwritten with the decoded values.
-template <int RPW, bool EF, bool OUT, bool DEQ_BACK>
+template <int RPW, bool EF, bool OUT, bool DEQ_BACK, bool FULL>
 __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, float mx, int len, int wave, int lane,
                                                       float* __restrict__ residual, uint8_t* __restrict__ codes,
                                                       float* __restrict__ minmax_c, float* __restrict__ out)
@@ -114,11 +114,10 @@ __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, fl
         minmax_c[0] = mn;
         minmax_c[1] = mx;
     }
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
+    unrolled<RPW>([&](int i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
-        if (remain <= 0) continue;
+        const int remain = row_remain<FULL>(len, off);
+        if (remain <= 0) return;
         const float q0 = quantise(v[i].x, mn, inv), q1 = quantise(v[i].y, mn, inv);
         const float q2 = quantise(v[i].z, mn, inv), q3 = quantise(v[i].w, mn, inv);
         store_codes_row(codes + off, lane, remain, pack_codes(q0, q1, q2, q3));
@@ -139,7 +138,7 @@ __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, fl
             if (OUT) store_row(out + off, lane, remain, deq);
             if (DEQ_BACK) v[i] = deq;
         }
-    }
+    });
 }
 
 }  // namespace bagua

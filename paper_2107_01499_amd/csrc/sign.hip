@@ -16,32 +16,28 @@ namespace bagua {
 // ------------------------------------------------------------------------------------------
 // MOM: the compressed tensor is the local momentum beta1*m + omb1*x of the compression stage of
 // 1-bit Adam (x is then the gradient; m is read only).
-template <int RPW, bool EF, bool MOM>
-__device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
-                                                    uint32_t chunk, uint32_t* __restrict__ bits,
-                                                    float* __restrict__ scale, const float* __restrict__ mom,
-                                                    float beta1, float omb1, size_t c, float* s_q, int pace)
+template <int RPW, bool EF, bool MOM, bool FULL>
+__device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, float* __restrict__ residual, int len, uint32_t chunk,
+                                                   uint32_t* __restrict__ bits, float* __restrict__ scale_c,
+                                                   const float* __restrict__ mom, float beta1, float omb1, float* s_q, int pace)
 {
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-
     f4 v[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
+        const int remain = row_remain<FULL>(len, off);
         v[i] = f4{0.f, 0.f, 0.f, 0.f};
-        if (remain > 0) v[i] = load_row(x + base + off, lane, remain, 0.0f);
-        if (pace) pace_loads();
+        if (remain > 0) v[i] = load_row(x + off, lane, remain, 0.0f);
+        if (!FULL && pace) pace_loads();
     }
     if (MOM) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int off = static_cast<int>(wave * RPW + i) * kRow;
-            const int remain = len - off;
+            const int remain = row_remain<FULL>(len, off);
             if (remain > 0) {
-                const f4 m = load_row(mom + base + off, lane, remain, 0.0f);
+                const f4 m = load_row(mom + off, lane, remain, 0.0f);
                 v[i].x = beta1 * m.x + omb1 * v[i].x;
                 v[i].y = beta1 * m.y + omb1 * v[i].y;
                 v[i].z = beta1 * m.z + omb1 * v[i].z;
@@ -53,10 +49,10 @@ __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x,
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int off = static_cast<int>(wave * RPW + i) * kRow;
-            const int remain = len - off;
+            const int remain = row_remain<FULL>(len, off);
             if (remain > 0) {
-                const f4 d = load_row(residual + base + off, lane, remain, 0.0f);
-                if (pace) pace_loads();
+                const f4 d = load_row(residual + off, lane, remain, 0.0f);
+                if (!FULL && pace) pace_loads();
                 v[i].x = v[i].x + d.x;
                 v[i].y = v[i].y + d.y;
                 v[i].z = v[i].z + d.z;
@@ -64,22 +60,37 @@ __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x,
             }
         }
     }
-    sign_encode_chunk<RPW, EF, false>(v, len, chunk, wave, lane, nwaves, EF ? residual + base : nullptr,
-                                      bits + (base >> 5), scale + c, nullptr, s_q);
+    sign_encode_chunk<RPW, EF, false, FULL>(v, len, chunk, wave, lane, nwaves, residual, bits, scale_c, nullptr, s_q);
 }
 
-template <int RPW, bool EF, bool MOM = false>
+template <int RPW, bool EF, bool MOM, bool SHORT>
+__device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
+                                                    uint32_t chunk, uint32_t* __restrict__ bits,
+                                                    float* __restrict__ scale, const float* __restrict__ mom,
+                                                    float beta1, float omb1, size_t c, float* s_q, int pace)
+{
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    float* res_c = EF ? residual + base : nullptr;
+    const float* mom_c = MOM ? mom + base : nullptr;
+    uint32_t* bits_c = bits + (base >> 5);
+    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
+        sign_compress_rows<RPW, EF, MOM, true>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q, 0);
+    else sign_compress_rows<RPW, EF, MOM, false>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q, pace);
+}
+
+template <int RPW, bool EF, bool MOM, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_sign_compress(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
                 uint32_t* __restrict__ bits, float* __restrict__ scale, const float* __restrict__ mom, float beta1,
                 float omb1, int pace)
 {
     extern __shared__ float s_q[];
-    sign_compress_chunk<RPW, EF, MOM>(x, residual, n, chunk, bits, scale, mom, beta1, omb1, blockIdx.x, s_q, pace);
+    sign_compress_chunk<RPW, EF, MOM, SHORT>(x, residual, n, chunk, bits, scale, mom, beta1, omb1, blockIdx.x, s_q, pace);
 }
 
 // Batched: entry = [x, residual, bits, scale, n]; unit = chunk.
-template <int RPW, bool EF, typename TABLE>
+template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_sign_compress_batched(TABLE table, uint32_t chunk, int pace)
 {
@@ -87,7 +98,7 @@ k_sign_compress_batched(TABLE table, uint32_t chunk, int pace)
     const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
-    sign_compress_chunk<RPW, EF, false>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
+    sign_compress_chunk<RPW, EF, false, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                         table_ptr<uint32_t>(e[2]), table_ptr<float>(e[3]), nullptr, 0.0f,
                                         0.0f, blockIdx.x - bv.first_unit[b], s_q, pace);
 }
@@ -346,11 +357,11 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     const SignGeometry g = sign_geometry(n, chunk, BAGUA_RPW_SIGN, true);
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, hipLaunchKernelGGL((k_sign_compress<RPW, true>), g.grid, g.block, g.lds, stream, x,
-                                                     residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, false, SHORT>), g.grid, g.block,
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, hipLaunchKernelGGL((k_sign_compress<RPW, false>), g.grid, g.block, g.lds, stream, x,
-                                                     residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, false, SHORT>), g.grid, g.block,
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n))))
     }
     return launch_status();
 }
@@ -444,11 +455,11 @@ extern "C" int bagua_momentum_sign_compress_ef(const float* g, const float* m, f
     const uint32_t ch = static_cast<uint32_t>(chunk);
     const float omb1 = 1.0f - beta1;
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, hipLaunchKernelGGL((k_sign_compress<RPW, true, true>), geo.grid, geo.block, geo.lds,
-                                                       s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, true, SHORT>), geo.grid, geo.block,
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, hipLaunchKernelGGL((k_sign_compress<RPW, false, true>), geo.grid, geo.block, geo.lds,
-                                                       s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n)))
+        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, true, SHORT>), geo.grid, geo.block,
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n))))
     }
     return launch_status();
 }
@@ -497,9 +508,11 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, true, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk)))
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+                                          (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk))))
         } else {
-            BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_sign_compress_batched<RPW, false, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk)))
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+                                          (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk))))
         }
     });
 }

@@ -9,7 +9,7 @@ namespace bagua {
 
 // Sum of |v| over the chunk in the fixed order (see bagua_sign_compress_ef in the header).
 // s_q: LDS, rows*64 floats, used only when the chunk is spread over several waves.
-template <int RPW>
+template <int RPW, bool FULL>
 __device__ __forceinline__ float chunk_abs_sum(const f4 (&v)[RPW], int rows, int wave, int lane, int nwaves,
                                                float* s_q)
 {
@@ -17,7 +17,7 @@ __device__ __forceinline__ float chunk_abs_sum(const f4 (&v)[RPW], int rows, int
     if (nwaves == 1) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            if (i < rows) {
+            if (FULL || i < rows) {
                 const float p = fabsf(v[i].x) + fabsf(v[i].y);
                 const float q = fabsf(v[i].z) + fabsf(v[i].w);
                 acc = acc + (p + q);
@@ -28,7 +28,7 @@ __device__ __forceinline__ float chunk_abs_sum(const f4 (&v)[RPW], int rows, int
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int row = wave * RPW + i;
-            if (row < rows) {
+            if (FULL || row < rows) {
                 const float p = fabsf(v[i].x) + fabsf(v[i].y);
                 const float q = fabsf(v[i].z) + fabsf(v[i].w);
                 s_q[row * kWave + lane] = p + q;
@@ -60,25 +60,24 @@ __device__ __forceinline__ float sign_select(uint32_t t, uint32_t sc_bits, uint3
 
 // Encode the chunk held in v (absent elements must be +0.0f).  `bits` points at the word of the
 // chunk's first element; residual/out point at the chunk's first element.
-template <int RPW, bool EF, bool OUT>
+template <int RPW, bool EF, bool OUT, bool FULL = false>
 __device__ __forceinline__ void sign_encode_chunk(f4 (&v)[RPW], int len, uint32_t chunk, int wave, int lane,
                                                   int nwaves, float* __restrict__ residual,
                                                   uint32_t* __restrict__ bits, float* __restrict__ scale_c,
                                                   float* __restrict__ out, float* s_q)
 {
     const int rows = static_cast<int>((len + kRow - 1) / kRow);
-    const float sum = chunk_abs_sum<RPW>(v, rows, wave, lane, nwaves, s_q);
+    const float sum = chunk_abs_sum<RPW, FULL>(v, rows, wave, lane, nwaves, s_q);
     const bool pow2 = (chunk & (chunk - 1)) == 0;
     float scale;
     if (len == static_cast<int>(chunk) && pow2) scale = sum * (1.0f / static_cast<float>(chunk));
     else scale = sum / static_cast<float>(len);
     if (threadIdx.x == 0) *scale_c = scale;
     const float neg = -scale;
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
+    unrolled<RPW>([&](int i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
-        if (remain <= 0) continue;
+        const int remain = row_remain<FULL>(len, off);
+        if (remain <= 0) return;
         const bool full = remain >= kRow;   // wave-uniform: a complete row needs no per-element tail tests
         bool b0 = v[i].x >= 0.0f, b1 = v[i].y >= 0.0f, b2 = v[i].z >= 0.0f, b3 = v[i].w >= 0.0f;
         if (!full) {
@@ -107,7 +106,7 @@ __device__ __forceinline__ void sign_encode_chunk(f4 (&v)[RPW], int len, uint32_
             }
             if (OUT) store_row(out + off, lane, full ? kRow : remain, deq);
         }
-    }
+    });
 }
 
 }  // namespace bagua

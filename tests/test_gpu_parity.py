@@ -272,6 +272,42 @@ def test_ring_avg_lp_either_side_of_the_unrolled_range(bg, oracle, k, C, n):
     test_ring_avg_lp(bg, oracle, k, C, n)
 
 
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+@pytest.mark.parametrize("n,C", [(1 << 25, 4096), ((1 << 25) + 2048 + 77, 2048), ((1 << 26) + 5, 1024)])
+def test_long_launch_equals_its_parts(bg, codec, n, C):
+    """Launches of 2^25 elements and more (2^26 batched) keep their loads apart; a chunk does not see the difference, so
+    the parts, each a short launch, give the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(n + C)
+    x = torch.empty(n, device="cuda").normal_(0.0, 1e-3, generator=g)
+    res = torch.empty(n, device="cuda").normal_(0.0, 1e-5, generator=g)
+    cuts = [0, (n // 3) // C * C, (2 * n // 3) // C * C, n]
+
+    def compress(bounds, batched):
+        r, nc = res.clone(), bg.num_chunks(n, C)
+        codes = torch.full((n if codec == "minmax" else 4 * ((n + 31) // 32),), 0xAB, dtype=torch.uint8, device="cuda")
+        meta = torch.full(((2 if codec == "minmax" else 1) * nc,), float("nan"), device="cuda")
+        parts = []
+        for a, b in zip(bounds, bounds[1:]):
+            m = 2 if codec == "minmax" else 1
+            c = codes[a:b] if codec == "minmax" else codes[a // 8:a // 8 + 4 * ((b - a + 31) // 32)].view(torch.int32)
+            parts.append((x[a:b], r[a:b], c, meta[m * (a // C):m * bg.num_chunks(b, C)]))
+        if batched:
+            ws = torch.empty(bg.bagua_batch_workspace_bytes(len(parts), 0), dtype=torch.uint8, device="cuda")
+            call = bg.bagua_compress_minmax_u8_batched if codec == "minmax" else bg.bagua_sign_compress_ef_batched
+            call(*[list(p) for p in zip(*parts)][:2], C, *[list(p) for p in zip(*parts)][2:], ws)
+        else:
+            call = bg.bagua_compress_minmax_u8 if codec == "minmax" else bg.bagua_sign_compress_ef
+            for px, pr, pc, pm in parts:
+                call(px, pr, C, pc, pm)
+        return r, codes, meta
+
+    want = compress(cuts, False)
+    for got in (compress([0, n], False), compress(cuts, True)):
+        assert torch.equal(got[0].view(torch.int32), want[0].view(torch.int32))
+        assert torch.equal(got[1], want[1])
+        assert torch.equal(got[2].view(torch.int32), want[2].view(torch.int32))
+
+
 # ----------------------------------------------------------------------------- flatten
 def test_flatten_gaps_misaligned_and_tiny(bg, oracle):
     r = np.random.default_rng(0)
