@@ -76,10 +76,7 @@ __device__ __forceinline__ void st_stream(T* p, T v)
 #ifndef BAGUA_LP_GROUP
 #define BAGUA_LP_GROUP 1
 #endif
-// Workers whose code loads are issued together in the server-side kernels.
-#ifndef BAGUA_DRR_NJ
-#define BAGUA_DRR_NJ 1
-#endif
+// Workers whose sign words are fetched together in the sign codec's server-side kernel.
 #ifndef BAGUA_DRR_SIGN_NJ
 #define BAGUA_DRR_SIGN_NJ 8
 #endif

@@ -98,14 +98,12 @@ struct DrrEntrySrc {   // pointers in a batch entry: [eps, codes_out, meta_out, 
     __device__ __forceinline__ const float* meta(int j) const { return table_ptr<const float>(e[5 + k + j]); }
 };
 
-template <int RPW, bool EF, bool OUT, typename SRC>
-__device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t n,
-                                                 uint32_t chunk, uint8_t* __restrict__ codes_out,
-                                                 float* __restrict__ minmax_out, float* __restrict__ out, size_t c,
-                                                 float* s_red, float* s_mn, float* s_step)
+// `base`, `len`: the chunk's first element and its length.
+template <int RPW, bool EF, bool OUT, bool FULL, typename SRC>
+__device__ __forceinline__ void drr_minmax_rows(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t base, int len,
+                                                size_t c, uint8_t* __restrict__ codes_out, float* __restrict__ minmax_out,
+                                                float* __restrict__ out, float* s_red, float* s_mn, float* s_step)
 {
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
     // per-worker (min, step) of this chunk: one lane per worker, so the k divisions run side by side
@@ -118,10 +116,17 @@ __device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float in
     __syncthreads();
 
     f4 v[RPW];
-    // Workers are summed in ascending order; the code loads of NJ workers are issued together so
-    // that NJ*RPW dword loads are in flight per wave before the first is consumed.
-    constexpr int NJ = BAGUA_DRR_NJ;
-    auto accumulate = [&](int j, uint32_t (&w)[RPW]) {
+    // workers are summed in ascending order
+    for (int j = 0; j < k; ++j) {
+        const uint8_t* cj = static_cast<const uint8_t*>(src.code(j)) + base;
+        uint32_t w[RPW];
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const int off = static_cast<int>(wave * RPW + i) * kRow;
+            const int remain = row_remain<FULL>(len, off);
+            w[i] = 0;
+            if (remain > 0) w[i] = load_codes_row(cj + off, lane, remain);
+        }
         const float mn = s_mn[j], step = s_step[j];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
@@ -139,29 +144,16 @@ __device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float in
                 v[i].w = v[i].w + d.w;
             }
         }
-    };
-    auto fetch = [&](int j, uint32_t (&w)[RPW]) {
-        const uint8_t* cj = static_cast<const uint8_t*>(src.code(j)) + base;
+    }
+    f4 e[RPW];
+    if (EF) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int off = static_cast<int>(wave * RPW + i) * kRow;
-            const int remain = len - off;
-            w[i] = 0;
-            if (remain > 0) w[i] = load_codes_row(cj + off, lane, remain);
+            const int remain = row_remain<FULL>(len, off);
+            e[i] = f4{0.f, 0.f, 0.f, 0.f};
+            if (remain > 0) e[i] = load_row(eps + base + off, lane, remain, 0.0f);
         }
-    };
-    int j = 0;
-    for (; j + NJ <= k; j += NJ) {
-        uint32_t w[NJ][RPW];
-#pragma unroll
-        for (int u = 0; u < NJ; ++u) fetch(j + u, w[u]);
-#pragma unroll
-        for (int u = 0; u < NJ; ++u) accumulate(j + u, w[u]);
-    }
-    for (; j < k; ++j) {
-        uint32_t w[RPW];
-        fetch(j, w);
-        accumulate(j, w);
     }
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -169,26 +161,46 @@ __device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float in
         v[i].y = v[i].y * inv_k;
         v[i].z = v[i].z * inv_k;
         v[i].w = v[i].w * inv_k;
-    }
-    if (EF) {
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const int off = static_cast<int>(wave * RPW + i) * kRow;
-            const int remain = len - off;
-            if (remain > 0) {
-                const f4 d = load_row(eps + base + off, lane, remain, 0.0f);
-                v[i].x = v[i].x + d.x;
-                v[i].y = v[i].y + d.y;
-                v[i].z = v[i].z + d.z;
-                v[i].w = v[i].w + d.w;
-            }
+        if (EF && row_remain<FULL>(len, static_cast<int>(wave * RPW + i) * kRow) > 0) {
+            v[i].x = v[i].x + e[i].x;
+            v[i].y = v[i].y + e[i].y;
+            v[i].z = v[i].z + e[i].z;
+            v[i].w = v[i].w + e[i].w;
         }
     }
-    minmax_encode_chunk<RPW, EF, OUT>(v, len, wave, lane, nwaves, EF ? eps + base : nullptr,
-                                      codes_out + base, minmax_out + 2 * c, OUT ? out + base : nullptr, s_red);
+    minmax_encode_chunk<RPW, EF, OUT, false, FULL>(v, len, wave, lane, nwaves, EF ? eps + base : nullptr, codes_out + base,
+                                                   minmax_out + 2 * c, OUT ? out + base : nullptr, s_red);
 }
 
-template <int RPW, bool EF, bool OUT>
+template <int RPW, bool EF, bool OUT, bool FOLD, typename SRC>
+__device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t n,
+                                                 uint32_t chunk, uint8_t* __restrict__ codes_out,
+                                                 float* __restrict__ minmax_out, float* __restrict__ out, size_t c,
+                                                 float* s_red, float* s_mn, float* s_step)
+{
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    if (FOLD && chunk_full<RPW>(len, blockDim.x >> 6))
+        drr_minmax_rows<RPW, EF, OUT, true>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step);
+    else drr_minmax_rows<RPW, EF, OUT, false>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step);
+}
+
+// Whether the server step folds the tail tests of complete chunks away.  With the tests a wave waits for one row's
+// codes before it requests the next; four rows per wave make that a long chain.  Folded away against kept:
+//   chunks above 4096 (8 or 16 waves): 16 workers x 335 M, C = 8192, 1443 -> 1341 us; 25.7 M 118 -> 105 us; 3 x 16.8 M,
+//   C = 16384, 48 -> 38 us;
+//   chunks up to 4096: 8 workers x 25.7 M, C = 4096, 92.5 -> 87.8 us, 2 workers, C = 2048, 52.6 -> 47.5 us, 16 x 33 M
+//   137 -> 135 us; but with many code streams and more elements the slower chain streams better: 16 x 50 M 199 -> 206 us,
+//   8 x 134 M 361 -> 369 us, against 242 -> 233 us with two workers.
+inline bool drr_minmax_fold(size_t elements, size_t chunk, int k)
+{
+    return chunk > 4096 || k <= 4 || elements < (static_cast<size_t>(1) << 25);
+}
+#define BAGUA_DISPATCH_FOLD(is_folded, stmt)               \
+    if (is_folded) { constexpr bool FOLD = true; stmt; }    \
+    else { constexpr bool FOLD = false; stmt; }
+
+template <int RPW, bool EF, bool OUT, bool FOLD>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_minmax(PtrTable codes_in, PtrTable meta_in, int k, float inv_k, float* __restrict__ eps, size_t n,
              uint32_t chunk, uint8_t* __restrict__ codes_out, float* __restrict__ minmax_out,
@@ -196,11 +208,11 @@ k_drr_minmax(PtrTable codes_in, PtrTable meta_in, int k, float inv_k, float* __r
 {
     __shared__ float s_red[2 * kMaxWaves];
     __shared__ float s_mn[BAGUA_MAX_WORKERS], s_step[BAGUA_MAX_WORKERS];
-    drr_minmax_chunk<RPW, EF, OUT>(DrrTableSrc{codes_in, meta_in}, k, inv_k, eps, n, chunk, codes_out, minmax_out, out,
+    drr_minmax_chunk<RPW, EF, OUT, FOLD>(DrrTableSrc{codes_in, meta_in}, k, inv_k, eps, n, chunk, codes_out, minmax_out, out,
                                    blockIdx.x, s_red, s_mn, s_step);
 }
 
-template <int RPW, bool EF, bool OUT, typename TABLE>
+template <int RPW, bool EF, bool OUT, bool FOLD, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk)
 {
@@ -209,7 +221,7 @@ k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk)
     const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
-    drr_minmax_chunk<RPW, EF, OUT>(DrrEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
+    drr_minmax_chunk<RPW, EF, OUT, FOLD>(DrrEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
                                    table_ptr<uint8_t>(e[1]), table_ptr<float>(e[2]),
                                    table_ptr<float>(e[3]), blockIdx.x - bv.first_unit[b], s_red, s_mn, s_step);
 }
@@ -268,8 +280,9 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
 #define BAGUA_DRR(EFv, OUTv)                                                                                   \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv>), grid, block, 0, stream, ct, mt, \
-                                               k, inv_k, eps, n, ch, codes_out, minmax_out, out))
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(n, chunk, k),                                  \
+                                                hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv, FOLD>), grid, block, 0, stream, ct, mt, \
+                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out)))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
     else if (out) { BAGUA_DRR(false, true) }
@@ -289,8 +302,9 @@ int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspac
     return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
 #define BAGUA_DRR(EFv, OUTv)                                                                                               \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, TABLE>), grid, block, 0, stream, tab, \
-                                               k, inv_k, ch))
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(table[B] * chunk, chunk, k),                               \
+                                                hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, FOLD, TABLE>), grid, block, 0, \
+                                                                   stream, tab, k, inv_k, ch)))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
         else if (with_out) { BAGUA_DRR(false, true) }

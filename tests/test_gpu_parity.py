@@ -308,6 +308,30 @@ def test_long_launch_equals_its_parts(bg, codec, n, C):
         assert torch.equal(got[2].view(torch.int32), want[2].view(torch.int32))
 
 
+def test_server_step_long_launch_equals_its_parts(bg):
+    """Five workers, C = 2048: from 2^25 elements on the MinMax server step takes the other of its two instances."""
+    k, C, n = 5, 2048, (1 << 25) + 2048 + 77
+    g = torch.Generator(device="cuda").manual_seed(7)
+    nc = bg.num_chunks(n, C)
+    codes = [torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=g) for _ in range(k)]
+    meta = [torch.empty(2 * nc, device="cuda").uniform_(0.0, 1e-3, generator=g) for _ in range(k)]
+    for m in meta:
+        m[0::2].neg_()
+    eps = torch.empty(n, device="cuda").normal_(0.0, 1e-5, generator=g)
+
+    def step(bounds):
+        e, c = eps.clone(), torch.full((n,), 0xAB, dtype=torch.uint8, device="cuda")
+        m, out = torch.full((2 * nc,), float("nan"), device="cuda"), torch.full((n,), float("nan"), device="cuda")
+        for a, b in zip(bounds, bounds[1:]):
+            ma, mb = 2 * (a // C), 2 * bg.num_chunks(b, C)
+            bg.bagua_decompress_reduce_recompress(bg.CODEC_MINMAX_U8, [x[a:b] for x in codes], [x[ma:mb] for x in meta], e[a:b], b - a,
+                                                  C, c[a:b], m[ma:mb], out[a:b])
+        return e.view(torch.int32), c, m.view(torch.int32), out.view(torch.int32)
+
+    for got, want in zip(step([0, n]), step([0, n // 2 // C * C, n])):
+        assert torch.equal(got, want)
+
+
 # ----------------------------------------------------------------------------- flatten
 def test_flatten_gaps_misaligned_and_tiny(bg, oracle):
     r = np.random.default_rng(0)
