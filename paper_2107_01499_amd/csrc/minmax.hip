@@ -16,7 +16,7 @@ namespace bagua {
 // One workgroup per chunk, block = 64 * ceil(rows / RPW); c = index of the chunk in its bucket.
 template <int RPW, bool EF, bool FULL>
 __device__ __forceinline__ void compress_minmax_rows(const float* __restrict__ x, float* __restrict__ residual, int len,
-                                                     uint8_t* __restrict__ codes, float* __restrict__ minmax_c, float* s_red, int pace)
+                                                     uint8_t* __restrict__ codes, float* __restrict__ minmax_c, float* s_red, int pace, int keep)
 {
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     f4 v[RPW];
@@ -43,35 +43,35 @@ __device__ __forceinline__ void compress_minmax_rows(const float* __restrict__ x
             }
         }
     }
-    minmax_encode_chunk<RPW, EF, false, false, FULL>(v, len, wave, lane, nwaves, residual, codes, minmax_c, nullptr, s_red);
+    minmax_encode_chunk<RPW, EF, false, false, FULL>(v, len, wave, lane, nwaves, residual, codes, minmax_c, nullptr, s_red, keep);
 }
 
 template <int RPW, bool EF, bool SHORT>
 __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
                                                       uint32_t chunk, uint8_t* __restrict__ codes,
-                                                      float* __restrict__ minmax, size_t c, float* s_red, int pace)
+                                                      float* __restrict__ minmax, size_t c, float* s_red, int pace, int keep)
 {
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     float* res_c = EF ? residual + base : nullptr;
     if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
-        compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0);
-    else compress_minmax_rows<RPW, EF, false>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, pace);
+        compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0, 1);
+    else compress_minmax_rows<RPW, EF, false>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, pace, keep);
 }
 
 template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_minmax(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
-                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace)
+                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace, int keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace);
+    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace, keep);
 }
 
 // Batched: entry = [x, residual, codes, minmax, n]; unit = chunk.
 template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace)
+k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, int keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const BatchView bv = table.view();
@@ -79,7 +79,7 @@ k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace)
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     compress_minmax_chunk<RPW, EF, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                    table_ptr<uint8_t>(e[2]), table_ptr<float>(e[3]),
-                                   blockIdx.x - bv.first_unit[b], s_red, pace);
+                                   blockIdx.x - bv.first_unit[b], s_red, pace, keep);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -102,7 +102,7 @@ struct DrrEntrySrc {   // pointers in a batch entry: [eps, codes_out, meta_out, 
 template <int RPW, bool EF, bool OUT, bool FULL, typename SRC>
 __device__ __forceinline__ void drr_minmax_rows(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t base, int len,
                                                 size_t c, uint8_t* __restrict__ codes_out, float* __restrict__ minmax_out,
-                                                float* __restrict__ out, float* s_red, float* s_mn, float* s_step)
+                                                float* __restrict__ out, float* s_red, float* s_mn, float* s_step, int keep)
 {
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
@@ -169,20 +169,20 @@ __device__ __forceinline__ void drr_minmax_rows(const SRC& src, int k, float inv
         }
     }
     minmax_encode_chunk<RPW, EF, OUT, false, FULL>(v, len, wave, lane, nwaves, EF ? eps + base : nullptr, codes_out + base,
-                                                   minmax_out + 2 * c, OUT ? out + base : nullptr, s_red);
+                                                   minmax_out + 2 * c, OUT ? out + base : nullptr, s_red, keep);
 }
 
 template <int RPW, bool EF, bool OUT, bool FOLD, typename SRC>
 __device__ __forceinline__ void drr_minmax_chunk(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t n,
                                                  uint32_t chunk, uint8_t* __restrict__ codes_out,
                                                  float* __restrict__ minmax_out, float* __restrict__ out, size_t c,
-                                                 float* s_red, float* s_mn, float* s_step)
+                                                 float* s_red, float* s_mn, float* s_step, int keep)
 {
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     if (FOLD && chunk_full<RPW>(len, blockDim.x >> 6))
-        drr_minmax_rows<RPW, EF, OUT, true>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step);
-    else drr_minmax_rows<RPW, EF, OUT, false>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step);
+        drr_minmax_rows<RPW, EF, OUT, true>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step, keep);
+    else drr_minmax_rows<RPW, EF, OUT, false>(src, k, inv_k, eps, base, len, c, codes_out, minmax_out, out, s_red, s_mn, s_step, keep);
 }
 
 // Whether the server step folds the tail tests of complete chunks away.  With the tests a wave waits for one row's
@@ -204,17 +204,17 @@ template <int RPW, bool EF, bool OUT, bool FOLD>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_minmax(PtrTable codes_in, PtrTable meta_in, int k, float inv_k, float* __restrict__ eps, size_t n,
              uint32_t chunk, uint8_t* __restrict__ codes_out, float* __restrict__ minmax_out,
-             float* __restrict__ out)
+             float* __restrict__ out, int keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     __shared__ float s_mn[BAGUA_MAX_WORKERS], s_step[BAGUA_MAX_WORKERS];
     drr_minmax_chunk<RPW, EF, OUT, FOLD>(DrrTableSrc{codes_in, meta_in}, k, inv_k, eps, n, chunk, codes_out, minmax_out, out,
-                                   blockIdx.x, s_red, s_mn, s_step);
+                                   blockIdx.x, s_red, s_mn, s_step, keep);
 }
 
 template <int RPW, bool EF, bool OUT, bool FOLD, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk)
+k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk, int keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     __shared__ float s_mn[BAGUA_MAX_WORKERS], s_step[BAGUA_MAX_WORKERS];
@@ -223,7 +223,7 @@ k_drr_minmax_batched(TABLE table, int k, float inv_k, uint32_t chunk)
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     drr_minmax_chunk<RPW, EF, OUT, FOLD>(DrrEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
                                    table_ptr<uint8_t>(e[1]), table_ptr<float>(e[2]),
-                                   table_ptr<float>(e[3]), blockIdx.x - bv.first_unit[b], s_red, s_mn, s_step);
+                                   table_ptr<float>(e[3]), blockIdx.x - bv.first_unit[b], s_red, s_mn, s_step, keep);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -258,10 +258,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(1, n))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(1, n))))
     }
     return launch_status();
 }
@@ -282,7 +282,7 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
 #define BAGUA_DRR(EFv, OUTv)                                                                                   \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(n, chunk, k),                                  \
                                                 hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv, FOLD>), grid, block, 0, stream, ct, mt, \
-                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out)))
+                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out, keep_codes(1, n))))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
     else if (out) { BAGUA_DRR(false, true) }
@@ -304,7 +304,7 @@ int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspac
 #define BAGUA_DRR(EFv, OUTv)                                                                                               \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(table[B] * chunk, chunk, k),                               \
                                                 hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, FOLD, TABLE>), grid, block, 0, \
-                                                                   stream, tab, k, inv_k, ch)))
+                                                                   stream, tab, k, inv_k, ch, keep_codes(1, table[B] * chunk))))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
         else if (with_out) { BAGUA_DRR(false, true) }
@@ -388,10 +388,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk))))
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(1, total * chunk))))
         } else {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk))))
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(1, total * chunk))))
         }
     });
 }

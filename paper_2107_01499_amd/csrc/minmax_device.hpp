@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t pack_codes(float q0, float q1, float q2, flo
 template <int RPW, bool EF, bool OUT, bool DEQ_BACK, bool FULL = false>
 __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, float mx, int len, int wave, int lane,
                                                       float* __restrict__ residual, uint8_t* __restrict__ codes,
-                                                      float* __restrict__ minmax_c, float* __restrict__ out);
+                                                      float* __restrict__ minmax_c, float* __restrict__ out, int keep);
 
 // Encode the chunk held in v: writes codes, (min,max), and optionally the updated residual
 // (v - decode) and the decoded values.  Pointers are already offset to the start of the chunk.
@@ -93,11 +93,11 @@ template <int RPW, bool EF, bool OUT, bool DEQ_BACK = false, bool FULL = false>
 __device__ __forceinline__ void minmax_encode_chunk(f4 (&v)[RPW], int len, int wave, int lane, int nwaves,
                                                     float* __restrict__ residual, uint8_t* __restrict__ codes,
                                                     float* __restrict__ minmax_c, float* __restrict__ out,
-                                                    float* s_red)
+                                                    float* s_red, int keep)
 {
     float mn, mx;
     chunk_minmax<RPW, FULL>(v, len, wave, lane, nwaves, s_red, mn, mx);
-    minmax_quantise_chunk<RPW, EF, OUT, DEQ_BACK, FULL>(v, mn, mx, len, wave, lane, residual, codes, minmax_c, out);
+    minmax_quantise_chunk<RPW, EF, OUT, DEQ_BACK, FULL>(v, mn, mx, len, wave, lane, residual, codes, minmax_c, out, keep);
 }
 
 // Quantise the chunk held in v given its canonical (min, max): writes codes, (min,max), and optionally the
@@ -105,7 +105,7 @@ __device__ __forceinline__ void minmax_encode_chunk(f4 (&v)[RPW], int len, int w
 template <int RPW, bool EF, bool OUT, bool DEQ_BACK, bool FULL>
 __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, float mx, int len, int wave, int lane,
                                                       float* __restrict__ residual, uint8_t* __restrict__ codes,
-                                                      float* __restrict__ minmax_c, float* __restrict__ out)
+                                                      float* __restrict__ minmax_c, float* __restrict__ out, int keep)
 {
     const float r = mx - mn;
     const float step = (r == 0.0f) ? 0.0f : r / 255.0f;
@@ -120,7 +120,7 @@ __device__ __forceinline__ void minmax_quantise_chunk(f4 (&v)[RPW], float mn, fl
         if (remain <= 0) return;
         const float q0 = quantise(v[i].x, mn, inv), q1 = quantise(v[i].y, mn, inv);
         const float q2 = quantise(v[i].z, mn, inv), q3 = quantise(v[i].w, mn, inv);
-        store_codes_row(codes + off, lane, remain, pack_codes(q0, q1, q2, q3));
+        store_codes_row(codes + off, lane, remain, pack_codes(q0, q1, q2, q3), keep);
         if (EF || OUT || DEQ_BACK) {
             f4 deq;
             deq.x = mn + q0 * step;

@@ -72,7 +72,7 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 // next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows: 108 VGPRs, no spill at 1024 threads.
 // 16 peers x 25.6 M elements, C = 8192: 1.33 ms (5.28 TB/s); encode per peer + a mixing pass over the public copies,
 // 25 bytes per element per peer, took 1.81 ms.
-template <int K, int RPW>
+template <int K, int RPW, int KEEP>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n,
               uint32_t chunk, float third)
@@ -128,7 +128,7 @@ k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable code
             // d <- decode(Q(d)); codes and (min,max) of peer i are written on the way
             minmax_quantise_chunk<RPW, false, false, true>(d[gi], mn[gi], mx[gi], len, wave, lane, nullptr,
                                                            static_cast<uint8_t*>(codes.p[i]) + base,
-                                                           static_cast<float*>(minmax.p[i]) + 2 * c, nullptr);
+                                                           static_cast<float*>(minmax.p[i]) + 2 * c, nullptr, KEEP);
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
                 const int off = static_cast<int>(wave * RPW + r) * kRow;
@@ -166,12 +166,12 @@ __device__ __forceinline__ void lp_load(const float* x_c, const float* hat_c, in
 // stored), x = x - h, what the peer adds to the mix.  One barrier.
 template <int RPW>
 __device__ __forceinline__ void lp_publish(f4 (&x)[RPW], f4 (&h)[RPW], float* hat_c, uint8_t* codes_c, float* minmax_c, int len,
-                                           int wave, int lane, int nwaves, float* s_red)
+                                           int wave, int lane, int nwaves, float* s_red, int keep)
 {
     f4 d[RPW];
 #pragma unroll
     for (int r = 0; r < RPW; ++r) d[r] = sub4(x[r], h[r]);
-    minmax_encode_chunk<RPW, false, false, true>(d, len, wave, lane, nwaves, nullptr, codes_c, minmax_c, nullptr, s_red);
+    minmax_encode_chunk<RPW, false, false, true>(d, len, wave, lane, nwaves, nullptr, codes_c, minmax_c, nullptr, s_red, keep);
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         const int off = static_cast<int>(wave * RPW + r) * kRow;
@@ -210,7 +210,7 @@ __device__ __forceinline__ void ring_mix(const f4 (&left)[RPW], const f4 (&mid)[
 template <int RPW>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
-                  uint32_t chunk, float third)
+                  uint32_t chunk, float third, int keep)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
     const size_t c = blockIdx.x;
@@ -226,7 +226,7 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
     for (int i = 0; i < k; ++i) {
         lp_load<RPW>(x_of(i), hat_of(i), len, wave, lane, x, h);
         lp_publish<RPW>(x, h, hat_of(i), static_cast<uint8_t*>(codes.p[i]) + base, static_cast<float*>(minmax.p[i]) + 2 * c, len,
-                        wave, lane, nwaves, s_red[i & 1]);
+                        wave, lane, nwaves, s_red[i & 1], keep);
         if (i >= 2) ring_mix<RPW>(left, mid, h, own, third, out_of(i - 1), len, wave, lane);
         copy_rows<RPW>(left, mid);
         copy_rows<RPW>(mid, h);
@@ -251,7 +251,7 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
 template <int RPW>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, uint32_t chunk,
-            uint8_t* __restrict__ codes, float* __restrict__ minmax)
+            uint8_t* __restrict__ codes, float* __restrict__ minmax, int keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const size_t c = blockIdx.x;
@@ -260,7 +260,7 @@ k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, 
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     f4 x[RPW], h[RPW];
     lp_load<RPW>(x_in + base, xhat + base, len, wave, lane, x, h);
-    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red);
+    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red, keep);
 }
 
 // ------------------------------------------------------------------------------------------ host
@@ -300,7 +300,8 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
                         const MutPtrTable& mm, size_t n, uint32_t chunk, float third, dim3 grid, dim3 block,
                         hipStream_t s)
 {
-    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third);
+    if (keep_codes(K, n)) hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, 1>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third);
+    else hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, 0>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third);
 }
 
 static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* const* xhat, uint8_t* const* codes,
@@ -331,7 +332,7 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
         }
     }
     BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
-                                               third))
+                                               third, keep_codes(k, n)))
     return launch_status();
 }
 
@@ -515,7 +516,7 @@ struct PeerLpJobs {
 // (three pairs and a single), C = 4096: 0.53 ms; encode + mix in two passes 0.83 ms.
 template <int RPW, bool PAIR>
 __global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)   // two rows per wave fit 64 VGPRs: full occupancy
-k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk)
+k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk, int keep)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
     const int job = blockIdx.y;
@@ -528,7 +529,7 @@ k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk)
     auto publish = [&](int sd) {
         lp_load<RPW>(jobs.x[sd][job] + base, jobs.hat[sd][job] + base, len, wave, lane, own[sd], h[sd]);
         lp_publish<RPW>(own[sd], h[sd], jobs.hat[sd][job] + base, jobs.codes[sd][job] + base, jobs.minmax[sd][job] + 2 * c, len,
-                        wave, lane, nwaves, s_red[sd]);
+                        wave, lane, nwaves, s_red[sd], keep);
     };
     auto mix = [&](int sd, int second) {   // the sum of a pair is the same one for both sides
 #pragma unroll
@@ -613,7 +614,7 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
         const int p = peer[i];
         if (peer[p] != i) {                             // chosen by nobody it chose: two passes
             BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, s, x_in[i], xhat[i], n, ch, codes[i],
-                                                       minmax[i]))
+                                                       minmax[i], keep_codes(k, n)))
             mix.x[nmix] = x_in[i];
             mix.hat_own[nmix] = xhat[i];
             mix.hat_peer[nmix] = xhat[p];
@@ -633,10 +634,12 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
         }
     }
     if (npairs) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, 0, s, pairs, n, ch))
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, 0, s, pairs, n, ch,
+                                                   keep_codes(k, n)))
     }
     if (nsingles) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch))
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch,
+                                                   keep_codes(k, n)))
     }
     if (nmix) {                                         // all public copies are advanced by now
         hipLaunchKernelGGL(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), nmix),
@@ -706,7 +709,7 @@ extern "C" int bagua_lp_encode(const float* x, float* xhat, size_t n, size_t chu
     const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, static_cast<hipStream_t>(stream), x, xhat,
-                                               n, static_cast<uint32_t>(chunk), codes, minmax))
+                                               n, static_cast<uint32_t>(chunk), codes, minmax, keep_codes(1, n)))
     return launch_status();
 }
 
