@@ -62,6 +62,12 @@ inline int keep_codes(size_t workers_in_call, size_t n)
     return workers_in_call * n <= (static_cast<size_t>(1) << (workers_in_call > 1 ? 28 : 27)) ? 1 : 0;
 }
 
+// A flattened bucket of n floats, which the compression reads next: 8 workers x 25.6 M elements in 5 buckets 793 -> 766 us,
+// 4 x 60 M 914 -> 869 us, 4 x 130 M 2153 -> 2115 us for the whole round.  (The momentum that every worker's sign compression
+// reads, 8 x 6.5 M elements 183 -> 163 us, 8 x 25.6 M 637 -> 580 us, but 4 x 100 M 1379 -> 1395 us, is loaded without
+// the hint in short launches; see also k_lp_encode.)
+inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); }
+
 // Preferred rows (of 256 elements) per wave for each chunked kernel (compile-time tuning knobs).
 // Measured on MI355X: two rows per wave (512 elements, 8 waves for a 4096-element chunk) stream
 // fastest in the worker-side kernels, the fused ring kernel and the sign codec's server kernel; the MinMax
@@ -209,6 +215,12 @@ __device__ __forceinline__ f4 load_row(const float* __restrict__ row, int lane, 
         r.w = (e + 3 < remain) ? row[e + 3] : fill;
     }
     return r;
+}
+// A complete row that is read again soon: without the streaming hint (see keep_codes).
+__device__ __forceinline__ f4 load_row_keep(const float* __restrict__ row, int lane, int remain, float fill)
+{
+    if (remain >= kRow) return reinterpret_cast<const f4*>(row)[lane];
+    return load_row(row, lane, remain, fill);
 }
 __device__ __forceinline__ void store_row(float* __restrict__ row, int lane, int remain, f4 v)
 {

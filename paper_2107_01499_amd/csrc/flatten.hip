@@ -20,12 +20,18 @@ namespace bagua {
 constexpr int kTileWaves = kTile / kRow;
 static_assert(kTile == 1024 && kTileWaves == 4, "the tile body below moves 16 bytes per lane of 256 lanes");
 
+// KEEP: the bucket is stored without the streaming hint (see keep_bucket).
 // One tile (kTile elements) of one bucket; `tile` = index of the tile in its bucket, `tid` = 0..255 = this lane's
 // place among the tile's 256 lanes.
+template <bool KEEP>
 __device__ __forceinline__ void flatten_tile(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile_first,
                                              uint32_t T, float* __restrict__ bucket, size_t bucket_numel, size_t tile,
                                              uint32_t tid)
 {
+    auto put = [](f4* p, f4 v) {
+        if (KEEP) *p = v;
+        else st_stream(p, v);
+    };
     const size_t tile0 = tile * kTile;
     const uint32_t lo0 = tile_first[tile], hi0 = tile_first[tile + 1];
 
@@ -42,14 +48,14 @@ __device__ __forceinline__ void flatten_tile(const TensorDesc* __restrict__ desc
 #pragma unroll
                 for (int g = 0; g < kTile / 1024; ++g) v[g] = ld_stream(s4 + g * 256 + tid);
 #pragma unroll
-                for (int g = 0; g < kTile / 1024; ++g) st_stream(b4 + g * 256 + tid, v[g]);
+                for (int g = 0; g < kTile / 1024; ++g) put(b4 + g * 256 + tid, v[g]);
                 return;
             }
             // same, source only 4-byte aligned: 128-bit loads with 4-byte declared alignment, aligned 128-bit stores
             f4* b4 = reinterpret_cast<f4*>(bucket + tile0);
 #pragma unroll
             for (int g = 0; g < kTile / 1024; ++g)
-                st_stream(b4 + g * 256 + tid, load_row_shifted(s + g * 1024, tid));
+                put(b4 + g * 256 + tid, load_row_shifted(s + g * 1024, tid));
             return;
         }
     }
@@ -84,7 +90,7 @@ __device__ __forceinline__ void flatten_tile(const TensorDesc* __restrict__ desc
             v.w = (e + 3 < bucket_numel) ? element_at(desc, t, T, e + 3) : 0.0f;
         }
         if (e + 4 <= bucket_numel) {
-            st_stream(reinterpret_cast<f4*>(bucket + e), v);
+            put(reinterpret_cast<f4*>(bucket + e), v);
         } else {
             bucket[e] = v.x;
             if (e + 1 < bucket_numel) bucket[e + 1] = v.y;
@@ -93,16 +99,17 @@ __device__ __forceinline__ void flatten_tile(const TensorDesc* __restrict__ desc
     }
 }
 
+template <bool KEEP>
 __global__ void __launch_bounds__(kWave)
 k_flatten(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile_first, uint32_t T,
           float* __restrict__ bucket, size_t bucket_numel)
 {
-    flatten_tile(desc, tile_first, T, bucket, bucket_numel, blockIdx.x / kTileWaves,
+    flatten_tile<KEEP>(desc, tile_first, T, bucket, bucket_numel, blockIdx.x / kTileWaves,
                  (blockIdx.x % kTileWaves) * kWave + threadIdx.x);
 }
 
 // Batched: entry = [planned workspace, T, bucket, bucket_numel]; unit = tile.
-template <typename TABLE>
+template <bool KEEP, typename TABLE>
 __global__ void __launch_bounds__(kWave)
 k_flatten_batched(TABLE table)
 {
@@ -113,7 +120,7 @@ k_flatten_batched(TABLE table)
     const size_t T = e[1];
     const unsigned char* ws = table_ptr<const unsigned char>(e[0]);
     const size_t desc_bytes = ((T ? T : 1) * sizeof(TensorDesc) + 15) & ~static_cast<size_t>(15);
-    flatten_tile(reinterpret_cast<const TensorDesc*>(ws), reinterpret_cast<const uint32_t*>(ws + desc_bytes),
+    flatten_tile<KEEP>(reinterpret_cast<const TensorDesc*>(ws), reinterpret_cast<const uint32_t*>(ws + desc_bytes),
                  static_cast<uint32_t>(T), table_ptr<float>(e[2]), e[3], unit - bv.first_unit[b],
                  (blockIdx.x % kTileWaves) * kWave + threadIdx.x);
 }
@@ -338,7 +345,8 @@ extern "C" int bagua_bucket_flatten_run(const void* workspace, size_t T, float* 
     if (T > 0xfffffff0u || num_tiles(bucket_numel) > kMaxGrid / kTileWaves) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned16(workspace) || !aligned16(bucket)) return BAGUA_ERR_ALIGNMENT;
     const FlattenPlanView pv = plan_view(workspace, T);
-    hipLaunchKernelGGL(k_flatten, dim3(static_cast<unsigned>(num_tiles(bucket_numel) * kTileWaves)), dim3(kWave), 0,
+    hipLaunchKernelGGL(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
+                       dim3(static_cast<unsigned>(num_tiles(bucket_numel) * kTileWaves)), dim3(kWave), 0,
                        static_cast<hipStream_t>(stream), pv.desc, pv.tile_first, static_cast<uint32_t>(T), bucket, bucket_numel);
     return launch_status();
 }
@@ -387,8 +395,9 @@ extern "C" int bagua_bucket_flatten_batched_run(const void* const* plans, const 
     if (total > kMaxGrid / kTileWaves) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
-        hipLaunchKernelGGL(k_flatten_batched<std::decay_t<decltype(tab)>>, dim3(static_cast<unsigned>(total * kTileWaves)), dim3(kWave),
-                           0, s, tab);
+        using TABLE = std::decay_t<decltype(tab)>;
+        hipLaunchKernelGGL((keep_bucket(total * kTile) ? k_flatten_batched<true, TABLE> : k_flatten_batched<false, TABLE>),
+                           dim3(static_cast<unsigned>(total * kTileWaves)), dim3(kWave), 0, s, tab);
     });
 }
 
@@ -512,7 +521,8 @@ extern "C" int bagua_bucket_flatten_static(const void* const* src, const size_t*
     const size_t tiles = num_tiles(bucket_numel);
     hipLaunchKernelGGL(k_table_tiles, dim3(static_cast<unsigned>((tiles + 1 + 255) / 256)), dim3(256), 0, s, desc,
                        static_cast<uint32_t>(T), tile_first, tiles);
-    hipLaunchKernelGGL(k_flatten, dim3(static_cast<unsigned>(tiles * kTileWaves)), dim3(kWave), 0, s, desc, tile_first,
+    hipLaunchKernelGGL(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
+                       dim3(static_cast<unsigned>(tiles * kTileWaves)), dim3(kWave), 0, s, desc, tile_first,
                        static_cast<uint32_t>(T), bucket, bucket_numel);
     return launch_status();
 }

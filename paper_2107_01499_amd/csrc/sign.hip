@@ -37,7 +37,7 @@ __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, 
             const int off = static_cast<int>(wave * RPW + i) * kRow;
             const int remain = row_remain<FULL>(len, off);
             if (remain > 0) {
-                const f4 m = load_row(mom + off, lane, remain, 0.0f);
+                const f4 m = FULL ? load_row_keep(mom + off, lane, remain, 0.0f) : load_row(mom + off, lane, remain, 0.0f);
                 v[i].x = beta1 * m.x + omb1 * v[i].x;
                 v[i].y = beta1 * m.y + omb1 * v[i].y;
                 v[i].z = beta1 * m.z + omb1 * v[i].z;
