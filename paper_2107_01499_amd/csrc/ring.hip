@@ -72,7 +72,7 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 // next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows: 108 VGPRs, no spill at 1024 threads.
 // 16 peers x 25.6 M elements, C = 8192: 1.33 ms (5.28 TB/s); encode per peer + a mixing pass over the public copies,
 // 25 bytes per element per peer, took 1.81 ms.
-template <int K, int RPW, int KEEP>
+template <int K, int RPW, int KEEP, bool FOLD>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n,
               uint32_t chunk, float third)
@@ -83,65 +83,70 @@ k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable code
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
-    f4 h[K][RPW];    // new public copy xhat' of every peer
-    f4 own[K][RPW];  // x - xhat' of every peer
-    auto finalize = [&](int p) {
-#pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-            const int off = static_cast<int>(wave * RPW + r) * kRow;
-            const int remain = len - off;
-            const f4 s = add4(add4(h[(p + K - 1) % K][r], h[p][r]), h[(p + 1) % K][r]);
-            const f4 o = add4(mul4(s, third), own[p][r]);
-            if (remain > 0) store_row(static_cast<float*>(xout.p[p]) + base + off, lane, remain, o);
-        }
-    };
-    // Peers are taken in groups of G: the statistics of a whole group sit behind one barrier.
-    constexpr int G = BAGUA_LP_GROUP;
-#pragma unroll
-    for (int g0 = 0; g0 < K; g0 += G) {
-        f4 x[G][RPW], d[G][RPW];
-        float mn[G], mx[G];
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            const int i = g0 + gi;
-            if (i >= K) continue;
+    auto round = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        f4 h[K][RPW];    // new public copy xhat' of every peer
+        f4 own[K][RPW];  // x - xhat' of every peer
+        auto finalize = [&](int p) {
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
                 const int off = static_cast<int>(wave * RPW + r) * kRow;
-                const int remain = len - off;
-                x[gi][r] = f4{0.f, 0.f, 0.f, 0.f};
-                h[i][r] = f4{0.f, 0.f, 0.f, 0.f};
-                if (remain > 0) {
-                    x[gi][r] = load_row(static_cast<const float*>(xin.p[i]) + base + off, lane, remain, 0.0f);
-                    h[i][r] = load_row(static_cast<const float*>(xhat.p[i]) + base + off, lane, remain, 0.0f);
+                const int remain = row_remain<FULL>(len, off);
+                const f4 s = add4(add4(h[(p + K - 1) % K][r], h[p][r]), h[(p + 1) % K][r]);
+                const f4 o = add4(mul4(s, third), own[p][r]);
+                if (remain > 0) store_row(static_cast<float*>(xout.p[p]) + base + off, lane, remain, o);
+            }
+        };
+        // Peers are taken in groups of G: the statistics of a whole group sit behind one barrier.
+        constexpr int G = BAGUA_LP_GROUP;
+#pragma unroll
+        for (int g0 = 0; g0 < K; g0 += G) {
+            f4 x[G][RPW], d[G][RPW];
+            float mn[G], mx[G];
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                const int i = g0 + gi;
+                if (i >= K) continue;
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) {
+                    const int off = static_cast<int>(wave * RPW + r) * kRow;
+                    const int remain = row_remain<FULL>(len, off);
+                    x[gi][r] = f4{0.f, 0.f, 0.f, 0.f};
+                    h[i][r] = f4{0.f, 0.f, 0.f, 0.f};
+                    if (remain > 0) {
+                        x[gi][r] = load_row(static_cast<const float*>(xin.p[i]) + base + off, lane, remain, 0.0f);
+                        h[i][r] = load_row(static_cast<const float*>(xhat.p[i]) + base + off, lane, remain, 0.0f);
+                    }
+                    d[gi][r] = sub4(x[gi][r], h[i][r]);
                 }
-                d[gi][r] = sub4(x[gi][r], h[i][r]);
+                chunk_minmax_partial<RPW, FULL>(d[gi], len, wave, lane, nwaves, s_red[i], mn[gi], mx[gi]);
             }
-            chunk_minmax_partial<RPW>(d[gi], len, wave, lane, nwaves, s_red[i], mn[gi], mx[gi]);
-        }
-        if (nwaves > 1) __syncthreads();
+            if (nwaves > 1) __syncthreads();
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            const int i = g0 + gi;
-            if (i >= K) continue;
-            chunk_minmax_finish(nwaves, s_red[i], mn[gi], mx[gi]);
-            // d <- decode(Q(d)); codes and (min,max) of peer i are written on the way
-            minmax_quantise_chunk<RPW, false, false, true>(d[gi], mn[gi], mx[gi], len, wave, lane, nullptr,
-                                                           static_cast<uint8_t*>(codes.p[i]) + base,
-                                                           static_cast<float*>(minmax.p[i]) + 2 * c, nullptr, KEEP);
+            for (int gi = 0; gi < G; ++gi) {
+                const int i = g0 + gi;
+                if (i >= K) continue;
+                chunk_minmax_finish(nwaves, s_red[i], mn[gi], mx[gi]);
+                // d <- decode(Q(d)); codes and (min,max) of peer i are written on the way
+                minmax_quantise_chunk<RPW, false, false, true, FULL>(d[gi], mn[gi], mx[gi], len, wave, lane, nullptr,
+                                                               static_cast<uint8_t*>(codes.p[i]) + base,
+                                                               static_cast<float*>(minmax.p[i]) + 2 * c, nullptr, KEEP);
 #pragma unroll
-            for (int r = 0; r < RPW; ++r) {
-                const int off = static_cast<int>(wave * RPW + r) * kRow;
-                const int remain = len - off;
-                h[i][r] = add4(h[i][r], d[gi][r]);
-                own[i][r] = sub4(x[gi][r], h[i][r]);
-                if (remain > 0) store_row(static_cast<float*>(xhat.p[i]) + base + off, lane, remain, h[i][r]);
+                for (int r = 0; r < RPW; ++r) {
+                    const int off = static_cast<int>(wave * RPW + r) * kRow;
+                    const int remain = row_remain<FULL>(len, off);
+                    h[i][r] = add4(h[i][r], d[gi][r]);
+                    own[i][r] = sub4(x[gi][r], h[i][r]);
+                    if (remain > 0) store_row(static_cast<float*>(xhat.p[i]) + base + off, lane, remain, h[i][r]);
+                }
+                if (i >= 2) finalize(i - 1);
             }
-            if (i >= 2) finalize(i - 1);
         }
-    }
-    finalize(K - 1);
-    if (K > 1) finalize(0);
+        finalize(K - 1);
+        if (K > 1) finalize(0);
+    };
+    if (FOLD && chunk_full<RPW>(len, nwaves)) round(std::true_type{});
+    else round(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------ LP, any number of peers
@@ -302,8 +307,20 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
                         const MutPtrTable& mm, size_t n, uint32_t chunk, float third, dim3 grid, dim3 block,
                         hipStream_t s)
 {
-    if (keep_codes(K, n)) hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, 1>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third);
-    else hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, 0>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third);
+#define BAGUA_RING(KEEPv, FOLDv) \
+    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FOLDv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third)
+    // Tail tests folded away (FOLD), so that a wave's loads are in flight together: 16 peers x 25.6 M, C = 8192, 1316 ->
+    // 1265 us, 7 x 8 M 168 -> 164 us, and in short launches: 8 x 1 M, C = 4096, 30.5 -> 27.3 us, 4 x 1 M 16.0 -> 13.6 us.
+    // Chunks up to 4096 elements of longer launches stream better with the tests, which keep a wave's rows apart: 8 x
+    // 25.6 M, C = 4096, 587 against 613 us, 12 x 3 M 138 against 141 us; so do three peers (110 against 112 us, 12.6 M).
+    if (K >= 4 && n < (static_cast<size_t>(1) << (chunk > 4096 ? 26 : 21))) {
+        if (keep_codes(K, n)) BAGUA_RING(1, (K >= 4));
+        else BAGUA_RING(0, (K >= 4));
+    } else {
+        if (keep_codes(K, n)) BAGUA_RING(1, false);
+        else BAGUA_RING(0, false);
+    }
+#undef BAGUA_RING
 }
 
 static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* const* xhat, uint8_t* const* codes,
