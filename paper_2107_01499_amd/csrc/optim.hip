@@ -157,17 +157,22 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
 
     // parameters (and momentum) do not depend on the decode: request them first
     f4 p[RPW], m[RPW];
+    auto load = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
-        p[i] = f4{0.f, 0.f, 0.f, 0.f};
-        m[i] = p[i];
-        if (remain > 0) {
-            p[i] = load_row(param + base + off, lane, remain, 0.0f);
-            if (MOM) m[i] = load_row(mbuf + base + off, lane, remain, 0.0f);
+        for (int i = 0; i < RPW; ++i) {
+            const int off = static_cast<int>(wave * RPW + i) * kRow;
+            const int remain = row_remain<FULL>(len, off);
+            p[i] = f4{0.f, 0.f, 0.f, 0.f};
+            m[i] = p[i];
+            if (remain > 0) {
+                p[i] = load_row(param + base + off, lane, remain, 0.0f);
+                if (MOM) m[i] = load_row(mbuf + base + off, lane, remain, 0.0f);
+            }
         }
-    }
+    };
+    if (chunk_full<RPW>(len, blockDim.x >> 6)) load(std::true_type{});   // no tail tests: all loads in flight together
+    else load(std::false_type{});
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
@@ -221,19 +226,24 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
 
     // parameters and optimizer state do not depend on the decode: request them first
     f4 p[RPW], m[RPW], v[RPW];
+    auto load = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = len - off;
-        p[i] = f4{0.f, 0.f, 0.f, 0.f};
-        m[i] = p[i];
-        v[i] = f4{1.f, 1.f, 1.f, 1.f};
-        if (remain > 0) {
-            p[i] = load_row(param + base + off, lane, remain, 0.0f);
-            v[i] = load_row(vbuf + base + off, lane, remain, 1.0f);
-            if (!FROZEN) m[i] = load_row(mbuf + base + off, lane, remain, 0.0f);
+        for (int i = 0; i < RPW; ++i) {
+            const int off = static_cast<int>(wave * RPW + i) * kRow;
+            const int remain = row_remain<FULL>(len, off);
+            p[i] = f4{0.f, 0.f, 0.f, 0.f};
+            m[i] = p[i];
+            v[i] = f4{1.f, 1.f, 1.f, 1.f};
+            if (remain > 0) {
+                p[i] = load_row(param + base + off, lane, remain, 0.0f);
+                v[i] = load_row(vbuf + base + off, lane, remain, 1.0f);
+                if (!FROZEN) m[i] = load_row(mbuf + base + off, lane, remain, 0.0f);
+            }
         }
-    }
+    };
+    if (chunk_full<RPW>(len, blockDim.x >> 6)) load(std::true_type{});
+    else load(std::false_type{});
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
