@@ -13,6 +13,8 @@
 
 namespace bagua {
 
+constexpr int kNarrowRows = 16;   // rows of a chunk of 4096 elements
+
 __device__ __forceinline__ f4 add4(f4 a, f4 b) { return f4{a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w}; }
 __device__ __forceinline__ f4 sub4(f4 a, f4 b) { return f4{a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w}; }
 __device__ __forceinline__ f4 mul4(f4 a, float s) { return f4{a.x * s, a.y * s, a.z * s, a.w * s}; }
@@ -69,84 +71,98 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 // Peers are processed in order; peer p's output is formed as soon as the new public copies of
 // p-1, p, p+1 exist, so only a short window of peers is live in registers at any time.
 // Bound by the memory system's rate for 5 K interleaved streams.  Unrolled over the peers (the compiler moves the
-// next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows: 108 VGPRs, no spill at 1024 threads.
-// 16 peers x 25.6 M elements, C = 8192: 1.33 ms (5.28 TB/s); encode per peer + a mixing pass over the public copies,
-// 25 bytes per element per peer, took 1.81 ms.
-template <int K, int RPW, int KEEP, bool FOLD>
-__global__ void __launch_bounds__(wg_threads_max(RPW))
+// next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows.  16 peers x 25.6 M elements, C = 8192:
+// 1.25 ms (5.6 TB/s); encode per peer + a mixing pass over the public copies, 25 bytes per element per peer, took 1.81 ms.
+//
+// The unrolled body stands here once, in the kernel itself.  Two of them (with and without tail tests) do not fit the
+// instruction cache, which short launches pay for, and a body called through a lambda is scheduled differently.  Before
+// -> now: 8 peers x 1 M, C = 1024, 34.0 -> 26.2 us, C = 4096, 31.0 -> 28.4 us; 16 x 1 M, C = 2048, 64 -> 47 us; 7 x
+// 3.2 M, C = 3072, 83 -> 73 us; 2 x 4.2 M, 26.6 -> 24.7 us (66 VGPRs were one workgroup per CU too few, 64 are not).
+//   FULL: no tail tests, so that a wave's loads are in flight together; a chunk that is cut short takes the loop over
+//         the peers below instead.
+//   WIDE: chunks above 4096 elements, more than eight waves.
+template <int RPW>
+__device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const MutPtrTable& xout, const MutPtrTable& xhat,
+                                                  const MutPtrTable& codes, const MutPtrTable& minmax, int k, size_t base, size_t c,
+                                                  int len, float third, int keep, float (*s_red)[2 * kMaxWaves]);
+
+template <int K, int RPW, int KEEP, bool FULL, bool WIDE>
+__global__ void __launch_bounds__(WIDE ? wg_threads_max(RPW) : kWave * (kNarrowRows / RPW), K <= 2 ? 8 : 1)
 k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n,
               uint32_t chunk, float third)
 {
+    static_assert(!FULL || K >= 2, "the loop needs two entries of s_red");
     __shared__ float s_red[K][2 * kMaxWaves];
     const size_t c = blockIdx.x;
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
-    auto round = [&](auto full) {
-        constexpr bool FULL = decltype(full)::value;
-        f4 h[K][RPW];    // new public copy xhat' of every peer
-        f4 own[K][RPW];  // x - xhat' of every peer
-        auto finalize = [&](int p) {
+    if constexpr (FULL) {
+        if (!chunk_full<RPW>(len, nwaves)) {
+            ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, K, base, c, len, third, KEEP, s_red);
+            return;
+        }
+    }
+    f4 h[K][RPW];    // new public copy xhat' of every peer
+    f4 own[K][RPW];  // x - xhat' of every peer
+    auto finalize = [&](int p) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            const int off = static_cast<int>(wave * RPW + r) * kRow;
+            const int remain = row_remain<FULL>(len, off);
+            const f4 s = add4(add4(h[(p + K - 1) % K][r], h[p][r]), h[(p + 1) % K][r]);
+            const f4 o = add4(mul4(s, third), own[p][r]);
+            if (remain > 0) store_row(static_cast<float*>(xout.p[p]) + base + off, lane, remain, o);
+        }
+    };
+    // Peers are taken in groups of G: the statistics of a whole group sit behind one barrier.
+    constexpr int G = BAGUA_LP_GROUP;
+#pragma unroll
+    for (int g0 = 0; g0 < K; g0 += G) {
+        f4 x[G][RPW], d[G][RPW];
+        float mn[G], mx[G];
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            const int i = g0 + gi;
+            if (i >= K) continue;
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
                 const int off = static_cast<int>(wave * RPW + r) * kRow;
                 const int remain = row_remain<FULL>(len, off);
-                const f4 s = add4(add4(h[(p + K - 1) % K][r], h[p][r]), h[(p + 1) % K][r]);
-                const f4 o = add4(mul4(s, third), own[p][r]);
-                if (remain > 0) store_row(static_cast<float*>(xout.p[p]) + base + off, lane, remain, o);
-            }
-        };
-        // Peers are taken in groups of G: the statistics of a whole group sit behind one barrier.
-        constexpr int G = BAGUA_LP_GROUP;
-#pragma unroll
-        for (int g0 = 0; g0 < K; g0 += G) {
-            f4 x[G][RPW], d[G][RPW];
-            float mn[G], mx[G];
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                const int i = g0 + gi;
-                if (i >= K) continue;
-#pragma unroll
-                for (int r = 0; r < RPW; ++r) {
-                    const int off = static_cast<int>(wave * RPW + r) * kRow;
-                    const int remain = row_remain<FULL>(len, off);
-                    x[gi][r] = f4{0.f, 0.f, 0.f, 0.f};
-                    h[i][r] = f4{0.f, 0.f, 0.f, 0.f};
-                    if (remain > 0) {
-                        x[gi][r] = load_row(static_cast<const float*>(xin.p[i]) + base + off, lane, remain, 0.0f);
-                        h[i][r] = load_row(static_cast<const float*>(xhat.p[i]) + base + off, lane, remain, 0.0f);
-                    }
-                    d[gi][r] = sub4(x[gi][r], h[i][r]);
+                x[gi][r] = f4{0.f, 0.f, 0.f, 0.f};
+                h[i][r] = f4{0.f, 0.f, 0.f, 0.f};
+                if (remain > 0) {
+                    x[gi][r] = load_row(static_cast<const float*>(xin.p[i]) + base + off, lane, remain, 0.0f);
+                    h[i][r] = load_row(static_cast<const float*>(xhat.p[i]) + base + off, lane, remain, 0.0f);
                 }
-                chunk_minmax_partial<RPW, FULL>(d[gi], len, wave, lane, nwaves, s_red[i], mn[gi], mx[gi]);
+                d[gi][r] = sub4(x[gi][r], h[i][r]);
             }
-            if (nwaves > 1) __syncthreads();
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                const int i = g0 + gi;
-                if (i >= K) continue;
-                chunk_minmax_finish(nwaves, s_red[i], mn[gi], mx[gi]);
-                // d <- decode(Q(d)); codes and (min,max) of peer i are written on the way
-                minmax_quantise_chunk<RPW, false, false, true, FULL>(d[gi], mn[gi], mx[gi], len, wave, lane, nullptr,
-                                                               static_cast<uint8_t*>(codes.p[i]) + base,
-                                                               static_cast<float*>(minmax.p[i]) + 2 * c, nullptr, KEEP);
-#pragma unroll
-                for (int r = 0; r < RPW; ++r) {
-                    const int off = static_cast<int>(wave * RPW + r) * kRow;
-                    const int remain = row_remain<FULL>(len, off);
-                    h[i][r] = add4(h[i][r], d[gi][r]);
-                    own[i][r] = sub4(x[gi][r], h[i][r]);
-                    if (remain > 0) store_row(static_cast<float*>(xhat.p[i]) + base + off, lane, remain, h[i][r]);
-                }
-                if (i >= 2) finalize(i - 1);
-            }
+            chunk_minmax_partial<RPW, FULL>(d[gi], len, wave, lane, nwaves, s_red[i], mn[gi], mx[gi]);
         }
-        finalize(K - 1);
-        if (K > 1) finalize(0);
-    };
-    if (FOLD && chunk_full<RPW>(len, nwaves)) round(std::true_type{});
-    else round(std::false_type{});
+        if (nwaves > 1) __syncthreads();
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            const int i = g0 + gi;
+            if (i >= K) continue;
+            chunk_minmax_finish(nwaves, s_red[i], mn[gi], mx[gi]);
+            // d <- decode(Q(d)); codes and (min,max) of peer i are written on the way
+            minmax_quantise_chunk<RPW, false, false, true, FULL>(d[gi], mn[gi], mx[gi], len, wave, lane, nullptr,
+                                                                 static_cast<uint8_t*>(codes.p[i]) + base,
+                                                                 static_cast<float*>(minmax.p[i]) + 2 * c, nullptr, KEEP);
+#pragma unroll
+            for (int r = 0; r < RPW; ++r) {
+                const int off = static_cast<int>(wave * RPW + r) * kRow;
+                const int remain = row_remain<FULL>(len, off);
+                h[i][r] = add4(h[i][r], d[gi][r]);
+                own[i][r] = sub4(x[gi][r], h[i][r]);
+                if (remain > 0) store_row(static_cast<float*>(xhat.p[i]) + base + off, lane, remain, h[i][r]);
+            }
+            if (i >= 2) finalize(i - 1);
+        }
+    }
+    finalize(K - 1);
+    if (K > 1) finalize(0);
 }
 
 // ------------------------------------------------------------------------------------------ LP, any number of peers
@@ -211,17 +227,14 @@ __device__ __forceinline__ void ring_mix(const f4 (&left)[RPW], const f4 (&mid)[
 // The same with the peers in a loop, for what the unrolled kernel cannot hold: the first peer's new copy is not kept
 // for the wrap-around but read again at the end (12 bytes per element of a round, mostly from cache), which keeps four
 // rows per wave within 128 VGPRs.  8 peers x 25.6 M elements, C = 16384: 0.71 ms against 0.98 ms in two passes.  Up to
-// 32 rows it is 1-10 % slower than the unrolled kernel (8 peers x 109 M: 3.03 against 2.84 ms).  Requesting the next
-// peer's rows ahead was slower in every launch of more than one workgroup per CU.
+// 32 rows it is 1-10 % slower than the unrolled kernel (8 peers x 109 M: 3.03 against 2.84 ms), except for chunks whose
+// last wave has one row only (see launch_lp_k).  Requesting the next peer's rows ahead was slower in every launch of
+// more than one workgroup per CU.
 template <int RPW>
-__global__ void __launch_bounds__(wg_threads_max(RPW))
-k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
-                  uint32_t chunk, float third, int keep)
+__device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const MutPtrTable& xout, const MutPtrTable& xhat,
+                                                  const MutPtrTable& codes, const MutPtrTable& minmax, int k, size_t base, size_t c,
+                                                  int len, float third, int keep, float (*s_red)[2 * kMaxWaves])
 {
-    __shared__ float s_red[2][2 * kMaxWaves];
-    const size_t c = blockIdx.x;
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     auto x_of = [&](int i) { return static_cast<const float*>(xin.p[i]) + base; };
     auto hat_of = [&](int i) { return static_cast<float*>(xhat.p[i]) + base; };
@@ -250,6 +263,18 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
 #pragma unroll
     for (int r = 0; r < RPW; ++r) x[r] = sub4(x[r], h[r]);
     ring_mix<RPW>(mid, h, right, x, third, out_of(0), len, wave, lane);
+}
+
+template <int RPW>
+__global__ void __launch_bounds__(wg_threads_max(RPW))
+k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
+                  uint32_t chunk, float third, int keep)
+{
+    __shared__ float s_red[2][2 * kMaxWaves];
+    const size_t c = blockIdx.x;
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
 }
 
 // ------------------------------------------------------------------------------------------ LP, one peer
@@ -302,24 +327,37 @@ static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, 
     return launch_status();
 }
 
+// Which instance runs (K peers, chunks of at most 32 rows), all figures by this rule against the other instance:
+//   no tail tests (FULL) in wide chunks: 16 peers x 25.6 M, C = 8192, 1258 -> 1209 us, 8 x 100 M 2578 -> 2500 us, 8 x 2 M
+//     55 -> 49 us; C = 6144, 8 x 100 M, 2672 -> 2501 us; only 4 and 5 peers x 34-134 M at C = 8192 lose 1-3 %;
+//   and in short launches: below 2^21 elements, 8 x 1 M, C = 2048, 30.3 -> 25.5 us, 4 x 1 M, C = 4096, 16.8 -> 15.1 us.
+//     In longer ones chunks up to 4096 elements stream better with the tests, which keep a wave's rows apart: 16 x 3.2 M,
+//     C = 2048, 149 against 159 us, 16 x 25.6 M, C = 4096, 1307 against 1349 us;
+//   two and three peers hold little enough without: 3 x 2 M, C = 6144, 23 against 26 us;
+//   an odd number of rows never fills the last wave; from 8 peers on the loop is then faster than unrolled tail tests: 8 x
+//     25.6 M, C = 5376, 761 -> 704 us, 16 x 25.6 M 1428 -> 1393 us, but 4 x 25.6 M 335 against 364 us.
 template <int K>
 static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtrTable& hat, const MutPtrTable& cd,
                         const MutPtrTable& mm, size_t n, uint32_t chunk, float third, dim3 grid, dim3 block,
                         hipStream_t s)
 {
-#define BAGUA_RING(KEEPv, FOLDv) \
-    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FOLDv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third)
-    // Tail tests folded away (FOLD), so that a wave's loads are in flight together: 16 peers x 25.6 M, C = 8192, 1316 ->
-    // 1265 us, 7 x 8 M 168 -> 164 us, and in short launches: 8 x 1 M, C = 4096, 30.5 -> 27.3 us, 4 x 1 M 16.0 -> 13.6 us.
-    // Chunks up to 4096 elements of longer launches stream better with the tests, which keep a wave's rows apart: 8 x
-    // 25.6 M, C = 4096, 587 against 613 us, 12 x 3 M 138 against 141 us; so do three peers (110 against 112 us, 12.6 M).
-    if (K >= 4 && n < (static_cast<size_t>(1) << (chunk > 4096 ? 26 : 21))) {
-        if (keep_codes(K, n)) BAGUA_RING(1, (K >= 4));
-        else BAGUA_RING(0, (K >= 4));
-    } else {
-        if (keep_codes(K, n)) BAGUA_RING(1, false);
-        else BAGUA_RING(0, false);
+    const bool wide = chunk > kNarrowRows * kRow, odd = chunk % (BAGUA_RPW_LP * kRow) != 0;
+    const int keep = keep_codes(K, n);
+#define BAGUA_RING_KEEP(KEEPv, FULLv, WIDEv)                                                                                  \
+    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third)
+#define BAGUA_RING(FULLv, WIDEv)                   \
+    {                                              \
+        if (keep) BAGUA_RING_KEEP(1, FULLv, WIDEv); \
+        else BAGUA_RING_KEEP(0, FULLv, WIDEv);      \
+        return;                                    \
     }
+    if constexpr (K >= 4) {
+        if (!odd && (wide || n < (static_cast<size_t>(1) << 21))) BAGUA_RING(true, true)
+    }
+    if (!wide) BAGUA_RING(false, false)
+    if constexpr (K < 8) BAGUA_RING(false, true)
+    hipLaunchKernelGGL((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep);
+#undef BAGUA_RING_KEEP
 #undef BAGUA_RING
 }
 

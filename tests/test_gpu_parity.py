@@ -267,9 +267,13 @@ def test_ring_avg_lp(bg, oracle, k, C, n):
 @pytest.mark.parametrize("k,C,n", [(12, 4096, 3 * 4096 + 77), (16, 8192, 2 * 8192 + 300), (13, 7936, 20001),   # unrolled over the peers
                                    (17, 8192, 8192 + 1), (32, 256, 1027), (1, 16384, 16385), (2, 8448, 3 * 8448 - 5),   # loop over the peers
                                    (3, 16384, 40000),
-                                   (4, 4096, (1 << 21) - 4096), (4, 4096, 1 << 21)])   # tail tests folded away below 2^21
+                                   (4, 4096, (1 << 21) - 4096), (4, 4096, 1 << 21),    # tail tests folded away below 2^21
+                                   (16, 512, 5 * 512), (5, 1024, 1023), (4, 2048, 2 * 2048 + 1),   # complete and cut short chunks there
+                                   (3, 8192, 8192 + 3), (7, 5376, 2 * 5376 + 9), (8, 5376, 2 * 5376 + 9),   # odd number of rows
+                                   (9, 4096, 1 << 21), (4, 4352, 4352 - 1), (6, 6144, 3 * 6144 - 256)])
 def test_ring_avg_lp_either_side_of_the_unrolled_range(bg, oracle, k, C, n):
-    """Every peer's codes, statistics, public copy and output over two rounds, around k = 16 and 32 rows per chunk."""
+    """Every peer's codes, statistics, public copy and output over two rounds, around k = 16 and 32 rows per chunk, and for
+    every way a chunk can be cut short."""
     test_ring_avg_lp(bg, oracle, k, C, n)
 
 
