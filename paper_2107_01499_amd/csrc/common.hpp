@@ -54,12 +54,21 @@ __device__ __forceinline__ void st_stream(T* p, T v)
 // Codes: the server step (or the network) reads them next, and the next round overwrites them.  By the code bytes that
 // one call writes, with the hint -> without: MinMax round of 8 workers x 25.6 M, C = 4096, 575 -> 556 us, 2 x 100 M
 // 851 -> 809 us, 16 x 100 M 3968 -> 4036 us, 2 x 300 M 2588 -> 2637 us;
-// intra-node average 2 x 100 M 1113 -> 1035 us; ring of 8 x 25.6 M (205 MB) 660 -> 611 us, of 16 x 25.6 M (409 MB) 1353 -> 1383 us; gossip 8 x
-// 25.6 M 615 -> 574 us, 4 x 100 M 1240 -> 1260 us.  The line for one worker per call is drawn for few workers: what the
+// intra-node average 2 x 100 M 1113 -> 1035 us.  The line for one worker per call is drawn for few workers: what the
 // others write is not known here.
-inline int keep_codes(size_t workers_in_call, size_t n)
+inline int keep_codes(size_t n)
 {
-    return workers_in_call * n <= (static_cast<size_t>(1) << (workers_in_call > 1 ? 28 : 27)) ? 1 : 0;
+    return n <= (static_cast<size_t>(1) << 27) ? 1 : 0;
+}
+
+// The codes of a whole ring or gossip round, `elements` of all peers together.  Other work runs between two rounds, so the
+// line is the one of rounds on buffers that the caches do not hold (three sets in turn).  With the hint -> without: ring of
+// 8, C = 4096, by the codes of the round: 16 MB 47.9 -> 46.9 us, 48 MB 142 -> 135 us, 88 MB 269 -> 255 us, 96 MB 287 -> 284 us,
+// 128 MB 388 -> 403 us, 192 MB 601 -> 619 us; rings of 2, 4 and 16 peers and gossip of 2 to 8 cross at 90 to 105 MB too.
+// (The same round over and over on one set of buffers gains up to 205 MB.)
+inline int keep_codes_of_round(size_t elements)
+{
+    return elements <= (static_cast<size_t>(11) << 23) ? 1 : 0;
 }
 
 // A flattened bucket of n floats, which the compression reads next: 8 workers x 25.6 M elements in 5 buckets 793 -> 766 us,

@@ -247,7 +247,7 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
 #define BAGUA_FC(EFv, WBv)                                                                                       \
     BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, codes,  \
-                                               minmax, bucket_out, keep_codes(1, bucket_numel)))
+                                               minmax, bucket_out, keep_codes(bucket_numel)))
     if (residual && bucket_out) { BAGUA_FC(true, true) }
     else if (residual) { BAGUA_FC(true, false) }
     else if (bucket_out) { BAGUA_FC(false, true) }
@@ -318,10 +318,10 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(1, n)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(n)))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(1, n)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(n)))
     }
     return launch_status();
 }

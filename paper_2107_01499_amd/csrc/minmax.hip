@@ -258,10 +258,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(1, n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(n))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(1, n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(n))))
     }
     return launch_status();
 }
@@ -282,7 +282,7 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
 #define BAGUA_DRR(EFv, OUTv)                                                                                   \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(n, chunk, k),                                  \
                                                 hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv, FOLD>), grid, block, 0, stream, ct, mt, \
-                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out, keep_codes(1, n))))
+                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out, keep_codes(n))))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
     else if (out) { BAGUA_DRR(false, true) }
@@ -304,7 +304,7 @@ int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspac
 #define BAGUA_DRR(EFv, OUTv)                                                                                               \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(table[B] * chunk, chunk, k),                               \
                                                 hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, FOLD, TABLE>), grid, block, 0, \
-                                                                   stream, tab, k, inv_k, ch, keep_codes(1, table[B] * chunk))))
+                                                                   stream, tab, k, inv_k, ch, keep_codes(table[B] * chunk))))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
         else if (with_out) { BAGUA_DRR(false, true) }
@@ -388,10 +388,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(1, total * chunk))))
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(total * chunk))))
         } else {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(1, total * chunk))))
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(total * chunk))))
         }
     });
 }

@@ -342,7 +342,7 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
                         hipStream_t s)
 {
     const bool wide = chunk > kNarrowRows * kRow, odd = chunk % (BAGUA_RPW_LP * kRow) != 0;
-    const int keep = keep_codes(K, n);
+    const int keep = keep_codes_of_round(K * n);
 #define BAGUA_RING_KEEP(KEEPv, FULLv, WIDEv)                                                                                  \
     hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third)
 #define BAGUA_RING(FULLv, WIDEv)                   \
@@ -389,7 +389,7 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
         }
     }
     BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
-                                               third, keep_codes(k, n)))
+                                               third, keep_codes_of_round(k * n)))
     return launch_status();
 }
 
@@ -671,7 +671,7 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
         const int p = peer[i];
         if (peer[p] != i) {                             // chosen by nobody it chose: two passes
             BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, s, x_in[i], xhat[i], n, ch, codes[i],
-                                                       minmax[i], keep_codes(k, n)))
+                                                       minmax[i], keep_codes_of_round(k * n)))
             mix.x[nmix] = x_in[i];
             mix.hat_own[nmix] = xhat[i];
             mix.hat_peer[nmix] = xhat[p];
@@ -692,11 +692,11 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
     }
     if (npairs) {
         BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, 0, s, pairs, n, ch,
-                                                   keep_codes(k, n)))
+                                                   keep_codes_of_round(k * n)))
     }
     if (nsingles) {
         BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch,
-                                                   keep_codes(k, n)))
+                                                   keep_codes_of_round(k * n)))
     }
     if (nmix) {                                         // all public copies are advanced by now
         hipLaunchKernelGGL(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), nmix),
@@ -766,7 +766,7 @@ extern "C" int bagua_lp_encode(const float* x, float* xhat, size_t n, size_t chu
     const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, static_cast<hipStream_t>(stream), x, xhat,
-                                               n, static_cast<uint32_t>(chunk), codes, minmax, keep_codes(1, n)))
+                                               n, static_cast<uint32_t>(chunk), codes, minmax, keep_codes(n)))
     return launch_status();
 }
 

@@ -337,6 +337,35 @@ def test_server_step_long_launch_equals_its_parts(bg):
         assert torch.equal(got, want)
 
 
+# Rounds whose codes are stored past the caches (more than 11 * 2^23 of them) against parts whose codes are kept there.
+@pytest.mark.parametrize("k,C,n,peer", [(16, 8192, 6000001, None), (8, 4096, 12000001, None), (5, 2048, 19000001, None),    # unrolled
+                                        (17, 4096, 5600001, None), (6, 16384, 16000001, None), (9, 5376, 10500001, None),   # loop
+                                        (5, 4096, 19000001, [1, 0, 3, 2, 4]), (5, 8192, 19000001, [4, 2, 1, 3, 0]),        # pairs and a single
+                                        (4, 16384, 24000001, [1, 0, 2, 3]), (5, 2048, 19000001, [1, 2, 0, 4, 3])])         # one-way choices
+def test_long_round_equals_its_parts(bg, k, C, n, peer):
+    g = torch.Generator(device="cuda").manual_seed(k + C + n)
+    nc = bg.num_chunks(n, C)
+    base = torch.empty(n, device="cuda").normal_(0.0, 0.02, generator=g)
+    x = [base + torch.empty(n, device="cuda").normal_(0.0, 1e-3, generator=g) for _ in range(k)]
+    cuts = [0, (n // 3) // C * C, (2 * n // 3) // C * C, n]
+
+    def run(bounds):
+        hat = [base.clone() for _ in range(k)]
+        out = [torch.full((n,), float("nan"), device="cuda") for _ in range(k)]
+        codes = [torch.full((n,), 0xAB, dtype=torch.uint8, device="cuda") for _ in range(k)]
+        mm = [torch.full((2 * nc,), float("nan"), device="cuda") for _ in range(k)]
+        for a, b in zip(bounds, bounds[1:]):
+            part = [[t[a:b] for t in ts] for ts in (x, out, hat, codes)] + [[m[2 * (a // C):2 * bg.num_chunks(b, C)] for m in mm]]
+            if peer is None:
+                bg.bagua_decentralized_avg(bg.AVG_LP_MINMAX_U8, *part, C)
+            else:
+                bg.bagua_decentralized_avg_peers_lp(*part, peer, C)
+        return [t.view(torch.int32) for t in hat + out + mm] + codes
+
+    for got, want in zip(run([0, n]), run(cuts)):
+        assert torch.equal(got, want)
+
+
 # ----------------------------------------------------------------------------- flatten
 def test_flatten_gaps_misaligned_and_tiny(bg, oracle):
     r = np.random.default_rng(0)
