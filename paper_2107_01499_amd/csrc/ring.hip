@@ -166,8 +166,8 @@ k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable code
 }
 
 // ------------------------------------------------------------------------------------------ LP, any number of peers
-// One peer's rows of a chunk: x and the public copy, as they are before the round.  READ_AGAIN: the caller's next launch
-// reads them once more.
+// One peer's rows of a chunk: x and the public copy, as they are before the round.  READ_AGAIN: without the streaming
+// hint, because the caller's next launch reads x and the new public copy, which is stored over the old one.
 template <int RPW, bool READ_AGAIN = false>
 __device__ __forceinline__ void lp_load(const float* x_c, const float* hat_c, int len, int wave, int lane, f4 (&x)[RPW], f4 (&h)[RPW])
 {
@@ -278,12 +278,12 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
 }
 
 // ------------------------------------------------------------------------------------------ LP, one peer
-// d = x - xhat; codes, minmax = Q(d); xhat <- xhat + decode.  x and xhat are loaded without the streaming hint, for the
-// mix that follows: encode + mix of 6.5 M elements 49 -> 47 us, 32 M 218 -> 198 us, 50 M 344 -> 319 us, 130 M 925 -> 898 us.
-template <int RPW>
+// d = x - xhat; codes, minmax = Q(d); xhat <- xhat + decode.  The codes are for other peers, nothing here reads them
+// next: they are streamed past the caches (kept there, encode + mix of 50 M elements takes 320 us instead of 315 us).
+template <int RPW, bool READ_AGAIN>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, uint32_t chunk,
-            uint8_t* __restrict__ codes, float* __restrict__ minmax, int keep)
+            uint8_t* __restrict__ codes, float* __restrict__ minmax)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const size_t c = blockIdx.x;
@@ -291,8 +291,26 @@ k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, 
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     f4 x[RPW], h[RPW];
-    lp_load<RPW, true>(x_in + base, xhat + base, len, wave, lane, x, h);
-    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red, keep);
+    lp_load<RPW, READ_AGAIN>(x_in + base, xhat + base, len, wave, lane, x, h);
+    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red, 0);
+}
+
+// `elements`: of all peers that are encoded before the first mix.  READ_AGAIN pays up to 2^27 of them; without -> with it,
+// encode + mix of one peer: 6.5 M 50.0 -> 46.6 us, 25.6 M 174 -> 158 us, 50 M 332 -> 315 us, 134 M 949 -> 936 us, 300 M 2169 ->
+// 2185 us; 8 workers that all choose one way: 8 x 4 M 173 -> 163 us, 8 x 16 M 633 -> 624 us, 8 x 25 M 959 -> 960 us, 8 x 50 M
+// 1888 -> 1963 us.
+static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk, uint8_t* codes, float* minmax, size_t elements,
+                             hipStream_t stream)
+{
+    const int rows = static_cast<int>(chunk / kRow);
+    const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
+    const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
+    const uint32_t ch = static_cast<uint32_t>(chunk);
+    if (elements <= (static_cast<size_t>(1) << 27)) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+    } else {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+    }
 }
 
 // ------------------------------------------------------------------------------------------ host
@@ -667,11 +685,12 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
     PeerLpJobs pairs{}, singles{};
     PeerMixJobs mix{};
     int npairs = 0, nsingles = 0, nmix = 0;
+    size_t encoded = 0;
+    for (int i = 0; i < k; ++i) encoded += peer[peer[i]] != i;
     for (int i = 0; i < k; ++i) {
         const int p = peer[i];
-        if (peer[p] != i) {                             // chosen by nobody it chose: two passes
-            BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, s, x_in[i], xhat[i], n, ch, codes[i],
-                                                       minmax[i], keep_codes_of_round(k * n)))
+        if (peer[p] != i) {                             // its choice chose somebody else: two passes
+            launch_lp_encode(x_in[i], xhat[i], n, chunk, codes[i], minmax[i], encoded * n, s);
             mix.x[nmix] = x_in[i];
             mix.hat_own[nmix] = xhat[i];
             mix.hat_peer[nmix] = xhat[p];
@@ -762,11 +781,7 @@ extern "C" int bagua_lp_encode(const float* x, float* xhat, size_t n, size_t chu
     if (!rc.disjoint()) return BAGUA_ERR_INVALID_ARG;
     if (num_chunks(n, chunk) > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(xhat) || !aligned16(codes) || !aligned4(minmax)) return BAGUA_ERR_ALIGNMENT;
-    const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
-    dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW>), grid, block, 0, static_cast<hipStream_t>(stream), x, xhat,
-                                               n, static_cast<uint32_t>(chunk), codes, minmax, keep_codes(n)))
+    launch_lp_encode(x, xhat, n, chunk, codes, minmax, n, static_cast<hipStream_t>(stream));
     return launch_status();
 }
 
