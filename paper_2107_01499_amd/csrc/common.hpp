@@ -51,15 +51,19 @@ __device__ __forceinline__ void st_stream(T* p, T v)
 // Except for what the next call of the round reads again while the 256 MB Infinity Cache can still hold it; such data is
 // stored, or loaded the first time, without the hint.
 //
-// Codes: the server step (or the network) reads them next, and the next round overwrites them.  By the code bytes that
-// one call writes, with the hint -> without: MinMax round of 8 workers x 25.6 M, C = 4096, 575 -> 556 us, 2 x 100 M
-// 851 -> 809 us, 16 x 100 M 3968 -> 4036 us, 2 x 300 M 2588 -> 2637 us;
-// intra-node average 2 x 100 M 1113 -> 1035 us.  The line for one worker per call is drawn for few workers: what the
-// others write is not known here.
-inline int keep_codes(size_t n)
+// The codes of one worker's call: the server step (or the network) reads them next, and the next round overwrites them.
+// How many workers follow is not known here, so only the first 2^25 codes of a call are kept: whole MinMax rounds, C = 4096,
+// all streamed -> this -> all kept: 2 workers x 100 M 846 -> 825 -> 806 us, 8 x 50 M 1099 -> 1058 -> 1064 us, 8 x 134 M 2922 ->
+// 2873 -> 2961 us, 16 x 100 M 3949 -> 3937 -> 4034 us, 16 x 134 M 5290 -> 5290 -> 5442 us.  Above 2^27 elements it gains
+// nothing: 2 x 335 M 2906 -> 2936 us.  The value: how many chunks of the launch, from the first on.
+inline uint32_t keep_chunks(size_t n, size_t chunk)
 {
-    return n <= (static_cast<size_t>(1) << 27) ? 1 : 0;
+    return n <= (static_cast<size_t>(1) << 27) ? static_cast<uint32_t>((static_cast<size_t>(1) << 25) / chunk) : 0;
 }
+
+// The server step's codes, which the decode reads next: 2 workers x 100 M 846 -> 833 us for the round, intra-node average and
+// round of 2 x 4 x 134 M 1474 -> 1421 us, 16 x 134 M +-0.
+inline int keep_server_codes(size_t n) { return n <= (static_cast<size_t>(1) << 27) ? 1 : 0; }
 
 // The codes of a whole ring or gossip round, `elements` of all peers together.  Other work runs between two rounds, so the
 // line is the one of rounds on buffers that the caches do not hold (three sets in turn).  With the hint -> without: ring of
@@ -225,7 +229,7 @@ __device__ __forceinline__ f4 load_row(const float* __restrict__ row, int lane, 
     }
     return r;
 }
-// A complete row that is read again soon: without the streaming hint (see keep_codes).
+// A complete row that is read again soon: without the streaming hint (see keep_chunks).
 __device__ __forceinline__ f4 load_row_keep(const float* __restrict__ row, int lane, int remain, float fill)
 {
     if (remain >= kRow) return reinterpret_cast<const f4*>(row)[lane];
@@ -254,7 +258,7 @@ __device__ __forceinline__ uint32_t load_codes_row(const uint8_t* __restrict__ r
         if (e + t < remain) w |= static_cast<uint32_t>(row[e + t]) << (8 * t);
     return w;
 }
-// keep (wave-uniform): without the streaming hint (see keep_codes).
+// keep (wave-uniform): without the streaming hint (see keep_chunks).
 __device__ __forceinline__ void store_codes_row(uint8_t* __restrict__ row, int lane, int remain, uint32_t w, int keep)
 {
     if (remain >= kRow) {

@@ -15,7 +15,7 @@ template <int RPW, bool EF, bool WB>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_flatten_compress_minmax(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile_first, uint32_t T,
                           float* __restrict__ residual, size_t n, uint32_t chunk, uint8_t* __restrict__ codes,
-                          float* __restrict__ minmax, float* __restrict__ bucket_out, int keep)
+                          float* __restrict__ minmax, float* __restrict__ bucket_out, uint32_t keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const size_t c = blockIdx.x;
@@ -55,7 +55,7 @@ k_flatten_compress_minmax(const TensorDesc* __restrict__ desc, const uint32_t* _
         }
     }
     minmax_encode_chunk<RPW, EF, false>(v, len, wave, lane, nwaves, EF ? residual + base : nullptr,
-                                        codes + base, minmax + 2 * c, nullptr, s_red, keep);
+                                        codes + base, minmax + 2 * c, nullptr, s_red, blockIdx.x < keep);
 }
 
 // The same gather in front of the 1-bit sign codec: bagua_bucket_flatten followed by bagua_sign_compress_ef.
@@ -111,7 +111,7 @@ k_flatten_sign_compress(const TensorDesc* __restrict__ desc, const uint32_t* __r
 template <int RPW, bool EF>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restrict__ residual, size_t n, uint32_t chunk,
-                         uint8_t* __restrict__ codes, float* __restrict__ minmax, int keep)
+                         uint8_t* __restrict__ codes, float* __restrict__ minmax, uint32_t keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const size_t c = blockIdx.x;
@@ -160,7 +160,7 @@ k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restric
         }
     }
     minmax_encode_chunk<RPW, EF, false>(v, len, wave, lane, nwaves, EF ? residual + base : nullptr,
-                                        codes + base, minmax + 2 * c, nullptr, s_red, keep);
+                                        codes + base, minmax + 2 * c, nullptr, s_red, blockIdx.x < keep);
 }
 
 // The same intra-node stage in front of the 1-bit sign codec.
@@ -247,7 +247,7 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
 #define BAGUA_FC(EFv, WBv)                                                                                       \
     BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, codes,  \
-                                               minmax, bucket_out, keep_codes(bucket_numel)))
+                                               minmax, bucket_out, keep_chunks(bucket_numel, chunk)))
     if (residual && bucket_out) { BAGUA_FC(true, true) }
     else if (residual) { BAGUA_FC(true, false) }
     else if (bucket_out) { BAGUA_FC(false, true) }
@@ -318,10 +318,10 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(n)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk)))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_codes(n)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk)))
     }
     return launch_status();
 }

@@ -54,7 +54,7 @@ __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ 
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     float* res_c = EF ? residual + base : nullptr;
-    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
+    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))   // so short that all its codes are kept
         compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0, 1);
     else compress_minmax_rows<RPW, EF, false>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, pace, keep);
 }
@@ -62,16 +62,16 @@ __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ 
 template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_minmax(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
-                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace, int keep)
+                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace, uint32_t keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace, keep);
+    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace, blockIdx.x < keep);
 }
 
 // Batched: entry = [x, residual, codes, minmax, n]; unit = chunk.
 template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, int keep)
+k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, uint32_t keep)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const BatchView bv = table.view();
@@ -79,7 +79,7 @@ k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, int keep)
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     compress_minmax_chunk<RPW, EF, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                    table_ptr<uint8_t>(e[2]), table_ptr<float>(e[3]),
-                                   blockIdx.x - bv.first_unit[b], s_red, pace, keep);
+                                   blockIdx.x - bv.first_unit[b], s_red, pace, blockIdx.x < keep);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -258,10 +258,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_codes(n))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk))))
     }
     return launch_status();
 }
@@ -282,7 +282,7 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
 #define BAGUA_DRR(EFv, OUTv)                                                                                   \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(n, chunk, k),                                  \
                                                 hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv, FOLD>), grid, block, 0, stream, ct, mt, \
-                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out, keep_codes(n))))
+                                                                   k, inv_k, eps, n, ch, codes_out, minmax_out, out, keep_server_codes(n))))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
     else if (out) { BAGUA_DRR(false, true) }
@@ -304,7 +304,7 @@ int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspac
 #define BAGUA_DRR(EFv, OUTv)                                                                                               \
     BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_FOLD(drr_minmax_fold(table[B] * chunk, chunk, k),                               \
                                                 hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, FOLD, TABLE>), grid, block, 0, \
-                                                                   stream, tab, k, inv_k, ch, keep_codes(table[B] * chunk))))
+                                                                   stream, tab, k, inv_k, ch, keep_server_codes(table[B] * chunk))))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
         else if (with_out) { BAGUA_DRR(false, true) }
@@ -388,10 +388,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(total * chunk))))
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk))))
         } else {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_codes(total * chunk))))
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk))))
         }
     });
 }
