@@ -74,7 +74,7 @@ __device__ __forceinline__ void sign_encode_chunk(f4 (&v)[RPW], int len, uint32_
     else scale = sum / static_cast<float>(len);
     if (threadIdx.x == 0) *scale_c = scale;
     const float neg = -scale;
-    unrolled<RPW>([&](int i) {
+    auto encode_row = [&](int i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
         const int remain = row_remain<FULL>(len, off);
         if (remain <= 0) return;
@@ -106,7 +106,13 @@ __device__ __forceinline__ void sign_encode_chunk(f4 (&v)[RPW], int len, uint32_
             }
             if (OUT) store_row(out + off, lane, full ? kRow : remain, deq);
         }
-    });
+    };
+    if constexpr (FULL) {
+        unrolled<RPW>(encode_row);
+    } else {   // as a loop: gathered, 8 workers x 7 M elements, C = 2048, 162.5 us with the rows written out, 159 us so
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) encode_row(i);
+    }
 }
 
 }  // namespace bagua
