@@ -213,6 +213,12 @@ __device__ __forceinline__ bool chunk_full(int len, int nwaves)
 {
     return len == RPW * kRow * nwaves;
 }
+// The same for one wave's rows, where no barrier stands in between.
+template <int RPW>
+__device__ __forceinline__ bool wave_full(int len, int wave)
+{
+    return len >= (wave + 1) * RPW * kRow;
+}
 // `remain` = number of valid elements counted from the start of the row (wave-uniform, may be <= 0
 // for an absent row or >= 256 for a full one).  Absent elements read as `fill`.
 __device__ __forceinline__ f4 load_row(const float* __restrict__ row, int lane, int remain, float fill)

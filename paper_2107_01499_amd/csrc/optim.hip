@@ -171,7 +171,7 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
             }
         }
     };
-    if (chunk_full<RPW>(len, blockDim.x >> 6)) load(std::true_type{});   // no tail tests: all loads in flight together
+    if (wave_full<RPW>(len, wave)) load(std::true_type{});   // no tail tests: all loads in flight together
     else load(std::false_type{});
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
@@ -242,7 +242,7 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
             }
         }
     };
-    if (chunk_full<RPW>(len, blockDim.x >> 6)) load(std::true_type{});
+    if (wave_full<RPW>(len, wave)) load(std::true_type{});
     else load(std::false_type{});
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
