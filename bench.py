@@ -395,7 +395,7 @@ class Workload:
         """Rows per wave the library picks for an unbatched worker-side launch (pick_rpw_worker in csrc/common.hpp)."""
         rows = chunk // 256
         rpw = 1 if 6 <= rows <= 8 else 2
-        while rpw < 8 and (rows + rpw - 1) // rpw > 16:
+        while rpw < 4 and (rows + rpw - 1) // rpw > 16:
             rpw *= 2
         return rpw
 

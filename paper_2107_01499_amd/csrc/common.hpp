@@ -106,6 +106,11 @@ inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); 
 #ifndef BAGUA_RPW_LP
 #define BAGUA_RPW_LP 2
 #endif
+// The rows per wave that every BAGUA_DISPATCH_RPW* below has an instance for; a launch with any other value would run the
+// instance of four and leave rows out.
+constexpr bool rpw_built(int rpw) { return rpw == 2 || rpw == 4; }
+static_assert(rpw_built(BAGUA_RPW_COMPRESS) && rpw_built(BAGUA_RPW_DRR) && rpw_built(BAGUA_RPW_SIGN) && rpw_built(BAGUA_RPW_DRR_SIGN) &&
+              rpw_built(BAGUA_RPW_TOPK) && rpw_built(BAGUA_RPW_DRR_TOPK) && rpw_built(BAGUA_RPW_LP), "no kernel instance for this many rows per wave");
 // Peers whose statistics share one barrier in the fused ring kernel.
 #ifndef BAGUA_LP_GROUP
 #define BAGUA_LP_GROUP 1

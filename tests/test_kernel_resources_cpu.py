@@ -1,5 +1,5 @@
-"""Registers of the compiled kernels, read from the metadata of the library that the build made.  A kernel body that is
-rewritten without a change of meaning can still lose a workgroup per CU, or spill."""
+"""Registers of the compiled kernels, read from the metadata of the library that the build made, and the compile-time
+choice of rows per wave.  A kernel body that is rewritten without a change of meaning can still lose a workgroup per CU, or spill."""
 import os
 import re
 import struct
@@ -9,7 +9,8 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2107_01499_amd", "lib", "libbagua_hip.so")
-LLVM = os.path.join(os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"))), "llvm", "bin")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LLVM = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "llvm", "bin")
 
 
 @pytest.fixture(scope="module")
@@ -48,3 +49,11 @@ def test_small_rings_and_pairs_run_at_full_occupancy(kernels, family):
     """64 VGPRs are eight waves per SIMD, four workgroups of 4096-element chunks per CU; with 66 it is three."""
     of = {n: v[0] for n, v in kernels.items() if family in n}
     assert of and max(of.values()) <= 64, of
+
+
+@pytest.mark.parametrize("knob", ["COMPRESS", "DRR", "SIGN", "DRR_SIGN", "TOPK", "DRR_TOPK", "LP"])
+def test_rows_per_wave_without_a_kernel_instance_do_not_build(knob):
+    src = os.path.join(ROOT, "paper_2107_01499_amd", "csrc", "api.hip")
+    cmd = [HIPCC, "--cuda-host-only", "-fsyntax-only", "-I" + os.path.dirname(src), "-I" + os.path.join(ROOT, "include"), src]
+    res = subprocess.run(cmd + ["-DBAGUA_RPW_%s=8" % knob], capture_output=True, text=True)
+    assert res.returncode != 0 and "no kernel instance" in res.stderr
