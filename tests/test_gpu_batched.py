@@ -293,3 +293,40 @@ def test_table_as_argument_and_uploaded(bg, oracle, monkeypatch, step, B):
         torch.cuda.synchronize()
         for b in range(B):
             same(host(out[b]), oracle.bucket_flatten([srcs[b]], [0], NS[b] + 3), "bucket %d" % b)
+
+
+def test_batched_server_step_and_flatten_of_long_launches(bg):
+    """Five workers, C = 2048, 2^25 elements and more in all: the other instance of the MinMax server step.  Buckets of more
+    than 2^27 elements in all: the flatten that streams them past the caches.  Both against bucket-by-bucket calls."""
+    k, C, ns = 5, 2048, [(1 << 24) + 77, 1 << 24, 2048 * 3 + 1]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    codes = [[torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=g) for _ in range(k)] for n in ns]
+    meta = [[torch.empty(2 * bg.num_chunks(n, C), device="cuda").uniform_(0.0, 1e-3, generator=g) for _ in range(k)] for n in ns]
+    for ms in meta:
+        for m in ms:
+            m[0::2].neg_()
+    eps = [torch.empty(n, device="cuda").normal_(0.0, 1e-5, generator=g) for n in ns]
+
+    def outputs():
+        return ([e.clone() for e in eps], [torch.full((n,), 0xAB, dtype=torch.uint8, device="cuda") for n in ns],
+                [torch.full((2 * bg.num_chunks(n, C),), float("nan"), device="cuda") for n in ns], [torch.full((n,), float("nan"), device="cuda") for n in ns])
+
+    e1, c1, m1, o1 = outputs()
+    bg.bagua_decompress_reduce_recompress_batched(bg.CODEC_MINMAX_U8, codes, meta, e1, ns, C, c1, m1, o1, ws_for(bg, len(ns), k))
+    e2, c2, m2, o2 = outputs()
+    for b, n in enumerate(ns):
+        bg.bagua_decompress_reduce_recompress(bg.CODEC_MINMAX_U8, codes[b], meta[b], e2[b], n, C, c2[b], m2[b], o2[b])
+    for got, want in zip(e1 + m1 + o1, e2 + m2 + o2):
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    assert all(torch.equal(a, b) for a, b in zip(c1, c2))
+    del codes, e1, c1, m1, o1, e2, c2, m2, o2
+
+    ns = [(1 << 26) + 4, (1 << 26) + 1000]
+    srcs = [torch.empty(n, device="cuda").normal_(generator=g) for n in ns]
+    plans = [torch.empty(bg.bagua_flatten_workspace_bytes(2, n), dtype=torch.uint8, device="cuda") for n in ns]
+    for s, n, ws in zip(srcs, ns, plans):
+        bg.bagua_flatten_plan([s[:1001], s[1001:]], [0, 1001], n, ws)
+    out = [torch.full((n,), float("nan"), device="cuda") for n in ns]
+    bg.bagua_bucket_flatten_batched_run(plans, [2, 2], out, ws_for(bg, 2))
+    for o, s in zip(out, srcs):
+        assert torch.equal(o.view(torch.int32), s.view(torch.int32))

@@ -341,7 +341,8 @@ def test_server_step_long_launch_equals_its_parts(bg):
 @pytest.mark.parametrize("k,C,n,peer", [(16, 8192, 6000001, None), (8, 4096, 12000001, None), (5, 2048, 19000001, None),    # unrolled
                                         (17, 4096, 5600001, None), (6, 16384, 16000001, None), (9, 5376, 10500001, None),   # loop
                                         (5, 4096, 19000001, [1, 0, 3, 2, 4]), (5, 8192, 19000001, [4, 2, 1, 3, 0]),        # pairs and a single
-                                        (4, 16384, 24000001, [1, 0, 2, 3]), (5, 2048, 19000001, [1, 2, 0, 4, 3])])         # one-way choices
+                                        (4, 16384, 24000001, [1, 0, 2, 3]), (5, 2048, 19000001, [1, 2, 0, 4, 3]),          # one-way choices
+                                        (4, 4096, 34000001, [1, 2, 3, 0])])   # and more than 2^27 elements encoded before the mix
 def test_long_round_equals_its_parts(bg, k, C, n, peer):
     g = torch.Generator(device="cuda").manual_seed(k + C + n)
     nc = bg.num_chunks(n, C)
@@ -363,6 +364,68 @@ def test_long_round_equals_its_parts(bg, k, C, n, peer):
         return [t.view(torch.int32) for t in hat + out + mm] + codes
 
     for got, want in zip(run([0, n]), run(cuts)):
+        assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n,C", [((1 << 25) + 3 * 2048 + 77, 2048), ((1 << 27) + 4096 + 5, 4096)])   # the first 2^25 codes kept; none
+def test_long_compressions_equal_their_parts(bg, n, C):
+    """The momentum form of the sign codec, and the MinMax compression behind the intra-node average and behind the gather."""
+    g = torch.Generator(device="cuda").manual_seed(n + C)
+    x, m = (torch.empty(n, device="cuda").normal_(0.0, 1e-3, generator=g) for _ in range(2))
+    res = torch.empty(n, device="cuda").normal_(0.0, 1e-5, generator=g)
+    nc, cuts = bg.num_chunks(n, C), [0, (n // 5) // C * C, (2 * n // 5) // C * C, (3 * n // 5) // C * C, (4 * n // 5) // C * C, n]
+
+    def run(bounds, call):
+        r, codes = res.clone(), torch.full((n,), 0xAB, dtype=torch.uint8, device="cuda")
+        bits, scale = torch.full(((n + 31) // 32,), 7, dtype=torch.int32, device="cuda"), torch.full((nc,), float("nan"), device="cuda")
+        mm = torch.full((2 * nc,), float("nan"), device="cuda")
+        for a, b in zip(bounds, bounds[1:]):
+            ca, cb = a // C, bg.num_chunks(b, C)
+            call(a, b, r[a:b], codes[a:b], mm[2 * ca:2 * cb], bits[a // 32:(b + 31) // 32], scale[ca:cb])
+        return r.view(torch.int32), codes, mm.view(torch.int32), bits, scale.view(torch.int32)
+
+    def momentum(a, b, r, codes, mm, bits, scale):
+        bg.bagua_momentum_sign_compress_ef(x[a:b], m[a:b], 0.9, r, C, bits, scale)
+
+    def plain(a, b, r, codes, mm, bits, scale):
+        bg.bagua_compress_minmax_u8(x[a:b], r, C, codes, mm)
+
+    def reduced(a, b, r, codes, mm, bits, scale):     # the mean of x and x is x
+        bg.bagua_reduce_compress_minmax_u8([x[a:b], x[a:b]], r, C, codes, mm)
+
+    def gathered(a, b, r, codes, mm, bits, scale):
+        ws = torch.empty(bg.bagua_flatten_workspace_bytes(2, b - a), dtype=torch.uint8, device="cuda")
+        half = (b - a) // 2 // 64 * 64
+        bg.bagua_flatten_plan([x[a:a + half], x[a + half:b]], [0, half], b - a, ws)
+        bg.bagua_flatten_compress_minmax_u8(ws, 2, r, b - a, C, codes, mm)
+        torch.cuda.synchronize()                      # ws is given back
+
+    want = run(cuts, momentum)
+    assert all(torch.equal(a, b) for a, b in zip(run([0, n], momentum), want))
+    want = run(cuts, plain)
+    for call in (plain, reduced, gathered):
+        for bounds in ([0, n], cuts):
+            assert all(torch.equal(a, b) for a, b in zip(run(bounds, call), want)), (call.__name__, len(bounds))
+
+
+@pytest.mark.parametrize("k,C,n", [(2, 4096, (1 << 27) + 4096 + 5)])   # the server step's codes are kept up to 2^27 of them
+def test_server_step_beyond_the_kept_codes(bg, k, C, n):
+    g = torch.Generator(device="cuda").manual_seed(11)
+    nc = bg.num_chunks(n, C)
+    codes = [torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=g) for _ in range(k)]
+    meta = [torch.empty(2 * nc, device="cuda").uniform_(0.0, 1e-3, generator=g) for _ in range(k)]
+    for m in meta:
+        m[0::2].neg_()
+
+    def step(bounds):
+        c, m = torch.full((n,), 0xAB, dtype=torch.uint8, device="cuda"), torch.full((2 * nc,), float("nan"), device="cuda")
+        for a, b in zip(bounds, bounds[1:]):
+            ma, mb = 2 * (a // C), 2 * bg.num_chunks(b, C)
+            bg.bagua_decompress_reduce_recompress(bg.CODEC_MINMAX_U8, [x[a:b] for x in codes], [x[ma:mb] for x in meta], None, b - a, C,
+                                                  c[a:b], m[ma:mb])
+        return c, m.view(torch.int32)
+
+    for got, want in zip(step([0, n]), step([0, n // 2 // C * C, n])):
         assert torch.equal(got, want)
 
 
