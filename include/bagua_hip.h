@@ -262,8 +262,9 @@ int bagua_decentralized_avg_peers(const float* const* x_in, float* const* x_out,
  * of Section 3.4; the compressed-difference reading used by bagua_decentralized_avg in LP mode):
  *   codes[i], minmax[i] = Q(x_in[i] - xhat[i])  (no error feedback);  xhat[i] <- xhat[i] + decode(codes[i]);
  *   x_out[i] = (xhat[i] + xhat[peer[i]]) * 0.5f + (x_in[i] - xhat[i])        with the updated xhat.
- *   peer    host[k], peer[i] in [0,k).  When the map is a perfect matching (peer[i] != i, peer[peer[i]] == i for
- *           all i) and chunk <= 4096 each pair is processed in one pass; any other map takes two passes.
+ *   peer    host[k], peer[i] in [0,k).  A matched pair (peer[peer[i]] == i) and a worker that is its own peer are
+ *           processed in one pass, whatever the others choose and for any chunk length; only a worker whose peer
+ *           chose somebody else takes two passes.
  *   x_in, x_out, xhat, codes, minmax as in bagua_decentralized_avg (LP mode); same aliasing and alignment rules.
  */
 int bagua_decentralized_avg_peers_lp(const float* const* x_in, float* const* x_out, float* const* xhat,

@@ -74,7 +74,7 @@ inline void batch_fill_lut(uint64_t* table, size_t B, size_t entry_words)
 }
 
 // A whole table as a kernel argument: an upload launch in front of the call takes 1.4-5 us and a gap.  8 workers x 5
-// buckets of 25.6 M elements in all (17 batched calls): 856 -> 826 us; 4 workers x 5 buckets of 1 M: 99 -> 69 us.  The
+// buckets of 25.6 M elements in all (17 batched calls): 868 -> 838 us; 4 workers x 5 buckets of 1 M: 99 -> 69 us.  The
 // limit keeps the launch below the 4 KiB of kernel arguments: 58 buckets of a compression, 21 of a server step with
 // eight workers.  The kernels read it through the scalar cache as they read a table in memory.
 constexpr int kInlineWords = 480;

@@ -48,8 +48,9 @@ __device__ __forceinline__ void st_stream(T* p, T v)
 #endif
 }
 
-// Except for what the next call of the round reads again while the 256 MB Infinity Cache can still hold it; such data is
-// stored, or loaded the first time, without the hint.
+// Except for what the next call of the round reads again, as long as the 256 MB Infinity Cache makes that faster; such data
+// is stored, or loaded the first time, without the hint.  The lines below are measured crossovers of whole rounds; they are
+// not the cache's capacity, a part of which helps too.
 //
 // The codes of one worker's call: the server step (or the network) reads them next, and the next round overwrites them.
 // How many workers follow is not known here, so only the first 2^25 codes of a call are kept: whole MinMax rounds, C = 4096,
@@ -76,7 +77,8 @@ inline int keep_codes_of_round(size_t elements)
 }
 
 // A flattened bucket of n floats, which the compression reads next: 8 workers x 25.6 M elements in 5 buckets 793 -> 766 us,
-// 4 x 60 M 914 -> 869 us, 4 x 130 M 2153 -> 2115 us for the whole round.  (The momentum that every worker's sign compression
+// 4 x 60 M 914 -> 869 us, 4 x 130 M 2153 -> 2115 us for the whole round; above the line 8 x 160 M 4768 -> 4921 us, 4 x 200 M
+// 3227 -> 3307 us, 2 x 160 M +-0.  (The momentum that every worker's sign compression
 // reads, 8 x 6.5 M elements 183 -> 163 us, 8 x 25.6 M 637 -> 580 us, but 4 x 100 M 1379 -> 1395 us, is loaded without
 // the hint in short launches; see also k_lp_encode.)
 inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); }

@@ -588,9 +588,12 @@ struct PeerLpJobs {
 };
 
 // Job after job over blockIdx.y, so that only one pair's ten streams are interleaved.  7 workers x 25.6 M elements
-// (three pairs and a single), C = 4096: 0.53 ms; encode + mix in two passes 0.83 ms.
+// (three pairs and a single), C = 4096: 0.50 ms; encode + mix in two passes 0.83 ms.
+// Two rows per wave are held in 64 VGPRs, eight waves per SIMD; the compiler would take 70.  Up to C = 6144 that is +-1 %.  At
+// C = 8192 it is two workgroups per CU instead of one: 8 x 1 M 27.9 -> 24.4 us, 2 x 6.5 M 45.3 -> 41.3 us, 4 x 12 M +-0, but
+// 4 x 25.6 M 303 -> 314 us and 8 x 100 M 2477 -> 2569 us.
 template <int RPW, bool PAIR>
-__global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)   // two rows per wave fit 64 VGPRs: full occupancy
+__global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)
 k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk, int keep)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
