@@ -390,34 +390,17 @@ class Workload:
                "compress_topk": U * k, "drr_topk": U, "decompress_unflatten": U * k, "flatten_sign_compress": U * k}
         return {p: per[p] for p in self.prims}
 
-    @staticmethod
-    def _rpw_worker(chunk):
-        """Rows per wave the library picks for an unbatched worker-side launch (pick_rpw_worker in csrc/common.hpp)."""
-        rows = chunk // 256
-        rpw = 1 if 6 <= rows <= 8 else 2
-        while rpw < 4 and (rows + rpw - 1) // rpw > 16:
-            rpw *= 2
-        return rpw
-
     def placement_note(self):
         over = self._placer.overflow if self._placer is not None else 0
         return self.placement + (" (%d tensors did not fit into the reservation and lie where the allocator put them)" % over if over else "")
 
     def kernel_name(self, p):
+        """The kernel function; which of its template instances runs is the library's choice by size."""
         if self.batched and p in ("flatten", "compress_minmax", "drr_minmax", "sign_compress", "drr_sign"):
-            return {"flatten": "k_flatten_batched", "compress_minmax": "k_compress_minmax_batched<2,true>",
-                    "drr_minmax": "k_drr_minmax_batched<4,true,true>", "sign_compress": "k_sign_compress_batched<2,true>",
-                    "drr_sign": "k_drr_sign_batched<2,true,true>"}[p]
-        return {"flatten": "k_flatten", "flatten_compress": "k_flatten_compress_minmax<2,true,%s>" %
-                ("true" if "sign_compress" in self.prims else "false"), "compress_minmax": "k_compress_minmax<%d,true>" % self._rpw_worker(self.C),
-                "drr_minmax": "k_drr_minmax<4,true,true>", "ring_fp": "k_ring_avg_fp<%d>" % self.k,
-                "ring_lp": "k_ring_avg_lp<%d,2>" % self.k, "sign_compress": "k_sign_compress<%d,true,false>" % self._rpw_worker(self.SC),
-                "drr_sign": "k_drr_sign<2,true,true>", "sgd_step": "k_decompress_sgd<0,true,false>",
-                "adam_step": "k_decompress_adam<0,false,false>", "momentum_sign": "k_sign_compress<%d,true,true>" % self._rpw_worker(self.SC),
-                "adam_frozen_step": "k_decompress_adam<1,true,false>",
-                "peer_fp": "k_peer_avg_fp", "peer_lp": "k_peer_avg_lp<2>", "lp_encode": "k_lp_encode<2>", "lp_apply_mix": "k_lp_apply_mix<true,true,false>", "reduce_compress": "k_reduce_compress_minmax<2,true>",
-                "compress_topk": "k_compress_topk<4,true>", "drr_topk": "k_drr_topk<4,true,true>",
-                "decompress_unflatten": "k_decompress_unflatten<0>", "flatten_sign_compress": "k_flatten_sign_compress<2,true,false>"}[p]
+            return "k_%s_batched" % p
+        return {"flatten_compress": "k_flatten_compress_minmax", "ring_fp": "k_ring_avg_fp", "ring_lp": "k_ring_avg_lp", "sgd_step": "k_decompress_sgd",
+                "adam_step": "k_decompress_adam", "momentum_sign": "k_sign_compress", "adam_frozen_step": "k_decompress_adam",
+                "peer_fp": "k_peer_avg_fp", "peer_lp": "k_peer_avg_lp", "reduce_compress": "k_reduce_compress_minmax"}.get(p, "k_" + p)
 
     # ---- one pass of the hot path ------------------------------------------------------------------
     def step(self, marks=None):
@@ -835,17 +818,23 @@ def ceilings(torch, bg):
 
 
 def read_traffic(workload, kernel):
-    """HBM bytes per launch of `kernel` from the committed rocprofv3 counter summary of this workload, if there is
-    one: profiles/traffic_<workload>.txt, lines `traffic_bytes_per_launch <kernel> <bytes>`."""
+    """HBM bytes per launch of `kernel` from the committed rocprofv3 counter summary of this workload, if there is one and
+    it was taken with this library: profiles/traffic_<workload>.txt, lines `traffic_bytes_per_launch <kernel> <bytes>` and
+    `source_sha16 <hash>`.  Returns (bytes or None, why not)."""
     path = os.path.join(ROOT, "profiles", "traffic_%s.txt" % workload)
+    fields = {}
     try:
-        for line in open(path):
-            f = line.split()
-            if len(f) == 3 and f[0] == "traffic_bytes_per_launch" and f[1] == kernel:
-                return float(f[2])
+        with open(path) as f:
+            for line in f:
+                w = line.split()
+                if len(w) in (2, 3) and w[0] in ("traffic_bytes_per_launch", "source_sha16"):
+                    fields.setdefault(" ".join(w[:-1]), w[-1])
     except OSError:
-        pass
-    return None
+        return None, "no counters committed for this block"
+    if fields.get("source_sha16") != source_hash():
+        return None, "the committed counters were taken with other sources of the library"
+    value = fields.get("traffic_bytes_per_launch " + kernel)
+    return (float(value), None) if value else (None, "no counters committed for this kernel")
 
 
 def source_hash():
@@ -898,13 +887,15 @@ def run_block(torch, bg, args, name, layout, only, extras):
     dom = max(prims, key=lambda p: prim_ms[p])
     dom_t = prim_ms[dom] * 1e-3 / nl[dom]
     achieved = ab[dom] / nl[dom] / dom_t / 1e9
-    traffic = read_traffic(name, wl.kernel_name(dom)) if layout == "flat" else None
+    traffic, why_not = read_traffic(name, wl.kernel_name(dom)) if layout == "flat" else (None, "counters are taken in the flat layout")
     roof = {"bound": "hbm", "kernel": wl.kernel_name(dom), "primitive": dom, "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "avg_launch_us": round(dom_t * 1e6, 3), "algorithmic_bytes_per_launch": ab[dom] / nl[dom]}
     if traffic is not None:
         roof["traffic_source"] = ("profiles/traffic_%s.txt: rocprofv3 FETCH_SIZE + WRITE_SIZE of an earlier run of this "
                                   "workload, scaled by what the same counters read for k_flatten (a copy of known size)" % name)
+    else:
+        roof["traffic_source"] = why_not
     launch = {"flat": "one launch per worker over all its buckets (contiguous)", "per_bucket": "one launch per bucket",
               "buckets": "separately allocated buckets, one batched launch per worker"}[layout]
     block = {"workload": "%s; %d buckets, %d padded elements per worker, %d simulated workers, chunk %d (sign codec %d); "

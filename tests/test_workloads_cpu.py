@@ -70,3 +70,19 @@ def test_bench_default_plan_names_the_largest_configurations():
     assert sorted(prims) == sorted(bench.ALL_PRIMS)          # every primitive exactly once in the headline
     assert bench.WORKLOADS["bert_large"]["k"] == 16 and bench.WORKLOADS["bert_large"]["chunk"] == 8192
     assert bench.WORKLOADS["onebit"]["sign_chunk"] == 2048 and bench.ONEBIT_N == 1500000000
+
+
+def test_bench_reports_counters_of_the_loaded_sources_only(tmp_path, monkeypatch):
+    """A summary of hardware counters that was taken with other sources, or names no source, is not reported."""
+    import bench
+    (tmp_path / "profiles").mkdir()
+    path = tmp_path / "profiles" / "traffic_w.txt"
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "source_hash", lambda: "0123456789abcdef")
+    assert bench.read_traffic("w", "k_a")[0] is None
+    path.write_text("traffic_bytes_per_launch k_a 1024\n")
+    assert bench.read_traffic("w", "k_a")[0] is None
+    path.write_text("source_sha16 fedcba9876543210\ntraffic_bytes_per_launch k_a 1024\n")
+    assert bench.read_traffic("w", "k_a")[0] is None
+    path.write_text("source_sha16 0123456789abcdef\ntraffic_bytes_per_launch k_a 1024\n")
+    assert bench.read_traffic("w", "k_a") == (1024.0, None) and bench.read_traffic("w", "k_b")[0] is None
