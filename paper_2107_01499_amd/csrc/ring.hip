@@ -72,7 +72,7 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 // p-1, p, p+1 exist, so only a short window of peers is live in registers at any time.
 // Bound by the memory system's rate for 5 K interleaved streams.  Unrolled over the peers (the compiler moves the
 // next peer's loads up) for K <= 16 and up to 32 rows, i.e. 16 waves of two rows.  16 peers x 25.6 M elements, C = 8192:
-// 1.25 ms (5.6 TB/s); encode per peer + a mixing pass over the public copies, 25 bytes per element per peer, took 1.81 ms.
+// 1.22 ms (5.7 TB/s); encode per peer + a mixing pass over the public copies, 25 bytes per element per peer, took 1.81 ms.
 //
 // The unrolled body stands here once, in the kernel itself.  Two of them (with and without tail tests) do not fit the
 // instruction cache, which short launches pay for, and a body called through a lambda is scheduled differently.  Before
