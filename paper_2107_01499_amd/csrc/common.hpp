@@ -140,6 +140,14 @@ constexpr int wg_threads_max(int rpw)
 }
 static_assert(wg_threads_max(1) <= 1024 && wg_threads_max(2) <= 1024 && 4 * kMaxWaves >= 64, "four rows per wave hold any chunk");
 
+// A kernel that moves many streams at once is fastest with no more waves on a CU than keep the memory busy: what is in
+// flight beyond that only spreads the accesses over more DRAM pages at a time (most of all where the streams lie close
+// together in HBM).  Such a launch asks for LDS that it does not use, so that at most `groups` of its workgroups fit a
+// CU: the largest multiple of the allocation's granule that leaves room for them.
+constexpr size_t kLdsPerCu = 160 * 1024, kLdsGranule = 1280;
+constexpr size_t lds_for_residency(int groups) { return kLdsPerCu / kLdsGranule / static_cast<size_t>(groups) * kLdsGranule; }
+static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets without asking the runtime for more");
+
 struct PtrTable {
     const void* p[BAGUA_MAX_WORKERS];
 };
