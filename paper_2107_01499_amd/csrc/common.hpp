@@ -86,7 +86,7 @@ inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); 
 // Preferred rows (of 256 elements) per wave for each chunked kernel (compile-time tuning knobs).
 // Measured on MI355X: two rows per wave (512 elements, 8 waves for a 4096-element chunk) stream
 // fastest in the worker-side kernels, the fused ring kernel and the sign codec's server kernel; the MinMax
-// server kernel and the top-K kernels prefer four.  Larger values are used only when a chunk would need more than 16 waves.
+// and the top-K server kernels prefer four.  Larger values are used only when a chunk would need more than 16 waves.
 #ifndef BAGUA_RPW_COMPRESS
 #define BAGUA_RPW_COMPRESS 2
 #endif
@@ -100,7 +100,7 @@ inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); 
 #define BAGUA_RPW_DRR_SIGN 2
 #endif
 #ifndef BAGUA_RPW_TOPK
-#define BAGUA_RPW_TOPK 4
+#define BAGUA_RPW_TOPK 2
 #endif
 #ifndef BAGUA_RPW_DRR_TOPK
 #define BAGUA_RPW_DRR_TOPK 4
@@ -195,6 +195,41 @@ __device__ __forceinline__ void unrolled(const F& f)
 }
 
 // ---------------------------------------------------------------- wave-level reductions
+// Exchanges between lanes on the vector ALU (data-parallel primitives).
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;              // quad_perm [1,0,3,2] and [2,3,0,1]: lane l reads l xor 1, l xor 2
+constexpr int kHalfMirror = 0x141, kMirror = 0x140;    // 7 - l in each half row, 15 - l in each row of 16 lanes
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118;   // lane l reads l - 1, ... of its row, or 0
+constexpr int kBcast15 = 0x142, kBcast31 = 0x143;      // lane 15 of the row before; lane 31 into rows 2 and 3
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __uint_as_float(dpp<CTRL>(__float_as_uint(v)));
+}
+// op over the lane's row of 16, in every lane of the row: with xor 1, 2 the four lanes of a quad hold the same value, so
+// the half mirror reads what lane l xor 4 holds, and the mirror then what lane l xor 8 holds.
+template <typename T, typename F>
+__device__ __forceinline__ T row16_reduce(T v, const F& op)
+{
+    v = op(v, dpp<kXor1>(v));
+    v = op(v, dpp<kXor2>(v));
+    v = op(v, dpp<kHalfMirror>(v));
+    return op(v, dpp<kMirror>(v));
+}
+// op over the wave: the butterfly of xor 1, 2, 4, 8, 16, 32, for a commutative op bit for bit.  Rows 1 and 3 add their
+// neighbour, row 3 then rows 0 and 1 together; lane 63 has the result (the lanes that no row reaches read 0 and are not used).
+template <typename T, typename F>
+__device__ __forceinline__ T wave_reduce(T v, const F& op)
+{
+    v = row16_reduce(v, op);
+    v = op(v, dpp<kBcast15>(v));
+    v = op(v, dpp<kBcast31>(v));
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
 __device__ __forceinline__ float wave_min(float v)
 {
 #pragma unroll

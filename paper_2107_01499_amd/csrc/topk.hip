@@ -2,212 +2,232 @@
 // compression the paper names when it motivates error compensation, Section 3.2): worker-side
 // compress with error feedback, server-side decompress-average-recompress, and decompress.
 //
-// Selection of the K largest |v| of a chunk (ties: lower index) without sorting: the chunk stays in
-// registers; a 4-pass radix select over the IEEE bit pattern of |v| (256-bin histograms in LDS,
-// integer atomics only, so the result does not depend on execution order) finds the K-th largest
-// magnitude T and how many elements equal to T are still needed; one packed prefix count in index
-// order (DPP scans on the vector ALU + one LDS exchange between waves) then gives every kept element
-// its output slot.  The first digit is the sign-stripped exponent, which takes only a handful of
-// values inside a chunk: its counters are replicated 16 times, interleaved over the LDS banks, so that
-// equal digits from the lanes of one wave do not serialise on one address.
+// Selection of the K largest |v| of a chunk (ties: lower index) without sorting: the chunk stays in registers and is
+// counted by the distance of each magnitude (as an integer: the bit pattern of |v|) below the chunk's largest one.  A
+// first histogram of 64 bins per binade finds the bin with the K-th largest magnitude; as long as that bin holds more
+// elements than are still needed, it alone is counted again, eight bits finer.  Integer atomics in LDS only, so the
+// result does not depend on execution order.  The kept elements' output slots come from ballots and bit counts.
 #include "launchers.hpp"
 
 #pragma clang fp contract(off)
 
 namespace bagua {
 
-#ifndef BAGUA_TOPK_COPIES
-#define BAGUA_TOPK_COPIES 16
-#endif
-constexpr int kCopies = BAGUA_TOPK_COPIES;  // interleaved copies of the first-pass histogram (spreads equal digits over banks)
-constexpr int kTopkLdsWords = 256 * kCopies + 4 * 256 + kMaxWaves;
+// Bins of the first histogram: distances in units of 2^17 = 64 bins per binade, the four binades below the largest
+// magnitude; what lies below is not counted, and looked at only if the bins do not reach the K-th.  Counted in a last
+// bin instead, where many lanes of a wave meet in one counter, a short launch (1 M elements, one workgroup per CU) took
+// 8.9 us instead of 7.2; two or four copies of the bins gained nothing.
+constexpr int kFirstShift = 17, kFirstBins = 256;
+constexpr int kNextBits = 8, kNextBins = 1 << kNextBits;
+constexpr int kHistWords = kFirstBins + 2 * kNextBins;
+constexpr int kTopkLdsWords = kHistWords + 2 * kMaxWaves;
 
 __device__ __forceinline__ uint32_t mag_key(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
-// Inclusive prefix sum over the 64 lanes on the vector ALU only: DPP row shifts inside each row of
-// 16 lanes, then the totals of the lower rows are added from lanes 15, 31 and 47.
-__device__ __forceinline__ uint32_t wave_prefix_incl(uint32_t x, int lane)
+struct OpMaxU { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; } };
+struct OpAddU { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
+
+// Inclusive prefix sum over the 64 lanes.
+__device__ __forceinline__ uint32_t wave_prefix_incl(uint32_t x)
 {
-    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x111, 0xf, 0xf, true));  // row_shr:1
-    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x112, 0xf, 0xf, true));  // row_shr:2
-    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x114, 0xf, 0xf, true));  // row_shr:4
-    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x118, 0xf, 0xf, true));  // row_shr:8
-    const uint32_t t0 = __builtin_amdgcn_readlane(static_cast<int>(x), 15);
-    const uint32_t t1 = __builtin_amdgcn_readlane(static_cast<int>(x), 31);
-    const uint32_t t2 = __builtin_amdgcn_readlane(static_cast<int>(x), 47);
-    const int row = lane >> 4;
-    return x + (row >= 1 ? t0 : 0u) + (row >= 2 ? t1 : 0u) + (row >= 3 ? t2 : 0u);
+    x += dpp<kShr1>(x);
+    x += dpp<kShr2>(x);
+    x += dpp<kShr4>(x);
+    x += dpp<kShr8>(x);
+    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), kBcast15, 0xa, 0xf, false));   // rows 1 and 3
+    x += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), kBcast31, 0xc, 0xf, false));   // rows 2 and 3
+    return x;
 }
 
-// All lanes of a wave: D = largest digit whose suffix count sum_{d >= D} h[d] reaches `need`,
-// above = sum_{d > D} h[d].  Requires 1 <= need <= sum of all bins.
-__device__ __forceinline__ void find_digit(const uint32_t* h, int lane, uint32_t need, uint32_t& D, uint32_t& above)
+// All lanes of a wave: bin = first of the 256 bins up to which the counts reach `need`, before = their sum below it,
+// in_bin = its count.  If all of them together do not reach `need`, bin = 256, before = their sum and in_bin = 0.
+__device__ __forceinline__ void find_bin(const uint32_t* h, int lane, uint32_t need, uint32_t& bin, uint32_t& before, uint32_t& in_bin)
 {
-    const uint4 hb = *reinterpret_cast<const uint4*>(h + 4 * lane);
-    const uint32_t c = hb.x + hb.y + hb.z + hb.w;
-    const uint32_t pre = wave_prefix_incl(c, lane);
-    const uint32_t total = __builtin_amdgcn_readlane(static_cast<int>(pre), 63);
-    const uint32_t suffix = total - pre + c;             // sum over lanes >= this one
-    const unsigned long long ok = __ballot(suffix >= need);  // lanes 0..L (suffix sums do not increase with the lane)
-    const int L = 63 - __builtin_clzll(ok);
-    uint32_t t = __builtin_amdgcn_readlane(static_cast<int>(suffix - c), L);  // everything above lane L's four bins
-    const uint32_t b3 = __builtin_amdgcn_readlane(static_cast<int>(hb.w), L);
-    const uint32_t b2 = __builtin_amdgcn_readlane(static_cast<int>(hb.z), L);
-    const uint32_t b1 = __builtin_amdgcn_readlane(static_cast<int>(hb.y), L);
-    if (t + b3 >= need) {
-        D = 4 * L + 3;
-    } else {
-        t += b3;
-        if (t + b2 >= need) {
-            D = 4 * L + 2;
-        } else {
-            t += b2;
-            if (t + b1 >= need) {
-                D = 4 * L + 1;
-            } else {
-                t += b1;
-                D = 4 * L;
-            }
-        }
+    const uint4 b = reinterpret_cast<const uint4*>(h)[lane];
+    const uint32_t c = b.x + b.y + b.z + b.w;
+    const uint32_t pre = wave_prefix_incl(c);
+    const unsigned long long reached = __ballot(pre >= need);
+    if (reached == 0) {
+        bin = 4 * kWave;
+        before = __builtin_amdgcn_readlane(static_cast<int>(pre), 63);
+        in_bin = 0;
+        return;
     }
-    above = t;
+    const int L = __builtin_ctzll(reached);   // the lane whose four bins hold it
+    const uint32_t below = __builtin_amdgcn_readlane(static_cast<int>(pre - c), L);
+    const uint32_t own = h[4 * L + (lane & 3)];
+    uint32_t run = own;   // inclusive sums over lanes 0..3; the others are not looked at
+    run += dpp<kShr1>(run);
+    run += dpp<kShr2>(run);
+    const int q = __builtin_ctzll(__ballot(below + run >= need));
+    bin = static_cast<uint32_t>(4 * L + q);
+    in_bin = __builtin_amdgcn_readlane(static_cast<int>(own), q);
+    before = below + __builtin_amdgcn_readlane(static_cast<int>(run), q) - in_bin;
 }
 
-// Zero the histograms (128-bit LDS stores) and synchronise.  Called while the chunk's global loads are
-// still in flight, so the clear costs no extra latency.
-__device__ __forceinline__ void topk_clear_lds(uint32_t* smem)
+__device__ __forceinline__ void topk_clear(uint32_t* hist, int words)
 {
-    static_assert((256 * kCopies + 4 * 256) % 4 == 0, "histogram words come in groups of four");
-    uint4* q = reinterpret_cast<uint4*>(smem);
-    for (int t = threadIdx.x; t < (256 * kCopies + 4 * 256) / 4; t += blockDim.x) q[t] = uint4{0u, 0u, 0u, 0u};
-    __syncthreads();
+    for (int t = threadIdx.x; t < words / 4; t += blockDim.x) reinterpret_cast<uint4*>(hist)[t] = uint4{0u, 0u, 0u, 0u};
 }
 
-// Encode the chunk held in v (absent elements are ignored).  idx_c/val_c point at the chunk's `keep`
-// output slots, residual/out at the chunk's first element (nullptr = not wanted).
-// smem: kTopkLdsWords words of LDS, cleared by topk_clear_lds (all waves must have passed its barrier).
-// FULL: every row of every wave of the workgroup is complete (len == RPW * 256 * nwaves), so no element needs a validity
-// test.
-template <int RPW, bool FULL>
-__device__ __forceinline__ void topk_encode_rows(const f4 (&v)[RPW], int len, uint32_t keep, int wave, int lane,
-                                                  int nwaves, float* __restrict__ residual,
-                                                  uint16_t* __restrict__ idx_c, float* __restrict__ val_c,
-                                                  float* __restrict__ out, uint32_t* smem)
+// Number of lanes below this one with their bit set, added to acc.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_t acc)
 {
-    uint32_t* copies = smem;                  // [256][kCopies], first pass only
-    uint32_t* hist = smem + 256 * kCopies;    // [4][256]
-    uint32_t* tot = hist + 4 * 256;
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), acc));
+}
+
+// What bounds it: HBM from 2048-element chunks on (12.2 bytes per element at 5.9 TB/s for 25.7 M elements), below that the
+// waves per CU.  Before (four radix passes from the exponent down, its histogram in 16 copies: 20 KB of LDS per chunk, seven
+// barriers, 122 vector instructions per element of a lane against 52) -> now, whole rounds: 3 workers x 33 M, C = 1024, 582
+// -> 398 us, 12 x 2.6 M, C = 2048, 144 -> 116 us, 8 x 25.7 M, C = 4096, 543 -> 530 us, 4 x 25.6 M, C = 16384, 574 -> 409 us.
+//
+// Encode the chunk held in v (absent elements must be +0.0f).  idx_c/val_c point at the chunk's `keep` output slots,
+// residual/out at the chunk's first element (nullptr = not wanted).
+// smem: kTopkLdsWords words of LDS, the first kHistWords of them cleared (no barrier needed in between).
+template <int RPW>
+__device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, uint32_t keep, int wave, int lane, int nwaves,
+                                                  float* __restrict__ residual, uint16_t* __restrict__ idx_c,
+                                                  float* __restrict__ val_c, float* __restrict__ out, uint32_t* smem)
+{
+    uint32_t* first = smem;
+    uint32_t* next = smem + kFirstBins;   // two of them, used in turn
+    uint32_t* s_top = smem + kHistWords;
+    uint32_t* s_count = s_top + kMaxWaves;
     const uint32_t keff = (static_cast<int>(keep) < len) ? keep : static_cast<uint32_t>(len);
 
-    uint32_t key[RPW][4];
-    bool valid[RPW][4];
+    // ---- the largest magnitude of the chunk, and every element's distance below it (absent elements: beyond all others)
+    uint32_t top = 0;
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
-        const int e0 = static_cast<int>(wave * RPW + i) * kRow + lane * 4;
+        top = OpMaxU{}(OpMaxU{}(top, mag_key(v[i].x)), mag_key(v[i].y));
+        top = OpMaxU{}(OpMaxU{}(top, mag_key(v[i].z)), mag_key(v[i].w));
+    }
+    top = wave_reduce(top, OpMaxU{});
+    if (lane == 0) s_top[wave] = top;
+    __syncthreads();
+    if (nwaves > 1) {
+        if ((lane & (kMaxWaves - 1)) < nwaves) top = s_top[lane & (kMaxWaves - 1)];
+        top = __builtin_amdgcn_readfirstlane(static_cast<int>(row16_reduce(top, OpMaxU{})));
+    }
+    uint32_t dist[RPW][4];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
         const float el[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            key[i][e] = mag_key(el[e]);
-            valid[i][e] = FULL || e0 + e < len;
-        }
+        for (int e = 0; e < 4; ++e) dist[i][e] = top - mag_key(el[e]);
+    }
+    if (!wave_full<RPW>(len, wave)) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((wave * RPW + i) * kRow + lane * 4 + e >= len) dist[i][e] = 0xffffffffu;
     }
 
-    // ---- radix select: threshold key T and the number R of elements equal to T that are kept.
-    // First digit (sign-stripped exponent): values of one chunk share a handful of exponents, so equal
-    // digits are spread over kCopies interleaved counters to keep the LDS atomics from serialising.
-    uint32_t prefix = 0, need = keff;
+    // ---- threshold: the `need` first of the `in_bin` elements with distances in [lo, lo + 2^bits) are kept, and all below lo
 #pragma unroll
     for (int i = 0; i < RPW; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (valid[i][e]) atomicAdd(&copies[(key[i][e] >> 24) * kCopies + (lane & (kCopies - 1))], 1u);
-    __syncthreads();
-    for (int b = threadIdx.x; b < 256; b += blockDim.x) {
-        uint32_t sum = 0;
-#pragma unroll
-        for (int q = 0; q < kCopies; q += 4) {
-            const uint4 part = *reinterpret_cast<const uint4*>(copies + b * kCopies + q);
-            sum += part.x + part.y + part.z + part.w;
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t d = dist[i][e] >> kFirstShift;
+            if (d < kFirstBins) atomicAdd(&first[d], 1u);
         }
-        hist[b] = sum;
-    }
     __syncthreads();
-    {
-        uint32_t D, above;
-        find_digit(hist, lane, need, D, above);
-        need -= above;
-        prefix = D << 24;
-    }
-#pragma unroll
-    for (int pass = 1; pass < 4; ++pass) {
-        const int shift = 24 - 8 * pass;
-        const uint32_t himask = 0xffffffffu << (shift + 8);
-        bool cand[RPW][4];
-        bool any = false;
+    uint32_t need = keff, bin, before, in_bin;
+    find_bin(first, lane, need, bin, before, in_bin);
+    need -= before;
+    uint32_t lo = bin << kFirstShift;
+    uint32_t bits = bin == kFirstBins ? 31 : kFirstShift;
+    for (int pass = 0; in_bin != need && bits != 0; ++pass) {
+        uint32_t* h = next + (pass & 1) * kNextBins;
+        if (pass >= 2) {   // read last before the barrier of the previous pass
+            topk_clear(h, kNextBins);
+            __syncthreads();
+        }
+        const uint32_t shift = bits > kNextBits ? bits - kNextBits : 0;
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                cand[i][e] = valid[i][e] && (key[i][e] & himask) == prefix;
-                any = any || cand[i][e];
+                const uint32_t r = dist[i][e] - lo;
+                if ((r >> bits) == 0) atomicAdd(&h[r >> shift], 1u);
             }
-        if (__ballot(any) != 0) {  // after the first pass most waves hold no candidate at all
-#pragma unroll
-            for (int i = 0; i < RPW; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (cand[i][e]) atomicAdd(&hist[pass * 256 + ((key[i][e] >> shift) & 255u)], 1u);
-        }
         __syncthreads();
-        uint32_t D, above;
-        find_digit(hist + pass * 256, lane, need, D, above);
-        need -= above;
-        prefix |= D << shift;
+        find_bin(h, lane, need, bin, before, in_bin);
+        need -= before;
+        lo += bin << shift;
+        bits = shift;
     }
-    const uint32_t T = prefix, R = need;
+    // Either all of the last bin is kept, or it is one magnitude of which the first `need` in index order are kept.
+    const bool ties = in_bin != need;
+    const uint32_t limit = ties ? lo : lo + (1u << bits);   // kept: dist < limit (and some of the ties)
 
-    // ---- packed prefix counts in index order: low half = elements > T, high half = elements == T
-    uint32_t lane_excl[RPW];
-    uint32_t run = 0;
+    // ---- counts of the waves before this one: low half = dist < limit, high half = ties
+    uint32_t count = 0;
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        uint32_t c = 0;
+    for (int i = 0; i < RPW; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (valid[i][e]) c += (key[i][e] > T ? 1u : 0u) + (key[i][e] == T ? 0x10000u : 0u);
-        const uint32_t inc = wave_prefix_incl(c, lane);
-        lane_excl[i] = run + inc - c;
-        run += __builtin_amdgcn_readlane(static_cast<int>(inc), 63);
+        for (int e = 0; e < 4; ++e) {
+            count += __builtin_popcountll(__ballot(dist[i][e] < limit));
+            if (ties) count += static_cast<uint32_t>(__builtin_popcountll(__ballot(dist[i][e] == limit))) << 16;
+        }
+    uint32_t pos = 0;   // output slots used by the waves before this one
+    if (nwaves > 1) {
+        if (lane == 0) s_count[wave] = count;
+        __syncthreads();
+        const int w = lane & (kMaxWaves - 1);
+        pos = __builtin_amdgcn_readfirstlane(static_cast<int>(row16_reduce(w < wave ? s_count[w] : 0u, OpAddU{})));
     }
-    if (lane == 0) tot[wave] = run;
-    __syncthreads();
-    uint32_t before_wave = 0;
-    for (int w = 0; w < wave; ++w) before_wave += tot[w];
+    uint32_t bound = limit;
+    if (ties) {   // those of the ties that are not kept move beyond the bound
+        uint32_t tie = pos >> 16;
+        pos = (pos & 0xffffu) + (tie < need ? tie : need);
+        bound = limit + 1;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            uint32_t mine = tie;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned long long m = __ballot(dist[i][e] == limit);
+                mine = lanes_below(m, mine);
+                tie += __builtin_popcountll(m);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (dist[i][e] == limit) {
+                    if (mine >= need) dist[i][e] = 0xffffffffu;
+                    ++mine;
+                }
+            }
+        }
+    }
 
     // ---- emit
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         const int off = static_cast<int>(wave * RPW + i) * kRow;
-        const int remain = row_remain<FULL>(len, off);
+        const int remain = len - off;
         if (remain <= 0) continue;
-        const int e0 = off + lane * 4;
-        const float el[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-        float res[4], dec[4];
-        uint32_t before = before_wave + lane_excl[i];
+        uint32_t mine = pos;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint32_t bgt = before & 0xffffu, beq = before >> 16;
-            const bool gt = valid[i][e] && key[i][e] > T, eq = valid[i][e] && key[i][e] == T;
-            const bool sel = gt || (eq && beq < R);
+            const unsigned long long m = __ballot(dist[i][e] < bound);
+            mine = lanes_below(m, mine);
+            pos += __builtin_popcountll(m);
+        }
+        const float el[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+        float res[4], dec[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool sel = dist[i][e] < bound;
             const float stored = el[e] + 0.0f;  // -0 is stored as +0
             if (sel) {
-                const uint32_t pos = bgt + (beq < R ? beq : R);
-                idx_c[pos] = static_cast<uint16_t>(e0 + e);
-                val_c[pos] = stored;
+                idx_c[mine] = static_cast<uint16_t>(off + lane * 4 + e);
+                val_c[mine] = stored;
+                ++mine;
             }
             res[e] = sel ? 0.0f : el[e];
             dec[e] = sel ? stored : 0.0f;
-            before += (gt ? 1u : 0u) + (eq ? 0x10000u : 0u);
         }
         if (residual) store_row(residual + off, lane, remain, f4{res[0], res[1], res[2], res[3]});
         if (out) store_row(out + off, lane, remain, f4{dec[0], dec[1], dec[2], dec[3]});
@@ -218,24 +238,13 @@ __device__ __forceinline__ void topk_encode_rows(const f4 (&v)[RPW], int len, ui
     }
 }
 
-template <int RPW>
-__device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, uint32_t keep, int wave, int lane,
-                                                  int nwaves, float* __restrict__ residual,
-                                                  uint16_t* __restrict__ idx_c, float* __restrict__ val_c,
-                                                  float* __restrict__ out, uint32_t* smem)
-{
-    // the same branch for every wave of the workgroup (the barriers inside are reached by all of them either way)
-    if (len == RPW * kRow * nwaves) topk_encode_rows<RPW, true>(v, len, keep, wave, lane, nwaves, residual, idx_c, val_c, out, smem);
-    else topk_encode_rows<RPW, false>(v, len, keep, wave, lane, nwaves, residual, idx_c, val_c, out, smem);
-}
-
 // ------------------------------------------------------------------------------------------ worker side
 template <int RPW, bool EF>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk, uint32_t keep,
                 uint16_t* __restrict__ idx, float* __restrict__ val)
 {
-    extern __shared__ uint32_t smem[];
+    __shared__ __align__(16) uint32_t smem[kTopkLdsWords];
     const size_t c = blockIdx.x;
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
@@ -261,7 +270,7 @@ k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_
     // rows need not fill its last wave: 4 x 112 M, C = 1536, 1972 -> 1834 us, C = 768, 3199 -> 3034 us.
     if (wave_full<RPW>(len, wave)) load(std::true_type{});
     else load(std::false_type{});
-    topk_clear_lds(smem);
+    topk_clear(smem, kHistWords);   // while the loads are in flight
     if (EF) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
@@ -279,6 +288,45 @@ k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_
 // The k sparse chunks are summed into a dense LDS copy of the chunk, one worker after the other
 // (ascending order; a worker's indices are unique, so its adds never collide), then averaged,
 // the server error state is added and the result is sparsified again.
+
+// dense[index] += value, worker after worker.  E entries per thread and pass over a worker's list; as many workers' passes
+// as make eight entries are fetched together, so the chain of k dependent steps pays one memory latency per group.
+template <int E>
+__device__ __forceinline__ void sum_entries(const PtrTable& idx_in, const PtrTable& val_in, int k, size_t entry0, uint32_t keep,
+                                            int len, float* dense)
+{
+    constexpr int G = 8 / E;
+    const uint32_t passes = E < 8 ? 1 : (keep + E * blockDim.x - 1) / (E * blockDim.x);
+    for (int j0 = 0; j0 < k; j0 += G) {
+        for (uint32_t pass = 0; pass < passes; ++pass) {
+            uint32_t p[G][E];
+            float a[G][E];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const uint32_t t = (pass * E + e) * blockDim.x + threadIdx.x;
+                    p[g][e] = 0xFFFFu;
+                    a[g][e] = 0.0f;
+                    if (j0 + g < k && t < keep) {
+                        p[g][e] = static_cast<const uint16_t*>(idx_in.p[j0 + g])[entry0 + t];
+                        a[g][e] = static_cast<const float*>(val_in.p[j0 + g])[entry0 + t];
+                    }
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                if (j0 + g >= k) break;
+                if (pass == 0) __syncthreads();  // the previous worker's sums (or the clear) are complete
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (static_cast<int>(p[g][e]) < len) dense[p[g][e]] = dense[p[g][e]] + a[g][e];
+            }
+        }
+    }
+    __syncthreads();
+}
+
 template <int RPW, bool EF, bool OUT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_topk(PtrTable idx_in, PtrTable val_in, int k, float inv_k, uint32_t keep, float* __restrict__ eps, size_t n,
@@ -308,43 +356,11 @@ k_drr_topk(PtrTable idx_in, PtrTable val_in, int k, float inv_k, uint32_t keep, 
         else load(std::false_type{});
     }
     for (uint32_t t = threadIdx.x; t < chunk / 4; t += blockDim.x) reinterpret_cast<f4*>(dense)[t] = f4{0.f, 0.f, 0.f, 0.f};
-    if (keep <= blockDim.x) {
-        // one entry per thread and worker: the entries of up to eight workers are fetched together, so the
-        // chain of k dependent steps pays one memory latency per group instead of one per worker
-        constexpr int G = 8;
-        const uint32_t t = threadIdx.x;
-        for (int j0 = 0; j0 < k; j0 += G) {
-            uint32_t p[G];
-            float a[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                p[g] = 0xFFFFu;
-                a[g] = 0.0f;
-                if (j0 + g < k && t < keep) {
-                    p[g] = static_cast<const uint16_t*>(idx_in.p[j0 + g])[c * keep + t];
-                    a[g] = static_cast<const float*>(val_in.p[j0 + g])[c * keep + t];
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (j0 + g >= k) break;
-                __syncthreads();  // the previous worker's sums (or the clear) are complete
-                if (static_cast<int>(p[g]) < len) dense[p[g]] = dense[p[g]] + a[g];
-            }
-        }
-        __syncthreads();
-    } else {
-        __syncthreads();
-        for (int j = 0; j < k; ++j) {
-            const uint16_t* ij = static_cast<const uint16_t*>(idx_in.p[j]) + c * keep;
-            const float* vj = static_cast<const float*>(val_in.p[j]) + c * keep;
-            for (uint32_t t = threadIdx.x; t < keep; t += blockDim.x) {
-                const uint32_t p = ij[t];
-                if (static_cast<int>(p) < len) dense[p] = dense[p] + vj[t];
-            }
-            __syncthreads();
-        }
-    }
+    const size_t entry0 = c * keep;
+    if (keep <= blockDim.x) sum_entries<1>(idx_in, val_in, k, entry0, keep, len, dense);
+    else if (keep <= 2 * blockDim.x) sum_entries<2>(idx_in, val_in, k, entry0, keep, len, dense);
+    else if (keep <= 4 * blockDim.x) sum_entries<4>(idx_in, val_in, k, entry0, keep, len, dense);
+    else sum_entries<8>(idx_in, val_in, k, entry0, keep, len, dense);
     f4 v[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -366,7 +382,7 @@ k_drr_topk(PtrTable idx_in, PtrTable val_in, int k, float inv_k, uint32_t keep, 
         }
     }
     __syncthreads();  // the dense copy is dead: its LDS is reused by the selection
-    topk_clear_lds(smem);
+    topk_clear(smem, kHistWords);
     topk_encode_chunk<RPW>(v, len, keep, wave, lane, nwaves, EF ? eps + base : nullptr, idx_out + c * keep,
                            val_out + c * keep, OUT ? out + base : nullptr, smem);
 }
@@ -418,14 +434,13 @@ extern "C" int bagua_compress_topk_ef(const float* x, float* residual, size_t n,
     const int rows = static_cast<int>(chunk / kRow);
     const int rpw = pick_rpw(rows, BAGUA_RPW_TOPK);
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
-    const size_t lds = kTopkLdsWords * sizeof(uint32_t);
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, true>), grid, block, lds, s, x, residual, n, ch, kp,
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, true>), grid, block, 0, s, x, residual, n, ch, kp,
                                                    idx, val))
     } else {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, false>), grid, block, lds, s, x, residual, n, ch, kp,
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, false>), grid, block, 0, s, x, residual, n, ch, kp,
                                                    idx, val))
     }
     return launch_status();
