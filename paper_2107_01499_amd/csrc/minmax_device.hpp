@@ -29,8 +29,8 @@ __device__ __forceinline__ void chunk_minmax_partial(const f4 (&v)[RPW], int len
             if (e + 3 < remain) { mn = fminf(mn, v[i].w); mx = fmaxf(mx, v[i].w); }
         }
     }
-    mn = wave_min(mn);
-    mx = wave_max(mx);
+    mn = wave_reduce(mn, OpMinF{});
+    mx = wave_reduce(mx, OpMaxF{});
     if (nwaves > 1 && lane == 0) {
         s_red[wave] = mn;
         s_red[kMaxWaves + wave] = mx;
@@ -42,10 +42,14 @@ __device__ __forceinline__ void chunk_minmax_partial(const f4 (&v)[RPW], int len
 __device__ __forceinline__ void chunk_minmax_finish(int nwaves, const float* s_red, float& mn, float& mx)
 {
     if (nwaves > 1) {
-        for (int w = 0; w < nwaves; ++w) {
-            mn = fminf(mn, s_red[w]);
-            mx = fmaxf(mx, s_red[kMaxWaves + w]);
+        // every row of 16 lanes reads all pairs at once; a lane without one keeps its own wave's
+        const int w = (threadIdx.x & 63) & (kMaxWaves - 1);
+        if (w < nwaves) {
+            mn = s_red[w];
+            mx = s_red[kMaxWaves + w];
         }
+        mn = row16_reduce(mn, OpMinF{});
+        mx = row16_reduce(mx, OpMaxF{});
     }
     mn = mn + 0.0f;
     mx = mx + 0.0f;

@@ -24,7 +24,7 @@ k_probe_read(const float* __restrict__ x, size_t n, float* __restrict__ tile_sum
     float s = 0.0f;
 #pragma unroll
     for (int r = 0; r < kProbeRows; ++r) s = s + ((v[r].x + v[r].y) + (v[r].z + v[r].w));
-    s = wave_butterfly_sum(s);
+    s = wave_reduce(s, OpAddF{});
     if (lane == 0) s_part[wave] = s;
     __syncthreads();
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);

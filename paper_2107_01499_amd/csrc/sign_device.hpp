@@ -37,16 +37,16 @@ __device__ __forceinline__ float chunk_abs_sum(const f4 (&v)[RPW], int rows, int
         __syncthreads();
         for (int row = 0; row < rows; ++row) acc = acc + s_q[row * kWave + lane];
     }
-    return wave_butterfly_sum(acc);
+    return wave_reduce(acc, OpAddF{});
 }
 
 // OR of the 4-bit nibbles of the 8 lanes that share one 32-bit sign word.
 __device__ __forceinline__ uint32_t gather_word(uint32_t nib, int lane)
 {
     uint32_t w = nib << (4 * (lane & 7));
-    w |= __shfl_xor(w, 1, kWave);
-    w |= __shfl_xor(w, 2, kWave);
-    w |= __shfl_xor(w, 4, kWave);
+    w |= dpp<kXor1>(w);
+    w |= dpp<kXor2>(w);
+    w |= dpp<kHalfMirror>(w);   // the four lanes of a quad hold the same by now
     return w;
 }
 
