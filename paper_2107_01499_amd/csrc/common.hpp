@@ -148,6 +148,30 @@ constexpr size_t kLdsPerCu = 160 * 1024, kLdsGranule = 1280;
 constexpr size_t lds_for_residency(int groups) { return kLdsPerCu / kLdsGranule / static_cast<size_t>(groups) * kLdsGranule; }
 static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets without asking the runtime for more");
 
+// Which chunk a workgroup takes.  Workgroup b runs on die (XCD) b % 8; in the order of the workgroups neighbouring chunks lie on
+// different dies, and a die's share of a stream is every eighth chunk.  Here a die takes 2^lg chunks in a row and the eight of
+// them 8 * 2^lg together; what is left at the end keeps the plain order.  What it does to the memory system was measured, not
+// derived: the dies then touch fewer, longer stretches of every stream.  Lengths from 2^0 to 2^8, 50 M elements per worker, the
+// gain of a whole round in %, worker-side kernels of both codecs and the LP ring:
+//   chunks up to 1024: 2^7 +0.6 .. +2.7, 2^5 -0.8 .. +2.2;
+//   1536 to 4096: 2^5 +0.5 .. +3.8 except 4096 elements gathered or reduced, -0.2 .. +1.0; 2^2 down to -2;
+//   longer: 2^2 +1.0 .. +5.6, 2^5 -1.4 .. +5.1, 2^7 negative.
+// From 2048 chunks on; below, +1 .. -6 without a pattern.  The server steps, the decodes, the top-K codec, the gossip pairs and the
+// full-precision kernels gained nothing at any length (the ring of eight -1 .. -8 %).
+struct ChunkOrder {
+    uint32_t lg, end;   // chunks from `end` on: plain order
+    __device__ __forceinline__ uint32_t operator()(uint32_t b) const
+    {
+        const uint32_t r = b & ((8u << lg) - 1u);
+        return b < end ? b - r + ((r & 7u) << lg) + (r >> 3) : b;
+    }
+};
+inline ChunkOrder chunk_order(size_t chunks, size_t chunk)
+{
+    const uint32_t lg = chunks < 2048 ? 0 : chunk <= 1024 ? 7 : chunk <= 4096 ? 5 : 2;
+    return ChunkOrder{lg, static_cast<uint32_t>(chunks) & ~((8u << lg) - 1u)};
+}
+
 struct PtrTable {
     const void* p[BAGUA_MAX_WORKERS];
 };

@@ -15,10 +15,10 @@ template <int RPW, bool EF, bool WB>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_flatten_compress_minmax(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile_first, uint32_t T,
                           float* __restrict__ residual, size_t n, uint32_t chunk, uint8_t* __restrict__ codes,
-                          float* __restrict__ minmax, float* __restrict__ bucket_out, uint32_t keep)
+                          float* __restrict__ minmax, float* __restrict__ bucket_out, uint32_t keep, ChunkOrder order)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -63,10 +63,10 @@ template <int RPW, bool EF, bool WB>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_flatten_sign_compress(const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ tile_first, uint32_t T,
                         float* __restrict__ residual, size_t n, uint32_t chunk, uint32_t* __restrict__ bits,
-                        float* __restrict__ scale, float* __restrict__ bucket_out)
+                        float* __restrict__ scale, float* __restrict__ bucket_out, ChunkOrder order)
 {
     extern __shared__ float s_q[];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -111,10 +111,10 @@ k_flatten_sign_compress(const TensorDesc* __restrict__ desc, const uint32_t* __r
 template <int RPW, bool EF>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restrict__ residual, size_t n, uint32_t chunk,
-                         uint8_t* __restrict__ codes, float* __restrict__ minmax, uint32_t keep)
+                         uint8_t* __restrict__ codes, float* __restrict__ minmax, uint32_t keep, ChunkOrder order)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -167,10 +167,10 @@ k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restric
 template <int RPW, bool EF>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_reduce_compress_sign(PtrTable xs, int k_local, float inv_k, float* __restrict__ residual, size_t n, uint32_t chunk,
-                       uint32_t* __restrict__ bits, float* __restrict__ scale)
+                       uint32_t* __restrict__ bits, float* __restrict__ scale, ChunkOrder order)
 {
     extern __shared__ float s_q[];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -251,7 +251,7 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
 #define BAGUA_FC(EFv, WBv)                                                                                       \
     BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, codes,  \
-                                               minmax, bucket_out, keep))
+                                               minmax, bucket_out, keep, chunk_order(grid.x, chunk)))
     if (residual && bucket_out) { BAGUA_FC(true, true) }
     else if (residual) { BAGUA_FC(true, false) }
     else if (bucket_out) { BAGUA_FC(false, true) }
@@ -285,7 +285,7 @@ extern "C" int bagua_flatten_sign_compress_ef(const void* workspace, size_t T, f
 #define BAGUA_FS(EFv, WBv)                                                                                       \
     BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_sign_compress<RPW, EFv, WBv>), grid, block, lds, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, bits,   \
-                                               scale, bucket_out))
+                                               scale, bucket_out, chunk_order(grid.x, chunk)))
     if (residual && bucket_out) { BAGUA_FS(true, true) }
     else if (residual) { BAGUA_FS(true, false) }
     else if (bucket_out) { BAGUA_FS(false, true) }
@@ -322,10 +322,10 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk), chunk_order(grid.x, chunk)))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk), chunk_order(grid.x, chunk)))
     }
     return launch_status();
 }
@@ -360,10 +360,10 @@ extern "C" int bagua_reduce_compress_sign_ef(const float* const* x, int k_local,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, true>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale))
+                                                   inv_k, residual, n, ch, bits, scale, chunk_order(grid.x, chunk)))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, false>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale))
+                                                   inv_k, residual, n, ch, bits, scale, chunk_order(grid.x, chunk)))
     }
     return launch_status();
 }

@@ -62,24 +62,24 @@ __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ 
 template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_minmax(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
-                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace, uint32_t keep)
+                  uint8_t* __restrict__ codes, float* __restrict__ minmax, int pace, uint32_t keep, ChunkOrder order)
 {
     __shared__ float s_red[2 * kMaxWaves];
-    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, blockIdx.x, s_red, pace, blockIdx.x < keep);
+    compress_minmax_chunk<RPW, EF, SHORT>(x, residual, n, chunk, codes, minmax, order(blockIdx.x), s_red, pace, blockIdx.x < keep);
 }
 
 // Batched: entry = [x, residual, codes, minmax, n]; unit = chunk.
 template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, uint32_t keep)
+k_compress_minmax_batched(TABLE table, uint32_t chunk, int pace, uint32_t keep, ChunkOrder order)
 {
     __shared__ float s_red[2 * kMaxWaves];
     const BatchView bv = table.view();
-    const uint32_t b = batch_find(bv, blockIdx.x);
+    const uint32_t unit = order(blockIdx.x), b = batch_find(bv, unit);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     compress_minmax_chunk<RPW, EF, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                    table_ptr<uint8_t>(e[2]), table_ptr<float>(e[3]),
-                                   blockIdx.x - bv.first_unit[b], s_red, pace, blockIdx.x < keep);
+                                   unit - bv.first_unit[b], s_red, pace, blockIdx.x < keep);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -258,10 +258,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk))))
     }
     return launch_status();
 }
@@ -388,10 +388,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk))))
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk), chunk_order(total, chunk))))
         } else {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk))))
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk), chunk_order(total, chunk))))
         }
     });
 }

@@ -83,11 +83,11 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
 template <int K, int RPW, int KEEP, bool FULL, bool WIDE>
 __global__ void __launch_bounds__(WIDE ? wg_threads_max(RPW) : kWave * (kNarrowRows / RPW), K <= 2 ? 8 : 1)
 k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n,
-              uint32_t chunk, float third)
+              uint32_t chunk, float third, ChunkOrder order)
 {
     static_assert(!FULL || K >= 2, "the loop needs two entries of s_red");
     __shared__ float s_red[K][2 * kMaxWaves];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -262,10 +262,10 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
 template <int RPW>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
-                  uint32_t chunk, float third, int keep)
+                  uint32_t chunk, float third, int keep, ChunkOrder order)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
@@ -362,8 +362,9 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
 {
     const bool wide = chunk > kNarrowRows * kRow, odd = chunk % (BAGUA_RPW_LP * kRow) != 0;
     const int keep = keep_codes_of_round(K * n);
+    const ChunkOrder order = chunk_order(grid.x, chunk);
 #define BAGUA_RING_KEEP(KEEPv, FULLv, WIDEv)                                                                                  \
-    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third)
+    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third, order)
 #define BAGUA_RING(FULLv, WIDEv)                   \
     {                                              \
         if (keep) BAGUA_RING_KEEP(1, FULLv, WIDEv); \
@@ -375,7 +376,7 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
     }
     if (!wide) BAGUA_RING(false, false)
     if constexpr (K < 8) BAGUA_RING(false, true)
-    hipLaunchKernelGGL((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep);
+    hipLaunchKernelGGL((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep, order);
 #undef BAGUA_RING_KEEP
 #undef BAGUA_RING
 }
@@ -408,7 +409,7 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
         }
     }
     BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
-                                               third, keep_codes_of_round(k * n)))
+                                               third, keep_codes_of_round(k * n), chunk_order(nc, chunk)))
     return launch_status();
 }
 

@@ -83,24 +83,24 @@ template <int RPW, bool EF, bool MOM, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_sign_compress(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
                 uint32_t* __restrict__ bits, float* __restrict__ scale, const float* __restrict__ mom, float beta1,
-                float omb1, int pace)
+                float omb1, int pace, ChunkOrder order)
 {
     extern __shared__ float s_q[];
-    sign_compress_chunk<RPW, EF, MOM, SHORT>(x, residual, n, chunk, bits, scale, mom, beta1, omb1, blockIdx.x, s_q, pace);
+    sign_compress_chunk<RPW, EF, MOM, SHORT>(x, residual, n, chunk, bits, scale, mom, beta1, omb1, order(blockIdx.x), s_q, pace);
 }
 
 // Batched: entry = [x, residual, bits, scale, n]; unit = chunk.
 template <int RPW, bool EF, bool SHORT, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
-k_sign_compress_batched(TABLE table, uint32_t chunk, int pace)
+k_sign_compress_batched(TABLE table, uint32_t chunk, int pace, ChunkOrder order)
 {
     extern __shared__ float s_q[];
     const BatchView bv = table.view();
-    const uint32_t b = batch_find(bv, blockIdx.x);
+    const uint32_t unit = order(blockIdx.x), b = batch_find(bv, unit);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
     sign_compress_chunk<RPW, EF, false, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                         table_ptr<uint32_t>(e[2]), table_ptr<float>(e[3]), nullptr, 0.0f,
-                                        0.0f, blockIdx.x - bv.first_unit[b], s_q, pace);
+                                        0.0f, unit - bv.first_unit[b], s_q, pace);
 }
 
 // Server side with the sign codec: a = (sum_j +-scale_j) * inv_k in ascending j; w = a (+ eps).
@@ -358,10 +358,10 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, false, SHORT>), g.grid, g.block,
-                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n))))
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), chunk_order(g.grid.x, chunk))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, false, SHORT>), g.grid, g.block,
-                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n))))
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), chunk_order(g.grid.x, chunk))))
     }
     return launch_status();
 }
@@ -456,10 +456,10 @@ extern "C" int bagua_momentum_sign_compress_ef(const float* g, const float* m, f
     const float omb1 = 1.0f - beta1;
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n))))
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), chunk_order(geo.grid.x, chunk))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n))))
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), chunk_order(geo.grid.x, chunk))))
     }
     return launch_status();
 }
@@ -509,10 +509,10 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                          (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk))))
+                                          (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
         } else {
             BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                          (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk))))
+                                          (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
         }
     });
 }

@@ -1,0 +1,91 @@
+"""Launches around the number of chunks from which the workgroups take the chunks in another order than their own (2048; then
+runs of 128, 32 and 4 chunks for chunk lengths up to 1024, up to 4096 and above), with and without chunks left over."""
+import numpy as np
+import pytest
+import torch
+
+from bagua_workloads import draw
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bg():
+    import paper_2107_01499_amd as b
+    assert torch.cuda.is_available()
+    return b
+
+
+def same(t, want):
+    return np.array_equal(t.cpu().numpy().view(np.uint8), want.view(np.uint8))
+
+
+def room(codec, n, nc):
+    if codec == "minmax":
+        return torch.full((n,), 255, dtype=torch.uint8, device="cuda"), torch.full((2 * nc,), float("nan"), device="cuda")
+    return torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device="cuda"), torch.full((nc,), float("nan"), device="cuda")
+
+
+CASES = [(256, 2047 * 256), (256, 2047 * 256 + 1), (256, 2049 * 256), (1024, 3071 * 1024 - 5), (1280, 2048 * 1280), (1280, 2303 * 1280 + 700),
+         (4352, 2048 * 4352), (4352, 2079 * 4352 + 3)]
+
+
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+@pytest.mark.parametrize("chunk,n", CASES)
+def test_worker_side(bg, oracle, codec, chunk, n):
+    print("order %s C=%d n=%d" % (codec, chunk, n), flush=True)
+    nc = bg.num_chunks(n, chunk)
+    xs = [draw("normal", n, 31 * chunk + j, "cpu", 1e-3) for j in range(2)]
+    res = draw("normal", n, 31 * chunk + 9, "cpu", 1e-4)
+    plain, fused, reduce_, gather, batched, want_reduce = (
+        (bg.bagua_compress_minmax_u8, oracle.compress_minmax_u8, bg.bagua_reduce_compress_minmax_u8, bg.bagua_flatten_compress_minmax_u8,
+         bg.bagua_compress_minmax_u8_batched, oracle.reduce_compress_minmax_u8) if codec == "minmax" else
+        (bg.bagua_sign_compress_ef, oracle.sign_compress_ef, bg.bagua_reduce_compress_sign_ef, bg.bagua_flatten_sign_compress_ef,
+         bg.bagua_sign_compress_ef_batched, oracle.reduce_compress_sign))
+    xg = [x.cuda() for x in xs]
+    want_r = res.numpy().copy()
+    want = fused(xs[0].numpy(), want_r, chunk)
+
+    codes, meta = room(codec, n, nc)
+    r = res.cuda()
+    plain(xg[0], r, chunk, codes, meta)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
+
+    codes, meta = room(codec, n, nc)
+    r = res.cuda()
+    ws = torch.empty(bg.bagua_flatten_workspace_bytes(1, n), dtype=torch.uint8, device="cuda")
+    bg.bagua_flatten_plan([xg[0]], [0], n, ws)
+    gather(ws, 1, r, n, chunk, codes, meta)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
+
+    codes, meta = room(codec, n, nc)
+    r = res.cuda()
+    cut = nc // 3 * chunk                                   # two buckets; a bucket's codes start at a whole chunk
+    at = cut if codec == "minmax" else cut // 32
+    mat = 2 * cut // chunk if codec == "minmax" else cut // chunk
+    ws = torch.empty(bg.bagua_batch_workspace_bytes(2, 0), dtype=torch.uint8, device="cuda")
+    batched([xg[0][:cut], xg[0][cut:]], [r[:cut], r[cut:]], chunk, [codes[:at], codes[at:]], [meta[:mat], meta[mat:]], ws)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
+
+    want_r = res.numpy().copy()
+    want = want_reduce([x.numpy() for x in xs], want_r, chunk)
+    codes, meta = room(codec, n, nc)
+    r = res.cuda()
+    reduce_(xg, r, chunk, codes, meta)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
+
+
+@pytest.mark.parametrize("k,chunk,n", [(2, 256, 2047 * 256 + 1), (3, 1024, 3071 * 1024 - 5), (4, 1280, 2303 * 1280 + 700), (2, 4352, 2079 * 4352 + 3),
+                                       (5, 4608, 2051 * 4608 + 300), (2, 8448, 2053 * 8448 + 8)])
+def test_ring(bg, oracle, k, chunk, n):
+    print("order ring k=%d C=%d n=%d" % (k, chunk, n), flush=True)
+    nc = bg.num_chunks(n, chunk)
+    xs = [draw("normal", n, 17 * chunk + j, "cpu", 0.02) for j in range(k)]
+    hats = [draw("normal", n, 17 * chunk + 50 + j, "cpu", 0.02) for j in range(k)]
+    hg, out = [h.cuda() for h in hats], [torch.full((n,), float("nan"), device="cuda") for _ in range(k)]
+    wire = [room("minmax", n, nc) for _ in range(k)]
+    bg.bagua_decentralized_avg(bg.AVG_LP_MINMAX_U8, [x.cuda() for x in xs], out, hg, [w[0] for w in wire], [w[1] for w in wire], chunk)
+    want_hat = [h.numpy().copy() for h in hats]
+    want_out, want_codes, want_mm = oracle.ring_avg_lp([x.numpy() for x in xs], want_hat, chunk)
+    for j in range(k):
+        assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(wire[j][0], want_codes[j]) and same(wire[j][1], want_mm[j])
