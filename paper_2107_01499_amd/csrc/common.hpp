@@ -78,9 +78,8 @@ inline int keep_codes_of_round(size_t elements)
 
 // A flattened bucket of n floats, which the compression reads next: 8 workers x 25.6 M elements in 5 buckets 793 -> 766 us,
 // 4 x 60 M 914 -> 869 us, 4 x 130 M 2153 -> 2115 us for the whole round; above the line 8 x 160 M 4768 -> 4921 us, 4 x 200 M
-// 3227 -> 3307 us, 2 x 160 M +-0.  (The momentum that every worker's sign compression
-// reads, 8 x 6.5 M elements 183 -> 163 us, 8 x 25.6 M 637 -> 580 us, but 4 x 100 M 1379 -> 1395 us, is loaded without
-// the hint in short launches; see also k_lp_encode.)
+// 3227 -> 3307 us, 2 x 160 M +-0.  (The momentum that every worker's sign compression reads: see mom_keep; the replica that
+// encode and mix both read: see k_lp_encode.)
 inline bool keep_bucket(size_t n) { return n <= (static_cast<size_t>(1) << 27); }
 
 // Preferred rows (of 256 elements) per wave for each chunked kernel (compile-time tuning knobs).

@@ -27,3 +27,15 @@ def test_ring_fp(bg, oracle, k, n):
     bg.bagua_decentralized_avg(bg.AVG_FP, [x.cuda() for x in xs], out)
     want = oracle.ring_avg_fp([x.numpy() for x in xs])
     assert all(same(o, w) for o, w in zip(out, want))
+
+
+@pytest.mark.parametrize("n,chunk", [((1 << 26), 2048), ((1 << 26) + 1, 2048), ((1 << 26) + 77, 16384), (3 * (1 << 24) * 2 - 5, 1536)])
+def test_momentum_compression(bg, oracle, n, chunk):
+    print("momentum n=%d C=%d" % (n, chunk), flush=True)
+    g, m, r = (draw("normal", n, 91 + i, "cpu", s) for i, s in enumerate((1e-3, 1e-3, 1e-4)))
+    bits, scale = torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device="cuda"), torch.full((bg.num_chunks(n, chunk),), float("nan"), device="cuda")
+    res = r.cuda()
+    bg.bagua_momentum_sign_compress_ef(g.cuda(), m.cuda(), 0.9, res, chunk, bits, scale)
+    want_r = r.numpy().copy()
+    want_bits, want_scale = oracle.momentum_sign_compress_ef(g.numpy(), m.numpy(), 0.9, want_r, chunk)
+    assert same(bits, want_bits) and same(scale, want_scale) and same(res, want_r)
