@@ -155,8 +155,9 @@ static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets wi
 //   chunks up to 1024: 2^7 +0.6 .. +2.7, 2^5 -0.8 .. +2.2;
 //   1536 to 4096: 2^5 +0.5 .. +3.8 except 4096 elements gathered or reduced, -0.2 .. +1.0; 2^2 down to -2;
 //   longer: 2^2 +1.0 .. +5.6, 2^5 -1.4 .. +5.1, 2^7 negative.
-// From 2048 chunks on; below, +1 .. -6 without a pattern.  The server steps, the decodes, the top-K codec, the gossip pairs and the
-// full-precision kernels gained nothing at any length (the ring of eight -1 .. -8 %).
+// Top-K: 0 .. +3 (4 x 60 M, C = 1536, 831 -> 807 us); gossip pairs of chunks above 4096: -0.6 .. +5.7 (8 x 60 M, C = 8192, 1530 -> 1448).
+// From 2048 chunks on; below, +1 .. -6 without a pattern.  The server steps, the decodes and the full-precision kernels gained
+// nothing at any length (the ring of eight -1 .. -8 %).
 struct ChunkOrder {
     uint32_t lg, end;   // chunks from `end` on: plain order
     __device__ __forceinline__ uint32_t operator()(uint32_t b) const

@@ -242,10 +242,10 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
 template <int RPW, bool EF>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk, uint32_t keep,
-                uint16_t* __restrict__ idx, float* __restrict__ val)
+                uint16_t* __restrict__ idx, float* __restrict__ val, ChunkOrder order)
 {
     __shared__ __align__(16) uint32_t smem[kTopkLdsWords];
-    const size_t c = blockIdx.x;
+    const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
@@ -438,10 +438,10 @@ extern "C" int bagua_compress_topk_ef(const float* x, float* residual, size_t n,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, true>), grid, block, 0, s, x, residual, n, ch, kp,
-                                                   idx, val))
+                                                   idx, val, chunk_order(grid.x, chunk)))
     } else {
         BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, false>), grid, block, 0, s, x, residual, n, ch, kp,
-                                                   idx, val))
+                                                   idx, val, chunk_order(grid.x, chunk)))
     }
     return launch_status();
 }

@@ -89,3 +89,30 @@ def test_ring(bg, oracle, k, chunk, n):
     want_out, want_codes, want_mm = oracle.ring_avg_lp([x.numpy() for x in xs], want_hat, chunk)
     for j in range(k):
         assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(wire[j][0], want_codes[j]) and same(wire[j][1], want_mm[j])
+
+
+@pytest.mark.parametrize("chunk,n", [(256, 2047 * 256 + 1), (1024, 3071 * 1024 - 5), (1280, 2303 * 1280 + 700), (4352, 2079 * 4352 + 3)])
+def test_topk(bg, oracle, chunk, n):
+    print("order topk C=%d n=%d" % (chunk, n), flush=True)
+    keep, nc = chunk // 32, bg.num_chunks(n, chunk)
+    x, res = draw("normal", n, 7 * chunk, "cpu", 1e-3), draw("normal", n, 7 * chunk + 1, "cpu", 1e-4)
+    idx, val, r = torch.full((nc * keep,), -1, dtype=torch.int16, device="cuda"), torch.full((nc * keep,), float("nan"), device="cuda"), res.cuda()
+    bg.bagua_compress_topk_ef(x.cuda(), r, chunk, keep, idx, val)
+    want_r = res.numpy().copy()
+    want_idx, want_val = oracle.compress_topk(x.numpy(), want_r, chunk, keep)
+    assert same(idx, want_idx) and same(val, want_val) and same(r, want_r)
+
+
+@pytest.mark.parametrize("chunk,n", [(4352, 2047 * 4352), (4352, 2079 * 4352 + 3), (8448, 2053 * 8448 + 8)])
+def test_peers(bg, oracle, chunk, n):
+    print("order peers C=%d n=%d" % (chunk, n), flush=True)
+    peer, nc = [1, 0, 2], bg.num_chunks(n, chunk)
+    xs = [draw("normal", n, 13 * chunk + j, "cpu", 0.02) for j in range(3)]
+    hats = [draw("normal", n, 13 * chunk + 50 + j, "cpu", 0.02) for j in range(3)]
+    hg, out = [h.cuda() for h in hats], [torch.full((n,), float("nan"), device="cuda") for _ in range(3)]
+    wire = [room("minmax", n, nc) for _ in range(3)]
+    bg.bagua_decentralized_avg_peers_lp([x.cuda() for x in xs], out, hg, [w[0] for w in wire], [w[1] for w in wire], peer, chunk)
+    want_hat = [h.numpy().copy() for h in hats]
+    want_out, want_codes, want_mm = oracle.peer_avg_lp([x.numpy() for x in xs], want_hat, peer, chunk)
+    for j in range(3):
+        assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(wire[j][0], want_codes[j]) and same(wire[j][1], want_mm[j])
