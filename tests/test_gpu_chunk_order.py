@@ -116,3 +116,21 @@ def test_peers(bg, oracle, chunk, n):
     want_out, want_codes, want_mm = oracle.peer_avg_lp([x.numpy() for x in xs], want_hat, peer, chunk)
     for j in range(3):
         assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(wire[j][0], want_codes[j]) and same(wire[j][1], want_mm[j])
+
+
+@pytest.mark.parametrize("chunk,n", [(256, 8193), (512, 512 * 8 - 1), (512, 512 * 8), (512, 512 * 17 + 300), (768, 768 * 33 + 5), (1024, 1024 * 40), (4096, 4096 * 23 + 256), (16384, 16384 * 19 - 1),
+                                     (2048, 1 << 25), (2048, (1 << 25) + 1)])
+def test_share_of_a_ring(bg, oracle, chunk, n):
+    """Encode + mix of peer 1 of three; the rows are mixed in the order of the encode up to 2^25 elements."""
+    print("order share C=%d n=%d" % (chunk, n), flush=True)
+    xs = [draw("normal", n, 19 * chunk + j, "cpu", 0.02) for j in range(3)]
+    hats = [draw("normal", n, 19 * chunk + 50 + j, "cpu", 0.02) for j in range(3)]
+    want_hat = [h.numpy().copy() for h in hats]
+    want_out, want_codes, want_mm = oracle.ring_avg_lp([x.numpy() for x in xs], want_hat, chunk)
+    hg, out, x = [h.cuda() for h in hats], torch.full((n,), float("nan"), device="cuda"), xs[1].cuda()
+    codes, mm = room("minmax", n, bg.num_chunks(n, chunk))
+    bg.bagua_lp_encode(x, hg[1], chunk, codes, mm)
+    assert same(codes, want_codes[1]) and same(mm, want_mm[1]) and same(hg[1], want_hat[1])
+    sent = [(torch.from_numpy(want_codes[j]).cuda(), torch.from_numpy(want_mm[j]).cuda()) for j in (0, 2)]
+    bg.bagua_lp_apply_mix(x, hg[1], hg[0], hg[2], *sent[0], *sent[1], chunk, out)
+    assert same(out, want_out[1]) and same(hg[0], want_hat[0]) and same(hg[2], want_hat[2])
