@@ -146,6 +146,8 @@ static_assert(wg_threads_max(1) <= 1024 && wg_threads_max(2) <= 1024 && 4 * kMax
 constexpr size_t kLdsPerCu = 160 * 1024, kLdsGranule = 1280;
 constexpr size_t lds_for_residency(int groups) { return kLdsPerCu / kLdsGranule / static_cast<size_t>(groups) * kLdsGranule; }
 static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets without asking the runtime for more");
+// The least with which no more than two workgroups fit.
+constexpr size_t kLdsForTwo = (kLdsPerCu / kLdsGranule / 3 + 1) * kLdsGranule;
 
 // Which chunk a workgroup takes.  Workgroup b runs on die (XCD) b % 8; in the order of the workgroups neighbouring chunks lie on
 // different dies, and a die's share of a stream is every eighth chunk.  Here a die takes 2^lg chunks in a row and the eight of

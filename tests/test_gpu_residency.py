@@ -39,3 +39,17 @@ def test_momentum_compression(bg, oracle, n, chunk):
     want_r = r.numpy().copy()
     want_bits, want_scale = oracle.momentum_sign_compress_ef(g.numpy(), m.numpy(), 0.9, want_r, chunk)
     assert same(bits, want_bits) and same(scale, want_scale) and same(res, want_r)
+
+
+@pytest.mark.parametrize("n,chunk", [((1 << 24) - 1, 4096), ((1 << 24) + 5, 4096), ((1 << 24) + 3072 * 7, 2816)])
+def test_gossip_pairs(bg, oracle, n, chunk):
+    print("gossip n=%d C=%d" % (n, chunk), flush=True)
+    peer, nc = [1, 0, 2], bg.num_chunks(n, chunk)
+    xs, hats = ([draw("normal", n, s + j, "cpu", 0.02) for j in range(3)] for s in (60, 70))
+    hg, out = [h.cuda() for h in hats], [torch.full((n,), float("nan"), device="cuda") for _ in range(3)]
+    codes, mm = [torch.full((n,), 255, dtype=torch.uint8, device="cuda") for _ in range(3)], [torch.full((2 * nc,), float("nan"), device="cuda") for _ in range(3)]
+    bg.bagua_decentralized_avg_peers_lp([x.cuda() for x in xs], out, hg, codes, mm, peer, chunk)
+    want_hat = [h.numpy().copy() for h in hats]
+    want_out, want_codes, want_mm = oracle.peer_avg_lp([x.numpy() for x in xs], want_hat, peer, chunk)
+    for j in range(3):
+        assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(mm[j], want_mm[j]) and np.array_equal(codes[j].cpu().numpy(), want_codes[j])
