@@ -144,7 +144,11 @@ static_assert(wg_threads_max(1) <= 1024 && wg_threads_max(2) <= 1024 && 4 * kMax
 // together in HBM).  Such a launch asks for LDS that it does not use, so that at most `groups` of its workgroups fit a
 // CU: the largest multiple of the allocation's granule that leaves room for them.
 constexpr size_t kLdsPerCu = 160 * 1024, kLdsGranule = 1280;
-constexpr size_t lds_for_residency(int groups) { return kLdsPerCu / kLdsGranule / static_cast<size_t>(groups) * kLdsGranule; }
+// `own`: what the kernel uses of it anyway, if the launch's figure comes on top of that.
+constexpr size_t lds_for_residency(int groups, size_t own = 0)
+{
+    return (kLdsPerCu / kLdsGranule / static_cast<size_t>(groups) - (own + kLdsGranule - 1) / kLdsGranule) * kLdsGranule;
+}
 static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets without asking the runtime for more");
 // The least with which no more than two workgroups fit.
 constexpr size_t kLdsForTwo = (kLdsPerCu / kLdsGranule / 3 + 1) * kLdsGranule;
@@ -207,6 +211,18 @@ __device__ __forceinline__ int wave_index()
 inline bool short_launch(size_t elements_per_launch, bool batched = false)
 {
     return elements_per_launch < (static_cast<size_t>(1) << (batched ? 26 : 25));
+}
+
+// A batched worker-side launch of 2^26 elements or more with chunks of 1024, 1536 or 2048 elements (two, three or four waves): tail tests
+// folded away, and 16 waves on a CU at a time.  Each alone loses (without the bound up to -7 %, bounded to 24 waves or with the tests
+// -1 .. -30 %); tests and all waves -> this, whole rounds in buckets of 2.5 to 10 M: sign codec, 8 workers x 374 M, C = 2048, 6427 -> 6326
+// us, 8 x 134 M 2360 -> 2248, 2 x 134 M 816 -> 790, C = 1536 2333 -> 2226, C = 1024 2322 -> 2257; MinMax, 8 x 134 M, C = 2048, 2764 -> 2675,
+// C = 1536 2752 -> 2667, C = 1024 2734 -> 2652, 4 x 75 M 851 -> 801.  Longer chunks lose 1-14 %, 768 elements never fill the last
+// wave.  Unbatched launches run one row per wave and have nothing to gain.  The value: workgroups on a CU, or 0.
+inline int batched_groups(size_t elements, size_t chunk, unsigned threads)
+{
+    const bool pays = chunk >= 1024 && chunk <= 2048 && chunk % (2 * kRow) == 0 && elements >= (static_cast<size_t>(1) << 26);
+    return pays ? 16 / static_cast<int>(threads / kWave) : 0;
 }
 
 // f(0), ..., f(N - 1) written out.  A loop over the rows of a wave would do, but where N = 1 the compiler moves a store

@@ -54,8 +54,8 @@ __device__ __forceinline__ void compress_minmax_chunk(const float* __restrict__ 
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     float* res_c = EF ? residual + base : nullptr;
-    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))   // so short that all its codes are kept
-        compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0, 1);
+    if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
+        compress_minmax_rows<RPW, EF, true>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, 0, keep);
     else compress_minmax_rows<RPW, EF, false>(x + base, res_c, len, codes + base, minmax + 2 * c, s_red, pace, keep);
 }
 
@@ -384,14 +384,18 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
     const int rpw = pick_rpw(rows, BAGUA_RPW_COMPRESS);
     dim3 grid(static_cast<unsigned>(total)), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
+    const int groups = batched_groups(total * chunk, chunk, block.x);
+    const size_t lds = groups > 0 ? lds_for_residency(groups, 2 * kMaxWaves * sizeof(float)) : 0;
+    const bool is_short = short_launch(total * chunk, true);
+    const uint32_t keep = is_short ? static_cast<uint32_t>(total) : keep_chunks(total * chunk, chunk);   // a short launch keeps all its codes
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk), chunk_order(total, chunk))))
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk))))
         } else {
-            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, 0, s, tab, ch, pace_for(total * chunk), keep_chunks(total * chunk, chunk), chunk_order(total, chunk))))
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk))))
         }
     });
 }

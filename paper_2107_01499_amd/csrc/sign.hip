@@ -515,14 +515,16 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     SignGeometry g = sign_geometry(chunk, chunk, BAGUA_RPW_SIGN, false);
     g.grid = dim3(static_cast<unsigned>(total));
+    const int groups = batched_groups(total * chunk, chunk, g.block.x);
+    if (groups > 0) g.lds = lds_for_residency(groups);   // far more than the statistics need
     const uint32_t ch = static_cast<uint32_t>(chunk);
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
                                           (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
         } else {
-            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(total * chunk, true), hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
                                           (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
         }
     });

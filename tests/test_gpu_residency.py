@@ -53,3 +53,22 @@ def test_gossip_pairs(bg, oracle, n, chunk):
     want_out, want_codes, want_mm = oracle.peer_avg_lp([x.numpy() for x in xs], want_hat, peer, chunk)
     for j in range(3):
         assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(mm[j], want_mm[j]) and np.array_equal(codes[j].cpu().numpy(), want_codes[j])
+
+
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+@pytest.mark.parametrize("chunk,sizes", [(2048, [(1 << 25) + 2048 * 3, 1000, (1 << 25) - 2048 * 2 - 1000]), (1536, [1 << 25, 77, (1 << 25) + 1]), (1024, [(1 << 26) - 1025, 1])])
+def test_batched_worker_side(bg, oracle, codec, chunk, sizes):
+    """Just below (1024: one chunk short) and above 2^26 elements in chunks of two, three and four waves, with short buckets among them."""
+    print("batched %s C=%d" % (codec, chunk), flush=True)
+    xs, rs = ([draw("normal", n, s + b, "cpu", sg).numpy() for b, n in enumerate(sizes)] for s, sg in ((80, 1e-3), (90, 1e-4)))
+    words = [n if codec == "minmax" else (n + 31) // 32 for n in sizes]
+    metas = [(2 if codec == "minmax" else 1) * bg.num_chunks(n, chunk) for n in sizes]
+    codes = [torch.full((w,), -1 if codec == "sign" else 255, dtype=torch.int32 if codec == "sign" else torch.uint8, device="cuda") for w in words]
+    meta, rg = [torch.full((m,), float("nan"), device="cuda") for m in metas], [torch.from_numpy(r).cuda() for r in rs]
+    ws = torch.empty(bg.bagua_batch_workspace_bytes(len(sizes), 0), dtype=torch.uint8, device="cuda")
+    call, want_of = (bg.bagua_compress_minmax_u8_batched, oracle.compress_minmax_u8) if codec == "minmax" else (bg.bagua_sign_compress_ef_batched, oracle.sign_compress_ef)
+    call([torch.from_numpy(x).cuda() for x in xs], rg, chunk, codes, meta, ws)
+    for b, x in enumerate(xs):
+        want_r = rs[b].copy()
+        want = want_of(x, want_r, chunk)
+        assert np.array_equal(codes[b].cpu().numpy().view(np.uint8), want[0].view(np.uint8)) and same(meta[b], want[1]) and same(rg[b], want_r)
