@@ -40,14 +40,14 @@ __device__ __forceinline__ f4 decode_row(const void* __restrict__ codes, const f
 // One wave per 256-element row, four rows per workgroup.
 template <int CODEC, bool MOM, bool WD>
 __global__ void __launch_bounds__(kWave * kRowWaves)
-k_decompress_sgd(const void* __restrict__ codes, const float* __restrict__ meta, size_t n, uint32_t chunk,
-                 float* __restrict__ param, float* __restrict__ mbuf, float lr, float mu, float wd)
+k_decompress_sgd(const void* __restrict__ codes, const float* __restrict__ meta, size_t n, uint32_t rows_per_chunk,
+                 float* __restrict__ param, float* __restrict__ mbuf, float lr, float mu, float wd, ChunkOrder order)
 {
-    const size_t row = static_cast<size_t>(blockIdx.x) * kRowWaves + wave_index();
+    const uint32_t row = order(blockIdx.x) * kRowWaves + wave_index();
     const int lane = threadIdx.x & 63;
-    const size_t e0 = row * kRow;
+    const size_t e0 = static_cast<size_t>(row) * kRow;
     if (e0 >= n) return;
-    const size_t c = e0 / chunk;
+    const size_t c = row / rows_per_chunk;
     const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
 
     f4 p = load_row(param + e0, lane, remain, 0.0f);
@@ -81,15 +81,15 @@ k_decompress_sgd(const void* __restrict__ codes, const float* __restrict__ meta,
 // compression stage of 1-bit Adam: it replaces m, and v is only read.
 template <int CODEC, bool FROZEN, bool WD>
 __global__ void __launch_bounds__(kWave * kRowWaves)
-k_decompress_adam(const void* __restrict__ codes, const float* __restrict__ meta, size_t n, uint32_t chunk,
+k_decompress_adam(const void* __restrict__ codes, const float* __restrict__ meta, size_t n, uint32_t rows_per_chunk,
                   float* __restrict__ param, float* __restrict__ mbuf, float* __restrict__ vbuf, float lr, float beta1,
-                  float omb1, float beta2, float omb2, float eps, float wd)
+                  float omb1, float beta2, float omb2, float eps, float wd, ChunkOrder order)
 {
-    const size_t row = static_cast<size_t>(blockIdx.x) * kRowWaves + wave_index();
+    const uint32_t row = order(blockIdx.x) * kRowWaves + wave_index();
     const int lane = threadIdx.x & 63;
-    const size_t e0 = row * kRow;
+    const size_t e0 = static_cast<size_t>(row) * kRow;
     if (e0 >= n) return;
-    const size_t c = e0 / chunk;
+    const size_t c = row / rows_per_chunk;
     const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
 
     f4 p = load_row(param + e0, lane, remain, 0.0f);
@@ -314,11 +314,12 @@ extern "C" int bagua_decompress_sgd_step(int codec, const void* codes, const flo
     if (!aligned16(codes) || !aligned4(meta) || !aligned16(param) || !aligned16(momentum_buf)) return BAGUA_ERR_ALIGNMENT;
     dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), block(kWave * kRowWaves);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint32_t ch = static_cast<uint32_t>(chunk);
+    const uint32_t rpc = static_cast<uint32_t>(chunk / kRow);
+    const ChunkOrder order = n <= (static_cast<size_t>(1) << 24) ? row_order(grid.x, rpc) : ChunkOrder{0, 0};
     const bool mom = momentum_buf != nullptr, wd = weight_decay != 0.0f;
 #define BAGUA_SGD(CODEC, MOMv, WDv)                                                                          \
-    hipLaunchKernelGGL((k_decompress_sgd<CODEC, MOMv, WDv>), grid, block, 0, s, codes, meta, n, ch, param, \
-                       momentum_buf, lr, momentum, weight_decay)
+    hipLaunchKernelGGL((k_decompress_sgd<CODEC, MOMv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, \
+                       momentum_buf, lr, momentum, weight_decay, order)
 #define BAGUA_SGD_CODEC(CODEC)                       \
     if (mom && wd) BAGUA_SGD(CODEC, true, true);     \
     else if (mom) BAGUA_SGD(CODEC, true, false);     \
@@ -353,12 +354,13 @@ extern "C" int bagua_decompress_adam_step(int codec, const void* codes, const fl
         return BAGUA_ERR_ALIGNMENT;
     dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), block(kWave * kRowWaves);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint32_t ch = static_cast<uint32_t>(chunk);
+    const uint32_t rpc = static_cast<uint32_t>(chunk / kRow);
+    const ChunkOrder order = n <= (static_cast<size_t>(1) << 24) ? row_order(grid.x, rpc) : ChunkOrder{0, 0};
     const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
     const bool frozen = variance_frozen != 0, wd = weight_decay != 0.0f;
 #define BAGUA_ADAM(CODEC, FRv, WDv)                                                                            \
-    hipLaunchKernelGGL((k_decompress_adam<CODEC, FRv, WDv>), grid, block, 0, s, codes, meta, n, ch, param, m, \
-                       v, lr, beta1, omb1, beta2, omb2, eps, weight_decay)
+    hipLaunchKernelGGL((k_decompress_adam<CODEC, FRv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, m, \
+                       v, lr, beta1, omb1, beta2, omb2, eps, weight_decay, order)
 #define BAGUA_ADAM_CODEC(CODEC)                        \
     if (frozen && wd) BAGUA_ADAM(CODEC, true, true);   \
     else if (frozen) BAGUA_ADAM(CODEC, true, false);   \

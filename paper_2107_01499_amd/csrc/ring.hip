@@ -778,19 +778,6 @@ k_lp_apply_mix(const float* __restrict__ x, const float* __restrict__ h_own, flo
 }
 
 
-// In a bucket that the caches hold, the rows of a chunk are mixed on the die whose L2 they still lie in: the one where the encode of that
-// chunk, its workgroup c, has just read x and written the public copy.  Up to 2^25 elements; plain order -> this, encode + mix, on three
-// sets of buffers in turn: 1.5 M 15.2 -> 13.7 us, 4 M, C = 8192, 32.2 -> 27.0, C = 1024, 31.0 -> 27.4, 6.5 M, C = 4096, 46.6 -> 44.1, 13 M
-// 85.3 -> 83.0, 30 M 186.7 -> 183.4, C = 2048 187.8 -> 187.8; 45 M 283 -> 286.  Chunks whose workgroups (`groups` of them, of kRowWaves
-// rows) are not a power of two in number keep the plain order.
-static ChunkOrder mix_order(size_t n, unsigned groups, uint32_t rows_per_chunk)
-{
-    const uint32_t per = rows_per_chunk / kRowWaves;
-    if (n > (static_cast<size_t>(1) << 25) || per == 0 || per * kRowWaves != rows_per_chunk || (per & (per - 1)) != 0) return ChunkOrder{0, 0};
-    const uint32_t lg = static_cast<uint32_t>(__builtin_ctz(per));
-    return ChunkOrder{lg, groups & ~((8u << lg) - 1u)};
-}
-
 }  // namespace bagua
 
 extern "C" int bagua_lp_encode(const float* x, float* xhat, size_t n, size_t chunk, uint8_t* codes, float* minmax,
@@ -839,7 +826,7 @@ extern "C" int bagua_lp_apply_mix(const float* x, const float* xhat_own, float* 
     dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), block(kWave * kRowWaves);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint32_t rpc = static_cast<uint32_t>(chunk / kRow);
-    const ChunkOrder order = mix_order(n, grid.x, rpc);
+    const ChunkOrder order = n <= (static_cast<size_t>(1) << 25) ? row_order(grid.x, rpc) : ChunkOrder{0, 0};
     const float third = 1.0f / 3.0f;
 #define BAGUA_MIX(L, R, S)                                                                                            \
     hipLaunchKernelGGL((k_lp_apply_mix<L, R, S>), grid, block, 0, s, x, xhat_own, xhat_left, xhat_right, codes_left, \

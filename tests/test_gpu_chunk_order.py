@@ -134,3 +134,26 @@ def test_share_of_a_ring(bg, oracle, chunk, n):
     sent = [(torch.from_numpy(want_codes[j]).cuda(), torch.from_numpy(want_mm[j]).cuda()) for j in (0, 2)]
     bg.bagua_lp_apply_mix(x, hg[1], hg[0], hg[2], *sent[0], *sent[1], chunk, out)
     assert same(out, want_out[1]) and same(hg[0], want_hat[0]) and same(hg[2], want_hat[2])
+
+
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+@pytest.mark.parametrize("chunk,n", [(256, 8193), (512, 512 * 8 - 1), (512, 512 * 17 + 300), (768, 768 * 33 + 5), (4096, 4096 * 23 + 256), (16384, 16384 * 19 - 1), (2048, 1 << 24),
+                                     (2048, (1 << 24) + 1)])
+def test_optimizer_steps(bg, oracle, codec, chunk, n):
+    """The rows are updated in the order of the chunks up to 2^24 elements."""
+    print("order steps %s C=%d n=%d" % (codec, chunk, n), flush=True)
+    codes, meta = (oracle.compress_minmax_u8 if codec == "minmax" else oracle.sign_compress_ef)(draw("normal", n, 23 * chunk, "cpu", 1e-3).numpy(), None, chunk)
+    cid = bg.CODEC_MINMAX_U8 if codec == "minmax" else bg.CODEC_SIGN1
+    cg, mg = torch.from_numpy(codes.view(np.uint8 if codec == "minmax" else np.int32)).cuda(), torch.from_numpy(meta).cuda()
+    p, m = draw("normal", n, 23 * chunk + 1, "cpu", 0.02), draw("normal", n, 23 * chunk + 2, "cpu", 1e-3)
+    v = m * m + 1e-8
+    pg, mo = p.cuda(), m.cuda()
+    bg.bagua_decompress_sgd_step(cid, cg, mg, n, chunk, pg, mo, 1e-3, momentum=0.9, weight_decay=1e-4)
+    want_p, want_m = p.numpy().copy(), m.numpy().copy()
+    oracle.decompress_sgd_step(cid, codes, meta, n, chunk, want_p, want_m, 1e-3, momentum=0.9, weight_decay=1e-4)
+    assert same(pg, want_p) and same(mo, want_m)
+    pg, mo, vg = p.cuda(), m.cuda(), v.cuda()
+    bg.bagua_decompress_adam_step(cid, cg, mg, n, chunk, pg, mo, vg, 1e-4, variance_frozen=True)
+    want_p, want_m, want_v = p.numpy().copy(), m.numpy().copy(), v.numpy().copy()
+    oracle.decompress_adam_step(cid, codes, meta, n, chunk, want_p, want_m, want_v, 1e-4, variance_frozen=True)
+    assert same(pg, want_p) and same(mo, want_m) and same(vg, want_v)
