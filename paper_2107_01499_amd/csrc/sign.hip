@@ -4,7 +4,7 @@
 //
 // Lane l of a wave owns elements 4l..4l+3 of every 256-element row, so the group of four that the
 // fixed |v| summation order is defined on is exactly one lane's 128-bit load, accumulator m mod 64
-// is lane m mod 64, and the final xor butterfly is a wave-level shuffle reduction.
+// is lane m mod 64, and the final xor butterfly is a reduction over the wave.
 #include "batch.hpp"
 #include "launchers.hpp"
 #include "sign_device.hpp"
