@@ -230,15 +230,17 @@ inline bool short_launch(size_t elements_per_launch, bool batched = false)
     return elements_per_launch < (static_cast<size_t>(1) << (batched ? 26 : 25));
 }
 
-// A batched worker-side launch of 2^26 elements or more with chunks of 1024, 1536 or 2048 elements (two, three or four waves): tail tests
+// A batched worker-side launch of 2^26 to 2^29 elements with chunks of 1024, 1536 or 2048 elements (two, three or four waves): tail tests
 // folded away, and 16 waves on a CU at a time.  Each alone loses (without the bound up to -7 %, bounded to 24 waves or with the tests
 // -1 .. -30 %); tests and all waves -> this, whole rounds in buckets of 2.5 to 10 M: sign codec, 8 workers x 374 M, C = 2048, 6427 -> 6326
 // us, 8 x 134 M 2360 -> 2248, 2 x 134 M 816 -> 790, C = 1536 2333 -> 2226, C = 1024 2322 -> 2257; MinMax, 8 x 134 M, C = 2048, 2764 -> 2675,
 // C = 1536 2752 -> 2667, C = 1024 2734 -> 2652, 4 x 75 M 851 -> 801.  Longer chunks lose 1-14 %, 768 elements never fill the last
-// wave.  Unbatched launches run one row per wave and have nothing to gain.  The value: workgroups on a CU, or 0.
+// wave.  Unbatched launches run one row per wave and have nothing to gain.  Beyond 2^29, in time: 8 x 700 M, C = 2048, sign codec -0.5 %,
+// MinMax -1.1 .. +0.9 %, 8 x 1.5 G +-0.4 %, 4 x 700 M, MinMax, C = 1024 +2 %.  The value: workgroups on a CU, or 0.
 inline int batched_groups(size_t elements, size_t chunk, unsigned threads)
 {
-    const bool pays = chunk >= 1024 && chunk <= 2048 && chunk % (2 * kRow) == 0 && elements >= (static_cast<size_t>(1) << 26);
+    const bool pays = chunk >= 1024 && chunk <= 2048 && chunk % (2 * kRow) == 0 && elements >= (static_cast<size_t>(1) << 26) &&
+                      elements <= (static_cast<size_t>(1) << 29);
     return pays ? 16 / static_cast<int>(threads / kWave) : 0;
 }
 
