@@ -308,6 +308,13 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
 }
 
 // ------------------------------------------------------------------------------------------ host
+// Workgroups of a full-precision round: a row each up to 16 peers (k_ring_avg_fp), kRowWaves rows above.
+static size_t ring_fp_groups(int k, size_t n)
+{
+    const size_t rows = (n + kRow - 1) / kRow;
+    return k <= 16 ? rows : (rows + kRowWaves - 1) / kRowWaves;
+}
+
 // Waves (of K KB each) on a CU at a time, by buffers that lie back to back; unbounded -> bounded, in us.  The best numbers were 16,
 // 10 to 12, 8, 8 to 10, 5 or 6, 4 or 5 and 4 for 2, 3, 4, 5, 7 and 8, 12 and 16 peers, about 36 KB:
 //   8 x 109 M 1258 -> 1132 (6.2 TB/s; eight waves per workgroup, unbounded, 1238; 109 M lying far apart in HBM 1080 -> 1072),
@@ -318,9 +325,8 @@ template <int K>
 static void launch_fp_k(const PtrTable& in, const MutPtrTable& out, size_t n, float third, hipStream_t s)
 {
     constexpr int waves = (36 + K - 1) / K < 4 ? 4 : (36 + K - 1) / K;
-    const size_t rows = (n + kRow - 1) / kRow;
     const size_t lds = K >= 2 && 2 * K * n * sizeof(float) >= (static_cast<size_t>(1) << 27) ? lds_for_residency(waves) : 0;
-    hipLaunchKernelGGL((k_ring_avg_fp<K>), dim3(static_cast<unsigned>(rows)), dim3(kWave), lds, s, in, out, n, third);
+    hipLaunchKernelGGL((k_ring_avg_fp<K>), dim3(static_cast<unsigned>(ring_fp_groups(K, n))), dim3(kWave), lds, s, in, out, n, third);
 }
 
 static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, size_t n, hipStream_t stream)
@@ -331,8 +337,6 @@ static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, 
         in.p[i] = x_in[i];
         out.p[i] = x_out[i];
     }
-    const size_t rows = (n + kRow - 1) / kRow;
-    dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves));
     const float third = 1.0f / 3.0f;
     switch (k) {
 #define BAGUA_FP_CASE(K) case K: launch_fp_k<K>(in, out, n, third, stream); break;
@@ -341,7 +345,8 @@ static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, 
         BAGUA_FP_CASE(13) BAGUA_FP_CASE(14) BAGUA_FP_CASE(15) BAGUA_FP_CASE(16)
 #undef BAGUA_FP_CASE
         default:
-            hipLaunchKernelGGL(k_ring_avg_fp_any, grid, dim3(kWave * kRowWaves), 0, stream, in, out, k, n, third);
+            hipLaunchKernelGGL(k_ring_avg_fp_any, dim3(static_cast<unsigned>(ring_fp_groups(k, n))), dim3(kWave * kRowWaves), 0, stream, in,
+                               out, k, n, third);
     }
     return launch_status();
 }
@@ -447,8 +452,7 @@ extern "C" int bagua_decentralized_avg(int mode, const float* const* x_in, float
         if (!aligned16(x_in[i]) || !aligned16(x_out[i])) return BAGUA_ERR_ALIGNMENT;
         if (lp && (!aligned16(xhat[i]) || !aligned16(codes[i]) || !aligned4(minmax[i]))) return BAGUA_ERR_ALIGNMENT;
     }
-    const size_t rows = (n + kRow - 1) / kRow;
-    if ((rows + kRowWaves - 1) / kRowWaves > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
+    if ((lp ? num_chunks(n, chunk) : ring_fp_groups(k, n)) > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!lp) return launch_ring_fp(x_in, x_out, k, n, s);
     return launch_ring_lp(x_in, x_out, xhat, codes, minmax, k, n, chunk, s);

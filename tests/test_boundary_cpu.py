@@ -225,3 +225,14 @@ def test_validation_of_the_batched_and_fused_entry_points_without_gpu(bg):
     assert lib.bagua_probe_streams(one(A), one(B), None, 1, 1, 0, 1, 100, None) == INVALID             # n not a multiple of 256
     three = (ctypes.c_void_p * 3)(A, Cc, D)
     assert lib.bagua_probe_streams(three, one(B), None, 3, 1, 0, 1, 256, None) == UNSUPPORTED            # combination not offered
+
+
+@pytest.mark.parametrize("k", [1, 2, 16])
+def test_ring_larger_than_a_grid_is_refused_without_gpu(bg, k):
+    """One workgroup per row (full precision, up to 16 peers) or per chunk: the first sizes with more than 2^31 - 1 of them.  The
+    buffers are addresses only, each as far from the next as the call would need."""
+    UNSUPPORTED, n = 4, 256 * (1 << 31)
+    ptrs = [(ctypes.c_void_p * k)(*[(1 + 6 * i + j) << 42 for i in range(k)]) for j in range(5)]
+    lib = bg.binding.raw()
+    assert lib.bagua_decentralized_avg(0, ptrs[0], ptrs[1], None, None, None, k, n, 0, None) == UNSUPPORTED
+    assert lib.bagua_decentralized_avg(1, *ptrs, k, n, 256, None) == UNSUPPORTED
