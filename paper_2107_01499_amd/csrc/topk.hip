@@ -4,9 +4,11 @@
 //
 // Selection of the K largest |v| of a chunk (ties: lower index) without sorting: the chunk stays in registers and is
 // counted by the distance of each magnitude (as an integer: the bit pattern of |v|) below the chunk's largest one.  A
-// first histogram of 64 bins per binade finds the bin with the K-th largest magnitude; as long as that bin holds more
-// elements than are still needed, it alone is counted again, eight bits finer.  Integer atomics in LDS only, so the
-// result does not depend on execution order.  The kept elements' output slots come from ballots and bit counts.
+// first histogram of 64 bins per binade finds the bin with the K-th largest magnitude; if it does not reach that far
+// down (an outlier, layers of different scale, fewer than K values that are not zero), one of a bin per binade follows.
+// As long as the bin found holds more elements than are still needed, it alone is counted again, eight bits finer.
+// Integer atomics in LDS only, so the result does not depend on execution order.  The kept
+// elements' output slots come from ballots and bit counts.
 #include "launchers.hpp"
 
 #pragma clang fp contract(off)
@@ -17,10 +19,16 @@ namespace bagua {
 // magnitude; what lies below is not counted, and looked at only if the bins do not reach the K-th.  Counted in a last
 // bin instead, where many lanes of a wave meet in one counter, a short launch (1 M elements, one workgroup per CU) took
 // 8.9 us instead of 7.2; two or four copies of the bins gained nothing.
-constexpr int kFirstShift = 17, kFirstBins = 256;
-constexpr int kNextBits = 8, kNextBins = 1 << kNextBits;
-constexpr int kHistWords = kFirstBins + 2 * kNextBins;
+constexpr int kBinBits = 8, kBins = 1 << kBinBits;
+constexpr uint32_t kFirstShift = 17, kFirstBits = kFirstShift + kBinBits;
+// The binades below: one lane sums one binade, so 64 of them (the last one takes what lies farther down as well), in eight
+// copies, because a chunk's values share a handful of binades.
+constexpr uint32_t kBinadeShift = 23, kBinadeCopies = 8;
+// 0: the first histogram, 1 and 2: the binades.  Refinements take 1, 2 and 3, or 3, 0 and 1 behind the binades.  4.2 KB: 32
+// workgroups of one wave still fit a CU.
+constexpr int kHists = 4, kHistWords = kHists * kBins;
 constexpr int kTopkLdsWords = kHistWords + 2 * kMaxWaves;
+static_assert(kWave * kBinadeCopies == 2 * kBins, "the binades' counters take two histograms");
 
 __device__ __forceinline__ uint32_t mag_key(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
@@ -70,16 +78,70 @@ __device__ __forceinline__ void topk_clear(uint32_t* hist, int words)
     for (int t = threadIdx.x; t < words / 4; t += blockDim.x) reinterpret_cast<uint4*>(hist)[t] = uint4{0u, 0u, 0u, 0u};
 }
 
+// Adds the wave's elements with distances in [lo, lo + 2^bits) to h, one bin per 2^shift.  Lanes that meet in one counter are
+// served one after another; where many share a bin (`crowded`), all lanes that are in the bin of the first one that has
+// any are added at once.
+template <int RPW>
+__device__ __forceinline__ void count_bins(const uint32_t (&dist)[RPW][4], uint32_t lo, uint32_t bits, uint32_t shift, bool crowded, int lane, uint32_t* h)
+{
+    if (__builtin_expect(!crowded, 1)) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t r = dist[i][e] - lo;
+                if ((r >> bits) == 0) atomicAdd(&h[r >> shift], 1u);
+            }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t r = dist[i][e] - lo, bin = r >> shift;
+            const unsigned long long in = __ballot((r >> bits) == 0);
+            const int first = in != 0 ? __builtin_ctzll(in) : 0;
+            const unsigned long long same = in & __ballot(bin == static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(bin), first)));
+            const unsigned long long adds = (in & ~same) | (same & (0ull - same));   // same's first lane for all of them
+            if (adds >> lane & 1) atomicAdd(&h[bin], lane == first ? static_cast<uint32_t>(__builtin_popcountll(same)) : 1u);
+        }
+    }
+}
+
+// The wave's elements with distances from lo on, one bin per binade, zeros left out.
+template <int RPW>
+__device__ __forceinline__ void count_binades(const uint32_t (&dist)[RPW][4], uint32_t lo, uint32_t top, int lane, uint32_t* h)
+{
+    constexpr uint32_t kFar = (static_cast<uint32_t>(kWave) << kBinadeShift) - 1;   // in the last of the 64
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t r = dist[i][e] - lo;
+            if (r < top - lo) atomicAdd(&h[((r < kFar ? r : kFar) >> kBinadeShift) * kBinadeCopies + (lane & (kBinadeCopies - 1))], 1u);
+        }
+}
+
 // Number of lanes below this one with their bit set, added to acc.
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_t acc)
 {
     return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), acc));
 }
 
-// What bounds it: HBM from 2048-element chunks on (12.2 bytes per element at 5.9 TB/s for 25.7 M elements), below that the
-// waves per CU.  Before (four radix passes from the exponent down, its histogram in 16 copies: 20 KB of LDS per chunk, seven
-// barriers, 122 vector instructions per element of a lane against 52) -> now, whole rounds: 3 workers x 33 M, C = 1024, 582
-// -> 398 us, 12 x 2.6 M, C = 2048, 144 -> 116 us, 8 x 25.7 M, C = 4096, 543 -> 530 us, 4 x 25.6 M, C = 16384, 574 -> 409 us.
+// What bounds it: HBM from 2048-element chunks on if the magnitudes spread like a normal distribution's (12.2 bytes per element at
+// 5.9 TB/s for 25.7 M elements), below that the waves per CU.  Before (four radix passes from the exponent down, its histogram in
+// 16 copies: 20 KB of LDS per chunk, seven barriers, 122 vector instructions per element of a lane against 52) -> now, whole
+// rounds: 3 workers x 33 M, C = 1024, 582 -> 398 us, 12 x 2.6 M, C = 2048, 144 -> 116 us, 8 x 25.7 M, C = 4096, 543 -> 530 us,
+// 4 x 25.6 M, C = 16384, 574 -> 409 us.
+// Other data, 25.7 M elements without error state that fit the caches, compression / server step of 4 workers; the radix passes -> this
+// selection without count_binades and without the crowded form of count_bins -> with both:
+//                                          C = 4096, K = 128                    C = 1024, K = 32
+//   normal distribution                    33 / 39 -> 30.3 / 25 -> 30.7 / 25    74 / 89 -> 26.7 / 24 -> 27.1 / 24 us
+//   the same and one outlier per chunk     32 / 39 -> 52 / 98 -> 39 / 28        75 / 90 -> 43 / 95 -> 35 / 27 us
+//   all zero                               275 / 282 -> 355 / 360 -> 123 / 120  286 / 298 -> 348 / 356 -> 108 / 114 us
+//   99 % zero                              272 / 280 -> 360 / 360 -> 33 / 32    284 / 296 -> 348 / 353 -> 30 / 31 us
+//   all magnitudes equal                   274 / 39 -> 354 / 23 -> 123 / 23     286 / 90 -> 347 / 23 -> 108 / 23 us
+// What is left of the equal magnitudes is the first histogram: a test for them before it costs normal data 2 %.
 //
 // Encode the chunk held in v (absent elements must be +0.0f).  idx_c/val_c point at the chunk's `keep` output slots,
 // residual/out at the chunk's first element (nullptr = not wanted).
@@ -89,8 +151,6 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
                                                   float* __restrict__ residual, uint16_t* __restrict__ idx_c,
                                                   float* __restrict__ val_c, float* __restrict__ out, uint32_t* smem)
 {
-    uint32_t* first = smem;
-    uint32_t* next = smem + kFirstBins;   // two of them, used in turn
     uint32_t* s_top = smem + kHistWords;
     uint32_t* s_count = s_top + kMaxWaves;
     const uint32_t keff = (static_cast<int>(keep) < len) ? keep : static_cast<uint32_t>(len);
@@ -125,38 +185,57 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
     }
 
     // ---- threshold: the `need` first of the `in_bin` elements with distances in [lo, lo + 2^bits) are kept, and all below lo
-#pragma unroll
-    for (int i = 0; i < RPW; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t d = dist[i][e] >> kFirstShift;
-            if (d < kFirstBins) atomicAdd(&first[d], 1u);
-        }
+    count_bins<RPW>(dist, 0, kFirstBits, kFirstShift, false, lane, smem);
     __syncthreads();
     uint32_t need = keff, bin, before, in_bin;
-    find_bin(first, lane, need, bin, before, in_bin);
+    find_bin(smem, lane, need, bin, before, in_bin);
     need -= before;
-    uint32_t lo = bin << kFirstShift;
-    uint32_t bits = bin == kFirstBins ? 31 : kFirstShift;
-    for (int pass = 0; in_bin != need && bits != 0; ++pass) {
-        uint32_t* h = next + (pass & 1) * kNextBins;
-        if (pass >= 2) {   // read last before the barrier of the previous pass
-            topk_clear(h, kNextBins);
-            __syncthreads();
-        }
-        const uint32_t shift = bits > kNextBits ? bits - kNextBits : 0;
-#pragma unroll
-        for (int i = 0; i < RPW; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t r = dist[i][e] - lo;
-                if ((r >> bits) == 0) atomicAdd(&h[r >> shift], 1u);
-            }
+    uint32_t lo = bin << kFirstShift, bits = kFirstShift;
+    auto refine = [&](uint32_t* h, bool crowded) {
+        const uint32_t shift = bits > kBinBits ? bits - kBinBits : 0;
+        count_bins<RPW>(dist, lo, bits, shift, crowded, lane, h);
         __syncthreads();
         find_bin(h, lane, need, bin, before, in_bin);
         need -= before;
         lo += bin << shift;
         bits = shift;
+    };
+    // An eighth of a chunk in a 64th of a binade: values that are equal, or nearly so, and go on sharing their bins.
+    if (__builtin_expect(bin != kBins && in_bin <= static_cast<uint32_t>(len) / 8, 1)) {
+        uint32_t* h = smem;
+        while (in_bin != need && bits != 0) refine(h += kBins, false);   // at most three times
+    } else {
+        const bool far = bin == kBins;
+        if (far) {
+            uint32_t* h = smem + kBins;
+            count_binades<RPW>(dist, lo, top, lane, h);
+            __syncthreads();
+            const uint4 p = reinterpret_cast<const uint4*>(h)[2 * lane], q = reinterpret_cast<const uint4*>(h)[2 * lane + 1];
+            const uint32_t c = ((p.x + p.y) + (p.z + p.w)) + ((q.x + q.y) + (q.z + q.w));
+            const uint32_t pre = wave_prefix_incl(c);
+            const unsigned long long reached = __ballot(pre >= need);
+            if (reached == 0) {   // all of them are kept, and zeros
+                need -= __builtin_amdgcn_readlane(static_cast<int>(pre), kWave - 1);
+                lo = top;
+                bits = 0;
+            } else {
+                const int L = __builtin_ctzll(reached);
+                in_bin = L < kWave - 1 ? __builtin_amdgcn_readlane(static_cast<int>(c), L) : 0;   // the last one's range has the zeros in it
+                need -= __builtin_amdgcn_readlane(static_cast<int>(pre - c), L);
+                lo += static_cast<uint32_t>(L) << kBinadeShift;
+                bits = L < kWave - 1 ? kBinadeShift : 31;
+            }
+        }
+        int next = far ? 3 : 1;
+        bool crowded = !far;   // a binade's elements spread over the bins again
+        while (in_bin != need && bits != 0) {
+            // Behind the binades up to four refinements: the next one's histogram is cleared here, where every wave is past the
+            // barrier before which the waves read it last.
+            if (far) topk_clear(smem + ((next + 1) & (kHists - 1)) * kBins, kBins);
+            refine(smem + (next & (kHists - 1)) * kBins, crowded);
+            crowded = in_bin > static_cast<uint32_t>(len) / 8;
+            ++next;
+        }
     }
     // Either all of the last bin is kept, or it is one magnitude of which the first `need` in index order are kept.
     const bool ties = in_bin != need;
