@@ -124,6 +124,7 @@ static_assert(rpw_built(BAGUA_RPW_COMPRESS) && rpw_built(BAGUA_RPW_DRR) && rpw_b
 constexpr int kWave = 64;
 constexpr int kRow = 256;      // elements per wave-wide 128-bit access
 constexpr int kMaxWaves = 16;  // waves per workgroup (1024 threads)
+constexpr int kCus = 256, kWavesPerCu = 32;   // and the most waves that one holds
 // Rows (one wavefront each) per workgroup of the kernels that stream row by row without a chunk statistic (decode,
 // optimizer steps, peer averaging, the probes).  Measured: two waves per workgroup are 0.5-3 % faster than four and than one.
 #ifndef BAGUA_ROW_WAVES
@@ -445,6 +446,18 @@ inline int pick_rpw(int rows, int preferred)
 inline int pick_rpw_worker(int rows, int preferred)
 {
     return pick_rpw(rows, (preferred == 2 && rows >= 6 && rows <= 8) ? 1 : preferred);
+}
+
+// The top-K compression.  Two rows per wave, but four where a launch of chunks above 4096 elements then runs all at once instead of
+// in two goes, the second of them nearly empty.  Whole rounds of 8 workers, two -> four: C = 8192, 4.2 M elements 139.8 -> 126.5 us,
+// 6 M 171.8 -> 156.5, 8 M 210.4 -> 207.5; C = 6144, 4.2 M 137.8 -> 125.4, 6 M 170.2 -> 156.7; C = 4608, 4.2 M 130.0 -> 127.3.
+// Outside: C = 8192, 3 M 107.1 -> 108.5, 25 M 537 -> 547; C = 6144, 3 M 95.7 -> 103.7, 8 M 217.6 -> 222.0; C = 4608, 3 M 98.4 -> 108.3, 6 M
+// 170.9 -> 186.5; C = 4096 and below, 2 M to 15 M, +4 .. +12 %.
+inline int pick_rpw_topk(int rows, size_t chunks)
+{
+    const int rpw = pick_rpw(rows, BAGUA_RPW_TOPK), waves = (rows + rpw - 1) / rpw;
+    const size_t at_once = static_cast<size_t>(kCus * (kWavesPerCu / waves));
+    return rpw == 2 && waves > 8 && chunks > at_once && chunks <= static_cast<size_t>(4 * kCus) ? 4 : rpw;
 }
 
 // Expands `stmt` with a constexpr RPW equal to the runtime value rpw (2 or 4; chunks have at most 64 rows).

@@ -511,7 +511,7 @@ extern "C" int bagua_compress_topk_ef(const float* x, float* residual, size_t n,
     if (num_chunks(n, chunk) > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(residual) || !aligned2(idx) || !aligned4(val)) return BAGUA_ERR_ALIGNMENT;
     const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw(rows, BAGUA_RPW_TOPK);
+    const int rpw = pick_rpw_topk(rows, num_chunks(n, chunk));
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -120,6 +120,19 @@ def test_select_far_below_the_largest(bg, oracle, kind, C, keep):
     assert same(ig2, io) and same(vg2, vo) and same(og, oo)
 
 
+@pytest.mark.parametrize("C,chunks", [(8192, 512), (8192, 513), (8192, 1024), (8192, 1025), (4608, 769)])
+def test_rows_per_wave(bg, oracle, C, chunks):
+    """The launches between which the compression changes the rows per wave."""
+    n, keep = C * chunks - 5, C // 32
+    print("rows per wave C=%d chunks=%d" % (C, chunks), flush=True)
+    x, res = values("normal", n, chunks), values("normal", n, chunks + 1)
+    rg, slots = dev(res), chunks * keep
+    ig, vg = torch.zeros(slots, dtype=torch.int16, device="cuda"), torch.zeros(slots, device="cuda")
+    bg.bagua_compress_topk_ef(dev(x), rg, C, keep, ig, vg)
+    io, vo = oracle.compress_topk(x, res, C, keep)
+    assert same(ig, io) and same(vg, vo) and same(rg, res)
+
+
 def test_time_depends_little_on_the_data(bg):
     """Chunks whose lanes all meet in one counter against normally distributed ones, medians of event times on the same buffers: 3.4 to 3.9
     times as long, where counting them lane by lane in every pass takes 9.7 to 10.8 times; an outlier per chunk in the server step 1.0
