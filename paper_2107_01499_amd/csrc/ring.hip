@@ -20,14 +20,15 @@ __device__ __forceinline__ f4 sub4(f4 a, f4 b) { return f4{a.x - b.x, a.y - b.y,
 __device__ __forceinline__ f4 mul4(f4 a, float s) { return f4{a.x * s, a.y * s, a.z * s, a.w * s}; }
 
 // ------------------------------------------------------------------------------------------ FP
-// One wave per 256-element row and workgroup; K replicas held in registers.  Bound by how well the memory system copes with
-// 2 K streams, which depends on how much of them is in flight on a CU: see launch_fp_k.
-template <int K>
-__global__ void __launch_bounds__(kWave)
+// One wave per 256-element row, ROWS of them per workgroup; K replicas held in registers.  Bound by how well the memory system
+// copes with 2 K streams, which depends on how much of them is in flight on a CU: see ring_fp_waves.
+template <int K, int ROWS>
+__global__ void __launch_bounds__(kWave * ROWS)
 k_ring_avg_fp(PtrTable xin, MutPtrTable xout, size_t n, float third)
 {
-    const int lane = threadIdx.x;
-    const size_t e0 = static_cast<size_t>(blockIdx.x) * kRow;
+    const int lane = threadIdx.x & 63;
+    const size_t e0 = (static_cast<size_t>(blockIdx.x) * ROWS + (ROWS > 1 ? wave_index() : 0)) * kRow;
+    if (ROWS > 1 && e0 >= n) return;
     const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
     f4 x[K];
 #pragma unroll
@@ -308,25 +309,24 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
 }
 
 // ------------------------------------------------------------------------------------------ host
-// Workgroups of a full-precision round: a row each up to 16 peers (k_ring_avg_fp), kRowWaves rows above.
 static size_t ring_fp_groups(int k, size_t n)
 {
-    const size_t rows = (n + kRow - 1) / kRow;
-    return k <= 16 ? rows : (rows + kRowWaves - 1) / kRowWaves;
+    const size_t rows = (n + kRow - 1) / kRow, per = static_cast<size_t>(ring_fp_rows(k, n));
+    return (rows + per - 1) / per;
 }
 
-// Waves (of K KB each) on a CU at a time, by buffers that lie back to back; unbounded -> bounded, in us.  The best numbers were 16,
-// 10 to 12, 8, 8 to 10, 5 or 6, 4 or 5 and 4 for 2, 3, 4, 5, 7 and 8, 12 and 16 peers, about 36 KB:
-//   8 x 109 M 1258 -> 1132 (6.2 TB/s; eight waves per workgroup, unbounded, 1238; 109 M lying far apart in HBM 1080 -> 1072),
-//   8 x 20 M 233 -> 207, 8 x 4 M 46.5 -> 45.6, 4 x 100 M 544 -> 488, 4 x 4 M 23.0 -> 22.6, 2 x 100 M 253 -> 241, 16 x 60 M 1405
-//   -> 1271, 16 x 2 M 48.7 -> 46.5; a launch of less than 2^27 bytes runs in the caches and loses: 8 x 1 M 12.5 -> 13.0, 3 x 1 M
-//   7.2 -> 7.2.  One replica is a copy, which wants all the waves there are: 1 x 200 M 240 -> 269 with 24 of them.
 template <int K>
 static void launch_fp_k(const PtrTable& in, const MutPtrTable& out, size_t n, float third, hipStream_t s)
 {
-    constexpr int waves = (36 + K - 1) / K < 4 ? 4 : (36 + K - 1) / K;
-    const size_t lds = K >= 2 && 2 * K * n * sizeof(float) >= (static_cast<size_t>(1) << 27) ? lds_for_residency(waves) : 0;
-    hipLaunchKernelGGL((k_ring_avg_fp<K>), dim3(static_cast<unsigned>(ring_fp_groups(K, n))), dim3(kWave), lds, s, in, out, n, third);
+    const dim3 grid(static_cast<unsigned>(ring_fp_groups(K, n)));
+    if constexpr (K < 15) {
+        if (ring_fp_rows(K, n) == 8) {
+            hipLaunchKernelGGL((k_ring_avg_fp<K, 8>), grid, dim3(8 * kWave), 0, s, in, out, n, third);
+            return;
+        }
+    }
+    const size_t lds = K >= 2 && ring_fp_long(K, n) ? lds_for_residency(ring_fp_waves(K)) : 0;   // one replica is a copy
+    hipLaunchKernelGGL((k_ring_avg_fp<K, 1>), grid, dim3(kWave), lds, s, in, out, n, third);
 }
 
 static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, size_t n, hipStream_t stream)

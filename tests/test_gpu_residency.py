@@ -29,6 +29,12 @@ def test_ring_fp(bg, oracle, k, n):
     assert all(same(o, w) for o, w in zip(out, want))
 
 
+@pytest.mark.parametrize("k,n", [(1, (1 << 26) - 1), (1, (1 << 26) + 3), (3, 22369621), (3, 22369622), (8, (1 << 23) - 7), (8, (1 << 23) + 2), (14, 4793491), (15, 100), (16, (1 << 22) + 1), (17, 3000)])
+def test_ring_fp_rows_per_workgroup(bg, oracle, k, n):
+    """Either side of 2^29 bytes, where eight rows per workgroup become one, and the numbers of peers that have one row or two throughout."""
+    test_ring_fp(bg, oracle, k, n)
+
+
 @pytest.mark.parametrize("n,chunk", [((1 << 26), 2048), ((1 << 26) + 1, 2048), ((1 << 26) + 77, 16384), (3 * (1 << 24) * 2 - 5, 1536)])
 def test_momentum_compression(bg, oracle, n, chunk):
     print("momentum n=%d C=%d" % (n, chunk), flush=True)
