@@ -154,6 +154,17 @@ static_assert(lds_for_residency(4) <= 64 * 1024, "the most that a launch gets wi
 // The least with which no more than two workgroups fit.
 constexpr size_t kLdsForTwo = (kLdsPerCu / kLdsGranule / 3 + 1) * kLdsGranule;
 
+// Gossip pairs of chunks of 2561 to 4096 elements: two workgroups of six to eight waves on a CU instead of as many as fit, `elements` of
+// all pairs of the launch.  Unbounded -> two, buffers that lie far apart in HBM | back to back: one pair x 100 M 525.8 -> 525.1 | 541.5 ->
+// 539.5 us, x 45 M 234.3 -> 233.3 | 240.0 -> 239.1, two x 25 M 278.3 -> 274.2 | 270.4 -> 269.6, x 33 M, C = 3072, 364.0 -> 357.9 | 359.2 -> 354.3,
+// four x 17 M 370.6 -> 368.3 | 368.9 -> 367.0; below the line one pair x 33 M 171.3 -> 171.6 | 170.8 -> 172.3, x 25 M 132.7 -> 134.3 | 135.9
+// -> 135.7, x 17 M 89.6 -> 93.2 | 90.9 -> 93.3, two x 17 M 185.2 -> 185.3 | 176.8 -> 178.3.  Shorter chunks lose 1-3 %, longer ones do not
+// care.  Workers that sit out move half as many streams and lose 1-2 %: 25.6 M 68.8 -> 69.9 | 68.9 -> 70.1.
+inline size_t gossip_pairs_lds(size_t chunk, size_t elements)
+{
+    return chunk > 2560 && chunk <= 4096 && elements >= (static_cast<size_t>(5) << 23) ? kLdsForTwo : 0;
+}
+
 // The full-precision ring of up to 16 peers, one wave per row of all peers.  Two shapes, chosen by what a launch reads and writes:
 //   below 2^29 bytes eight rows per workgroup, as many workgroups as fit; from 15 peers on (68 VGPRs and more) one row;
 //   from there on one row per workgroup, and no more waves on a CU than keep the memory busy.

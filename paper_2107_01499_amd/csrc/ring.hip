@@ -691,10 +691,6 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
     const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const ChunkOrder order = chunk > 4096 ? chunk_order(nc, chunk) : ChunkOrder{0, 0};   // shorter chunks: -3 .. +1.5 %
-    // Two workgroups of six to eight waves on a CU instead of as many as fit, unbounded -> two, buffers that lie back to back | far apart in
-    // HBM: 7 x 25.6 M, C = 4096, 528 -> 519 | 508 -> 501 us, 8 x 60 M 1469 -> 1454 | 1261 -> 1260, 8 x 17 M 411 -> 400 | 360 -> 359, 4 x 100 M, C =
-    // 3072, 1234 -> 1142 | 1093 -> 1071, 2 x 40 M 223 -> 219 | 206 -> 207; 4 x 3 M loses 4 %, shorter chunks lose 1-3 %, longer ones do not care.
-    const size_t lds = chunk > 2560 && chunk <= 4096 && n >= (static_cast<size_t>(1) << 24) ? kLdsForTwo : 0;
     // matched pairs and workers that are their own peer: one pass
     PeerLpJobs pairs{}, singles{};
     PeerMixJobs mix{};
@@ -724,11 +720,11 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
         }
     }
     if (npairs) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, lds, s, pairs, n, ch,
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, gossip_pairs_lds(chunk, npairs * n), s, pairs, n, ch,
                                                    keep_codes_of_round(k * n), order))
     }
     if (nsingles) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, lds, s, singles, n, ch,
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch,
                                                    keep_codes_of_round(k * n), order))
     }
     if (nmix) {                                         // all public copies are advanced by now

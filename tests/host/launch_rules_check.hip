@@ -38,8 +38,17 @@ static void ring_fp()
     EXPECT(ring_fp_rows(17, 1) == kRowWaves && ring_fp_rows(17, line) == kRowWaves);
 }
 
+static void gossip()
+{
+    const size_t line = static_cast<size_t>(5) << 23;
+    EXPECT(gossip_pairs_lds(4096, line) == kLdsForTwo && gossip_pairs_lds(4096, line - 1) == 0 && gossip_pairs_lds(2816, line) == kLdsForTwo);
+    EXPECT(gossip_pairs_lds(2560, 4 * line) == 0 && gossip_pairs_lds(4352, 4 * line) == 0);
+    EXPECT(kLdsPerCu / kLdsForTwo == 2 && kLdsForTwo + 4 * kMaxWaves * sizeof(float) <= 64 * 1024);
+}
+
 int main()
 {
+    gossip();
     ring_fp();
     topk_rows();
     if (failed) return 1;

@@ -61,6 +61,11 @@ def test_gossip_pairs(bg, oracle, n, chunk):
         assert same(out[j], want_out[j]) and same(hg[j], want_hat[j]) and same(mm[j], want_mm[j]) and np.array_equal(codes[j].cpu().numpy(), want_codes[j])
 
 
+@pytest.mark.parametrize("n,chunk", [((5 << 23) - 3, 4096), ((5 << 23) + 5, 2816)])
+def test_gossip_pairs_either_side_of_the_bound(bg, oracle, n, chunk):
+    test_gossip_pairs(bg, oracle, n, chunk)
+
+
 @pytest.mark.parametrize("codec", ["minmax", "sign"])
 @pytest.mark.parametrize("chunk,sizes", [(2048, [(1 << 25) + 2048 * 3, 1000, (1 << 25) - 2048 * 2 - 1000]), (1536, [1 << 25, 77, (1 << 25) + 1]), (1024, [(1 << 26) - 1025, 1])])
 def test_batched_worker_side(bg, oracle, codec, chunk, sizes):
