@@ -199,7 +199,8 @@ inline int ring_fp_rows(int peers, size_t n)
 //   longer: 2^2 +1.0 .. +5.6, 2^5 -1.4 .. +5.1, 2^7 negative.
 // Top-K: 0 .. +3 (4 x 60 M, C = 1536, 831 -> 807 us); gossip pairs of chunks above 4096: -0.6 .. +5.7 (8 x 60 M, C = 8192, 1530 -> 1448).
 // From 2048 chunks on; below, +1 .. -6 without a pattern.  The server steps, the decodes and the full-precision kernels gained
-// nothing at any length (the ring of eight -1 .. -8 %).
+// nothing at any length (the ring of eight -1 .. -8 %).  From 2^28 elements on the longer chunks gain as much (batched MinMax, plain -> this:
+// 600 M, C = 2048, 1215 -> 1179 us, 700 M, C = 4096, 1443 -> 1405, 1.5 G, C = 16384, 3325 -> 3152), and short ones lose: see order_pays_*.
 struct ChunkOrder {
     uint32_t lg, end;   // chunks from `end` on: plain order
     __device__ __forceinline__ uint32_t operator()(uint32_t b) const
@@ -208,11 +209,22 @@ struct ChunkOrder {
         return b < end ? b - r + ((r & 7u) << lg) + (r >> 3) : b;
     }
 };
-inline ChunkOrder chunk_order(size_t chunks, size_t chunk)
+inline ChunkOrder chunk_order(size_t chunks, size_t chunk, bool pays = true)
 {
-    const uint32_t lg = chunks < 2048 ? 0 : chunk <= 1024 ? 7 : chunk <= 4096 ? 5 : 2;
-    return ChunkOrder{lg, static_cast<uint32_t>(chunks) & ~((8u << lg) - 1u)};
+    const uint32_t lg = !pays || chunks < 2048 ? 0 : chunk <= 1024 ? 7 : chunk <= 4096 ? 5 : 2;
+    return ChunkOrder{lg, lg == 0 ? 0 : static_cast<uint32_t>(chunks) & ~((8u << lg) - 1u)};
 }
+// Where short chunks keep the plain order, plain -> runs of 128 in us.  Contiguous input, chunks of 1024: sign codec, 268 M 503 -> 496, 350 M
+// 642 -> 647, 500 M 941 -> 953, 700 M 1284 -> 1292; MinMax, 268 M 554 -> 549, 350 M 700 -> 702, 500 M 997 -> 1007, 700 M 1381 -> 1392.  (C = 768
+// +-0.4 % above the line; C = 512 from 2^28 on between -1.1 and +2 % from one set of buffers to the next, without a pattern.)
+inline bool order_pays(size_t n, size_t chunk) { return chunk != 1024 || n <= (static_cast<size_t>(1) << 28); }
+// Intra-node average of three and more, chunks up to 512: MinMax, whole rounds of two nodes of four, C = 512, 35 M 368 -> 367, 50 M 528 ->
+// 534, 100 M 1062 -> 1105, C = 256, 25 M 290 -> 291, 35 M 397 -> 403; of eight, C = 256, 50 M 477 -> 491, sign codec 100 M 846 -> 867.  Two in a
+// node gain (50 M 391 -> 389, 100 M 792 -> 793), longer chunks do (C = 768, 100 M, 1074 -> 1054).
+inline bool order_pays_average(size_t n, size_t chunk, int k_local) { return chunk > 512 || k_local <= 2 || n <= (static_cast<size_t>(1) << 25); }
+// Gather and MinMax, chunks up to 512: whole rounds, C = 512, 4 x 50 M 557 -> 554, 4 x 134 M 1492 -> 1515, 2 x 300 M 2070 -> 2098; C = 256 +-0.
+// The sign codec gains (C = 512, 2 x 450 M 2637 -> 2623).
+inline bool order_pays_gather_minmax(size_t n, size_t chunk) { return chunk > 512 || n <= (static_cast<size_t>(1) << 26); }
 
 // Kernels that take row after row (`groups` workgroups of kRowWaves) behind one that takes chunk after chunk in plain order: the rows of a
 // chunk on the die of its workgroup, in whose L2 they may still lie.  Chunks whose workgroups are not a power of two in number keep

@@ -251,7 +251,8 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
 #define BAGUA_FC(EFv, WBv)                                                                                       \
     BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, codes,  \
-                                               minmax, bucket_out, keep, chunk_order(grid.x, chunk)))
+                                               minmax, bucket_out, keep,                   \
+                                               chunk_order(grid.x, chunk, order_pays_gather_minmax(bucket_numel, chunk))))
     if (residual && bucket_out) { BAGUA_FC(true, true) }
     else if (residual) { BAGUA_FC(true, false) }
     else if (bucket_out) { BAGUA_FC(false, true) }
@@ -322,10 +323,12 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk), chunk_order(grid.x, chunk)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk),
+                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk), chunk_order(grid.x, chunk)))
+                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk),
+                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
     }
     return launch_status();
 }
@@ -360,10 +363,12 @@ extern "C" int bagua_reduce_compress_sign_ef(const float* const* x, int k_local,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, true>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale, chunk_order(grid.x, chunk)))
+                                                   inv_k, residual, n, ch, bits, scale,
+                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, false>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale, chunk_order(grid.x, chunk)))
+                                                   inv_k, residual, n, ch, bits, scale,
+                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
     }
     return launch_status();
 }

@@ -258,10 +258,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk, order_pays(n, chunk)))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
-                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk))))
+                                                                                 stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
 }

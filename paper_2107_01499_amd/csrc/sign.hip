@@ -369,10 +369,10 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, false, SHORT>), g.grid, g.block,
-                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk))))
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, false, SHORT>), g.grid, g.block,
-                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk))))
+                                                     g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
 }
@@ -467,10 +467,10 @@ extern "C" int bagua_momentum_sign_compress_ef(const float* g, const float* m, f
     const float omb1 = 1.0f - beta1;
     if (residual) {
         BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk))))
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk, order_pays(n, chunk)))))
     } else {
         BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk))))
+                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
 }

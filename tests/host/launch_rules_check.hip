@@ -1,6 +1,7 @@
 // Host-only check of the rules by which launches are shaped (csrc/common.hpp), on either side of each line.  Built with
 // `hipcc --cuda-host-only` by tests/test_launch_rules_cpu.py.
 #include <cstdio>
+#include <vector>
 #include "common.hpp"
 using namespace bagua;
 
@@ -46,8 +47,43 @@ static void gossip()
     EXPECT(kLdsPerCu / kLdsForTwo == 2 && kLdsForTwo + 4 * kMaxWaves * sizeof(float) <= 64 * 1024);
 }
 
+// The order as the kernels apply it, on the host.
+static bool permutes(const ChunkOrder o, size_t groups)
+{
+    std::vector<bool> seen(groups, false);
+    for (size_t b = 0; b < groups; ++b) {
+        const uint32_t i = static_cast<uint32_t>(b), r = i & ((8u << o.lg) - 1u);
+        const uint32_t c = i < o.end ? i - r + ((r & 7u) << o.lg) + (r >> 3) : i;
+        if (c >= groups || seen[c]) return false;
+        seen[c] = true;
+    }
+    return true;
+}
+
+static void orders()
+{
+    for (const size_t chunk : {256, 1024, 1280, 4096, 4352, 16384})
+        for (const size_t chunks : {1, 7, 2047, 2048, 2049, 2055, 3071, 3072, 5000, 65537}) {
+            const ChunkOrder o = chunk_order(chunks, chunk);
+            EXPECT((o.lg == 0) == (chunks < 2048) && o.end <= chunks && permutes(o, chunks) && permutes(chunk_order(chunks, chunk, false), chunks));
+        }
+    for (const unsigned rows : {1, 2, 3, 4, 6, 8, 16, 48, 64})
+        for (const unsigned groups : {1, 31, 32, 33, 256, 1000, 4097}) EXPECT(permutes(row_order(groups, rows), groups));
+    EXPECT(chunk_order(size_t{1} << 20, 512, false).end == 0 && row_order(4096, 3).end == 0 && row_order(4096, 1).end == 0);
+
+    const size_t line = static_cast<size_t>(1) << 28, line_average = static_cast<size_t>(1) << 25, line_gather = static_cast<size_t>(1) << 26;
+    EXPECT(order_pays(line, 1024) && !order_pays(line + 1, 1024));
+    for (const size_t chunk : {256, 512, 768, 1280, 16384}) EXPECT(order_pays(8 * line, chunk));
+    for (const size_t chunk : {256, 512}) {
+        EXPECT(order_pays_average(line_average, chunk, 3) && !order_pays_average(line_average + 1, chunk, 3) && order_pays_average(line, chunk, 2));
+        EXPECT(order_pays_gather_minmax(line_gather, chunk) && !order_pays_gather_minmax(line_gather + 1, chunk));
+    }
+    EXPECT(order_pays_average(line, 768, 8) && order_pays_gather_minmax(line, 768));
+}
+
 int main()
 {
+    orders();
     gossip();
     ring_fp();
     topk_rows();

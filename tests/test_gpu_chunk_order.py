@@ -157,3 +157,32 @@ def test_optimizer_steps(bg, oracle, codec, chunk, n):
     want_p, want_m, want_v = p.numpy().copy(), m.numpy().copy(), v.numpy().copy()
     oracle.decompress_adam_step(cid, codes, meta, n, chunk, want_p, want_m, want_v, 1e-4, variance_frozen=True)
     assert same(pg, want_p) and same(mo, want_m) and same(vg, want_v)
+
+
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+@pytest.mark.parametrize("k_local", [2, 3])
+@pytest.mark.parametrize("n", [1 << 25, (1 << 25) + 300])
+def test_average_of_short_chunks(bg, oracle, codec, k_local, n):
+    """Either side of the size from which three and more in a node keep the plain order."""
+    print("order average %s k=%d n=%d" % (codec, k_local, n), flush=True)
+    xs, res = [draw("normal", n, 41 + j, "cpu", 1e-3) for j in range(k_local)], draw("normal", n, 40, "cpu", 1e-4)
+    call, want_of = ((bg.bagua_reduce_compress_minmax_u8, oracle.reduce_compress_minmax_u8) if codec == "minmax" else
+                     (bg.bagua_reduce_compress_sign_ef, oracle.reduce_compress_sign))
+    codes, meta = room(codec, n, bg.num_chunks(n, 512))
+    r, want_r = res.cuda(), res.numpy().copy()
+    call([x.cuda() for x in xs], r, 512, codes, meta)
+    want = want_of([x.numpy() for x in xs], want_r, 512)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
+
+
+@pytest.mark.parametrize("n", [1 << 26, (1 << 26) + 4])
+def test_gather_of_short_chunks(bg, oracle, n):
+    print("order gather n=%d" % n, flush=True)
+    x, res = draw("normal", n, 51, "cpu", 1e-3), draw("normal", n, 52, "cpu", 1e-4)
+    codes, meta = room("minmax", n, bg.num_chunks(n, 512))
+    r, want_r, xg = res.cuda(), res.numpy().copy(), x.cuda()
+    ws = torch.empty(bg.bagua_flatten_workspace_bytes(2, n), dtype=torch.uint8, device="cuda")
+    bg.bagua_flatten_plan([xg[:1000], xg[1000:]], [0, 1000], n, ws)
+    bg.bagua_flatten_compress_minmax_u8(ws, 2, r, n, 512, codes, meta)
+    want = oracle.compress_minmax_u8(x.numpy(), want_r, 512)
+    assert same(codes, want[0]) and same(meta, want[1]) and same(r, want_r)
