@@ -278,17 +278,23 @@ inline bool short_launch(size_t elements_per_launch, bool batched = false)
     return elements_per_launch < (static_cast<size_t>(1) << (batched ? 26 : 25));
 }
 
-// A batched worker-side launch of 2^26 to 2^29 elements with chunks of 1024, 1536 or 2048 elements (two, three or four waves): tail tests
-// folded away, and 16 waves on a CU at a time.  Each alone loses (without the bound up to -7 %, bounded to 24 waves or with the tests
-// -1 .. -30 %); tests and all waves -> this, whole rounds in buckets of 2.5 to 10 M: sign codec, 8 workers x 374 M, C = 2048, 6427 -> 6326
-// us, 8 x 134 M 2360 -> 2248, 2 x 134 M 816 -> 790, C = 1536 2333 -> 2226, C = 1024 2322 -> 2257; MinMax, 8 x 134 M, C = 2048, 2764 -> 2675,
-// C = 1536 2752 -> 2667, C = 1024 2734 -> 2652, 4 x 75 M 851 -> 801.  Longer chunks lose 1-14 %, 768 elements never fill the last
-// wave.  Unbatched launches run one row per wave and have nothing to gain.  Beyond 2^29, in time: 8 x 700 M, C = 2048, sign codec -0.5 %,
-// MinMax -1.1 .. +0.9 %, 8 x 1.5 G +-0.4 %, 4 x 700 M, MinMax, C = 1024 +2 %.  The value: workgroups on a CU, or 0.
+// A batched worker-side launch of 2^26 to 2^29 elements with chunks of 1536 or 2048 elements (three or four waves), to 2^28 with chunks of
+// 1024 (two): tail tests folded away, and 16 waves on a CU at a time.  Each alone loses (without the bound up to -7 %, bounded to 24
+// waves or with the tests -1 .. -30 %); tests and all waves -> this, whole rounds in buckets of 6.5 M, C = 1024 | 1536 | 2048:
+//   sign codec, 4 workers x 134 M 1304 -> 1272 | 1290 -> 1239 | 1317 -> 1273 us, 4 x 200 M 1905 -> 1862 | 1947 -> 1868 | 1973 -> 1912, 2 x 268 M
+//   1490 -> 1467 | 1555 -> 1490 | 1618 -> 1590, 4 x 374 M, 1536 | 2048, 3610 -> 3551 | 3581 -> 3533, 2 x 500 M 2841 -> 2829 | 2908 -> 2920;
+//   MinMax, 4 x 134 M 1474 -> 1429 | 1494 -> 1444 | 1456 -> 1391, 2 x 268 M 1772 -> 1746 | 1873 -> 1763 | 1796 -> 1751, 4 x 374 M, 1536 | 2048,
+//   4195 -> 4116 | 3980 -> 3992, 2 x 500 M 3333 -> 3316 | 3226 -> 3258.
+// Above 2^28 chunks of 1024 keep the tests and the plain order: sign codec, that -> folded in runs of 128, 4 x 300 M 2818 -> 2839, 4 x 450 M
+// 4267 -> 4346, 2 x 500 M 2875 -> 2922; MinMax 3269 -> 3292, 4964 -> 4998, 3335 -> 3366 (4 x 374 M +0.6, -0.8 %).  With 12 waves MinMax is up to
+// 1.3 % faster at C = 1536 from 300 M on and up to 7 % slower at 70 M; at 1024 and 2048 elements 16 are as fast or faster.  Longer
+// chunks lose 1-14 %, 768 elements never fill the last wave.  Unbatched launches of 1536 and 2048 elements run one row per wave
+// and gained nothing; of the others MinMax would gain 2.0 .. 4.5 % at C = 512 and about 1 % at C = 1024, the sign codec nothing.  Beyond
+// 2^29, in time: 8 x 700 M, C = 2048, sign codec -0.5 %, MinMax -1.1 .. +0.9 %, 8 x 1.5 G +-0.4 %.  The value: workgroups on a CU, or 0.
 inline int batched_groups(size_t elements, size_t chunk, unsigned threads)
 {
     const bool pays = chunk >= 1024 && chunk <= 2048 && chunk % (2 * kRow) == 0 && elements >= (static_cast<size_t>(1) << 26) &&
-                      elements <= (static_cast<size_t>(1) << 29);
+                      elements <= (static_cast<size_t>(1) << (chunk == 1024 ? 28 : 29));
     return pays ? 16 / static_cast<int>(threads / kWave) : 0;
 }
 

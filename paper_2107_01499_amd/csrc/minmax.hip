@@ -392,10 +392,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk))))
+                                        (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         } else {
             BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
-                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk))))
+                                        (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         }
     });
 }

@@ -522,10 +522,10 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
             BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                          (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
+                                          (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         } else {
             BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
-                                          (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk))))
+                                          (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         }
     });
 }

@@ -81,8 +81,26 @@ static void orders()
     EXPECT(order_pays_average(line, 768, 8) && order_pays_gather_minmax(line, 768));
 }
 
+static void batched()
+{
+    const size_t low = static_cast<size_t>(1) << 26, high = static_cast<size_t>(1) << 29;
+    for (const size_t chunk : {1024, 1536, 2048}) {
+        const unsigned threads = static_cast<unsigned>(chunk / (2 * kRow)) * kWave;
+        const size_t top = chunk == 1024 ? high / 2 : high;
+        EXPECT(batched_groups(low - 1, chunk, threads) == 0 && batched_groups(top + chunk, chunk, threads) == 0);
+        const int groups = batched_groups(low, chunk, threads);
+        EXPECT(groups * static_cast<int>(threads / kWave) <= 16 && (groups + 1) * static_cast<int>(threads / kWave) > 16 && batched_groups(top, chunk, threads) == groups);
+        // with what the MinMax kernel uses of it anyway, that many workgroups fit a CU and no more
+        const size_t own = 2 * kMaxWaves * sizeof(float), lds = lds_for_residency(groups, own);
+        const size_t granules = (lds + own + kLdsGranule - 1) / kLdsGranule;
+        EXPECT(lds + own <= 64 * 1024 && kLdsPerCu / kLdsGranule / granules == static_cast<size_t>(groups));
+    }
+    for (const size_t chunk : {512, 768, 1280, 1792, 2304, 4096}) EXPECT(batched_groups(2 * low, chunk, 128) == 0);
+}
+
 int main()
 {
+    batched();
     orders();
     gossip();
     ring_fp();

@@ -83,3 +83,8 @@ def test_batched_worker_side(bg, oracle, codec, chunk, sizes):
         want_r = rs[b].copy()
         want = want_of(x, want_r, chunk)
         assert np.array_equal(codes[b].cpu().numpy().view(np.uint8), want[0].view(np.uint8)) and same(meta[b], want[1]) and same(rg[b], want_r)
+
+
+@pytest.mark.parametrize("codec", ["minmax", "sign"])
+def test_batched_chunks_of_1024_beyond_the_line(bg, oracle, codec):
+    test_batched_worker_side(bg, oracle, codec, 1024, [(1 << 28) - 3, 5])
