@@ -298,6 +298,12 @@ inline int batched_groups(size_t elements, size_t chunk, unsigned threads)
     return pays ? 16 / static_cast<int>(threads / kWave) : 0;
 }
 
+// The momentum compression above which eight waves of one row stream the momentum (sign.hip: mom_fold).
+inline bool mom_streams(size_t n, int rows_per_wave, unsigned waves)
+{
+    return rows_per_wave == 1 && waves == 8 && n > (static_cast<size_t>(7) << 24);
+}
+
 // f(0), ..., f(N - 1) written out.  A loop over the rows of a wave would do, but where N = 1 the compiler moves a store
 // out of the one-trip loop before it unrolls it, and the store loses its nontemporal hint (-12 % at 100 M elements).
 template <int N, typename F>

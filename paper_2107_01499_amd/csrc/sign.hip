@@ -15,8 +15,10 @@ namespace bagua {
 
 // ------------------------------------------------------------------------------------------
 // MOM: the compressed tensor is the local momentum beta1*m + omb1*x of the compression stage of
-// 1-bit Adam (x is then the gradient; m is read only).
-template <int RPW, bool EF, bool MOM, bool FULL>
+// 1-bit Adam (x is then the gradient; m is read only), loaded without the nontemporal hint where the workgroup says `keep`, or
+// streamed throughout where a wave has tail tests.
+constexpr int kMomNone = 0, kMomKeep = 1, kMomStream = 2;
+template <int RPW, bool EF, int MOM, bool FULL>
 __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, float* __restrict__ residual, int len, uint32_t chunk,
                                                    uint32_t* __restrict__ bits, float* __restrict__ scale_c,
                                                    const float* __restrict__ mom, float beta1, float omb1, float* s_q, int pace, int keep)
@@ -31,13 +33,13 @@ __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, 
         if (remain > 0) v[i] = load_row(x + off, lane, remain, 0.0f);
         if (!FULL && pace) pace_loads();
     }
-    if (MOM) {
+    if (MOM != kMomNone) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int off = static_cast<int>(wave * RPW + i) * kRow;
             const int remain = row_remain<FULL>(len, off);
             if (remain > 0) {
-                const f4 m = FULL || keep ? load_row_keep(mom + off, lane, remain, 0.0f) : load_row(mom + off, lane, remain, 0.0f);
+                const f4 m = FULL || (MOM == kMomKeep && keep) ? load_row_keep(mom + off, lane, remain, 0.0f) : load_row(mom + off, lane, remain, 0.0f);
                 v[i].x = beta1 * m.x + omb1 * v[i].x;
                 v[i].y = beta1 * m.y + omb1 * v[i].y;
                 v[i].z = beta1 * m.z + omb1 * v[i].z;
@@ -63,7 +65,7 @@ __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, 
     sign_encode_chunk<RPW, EF, false, FULL>(v, len, chunk, wave, lane, nwaves, residual, bits, scale_c, nullptr, s_q);
 }
 
-template <int RPW, bool EF, bool MOM, bool SHORT>
+template <int RPW, bool EF, int MOM, bool SHORT>
 __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
                                                     uint32_t chunk, uint32_t* __restrict__ bits,
                                                     float* __restrict__ scale, const float* __restrict__ mom,
@@ -72,7 +74,7 @@ __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x,
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     float* res_c = EF ? residual + base : nullptr;
-    const float* mom_c = MOM ? mom + base : nullptr;
+    const float* mom_c = MOM != kMomNone ? mom + base : nullptr;
     uint32_t* bits_c = bits + (base >> 5);
     if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
         sign_compress_rows<RPW, EF, MOM, true>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q, 0, 1);
@@ -86,10 +88,14 @@ __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x,
 // 2377, 3 x 60 M, C = 1536, 679 -> 646, 2 x 66 M, C = 4096, 590 -> 584, 8 x 67 M, C = 2048, 1592 -> 1523; beyond, 4 x 100 M, C = 2048,
 // 1385 -> 1345, 8 x 134 M 3209 -> 3133, 2 x 134 M, C = 4096, 1186 -> 1177.  With 2^26 of them kept 16 x 100 M gains 1.7 % more, 2 x 134 M
 // loses; with all, -0.3 .. -0.9 % against none.
+// Eight waves of one row (chunks of 2048) stream it above 7 * 2^24 elements: the choice of the hint at run time costs them more than the
+// hint gives.  Chosen -> streamed: 4 x 250 M 3563 -> 3399 us, 8 x 200 M 4816 -> 4615, 4 x 200 M 2778 -> 2687, 8 x 134 M 3147 -> 3091, 2 x 134 M 1156 ->
+// 1142; below the line 4 x 100 M 1350 -> 1346, 16 x 100 M 4231 -> 4283, 8 x 80 M 1814 -> 1845.  Other chunks: C = 1536, 8 x 200 M, 4664 -> 4808, C =
+// 4096, 8 x 134 M, 3171 -> 3215, 4 x 250 M 3537 -> 3526, C = 8192, 3501 -> 3422.
 inline bool mom_fold(size_t n) { return n <= (static_cast<size_t>(1) << 26); }
 inline uint32_t mom_keep(size_t chunk) { return static_cast<uint32_t>((static_cast<size_t>(3) << 24) / chunk); }
 
-template <int RPW, bool EF, bool MOM, bool SHORT>
+template <int RPW, bool EF, int MOM, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_sign_compress(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk,
                 uint32_t* __restrict__ bits, float* __restrict__ scale, const float* __restrict__ mom, float beta1,
@@ -109,7 +115,7 @@ k_sign_compress_batched(TABLE table, uint32_t chunk, int pace, ChunkOrder order)
     const BatchView bv = table.view();
     const uint32_t unit = order(blockIdx.x), b = batch_find(bv, unit);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
-    sign_compress_chunk<RPW, EF, false, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
+    sign_compress_chunk<RPW, EF, kMomNone, SHORT>(table_ptr<const float>(e[0]), table_ptr<float>(e[1]), e[4], chunk,
                                         table_ptr<uint32_t>(e[2]), table_ptr<float>(e[3]), nullptr, 0.0f,
                                         0.0f, unit - bv.first_unit[b], s_q, pace, 0);
 }
@@ -368,10 +374,10 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     const SignGeometry g = sign_geometry(n, chunk, BAGUA_RPW_SIGN, true);
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, false, SHORT>), g.grid, g.block,
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, kMomNone, SHORT>), g.grid, g.block,
                                                      g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, false, SHORT>), g.grid, g.block,
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, kMomNone, SHORT>), g.grid, g.block,
                                                      g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
@@ -465,13 +471,19 @@ extern "C" int bagua_momentum_sign_compress_ef(const float* g, const float* m, f
     const SignGeometry geo = sign_geometry(n, chunk, BAGUA_RPW_SIGN, true);
     const uint32_t ch = static_cast<uint32_t>(chunk);
     const float omb1 = 1.0f - beta1;
-    if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk, order_pays(n, chunk)))))
+    const ChunkOrder order = chunk_order(geo.grid.x, chunk, order_pays(n, chunk));
+#define BAGUA_MOM(RPWv, EFv, MOMv, SHORTv)                                                                                      \
+    hipLaunchKernelGGL((k_sign_compress<RPWv, EFv, MOMv, SHORTv>), geo.grid, geo.block, geo.lds, s, g, residual, n, ch, bits, scale, \
+                       m, beta1, omb1, pace_for(n), mom_keep(chunk), order)
+    if (mom_streams(n, geo.rpw, geo.block.x / kWave)) {
+        if (residual) BAGUA_MOM(1, true, kMomStream, false);
+        else BAGUA_MOM(1, false, kMomStream, false);
+    } else if (residual) {
+        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), BAGUA_MOM(RPW, true, kMomKeep, SHORT)))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, true, SHORT>), geo.grid, geo.block,
-                                                     geo.lds, s, g, residual, n, ch, bits, scale, m, beta1, omb1, pace_for(n), mom_keep(chunk), chunk_order(geo.grid.x, chunk, order_pays(n, chunk)))))
+        BAGUA_DISPATCH_RPW_WORKER(geo.rpw, BAGUA_DISPATCH_SHORT(mom_fold(n), BAGUA_MOM(RPW, false, kMomKeep, SHORT)))
     }
+#undef BAGUA_MOM
     return launch_status();
 }
 

@@ -98,8 +98,16 @@ static void batched()
     for (const size_t chunk : {512, 768, 1280, 1792, 2304, 4096}) EXPECT(batched_groups(2 * low, chunk, 128) == 0);
 }
 
+static void momentum()
+{
+    const size_t line = static_cast<size_t>(7) << 24;
+    EXPECT(mom_streams(line + 1, 1, 8) && !mom_streams(line, 1, 8) && !mom_streams(2 * line, 1, 6) && !mom_streams(2 * line, 2, 8));
+    EXPECT(pick_rpw_worker(8, BAGUA_RPW_SIGN) == 1);
+}
+
 int main()
 {
+    momentum();
     batched();
     orders();
     gossip();

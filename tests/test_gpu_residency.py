@@ -88,3 +88,8 @@ def test_batched_worker_side(bg, oracle, codec, chunk, sizes):
 @pytest.mark.parametrize("codec", ["minmax", "sign"])
 def test_batched_chunks_of_1024_beyond_the_line(bg, oracle, codec):
     test_batched_worker_side(bg, oracle, codec, 1024, [(1 << 28) - 3, 5])
+
+
+@pytest.mark.parametrize("n,chunk", [(7 << 24, 2048), ((7 << 24) + 300, 2048), ((7 << 24) + 300, 1792)])
+def test_momentum_either_side_of_the_line(bg, oracle, n, chunk):
+    test_momentum_compression(bg, oracle, n, chunk)
