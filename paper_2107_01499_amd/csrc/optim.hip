@@ -37,7 +37,7 @@ __device__ __forceinline__ f4 decode_row(const void* __restrict__ codes, const f
     return g;
 }
 
-// One wave per 256-element row, four rows per workgroup.
+// One wave per 256-element row, kRowWaves rows per workgroup.
 template <int CODEC, bool MOM, bool WD>
 __global__ void __launch_bounds__(kWave * kRowWaves)
 k_decompress_sgd(const void* __restrict__ codes, const float* __restrict__ meta, size_t n, uint32_t rows_per_chunk,

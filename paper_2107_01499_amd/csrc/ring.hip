@@ -777,7 +777,6 @@ k_lp_apply_mix(const float* __restrict__ x, const float* __restrict__ h_own, flo
     store_row(x_out + e0, lane, remain, add4(mul4(s, third), sub4(xi, ho)));
 }
 
-
 }  // namespace bagua
 
 extern "C" int bagua_lp_encode(const float* x, float* xhat, size_t n, size_t chunk, uint8_t* codes, float* minmax,
