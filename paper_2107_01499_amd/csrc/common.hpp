@@ -165,29 +165,23 @@ inline size_t gossip_pairs_lds(size_t chunk, size_t elements)
     return chunk > 2560 && chunk <= 4096 && elements >= (static_cast<size_t>(5) << 23) ? kLdsForTwo : 0;
 }
 
-// The full-precision ring of up to 16 peers, one wave per row of all peers.  Two shapes, chosen by what a launch reads and writes:
-//   below 2^29 bytes eight rows per workgroup, as many workgroups as fit; from 15 peers on (68 VGPRs and more) one row;
-//   from there on one row per workgroup, and no more waves on a CU than keep the memory busy.
-// In us, eight rows -> one row, bounded, by buffers that lie far apart in HBM, as in a training process | back to back (of five to eight sets
-// of each; the sets differ by more than the shapes):
-//   8 x 110 M   1087 .. 1125 -> 1080 .. 1105 | 1110 .. 1240 -> 1089 .. 1132;   8 x 20 M   198 .. 206 -> 200 .. 205 | 214, 217 -> 203, 203;
-//   4 x 110 M   537 .. 560 -> 522 .. 547 | 542, 544 -> 531, 533;   2 x 110 M   292 .. 305 -> 261 .. 265 | 296, 298 -> 267, 269;
-//   12 x 55 M   830 .. 849 -> 834 .. 848 | 849, 871 -> 831, 844;   16 x 55 M   1116 .. 1139 -> 1108 .. 1126 | 1127, 1131 -> 1126, 1129.
+// The full-precision ring of up to 16 peers: one wave per row of all peers and workgroup, and in launches that read and write 2^27 bytes
+// or more no more waves on a CU than keep the memory busy.  In us, eight rows per workgroup and as many as fit -> this, sets of buffers in
+// turn that lie far apart in HBM, as in a training process | back to back:
+//   2 peers, 100 MB 18.0 -> 17.1 | 18.6 -> 17.5, 420 MB 66.0 -> 64.0 | 69.6 -> 64.3;   3 peers, 140 MB 24.3 -> 23.4 | 25.6 -> 24.3, 420 MB 66.5 ->
+//   65.5 | 70.7 -> 65.8;   5 peers, 300 MB 49.5 -> 47.6 | 53.6 -> 49.9;   8 peers, 140 MB 25.9 -> 24.6 | 28.2 -> 26.6, 300 MB 49.3 -> 49.0 | 56.8 -> 54.5;
+//   12 peers, 100 MB 17.9 -> 17.7 | 18.4 -> 18.4, 200 MB 33.8 -> 34.6 | 38.0 -> 36.3, 420 MB 70.0 -> 68.3 | 85.5 -> 73.8;   14 peers, 420 MB 72.0 -> 68.6
+//   | 88.5 -> 73.9;   8 x 110 M 1087 .. 1125 -> 1080 .. 1105 | 1110 .. 1240 -> 1089 .. 1132;   16 x 55 M 1116 .. 1139 -> 1108 .. 1126 | 1127 -> 1126.
 // The bench's own spread placement of 8 x 110 M, 1.103 .. 1.110 -> 1.119 ms, is the one large launch seen to lose more than 1 %.
-// Short launches, one row per workgroup instead of eight: 144 MB 2 .. 9 %, 416 MB 0 .. 3 % slower far apart, +-2 % back to back; 16
-// peers 4 .. 10 % faster.  The waves are the least with which buffers far apart lose nothing; back to back one or two fewer are
-// the fastest (8 x 110 M, far apart, 4, 5, 6, 7, 8, 10 waves: 1156, 1104, 1089, 1093, 1105, 1122 us).  One replica is a copy, which wants
-// all the waves there are: 1 x 200 M 240 -> 269 us with 24 of them.
-inline bool ring_fp_long(int peers, size_t n) { return 2 * static_cast<size_t>(peers) * n * sizeof(float) >= (static_cast<size_t>(1) << 29); }
+// The waves are the least with which buffers far apart lose nothing in long launches; back to back one or two fewer are the
+// fastest (8 x 110 M, far apart, 4, 5, 6, 7, 8, 10 waves: 1156, 1104, 1089, 1093, 1105, 1122 us; 8 peers, 300 MB, 5 -> 7 waves: 49.7 -> 49.0 | 52.7 ->
+// 54.5).  One replica is a copy, which wants all the waves there are: 1 x 200 M 240 -> 269 us with 24 of them.
+inline bool ring_fp_long(int peers, size_t n) { return 2 * static_cast<size_t>(peers) * n * sizeof(float) >= (static_cast<size_t>(1) << 27); }
 constexpr int ring_fp_waves(int peers)
 {
     return peers <= 2 ? 16 : peers == 3 ? 12 : peers <= 5 ? 9 : peers == 6 ? 8 : peers <= 8 ? 7 : peers <= 11 ? 6 : peers <= 14 ? 5 : 4;
 }
-inline int ring_fp_rows(int peers, size_t n)
-{
-    if (peers > 16) return kRowWaves;
-    return ring_fp_long(peers, n) || peers >= 15 ? 1 : 8;
-}
+constexpr int ring_fp_rows(int peers) { return peers > 16 ? kRowWaves : 1; }
 
 // Which chunk a workgroup takes.  Workgroup b runs on die (XCD) b % 8; in the order of the workgroups neighbouring chunks lie on
 // different dies, and a die's share of a stream is every eighth chunk.  Here a die takes 2^lg chunks in a row and the eight of

@@ -20,15 +20,14 @@ __device__ __forceinline__ f4 sub4(f4 a, f4 b) { return f4{a.x - b.x, a.y - b.y,
 __device__ __forceinline__ f4 mul4(f4 a, float s) { return f4{a.x * s, a.y * s, a.z * s, a.w * s}; }
 
 // ------------------------------------------------------------------------------------------ FP
-// One wave per 256-element row, ROWS of them per workgroup; K replicas held in registers.  Bound by how well the memory system
-// copes with 2 K streams, which depends on how much of them is in flight on a CU: see ring_fp_waves.
-template <int K, int ROWS>
-__global__ void __launch_bounds__(kWave * ROWS)
+// One wave per 256-element row and workgroup; K replicas held in registers.  Bound by how well the memory system copes with
+// 2 K streams, which depends on how much of them is in flight on a CU: see ring_fp_waves.
+template <int K>
+__global__ void __launch_bounds__(kWave)
 k_ring_avg_fp(PtrTable xin, MutPtrTable xout, size_t n, float third)
 {
-    const int lane = threadIdx.x & 63;
-    const size_t e0 = (static_cast<size_t>(blockIdx.x) * ROWS + (ROWS > 1 ? wave_index() : 0)) * kRow;
-    if (ROWS > 1 && e0 >= n) return;
+    const int lane = threadIdx.x;
+    const size_t e0 = static_cast<size_t>(blockIdx.x) * kRow;
     const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
     f4 x[K];
 #pragma unroll
@@ -311,7 +310,7 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
 // ------------------------------------------------------------------------------------------ host
 static size_t ring_fp_groups(int k, size_t n)
 {
-    const size_t rows = (n + kRow - 1) / kRow, per = static_cast<size_t>(ring_fp_rows(k, n));
+    const size_t rows = (n + kRow - 1) / kRow, per = static_cast<size_t>(ring_fp_rows(k));
     return (rows + per - 1) / per;
 }
 
@@ -319,14 +318,8 @@ template <int K>
 static void launch_fp_k(const PtrTable& in, const MutPtrTable& out, size_t n, float third, hipStream_t s)
 {
     const dim3 grid(static_cast<unsigned>(ring_fp_groups(K, n)));
-    if constexpr (K < 15) {
-        if (ring_fp_rows(K, n) == 8) {
-            hipLaunchKernelGGL((k_ring_avg_fp<K, 8>), grid, dim3(8 * kWave), 0, s, in, out, n, third);
-            return;
-        }
-    }
     const size_t lds = K >= 2 && ring_fp_long(K, n) ? lds_for_residency(ring_fp_waves(K)) : 0;   // one replica is a copy
-    hipLaunchKernelGGL((k_ring_avg_fp<K, 1>), grid, dim3(kWave), lds, s, in, out, n, third);
+    hipLaunchKernelGGL((k_ring_avg_fp<K>), grid, dim3(kWave), lds, s, in, out, n, third);
 }
 
 static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, size_t n, hipStream_t stream)

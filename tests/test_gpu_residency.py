@@ -31,7 +31,7 @@ def test_ring_fp(bg, oracle, k, n):
 
 @pytest.mark.parametrize("k,n", [(1, (1 << 26) - 1), (1, (1 << 26) + 3), (3, 22369621), (3, 22369622), (8, (1 << 23) - 7), (8, (1 << 23) + 2), (14, 4793491), (15, 100), (16, (1 << 22) + 1), (17, 3000)])
 def test_ring_fp_rows_per_workgroup(bg, oracle, k, n):
-    """Either side of 2^29 bytes, where eight rows per workgroup become one, and the numbers of peers that have one row or two throughout."""
+    """Longer launches than those above, either side of 2^29 bytes, and the numbers of peers around the last with a kernel of its own."""
     test_ring_fp(bg, oracle, k, n)
 
 
