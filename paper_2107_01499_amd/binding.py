@@ -1,18 +1,24 @@
-"""Thin ctypes binding of libbagua_hip.so (include/bagua_hip.h).
+"""Thin binding of libbagua_hip.so (include/bagua_hip.h).
 
 Argument marshalling only: every function takes torch tensors that already live on the GPU,
 passes their device pointers and the current HIP stream to the C entry point of the same name,
 and raises BaguaError on a non-zero status.  PyTorch is used for device memory and streams;
 no arithmetic of the method happens in Python and there is no CPU fallback: if the shared
 library is missing, importing this module fails.
+
+The calls of a round go through the extension lib/_native.so (csrc/native.cpp), which marshals an ordinary call in 0.4 us
+instead of 2.5 .. 17 us; it declines whatever is not ordinary (another tensor class, a wrong size or type, an argument that
+is not a plain number), and the body of the function below then decides through ctypes.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch  # noqa: F401  (must be imported before the library so that both share one HIP runtime)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libbagua_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "lib", "_native.so")
 
 CODEC_MINMAX_U8 = 0
 CODEC_SIGN1 = 1
@@ -98,6 +104,21 @@ def _load():
 _lib = _load()
 
 
+def _load_native():
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError("the host extension is not built (%s missing); run __graft_entry__.build() or "
+                          "python paper_2107_01499_amd/build.py" % NATIVE_PATH)
+    spec = importlib.util.spec_from_file_location(__name__.rpartition(".")[0] + "._native", NATIVE_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.bind({name: ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in EXPORTS}, BaguaError,
+             torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    return mod
+
+
+_native = _load_native()
+
+
 def status_string(status):
     return _lib.bagua_status_string(int(status)).decode()
 
@@ -180,12 +201,16 @@ def bagua_flatten_plan(srcs, dst_offset, bucket_numel, workspace, stream=None):
 
 
 def bagua_bucket_flatten_run(workspace, T, bucket, stream=None):
+    if _native.bagua_bucket_flatten_run(workspace, T, bucket, stream):
+        return
     _check("bagua_bucket_flatten_run", _lib.bagua_bucket_flatten_run(_ptr(workspace), T, _ptr(bucket, torch.float32),
                                                                      bucket.numel(), _stream(stream)))
 
 
 def bagua_bucket_unflatten_run(workspace, T, bucket, stream=None):
     """Inverse of the flatten: scatter the bucket back into the tensors the workspace was planned with."""
+    if _native.bagua_bucket_unflatten_run(workspace, T, bucket, stream):
+        return
     _check("bagua_bucket_unflatten_run", _lib.bagua_bucket_unflatten_run(_ptr(workspace), T, _ptr(bucket, torch.float32),
                                                                          bucket.numel(), _stream(stream)))
 
@@ -206,6 +231,8 @@ def bagua_bucket_flatten_static(srcs, dst_offset, bucket, stream=None):
 
 
 def bagua_compress_minmax_u8(x, residual, chunk, codes, minmax, stream=None):
+    if _native.bagua_compress_minmax_u8(x, residual, chunk, codes, minmax, stream):
+        return
     _check("bagua_compress_minmax_u8", _lib.bagua_compress_minmax_u8(
         _ptr(x, torch.float32), _ptr(residual, torch.float32, 4 * x.numel()), x.numel(), chunk,
         _ptr(codes, torch.uint8, x.numel()), _ptr(minmax, torch.float32, 8 * num_chunks(x.numel(), chunk)),
@@ -213,12 +240,16 @@ def bagua_compress_minmax_u8(x, residual, chunk, codes, minmax, stream=None):
 
 
 def bagua_flatten_compress_minmax_u8(workspace, T, residual, n, chunk, codes, minmax, bucket_out=None, stream=None):
+    if _native.bagua_flatten_compress_minmax_u8(workspace, T, residual, n, chunk, codes, minmax, bucket_out, stream):
+        return
     _check("bagua_flatten_compress_minmax_u8", _lib.bagua_flatten_compress_minmax_u8(
         _ptr(workspace), T, _ptr(residual, torch.float32, 4 * n), n, chunk, _ptr(codes, torch.uint8, n),
         _ptr(minmax, torch.float32, 8 * num_chunks(n, chunk)), _ptr(bucket_out, torch.float32, 4 * n), _stream(stream)))
 
 
 def bagua_flatten_sign_compress_ef(workspace, T, residual, n, chunk, bits, scale, bucket_out=None, stream=None):
+    if _native.bagua_flatten_sign_compress_ef(workspace, T, residual, n, chunk, bits, scale, bucket_out, stream):
+        return
     _check("bagua_flatten_sign_compress_ef", _lib.bagua_flatten_sign_compress_ef(
         _ptr(workspace), T, _ptr(residual, torch.float32, 4 * n), n, chunk, _ptr(bits, torch.int32, _code_bytes(CODEC_SIGN1, n)),
         _ptr(scale, torch.float32, _meta_bytes(CODEC_SIGN1, n, chunk)), _ptr(bucket_out, torch.float32, 4 * n), _stream(stream)))
@@ -226,6 +257,8 @@ def bagua_flatten_sign_compress_ef(workspace, T, residual, n, chunk, bits, scale
 
 def bagua_decompress_unflatten(codec, codes, meta, n, chunk, workspace, T, stream=None):
     """Decode a compressed bucket straight into the tensors the workspace was planned with."""
+    if _native.bagua_decompress_unflatten(codec, codes, meta, n, chunk, workspace, T, stream):
+        return
     _check("bagua_decompress_unflatten", _lib.bagua_decompress_unflatten(
         codec, _ptr(codes, None, _code_bytes(codec, n)), _ptr(meta, torch.float32, _meta_bytes(codec, n, chunk)), n, chunk,
         _ptr(workspace), T, _stream(stream)))
@@ -233,6 +266,9 @@ def bagua_decompress_unflatten(codec, codes, meta, n, chunk, workspace, T, strea
 
 def bagua_decompress_reduce_recompress(codec, codes_in, meta_in, server_residual, n, chunk, codes_out, meta_out,
                                        out_fp32=None, stream=None):
+    if _native.bagua_decompress_reduce_recompress(codec, codes_in, meta_in, server_residual, n, chunk, codes_out, meta_out,
+                                                  out_fp32, stream):
+        return
     k = len(codes_in)
     _same_len(k, meta_in=meta_in)
     _check("bagua_decompress_reduce_recompress", _lib.bagua_decompress_reduce_recompress(
@@ -243,6 +279,8 @@ def bagua_decompress_reduce_recompress(codec, codes_in, meta_in, server_residual
 
 
 def bagua_decentralized_avg(mode, x_in, x_out, xhat=None, codes=None, minmax=None, chunk=0, stream=None):
+    if _native.bagua_decentralized_avg(mode, x_in, x_out, xhat, codes, minmax, chunk, stream):
+        return
     k = len(x_in)
     n = x_in[0].numel()
     _same_len(k, x_out=x_out, xhat=xhat, codes=codes, minmax=minmax)
@@ -255,6 +293,8 @@ def bagua_decentralized_avg(mode, x_in, x_out, xhat=None, codes=None, minmax=Non
 
 
 def bagua_lp_encode(x, xhat, chunk, codes, minmax, stream=None):
+    if _native.bagua_lp_encode(x, xhat, chunk, codes, minmax, stream):
+        return
     n = x.numel()
     _check("bagua_lp_encode", _lib.bagua_lp_encode(
         _ptr(x, torch.float32), _ptr(xhat, torch.float32, 4 * n), n, chunk, _ptr(codes, torch.uint8, n),
@@ -263,6 +303,9 @@ def bagua_lp_encode(x, xhat, chunk, codes, minmax, stream=None):
 
 def bagua_lp_apply_mix(x, xhat_own, xhat_left, xhat_right, codes_left, minmax_left, codes_right, minmax_right, chunk,
                        x_out, stream=None):
+    if _native.bagua_lp_apply_mix(x, xhat_own, xhat_left, xhat_right, codes_left, minmax_left, codes_right, minmax_right, chunk,
+                                  x_out, stream):
+        return
     n = x.numel()
     mb = 8 * num_chunks(n, chunk)
     _check("bagua_lp_apply_mix", _lib.bagua_lp_apply_mix(
@@ -273,6 +316,8 @@ def bagua_lp_apply_mix(x, xhat_own, xhat_left, xhat_right, codes_left, minmax_le
 
 
 def bagua_reduce_compress_minmax_u8(xs, residual, chunk, codes, minmax, stream=None):
+    if _native.bagua_reduce_compress_minmax_u8(xs, residual, chunk, codes, minmax, stream):
+        return
     n = xs[0].numel()
     _check("bagua_reduce_compress_minmax_u8", _lib.bagua_reduce_compress_minmax_u8(
         _ptr_array(xs, torch.float32, 4 * n), len(xs), _ptr(residual, torch.float32, 4 * n), n, chunk,
@@ -280,6 +325,8 @@ def bagua_reduce_compress_minmax_u8(xs, residual, chunk, codes, minmax, stream=N
 
 
 def bagua_reduce_compress_sign_ef(xs, residual, chunk, bits, scale, stream=None):
+    if _native.bagua_reduce_compress_sign_ef(xs, residual, chunk, bits, scale, stream):
+        return
     n = xs[0].numel()
     _check("bagua_reduce_compress_sign_ef", _lib.bagua_reduce_compress_sign_ef(
         _ptr_array(xs, torch.float32, 4 * n), len(xs), _ptr(residual, torch.float32, 4 * n), n, chunk,
@@ -288,12 +335,16 @@ def bagua_reduce_compress_sign_ef(xs, residual, chunk, bits, scale, stream=None)
 
 
 def bagua_centralized_avg_fp(xs, out, stream=None):
+    if _native.bagua_centralized_avg_fp(xs, out, stream):
+        return
     n = xs[0].numel()
     _check("bagua_centralized_avg_fp", _lib.bagua_centralized_avg_fp(_ptr_array(xs, torch.float32, 4 * n), len(xs), n,
                                                                      _ptr(out, torch.float32, 4 * n), _stream(stream)))
 
 
 def bagua_decentralized_avg_peers(x_in, x_out, peer, stream=None):
+    if _native.bagua_decentralized_avg_peers(x_in, x_out, peer, stream):
+        return
     k, n = len(x_in), x_in[0].numel()
     if len(peer) != k:
         raise ValueError("peer must name one peer per worker")
@@ -304,6 +355,8 @@ def bagua_decentralized_avg_peers(x_in, x_out, peer, stream=None):
 
 
 def bagua_decentralized_avg_peers_lp(x_in, x_out, xhat, codes, minmax, peer, chunk, stream=None):
+    if _native.bagua_decentralized_avg_peers_lp(x_in, x_out, xhat, codes, minmax, peer, chunk, stream):
+        return
     k, n = len(x_in), x_in[0].numel()
     if len(peer) != k:
         raise ValueError("peer must name one peer per worker")
@@ -317,12 +370,17 @@ def bagua_decentralized_avg_peers_lp(x_in, x_out, xhat, codes, minmax, peer, chu
 
 def bagua_decompress_adam_step(codec, codes, meta, n, chunk, param, m, v, lr, beta1=0.9, beta2=0.999, eps=1e-8,
                                weight_decay=0.0, variance_frozen=False, stream=None):
+    if _native.bagua_decompress_adam_step(codec, codes, meta, n, chunk, param, m, v, lr, beta1, beta2, eps, weight_decay,
+                                          variance_frozen, stream):
+        return
     _check("bagua_decompress_adam_step", _lib.bagua_decompress_adam_step(
         codec, _ptr(codes, None, _code_bytes(codec, n)), _ptr(meta, torch.float32, _meta_bytes(codec, n, chunk)), n, chunk,
         _ptr(param, torch.float32, 4 * n), _ptr(m, torch.float32, 4 * n), _ptr(v, torch.float32, 4 * n), lr, beta1, beta2, eps, weight_decay, int(bool(variance_frozen)), _stream(stream)))
 
 
 def bagua_momentum_sign_compress_ef(g, m, beta1, residual, chunk, bits, scale, stream=None):
+    if _native.bagua_momentum_sign_compress_ef(g, m, beta1, residual, chunk, bits, scale, stream):
+        return
     _check("bagua_momentum_sign_compress_ef", _lib.bagua_momentum_sign_compress_ef(
         _ptr(g, torch.float32), _ptr(m, torch.float32, 4 * g.numel()), beta1, _ptr(residual, torch.float32, 4 * g.numel()),
         g.numel(), chunk, _ptr(bits, torch.int32, _code_bytes(CODEC_SIGN1, g.numel())),
@@ -330,6 +388,8 @@ def bagua_momentum_sign_compress_ef(g, m, beta1, residual, chunk, bits, scale, s
 
 
 def bagua_sign_compress_ef(x, residual, chunk, bits, scale, stream=None):
+    if _native.bagua_sign_compress_ef(x, residual, chunk, bits, scale, stream):
+        return
     _check("bagua_sign_compress_ef", _lib.bagua_sign_compress_ef(
         _ptr(x, torch.float32), _ptr(residual, torch.float32, 4 * x.numel()), x.numel(), chunk,
         _ptr(bits, torch.int32, _code_bytes(CODEC_SIGN1, x.numel())),
@@ -337,6 +397,8 @@ def bagua_sign_compress_ef(x, residual, chunk, bits, scale, stream=None):
 
 
 def bagua_decompress(codec, codes, meta, n, chunk, out, stream=None):
+    if _native.bagua_decompress(codec, codes, meta, n, chunk, out, stream):
+        return
     _check("bagua_decompress", _lib.bagua_decompress(codec, _ptr(codes, None, _code_bytes(codec, n)),
                                                      _ptr(meta, torch.float32, _meta_bytes(codec, n, chunk)), n, chunk,
                                                      _ptr(out, torch.float32, 4 * n), _stream(stream)))
@@ -344,6 +406,8 @@ def bagua_decompress(codec, codes, meta, n, chunk, out, stream=None):
 
 def bagua_decompress_sgd_step(codec, codes, meta, n, chunk, param, momentum_buf, lr, momentum=0.0, weight_decay=0.0,
                               stream=None):
+    if _native.bagua_decompress_sgd_step(codec, codes, meta, n, chunk, param, momentum_buf, lr, momentum, weight_decay, stream):
+        return
     _check("bagua_decompress_sgd_step", _lib.bagua_decompress_sgd_step(
         codec, _ptr(codes, None, _code_bytes(codec, n)), _ptr(meta, torch.float32, _meta_bytes(codec, n, chunk)), n, chunk,
         _ptr(param, torch.float32, 4 * n), _ptr(momentum_buf, torch.float32, 4 * n), lr, momentum, weight_decay,
@@ -352,6 +416,8 @@ def bagua_decompress_sgd_step(codec, codes, meta, n, chunk, param, momentum_buf,
 
 def bagua_decompress_sgd_step_topk(idx, val, n, chunk, keep, param, momentum_buf, lr, momentum=0.0, weight_decay=0.0,
                                    stream=None):
+    if _native.bagua_decompress_sgd_step_topk(idx, val, n, chunk, keep, param, momentum_buf, lr, momentum, weight_decay, stream):
+        return
     _check("bagua_decompress_sgd_step_topk", _lib.bagua_decompress_sgd_step_topk(
         _ptr(idx, torch.int16, 2 * keep * num_chunks(n, chunk)), _ptr(val, torch.float32, 4 * keep * num_chunks(n, chunk)),
         n, chunk, keep, _ptr(param, torch.float32, 4 * n), _ptr(momentum_buf, torch.float32, 4 * n), lr, momentum,
@@ -360,6 +426,9 @@ def bagua_decompress_sgd_step_topk(idx, val, n, chunk, keep, param, momentum_buf
 
 def bagua_decompress_adam_step_topk(idx, val, n, chunk, keep, param, m, v, lr, beta1=0.9, beta2=0.999, eps=1e-8,
                                     weight_decay=0.0, variance_frozen=False, stream=None):
+    if _native.bagua_decompress_adam_step_topk(idx, val, n, chunk, keep, param, m, v, lr, beta1, beta2, eps, weight_decay,
+                                               variance_frozen, stream):
+        return
     _check("bagua_decompress_adam_step_topk", _lib.bagua_decompress_adam_step_topk(
         _ptr(idx, torch.int16, 2 * keep * num_chunks(n, chunk)), _ptr(val, torch.float32, 4 * keep * num_chunks(n, chunk)),
         n, chunk, keep, _ptr(param, torch.float32, 4 * n), _ptr(m, torch.float32, 4 * n), _ptr(v, torch.float32, 4 * n),
@@ -367,6 +436,8 @@ def bagua_decompress_adam_step_topk(idx, val, n, chunk, keep, param, m, v, lr, b
 
 
 def bagua_compress_topk_ef(x, residual, chunk, keep, idx, val, stream=None):
+    if _native.bagua_compress_topk_ef(x, residual, chunk, keep, idx, val, stream):
+        return
     _check("bagua_compress_topk_ef", _lib.bagua_compress_topk_ef(
         _ptr(x, torch.float32), _ptr(residual, torch.float32, 4 * x.numel()), x.numel(), chunk, keep,
         _ptr(idx, torch.int16, 2 * keep * num_chunks(x.numel(), chunk)),
@@ -375,6 +446,9 @@ def bagua_compress_topk_ef(x, residual, chunk, keep, idx, val, stream=None):
 
 def bagua_decompress_reduce_recompress_topk(idx_in, val_in, keep, server_residual, n, chunk, idx_out, val_out,
                                             out_fp32=None, stream=None):
+    if _native.bagua_decompress_reduce_recompress_topk(idx_in, val_in, keep, server_residual, n, chunk, idx_out, val_out,
+                                                       out_fp32, stream):
+        return
     _same_len(len(idx_in), val_in=val_in)
     _check("bagua_decompress_reduce_recompress_topk", _lib.bagua_decompress_reduce_recompress_topk(
         _ptr_array(idx_in, torch.int16, 2 * keep * num_chunks(n, chunk)),
@@ -385,6 +459,8 @@ def bagua_decompress_reduce_recompress_topk(idx_in, val_in, keep, server_residua
 
 
 def bagua_decompress_topk(idx, val, n, chunk, keep, out, stream=None):
+    if _native.bagua_decompress_topk(idx, val, n, chunk, keep, out, stream):
+        return
     _check("bagua_decompress_topk", _lib.bagua_decompress_topk(
         _ptr(idx, torch.int16, 2 * keep * num_chunks(n, chunk)), _ptr(val, torch.float32, 4 * keep * num_chunks(n, chunk)),
         n, chunk, keep, _ptr(out, torch.float32, 4 * n), _stream(stream)))

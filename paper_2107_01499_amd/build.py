@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ into paper_2107_01499_amd/lib/libbagua_hip.so for gfx950.
+"""Compile the HIP sources under csrc/ into paper_2107_01499_amd/lib/libbagua_hip.so for gfx950, and csrc/native.cpp, the
+host path of the binding, into the Python extension lib/_native.so.
 
 Flags that are part of the numerical contract: -ffp-contract=off (no fused multiply-add, every
 operation rounds once), no fast-math (correctly rounded division, IEEE denormals), and packed fp32
@@ -13,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libbagua_hip.so")
+NATIVE = os.path.join(LIBDIR, "_native.so")
 SOURCES = ["api.hip", "batch.hip", "minmax.hip", "sign.hip", "ring.hip", "flatten.hip", "fused.hip", "optim.hip", "topk.hip", "probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -36,8 +38,22 @@ def _run(cmd, verbose):
         raise subprocess.CalledProcessError(res.returncode, cmd)
 
 
+def build_native(verbose=False, out=NATIVE):
+    """The host extension: plain C++ against the headers of this Python and its torch."""
+    import sysconfig
+    from importlib.util import find_spec
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    torch_dir = find_spec("torch").submodule_search_locations[0]
+    lib = os.path.join(torch_dir, "lib")
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
+          "-I" + os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
+          "-isystem", os.path.join(torch_dir, "include"), "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+          os.path.join(CSRC, "native.cpp"), "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out], verbose)
+    return out
+
+
 def build(verbose=False, extra=(), out=LIB):
-    """Compile every source to an object (in parallel), then link the shared library."""
+    """Compile every source to an object (in parallel), then link the shared library; the host extension beside it."""
     from concurrent.futures import ThreadPoolExecutor
     os.makedirs(os.path.dirname(out), exist_ok=True)
     objdir = out + ".obj"
@@ -50,7 +66,9 @@ def build(verbose=False, extra=(), out=LIB):
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+        native = pool.submit(build_native, verbose, os.path.join(os.path.dirname(out), "_native.so"))
         objs = list(pool.map(compile_one, SOURCES))
+        native.result()
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out], verbose)
     return out
 
