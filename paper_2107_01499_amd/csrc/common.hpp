@@ -431,6 +431,51 @@ __device__ __forceinline__ void store_codes_row(uint8_t* __restrict__ row, int l
     }
 }
 
+// A row of a chunk that may be cut short, read without a test: every lane makes one access and the lane on the edge the last one
+// that lies inside the chunk, so that what it gets begins `skip` elements before its own; settle() shifts it.  What a lane
+// beyond the end holds means nothing.  With the tests of load_row a wave waits for one row, and in load_codes_row for one byte, before it
+// asks for the next, and the one chunk that is cut short decides how long a short launch takes.  The access and settle() are two steps
+// because the compiler moves a load whose result is used under a condition behind the condition.  The buffer must hold four elements.
+struct RowAt {
+    int at, skip;   // in elements; at: from the beginning of the chunk
+};
+template <bool FULL>
+__device__ __forceinline__ RowAt row_at(int off, int len, int lane)
+{
+    if (FULL) return RowAt{off + lane * 4, 0};
+    off = off < len ? off : 0;   // a row that is not there: any address
+    const int e = off + lane * 4, last = len - 4;
+    const int at = e >= len ? last & ~3 : e < last ? e : last;
+    return RowAt{at, e - at};
+}
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32u __attribute__((aligned(1)));
+template <bool FULL>
+__device__ __forceinline__ f4 load_at(const float* __restrict__ chunk, RowAt r)
+{
+    if (FULL) return ld_stream(reinterpret_cast<const f4*>(chunk + r.at));
+    return __builtin_nontemporal_load(reinterpret_cast<const f4u*>(chunk + r.at));
+}
+template <bool FULL>
+__device__ __forceinline__ uint32_t load_codes_at(const uint8_t* __restrict__ chunk, RowAt r)
+{
+    if (FULL) return ld_stream(reinterpret_cast<const uint32_t*>(chunk + r.at));
+    return __builtin_nontemporal_load(reinterpret_cast<const u32u*>(chunk + r.at));
+}
+template <bool FULL>
+__device__ __forceinline__ f4 settle(f4 q, RowAt r)
+{
+    if (FULL) return q;
+    const bool one = (r.skip & 1) != 0, two = (r.skip & 2) != 0;
+    const f4 s = two ? f4{q.z, q.w, q.w, q.w} : q;
+    return one ? f4{s.y, s.z, s.w, s.w} : s;
+}
+template <bool FULL>
+__device__ __forceinline__ uint32_t settle(uint32_t w, RowAt r)
+{
+    return FULL ? w : w >> ((8 * r.skip) & 31);
+}
+
 __device__ __forceinline__ float byte_to_float(uint32_t w, int b) { return static_cast<float>((w >> (8 * b)) & 0xffu); }
 
 // Quantisation step of a chunk from its stored statistics: fl(fl(mx - mn) / 255), 0 for a flat chunk.

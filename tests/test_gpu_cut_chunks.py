@@ -1,0 +1,98 @@
+"""The chunk of a bucket that is cut short has a path of its own in short launches (one access per lane, the lane on the edge shifted): every
+remainder around the width of an access and of a row, chunks that a wave's rows divide and do not, and the lines between the forms of
+a launch, against the oracle, bit for bit.  The outputs lie between words that the call must not touch."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# (chunk, length): lengths around one access (4), one row (256), a chunk and two
+CUTS = [(C, m * C + r) for C, m in ((256, 0), (256, 3), (768, 2), (1536, 1), (2048, 2), (4096, 1), (8192, 1), (16384, 0), (16384, 1))
+        for r in (1, 2, 3, 4, 5, 7, 63, 64, 65, 255)] + [(C, C - r) for C in (512, 2048, 4096, 8192) for r in (1, 2, 3, 4, 5, 255, 256, 257)]
+
+
+@pytest.fixture(scope="module")
+def bg():
+    import paper_2107_01499_amd as b
+    assert torch.cuda.is_available()
+    return b
+
+
+class Guarded:
+    """A tensor with 64 words on either side that must keep their value."""
+
+    def __init__(self, values):
+        self.all = torch.full((values.size + 128,), 77, dtype=torch.from_numpy(values[:0]).dtype, device="cuda")
+        self.t = self.all[64:64 + values.size]
+        self.t.copy_(torch.from_numpy(values))
+
+    def check(self, want, what):
+        got = self.t.cpu().numpy()
+        assert got.tobytes() == np.ascontiguousarray(want).tobytes(), what
+        assert bool((self.all[:64] == 77).all()) and bool((self.all[64 + got.size:] == 77).all()), what + " (beside it)"
+
+
+def vals(n, seed, sigma=1e-3):
+    r = np.random.default_rng(seed)
+    v = (r.standard_normal(n) * sigma).astype(np.float32)
+    v[r.integers(0, n, max(1, n // 50))] = 0.0
+    return v
+
+
+def groups(items, size):
+    return [items[i:i + size] for i in range(0, len(items), size)]
+
+
+def server_minmax(bg, oracle, k, n, C, ef, out):
+    enc = [oracle.compress_minmax_u8(vals(n, 3 * j + n), None, C) for j in range(k)]
+    eps = vals(n, n, 1e-5)
+    ci, mi = [torch.from_numpy(c).cuda() for c, _ in enc], [torch.from_numpy(m).cuda() for _, m in enc]
+    e, co = Guarded(eps), Guarded(np.zeros(n, np.uint8))
+    mo, o = Guarded(np.zeros(2 * bg.num_chunks(n, C), np.float32)), Guarded(np.zeros(n, np.float32))
+    bg.bagua_decompress_reduce_recompress(0, ci, mi, e.t if ef else None, n, C, co.t, mo.t, o.t if out else None)
+    eps_o = eps.copy() if ef else None
+    cw, mw, ow = oracle.drr_minmax_u8([c for c, _ in enc], [m for _, m in enc], eps_o, C)
+    what = "k=%d n=%d C=%d" % (k, n, C)
+    co.check(cw, "codes " + what)
+    mo.check(mw, "minmax " + what)
+    if ef:
+        e.check(eps_o, "eps " + what)
+    if out:
+        o.check(ow, "out " + what)
+
+
+@pytest.mark.parametrize("cuts", groups(CUTS, 20), ids=lambda c: "%d-%d" % c[0])
+@pytest.mark.parametrize("k", [1, 3, 4, 9, 32])
+def test_server_step_minmax(bg, oracle, cuts, k):
+    for i, (C, n) in enumerate(cuts):
+        server_minmax(bg, oracle, k, n, C, ef=i % 3 != 0, out=i % 2 == 0)
+
+
+@pytest.mark.parametrize("k,C,n", [
+    (3, 2048, 1 << 20), (3, 2048, (1 << 20) + 1), (2, 768, (1 << 20) + 1),                         # one row per wave, two, an odd number
+    (2, 4096, (1 << 22) - 77), (2, 4096, 1 << 22), (2, 4096, (1 << 22) + 77),                      # ahead, behind
+    (5, 1536, (1 << 22) + 1541), (2, 8192, (1 << 22) + 5), (2, 16384, (1 << 20) + 3), (5, 2048, (1 << 25) + 2047),
+    (2, 16384, (1 << 26) + 1), (2, 1536, (1 << 26) + 2),                                           # the last with a body for the cut
+])
+def test_server_step_minmax_either_side_of_its_lines(bg, oracle, k, C, n):
+    server_minmax(bg, oracle, k, n, C, ef=True, out=False)
+
+
+@pytest.mark.parametrize("C,ns", [(2048, [3, 2048 * 5 + 1, 700001, 2]), (4096, [5, 4096, 4099, 12345]), (1536, [1536 * 3 + 4, 4, 9001]),
+                                  (8192, [2000003, 2500001]), (4096, [1, 3000001])])
+def test_server_step_minmax_batched(bg, oracle, C, ns):
+    k = 3
+    enc = [[oracle.compress_minmax_u8(vals(n, 3 * j + n), None, C) for j in range(k)] for n in ns]
+    eps = [vals(n, n, 1e-5) for n in ns]
+    e, co = [Guarded(v) for v in eps], [Guarded(np.zeros(n, np.uint8)) for n in ns]
+    mo = [Guarded(np.zeros(2 * bg.num_chunks(n, C), np.float32)) for n in ns]
+    ws = torch.empty(bg.bagua_batch_workspace_bytes(len(ns), k), dtype=torch.uint8, device="cuda")
+    bg.bagua_decompress_reduce_recompress_batched(
+        0, [[torch.from_numpy(c).cuda() for c, _ in b] for b in enc], [[torch.from_numpy(m).cuda() for _, m in b] for b in enc],
+        [g.t for g in e], ns, C, [g.t for g in co], [g.t for g in mo], None, ws)
+    for b in range(len(ns)):
+        cw, mw, _ = oracle.drr_minmax_u8([c for c, _ in enc[b]], [m for _, m in enc[b]], eps[b], C)
+        co[b].check(cw, "codes %d" % b)
+        mo[b].check(mw, "minmax %d" % b)
+        e[b].check(eps[b], "eps %d" % b)
