@@ -450,10 +450,12 @@ __device__ __forceinline__ RowAt row_at(int off, int len, int lane)
 }
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32u __attribute__((aligned(1)));
-template <bool FULL>
+template <bool FULL, bool READ_AGAIN = false>
 __device__ __forceinline__ f4 load_at(const float* __restrict__ chunk, RowAt r)
 {
+    if (FULL && READ_AGAIN) return *reinterpret_cast<const f4*>(chunk + r.at);
     if (FULL) return ld_stream(reinterpret_cast<const f4*>(chunk + r.at));
+    if (READ_AGAIN) return *reinterpret_cast<const f4u*>(chunk + r.at);
     return __builtin_nontemporal_load(reinterpret_cast<const f4u*>(chunk + r.at));
 }
 template <bool FULL>

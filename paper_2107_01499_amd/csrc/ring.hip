@@ -178,20 +178,38 @@ __device__ __forceinline__ void lp_load(const float* x_c, const float* hat_c, in
     }
 }
 
+// The same without a test, for a complete chunk (FULL) or one that is cut short: all of a wave's loads are in flight together.
+template <int RPW, bool FULL, bool READ_AGAIN>
+__device__ __forceinline__ void lp_load_at(const float* x_c, const float* hat_c, int len, int wave, int lane, f4 (&x)[RPW], f4 (&h)[RPW])
+{
+    RowAt at[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        at[r] = row_at<FULL>((wave * RPW + r) * kRow, len, lane);
+        x[r] = load_at<FULL, READ_AGAIN>(x_c, at[r]);
+        h[r] = load_at<FULL, READ_AGAIN>(hat_c, at[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        x[r] = settle<FULL>(x[r], at[r]);
+        h[r] = settle<FULL>(h[r], at[r]);
+    }
+}
+
 // Publish Q(x - h) of the rows just loaded and advance the public copy.  On return h = the new public copy (also
 // stored), x = x - h, what the peer adds to the mix.  One barrier.
-template <int RPW>
+template <int RPW, bool FULL = false>
 __device__ __forceinline__ void lp_publish(f4 (&x)[RPW], f4 (&h)[RPW], float* hat_c, uint8_t* codes_c, float* minmax_c, int len,
                                            int wave, int lane, int nwaves, float* s_red, int keep)
 {
     f4 d[RPW];
 #pragma unroll
     for (int r = 0; r < RPW; ++r) d[r] = sub4(x[r], h[r]);
-    minmax_encode_chunk<RPW, false, false, true>(d, len, wave, lane, nwaves, nullptr, codes_c, minmax_c, nullptr, s_red, keep);
+    minmax_encode_chunk<RPW, false, false, true, FULL>(d, len, wave, lane, nwaves, nullptr, codes_c, minmax_c, nullptr, s_red, keep);
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         const int off = static_cast<int>(wave * RPW + r) * kRow;
-        const int remain = len - off;
+        const int remain = row_remain<FULL>(len, off);
         h[r] = add4(h[r], d[r]);
         x[r] = sub4(x[r], h[r]);
         if (remain > 0) store_row(hat_c + off, lane, remain, h[r]);
@@ -271,10 +289,70 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
     ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
 }
 
+// Load and publish of a chunk in a launch short enough that its latency counts: neither a complete chunk nor one that is cut short has
+// tail tests on its loads.
+template <int RPW, bool READ_AGAIN>
+__device__ __forceinline__ void lp_encode_folded(const float* x_c, float* hat_c, uint8_t* codes_c, float* minmax_c, int len, int wave, int lane,
+                                                 int nwaves, f4 (&x)[RPW], f4 (&h)[RPW], float* s_red, int keep)
+{
+    if (chunk_full<RPW>(len, nwaves)) {
+        lp_load_at<RPW, true, READ_AGAIN>(x_c, hat_c, len, wave, lane, x, h);
+        lp_publish<RPW, true>(x, h, hat_c, codes_c, minmax_c, len, wave, lane, nwaves, s_red, keep);
+    } else {
+        lp_load_at<RPW, false, READ_AGAIN>(x_c, hat_c, len, wave, lane, x, h);
+        lp_publish<RPW, false>(x, h, hat_c, codes_c, minmax_c, len, wave, lane, nwaves, s_red, keep);
+    }
+}
+
+// ------------------------------------------------------------------------------------------ LP, in two launches
+// Every chunk of every peer by a workgroup of its own, then the mix row by row: 25 bytes per element of a peer instead of 17, but no
+// workgroup goes through the peers one after the other, which takes 1.6 to 5.6 us each (the unrolled kernel's instructions come from
+// memory in every launch, and each peer waits for its statistics).  One launch -> two, us (from graphs, four sets of buffers in turn):
+//   K = 8: C = 4096, 64 K elements per peer 13.3 -> 7.1, 256 K 19.1 -> 12.9, 1 M 27.3 -> 43.6; C = 8192, 64 K 17.1 -> 7.7, 256 K 27.7 -> 14.0, 1 M 35.5 -> 44.4;
+//   K = 16: C = 4096, 64 K 32.0 -> 9.0, 256 K 37.3 -> 22.8, 1 M 51.8 -> 79.9; C = 8192, 64 K 47.4 -> 9.0, 256 K 55.7 -> 23.8, 1 M 70.7 -> 80.9;
+//   C = 16384: K = 5, 64 K 25.6 -> 8.4, 1 M 38.8 -> 30.2, 2 M 46.5 -> 54.1; K = 16, 64 K 90.0 -> 12.1, 1 M 107.6 -> 82.7, 2 M 127.1 -> 168.9.
+// Fewer peers gain less than a second launch costs the host (K = 4, C = 2048, 64 K 7.3 -> 5.6, K = 3 6.2 -> 5.5).
+static bool ring_lp_two_launches(int k, size_t n, size_t chunk)
+{
+    const size_t per = chunk <= 4096 ? 24 * 1024 : chunk <= 8192 ? 48 * 1024 : 80 * 1024;
+    return k >= 5 && n >= 4 && n <= static_cast<size_t>(k) * per;   // n >= 4: row_at
+}
+
+template <int RPW>
+__global__ void __launch_bounds__(wg_threads_max(RPW))
+k_ring_publish(PtrTable xin, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, size_t n, uint32_t chunk)
+{
+    __shared__ float s_red[2 * kMaxWaves];
+    const size_t c = blockIdx.x;
+    const int i = blockIdx.y;
+    const size_t base = c * static_cast<size_t>(chunk);
+    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+    f4 x[RPW], h[RPW];
+    lp_encode_folded<RPW, true>(static_cast<const float*>(xin.p[i]) + base, static_cast<float*>(xhat.p[i]) + base,
+                                static_cast<uint8_t*>(codes.p[i]) + base, static_cast<float*>(minmax.p[i]) + 2 * c, len, wave, lane, nwaves, x,
+                                h, s_red, 0);
+}
+
+__global__ void __launch_bounds__(kWave * kRowWaves)
+k_ring_mix(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, int k, size_t n, float third, ChunkOrder order)
+{
+    const uint32_t row = order(blockIdx.x) * kRowWaves + wave_index();
+    const int lane = threadIdx.x & 63, i = blockIdx.y, l = i == 0 ? k - 1 : i - 1, r = i == k - 1 ? 0 : i + 1;
+    const size_t e0 = static_cast<size_t>(row) * kRow;
+    if (e0 >= n) return;
+    const int remain = static_cast<int>((n - e0 < static_cast<size_t>(kRow)) ? (n - e0) : kRow);
+    const f4 x = load_row(static_cast<const float*>(xin.p[i]) + e0, lane, remain, 0.0f);
+    const f4 h = load_row(static_cast<const float*>(xhat.p[i]) + e0, lane, remain, 0.0f);
+    const f4 hl = load_row_keep(static_cast<const float*>(xhat.p[l]) + e0, lane, remain, 0.0f);
+    const f4 hr = load_row_keep(static_cast<const float*>(xhat.p[r]) + e0, lane, remain, 0.0f);
+    store_row(static_cast<float*>(xout.p[i]) + e0, lane, remain, add4(mul4(add4(add4(hl, h), hr), third), sub4(x, h)));
+}
+
 // ------------------------------------------------------------------------------------------ LP, one peer
 // d = x - xhat; codes, minmax = Q(d); xhat <- xhat + decode.  The codes are for other peers, nothing here reads them
 // next: they are streamed past the caches (kept there, encode + mix of 50 M elements takes 320 us instead of 315 us).
-template <int RPW, bool READ_AGAIN>
+template <int RPW, bool READ_AGAIN, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, uint32_t chunk,
             uint8_t* __restrict__ codes, float* __restrict__ minmax)
@@ -285,9 +363,17 @@ k_lp_encode(const float* __restrict__ x_in, float* __restrict__ xhat, size_t n, 
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     f4 x[RPW], h[RPW];
-    lp_load<RPW, READ_AGAIN>(x_in + base, xhat + base, len, wave, lane, x, h);
-    lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red, 0);
+    if constexpr (SHORT) {
+        lp_encode_folded<RPW, READ_AGAIN>(x_in + base, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, x, h, s_red, 0);
+    } else {
+        lp_load<RPW, READ_AGAIN>(x_in + base, xhat + base, len, wave, lane, x, h);
+        lp_publish<RPW>(x, h, xhat + base, codes + base, minmax + 2 * c, len, wave, lane, nwaves, s_red, 0);
+    }
 }
+
+// Up to 2^23 elements the encode has no tail tests on its loads: encode + mix, 64 K, C = 4096, 5.4 -> 5.2 us, C = 16384 7.3 -> 7.0, 2 M, C =
+// 16384, 17.7 -> 17.2, 8 M 55.8 -> 55.2 (C = 8192); at 33 M +-0.2 %, C = 16384 +1 %.
+inline bool lp_encode_short(size_t n) { return n >= 4 && n <= (static_cast<size_t>(1) << 23); }
 
 // `elements`: of all peers that are encoded before the first mix.  READ_AGAIN pays up to 2^27 of them; without -> with it,
 // encode + mix of one peer: 6.5 M 50.0 -> 46.6 us, 25.6 M 174 -> 158 us, 50 M 332 -> 315 us, 134 M 949 -> 936 us, 300 M 2169 ->
@@ -300,10 +386,12 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
     const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
     const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
-    if (elements <= (static_cast<size_t>(1) << 27)) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+    if (lp_encode_short(n)) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+    } else if (elements <= (static_cast<size_t>(1) << 27)) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     } else {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, false, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     }
 }
 
@@ -397,6 +485,14 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
     const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
+    if (ring_lp_two_launches(k, n, chunk)) {
+        const size_t nrows = (n + kRow - 1) / kRow;
+        const dim3 all(static_cast<unsigned>(nc), k), mix(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), k);
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_publish<RPW>), all, block, 0, stream, in, hat, cd, mm, n, ch))
+        hipLaunchKernelGGL(k_ring_mix, mix, dim3(kWave * kRowWaves), 0, stream, in, out, hat, k, n, third,
+                           row_order(mix.x, static_cast<uint32_t>(rows)));
+        return launch_status();
+    }
     if (rpw == BAGUA_RPW_LP) {   // at most kMaxWaves waves of that many rows
         switch (k) {
 #define BAGUA_LP_CASE(K) case K: launch_lp_k<K>(in, out, hat, cd, mm, n, ch, third, grid, block, stream); return launch_status();
@@ -591,9 +687,15 @@ struct PeerLpJobs {
 // Two rows per wave are held in 64 VGPRs, eight waves per SIMD; the compiler would take 70.  Up to C = 6144 that is +-1 %.  At
 // C = 8192 it is two workgroups per CU instead of one: 8 x 1 M 27.9 -> 24.4 us, 2 x 6.5 M 45.3 -> 41.3 us, 4 x 12 M +-0, but
 // 4 x 25.6 M 303 -> 314 us and 8 x 100 M 2477 -> 2569 us.
-template <int RPW, bool PAIR>
+// SHORT: no tail tests on the loads, and the workers that sit out are jobs from `npairs` on in the pairs' launch.  Two launches with tests
+// -> one without, us: three pairs and a single, C = 4096, 64 K 8.7 -> 5.2, 256 K 12.0 -> 7.6, 1 M 23.6 -> 22.5, 8 M 163.3 -> 159.2, 16 M 338.8 ->
+// 345.2; C = 16384, 64 K 18.0 -> 10.6, 1 M 29.1 -> 22.2, 8 M 177.9 -> 172.8, 16 M 368.2 -> 374.6; one pair, C = 4096, 256 K 6.3 -> 5.6, 1 M 8.7 ->
+// 8.1, 2 M +-0, 8 M 47.9 -> 48.5; C = 16384, 2 M 17.0 -> 15.3, 4 M 27.7 -> 29.4.
+inline bool gossip_short(size_t n, int singles) { return n >= 4 && n <= (static_cast<size_t>(1) << (singles ? 23 : 21)); }
+
+template <int RPW, bool PAIR, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)
-k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk, int keep, ChunkOrder order)
+k_peer_avg_lp(PeerLpJobs jobs, int npairs, size_t n, uint32_t chunk, int keep, ChunkOrder order)
 {
     __shared__ float s_red[2][2 * kMaxWaves];
     const int job = blockIdx.y;
@@ -604,9 +706,15 @@ k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk, int keep, ChunkOrder or
 
     f4 h[2][RPW], own[2][RPW];
     auto publish = [&](int sd) {
-        lp_load<RPW>(jobs.x[sd][job] + base, jobs.hat[sd][job] + base, len, wave, lane, own[sd], h[sd]);
-        lp_publish<RPW>(own[sd], h[sd], jobs.hat[sd][job] + base, jobs.codes[sd][job] + base, jobs.minmax[sd][job] + 2 * c, len,
-                        wave, lane, nwaves, s_red[sd], keep);
+        const float* x_c = jobs.x[sd][job] + base;
+        float *hat_c = jobs.hat[sd][job] + base, *minmax_c = jobs.minmax[sd][job] + 2 * c;
+        uint8_t* codes_c = jobs.codes[sd][job] + base;
+        if constexpr (SHORT) {
+            lp_encode_folded<RPW, false>(x_c, hat_c, codes_c, minmax_c, len, wave, lane, nwaves, own[sd], h[sd], s_red[sd], keep);
+        } else {
+            lp_load<RPW>(x_c, hat_c, len, wave, lane, own[sd], h[sd]);
+            lp_publish<RPW>(own[sd], h[sd], hat_c, codes_c, minmax_c, len, wave, lane, nwaves, s_red[sd], keep);
+        }
     };
     auto mix = [&](int sd, int second) {   // the sum of a pair is the same one for both sides
 #pragma unroll
@@ -618,9 +726,13 @@ k_peer_avg_lp(PeerLpJobs jobs, size_t n, uint32_t chunk, int keep, ChunkOrder or
         }
     };
     publish(0);
-    if (PAIR) publish(1);
-    mix(0, PAIR ? 1 : 0);
-    if (PAIR) mix(1, 1);
+    if (PAIR && (!SHORT || job < npairs)) {
+        publish(1);
+        mix(0, 1);
+        mix(1, 1);
+    } else {
+        mix(0, 0);
+    }
 }
 
 // Second pass of the general case: worker i = blockIdx.y reads the advanced xhat of itself and of its peer.
@@ -712,12 +824,23 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
             }
         }
     }
-    if (npairs) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true>), dim3(grid.x, npairs), block, gossip_pairs_lds(chunk, npairs * n), s, pairs, n, ch,
+    if (npairs && gossip_short(n, nsingles)) {
+        for (int j = 0; j < nsingles; ++j) {
+            pairs.x[0][npairs + j] = singles.x[0][j];
+            pairs.out[0][npairs + j] = singles.out[0][j];
+            pairs.hat[0][npairs + j] = singles.hat[0][j];
+            pairs.codes[0][npairs + j] = singles.codes[0][j];
+            pairs.minmax[0][npairs + j] = singles.minmax[0][j];
+        }
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true, true>), dim3(grid.x, npairs + nsingles), block, 0, s, pairs, npairs, n, ch,
                                                    keep_codes_of_round(k * n), order))
+        nsingles = 0;
+    } else if (npairs) {
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true, false>), dim3(grid.x, npairs), block, gossip_pairs_lds(chunk, npairs * n), s, pairs, npairs,
+                                                   n, ch, keep_codes_of_round(k * n), order))
     }
     if (nsingles) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false>), dim3(grid.x, nsingles), block, 0, s, singles, n, ch,
+        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false, false>), dim3(grid.x, nsingles), block, 0, s, singles, 0, n, ch,
                                                    keep_codes_of_round(k * n), order))
     }
     if (nmix) {                                         // all public copies are advanced by now

@@ -96,3 +96,56 @@ def test_server_step_minmax_batched(bg, oracle, C, ns):
         co[b].check(cw, "codes %d" % b)
         mo[b].check(mw, "minmax %d" % b)
         e[b].check(eps[b], "eps %d" % b)
+
+
+def replicas(k, n, seed):
+    base = vals(n, seed, 0.02)
+    return [base + vals(n, seed + 1 + j) for j in range(k)], [base + vals(n, seed + 50 + j, 1e-4) for j in range(k)]
+
+
+def ring_low_precision(bg, oracle, k, n, C, peer=None):
+    x, hat = replicas(k, n, n + k)
+    hat_o = [h.copy() for h in hat]
+    hg, og = [Guarded(h) for h in hat], [Guarded(np.zeros(n, np.float32)) for _ in range(k)]
+    cg, mg = [Guarded(np.zeros(n, np.uint8)) for _ in range(k)], [Guarded(np.zeros(2 * bg.num_chunks(n, C), np.float32)) for _ in range(k)]
+    lists = [torch.from_numpy(v).cuda() for v in x], [g.t for g in og], [g.t for g in hg], [g.t for g in cg], [g.t for g in mg]
+    if peer is None:
+        bg.bagua_decentralized_avg(bg.AVG_LP_MINMAX_U8, *lists, C)
+        want = oracle.ring_avg_lp(x, hat_o, C)
+    else:
+        bg.bagua_decentralized_avg_peers_lp(*lists, peer, C)
+        want = oracle.peer_avg_lp(x, hat_o, peer, C)
+    for i in range(k):
+        what = " %d k=%d n=%d C=%d" % (i, k, n, C)
+        og[i].check(want[0][i], "out" + what)
+        hg[i].check(hat_o[i], "hat" + what)
+        cg[i].check(want[1][i], "codes" + what)
+        mg[i].check(want[2][i], "minmax" + what)
+
+
+@pytest.mark.parametrize("cuts", groups(CUTS, 20), ids=lambda c: "%d-%d" % c[0])
+@pytest.mark.parametrize("k,peer", [(5, None), (16, None), (2, [1, 0]), (5, [1, 0, 2, 4, 3]), (4, [1, 2, 3, 0])])   # two launches; gossip, one way
+def test_rounds_in_low_precision(bg, oracle, cuts, k, peer):
+    for C, n in cuts[::2 if k < 16 else 5]:
+        ring_low_precision(bg, oracle, k, n, C, peer)
+
+
+@pytest.mark.parametrize("k,C,n,peer", [
+    (5, 4096, 5 * 24 * 1024, None), (5, 4096, 5 * 24 * 1024 + 1, None), (8, 1536, 8 * 24 * 1024 - 3, None), (4, 4096, 65537, None),
+    (32, 8192, 100001, None), (6, 16384, 6 * 80 * 1024 - 1, None), (6, 16384, 6 * 80 * 1024 + 1, None), (6, 6400, 120003, None),
+    (2, 4096, (1 << 21) + 1, [1, 0]), (3, 4096, (1 << 21) + 1, [1, 0, 2]), (3, 2048, (1 << 23) + 5, [1, 0, 2]), (3, 16384, 1 << 21, [0, 2, 1]),
+    (3, 4096, 300001, [0, 1, 2])])
+def test_rounds_in_low_precision_either_side_of_their_lines(bg, oracle, k, C, n, peer):
+    ring_low_precision(bg, oracle, k, n, C, peer)
+
+
+@pytest.mark.parametrize("n,C", [(1, 256), (3, 256), (4, 256), (4097, 4096), (70001, 8192), ((1 << 23) - 1, 4096), ((1 << 23) + 1, 2048)])
+def test_encode_of_one_peer(bg, oracle, n, C):
+    x, hat = replicas(1, n, n)
+    h, c = Guarded(hat[0]), Guarded(np.zeros(n, np.uint8))
+    m = Guarded(np.zeros(2 * bg.num_chunks(n, C), np.float32))
+    bg.bagua_lp_encode(torch.from_numpy(x[0]).cuda(), h.t, C, c.t, m.t)
+    _, cw, mw = oracle.ring_avg_lp(x, hat, C)
+    c.check(cw[0], "codes")
+    m.check(mw[0], "minmax")
+    h.check(hat[0], "hat")
