@@ -478,6 +478,15 @@ __device__ __forceinline__ uint32_t settle(uint32_t w, RowAt r)
     return FULL ? w : w >> ((8 * r.skip) & 31);
 }
 
+// +0.0f in the elements from `len` on; e: the lane's first one.
+__device__ __forceinline__ void clear_absent(f4& v, int e, int len)
+{
+    v.x = e + 0 < len ? v.x : 0.0f;
+    v.y = e + 1 < len ? v.y : 0.0f;
+    v.z = e + 2 < len ? v.z : 0.0f;
+    v.w = e + 3 < len ? v.w : 0.0f;
+}
+
 __device__ __forceinline__ float byte_to_float(uint32_t w, int b) { return static_cast<float>((w >> (8 * b)) & 0xffu); }
 
 // Quantisation step of a chunk from its stored statistics: fl(fl(mx - mn) / 255), 0 for a flat chunk.

@@ -2,6 +2,8 @@
 // straight from the layer tensors (through the planned tensor table), so the flattened bucket is
 // never written to and re-read from HBM.  Result = bagua_bucket_flatten followed by
 // bagua_compress_minmax_u8, bit for bit; traffic = that of the compression alone.
+#include <type_traits>
+
 #include "flatten_device.hpp"
 #include "launchers.hpp"
 #include "minmax_device.hpp"
@@ -10,6 +12,14 @@
 #pragma clang fp contract(off)
 
 namespace bagua {
+
+// Rows per wave of the gathers: one up to 2^21 elements of chunks up to 4096, because a wave walks through the tensor table row after row.  Two -> one,
+// us per launch: MinMax, C = 4096, 64 K 4.3 -> 4.1, 1 M 5.8 -> 5.0, 2 M 7.4 -> 6.6, 4 M 11.2 -> 12.3; C = 1024, 64 K 4.2 -> 3.7, 1 M 5.6 -> 4.8, 2 M 7.2
+// -> 6.2; sign codec, C = 4096, 64 K 4.3 -> 4.0, 1 M 5.9 -> 4.7, 2 M 7.1 -> 5.8, 4 M 10.2 -> 11.0.
+inline int pick_rpw_gather(int rows, size_t n, int preferred)
+{
+    return rows <= kMaxWaves && n <= (static_cast<size_t>(1) << 21) ? 1 : pick_rpw_worker(rows, preferred);
+}
 
 template <int RPW, bool EF, bool WB>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
@@ -105,10 +115,89 @@ k_flatten_sign_compress(const TensorDesc* __restrict__ desc, const uint32_t* __r
                                       bits + (base >> 5), scale + c, nullptr, s_q);
 }
 
+// The average of the k_local workers' rows and the error state on top, in a short launch: eight rows of the workers (what fits 32
+// registers) and the error state are on their way at any time, without tests, and so is the chunk that is cut short.  What a lane holds
+// beyond the end of the chunk means nothing.
+template <int RPW, bool EF, bool FULL>
+__device__ __forceinline__ void average_rows_ahead(const PtrTable& xs, int k_local, float inv_k, const float* residual_c, size_t base, int len, int wave,
+                                                   int lane, f4 (&v)[RPW])
+{
+    constexpr int U = 8 / RPW;
+    RowAt at[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) at[i] = row_at<FULL>((wave * RPW + i) * kRow, len, lane);
+    f4 w[U][RPW];
+    auto fetch = [&](int u, int j) {
+        const float* xj = static_cast<const float*>(xs.p[j]) + base;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) w[u][i] = load_at<FULL>(xj, at[i]);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < k_local) fetch(u, u);
+    f4 d[RPW];
+    if (EF) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) d[i] = load_at<FULL>(residual_c, at[i]);
+    }
+    for (int j0 = 0; j0 < k_local; j0 += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u;
+            if (j >= k_local) break;
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) {
+                const f4 a = settle<FULL>(w[u][i], at[i]);
+                if (j == 0) {
+                    v[i] = a;
+                } else {
+                    v[i].x = v[i].x + a.x;
+                    v[i].y = v[i].y + a.y;
+                    v[i].z = v[i].z + a.z;
+                    v[i].w = v[i].w + a.w;
+                }
+            }
+            if (j + U < k_local) fetch(u, j + U);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        v[i].x = v[i].x * inv_k;
+        v[i].y = v[i].y * inv_k;
+        v[i].z = v[i].z * inv_k;
+        v[i].w = v[i].w * inv_k;
+        if (EF) {
+            const f4 e = settle<FULL>(d[i], at[i]);
+            v[i].x = v[i].x + e.x;
+            v[i].y = v[i].y + e.y;
+            v[i].z = v[i].z + e.z;
+            v[i].w = v[i].w + e.w;
+        }
+    }
+}
+
+// Up to 2^20 elements of chunks up to 8192.  Worker after worker -> this, us per launch: MinMax, 8 workers, C = 4096, 64 K 4.7 -> 4.1 (cut chunk
+// 7.4 -> 5.2), 256 K 8.5 -> 5.8, 1 M 10.2 -> 8.7, 2 M 14.7 -> 16.0; 4 workers, C = 8192, 1 M 7.9 -> 7.2, 2 M 9.9 -> 12.7; sign codec, 4 workers, C =
+// 2048, 64 K 3.3 -> 2.9, 256 K 4.6 -> 3.5, 1 M 5.9 -> 5.5, 2 M 9.2 -> 9.4.  C = 16384 (four rows per wave, 128 registers): 64 K 12.8 -> 16.5.
+inline bool short_average(size_t n, size_t chunk) { return n >= 4 && n <= (static_cast<size_t>(1) << 20) && chunk <= 8192; }
+// launch(rows per wave, whether it is a short launch), both as types.  Short chunks take one row per wave then.
+template <typename F>
+inline void average_shape(size_t n, size_t chunk, const F& launch)
+{
+    const int rows = static_cast<int>(chunk / kRow);
+    if (!short_average(n, chunk)) {
+        BAGUA_DISPATCH_RPW_WORKER(pick_rpw_worker(rows, 2), (launch(std::integral_constant<int, RPW>{}, std::false_type{})))
+    } else if (rows <= kMaxWaves) {
+        launch(std::integral_constant<int, 1>{}, std::true_type{});
+    } else {
+        launch(std::integral_constant<int, 2>{}, std::true_type{});
+    }
+}
+
 // Intra-node stage of hierarchical C_LP_S (Section 3.5): the k_local workers' uncompressed buckets are
 // averaged (ascending order, one multiply by inv_k) and the leader compresses the average with its
 // error state.  4*k_local + 9 bytes per element, one pass.
-template <int RPW, bool EF>
+template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restrict__ residual, size_t n, uint32_t chunk,
                          uint8_t* __restrict__ codes, float* __restrict__ minmax, uint32_t keep, ChunkOrder order)
@@ -120,6 +209,17 @@ k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restric
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
     f4 v[RPW];
+    if constexpr (SHORT) {
+        float* res_c = EF ? residual + base : nullptr;
+        if (chunk_full<RPW>(len, nwaves)) {
+            average_rows_ahead<RPW, EF, true>(xs, k_local, inv_k, res_c, base, len, wave, lane, v);
+            minmax_encode_chunk<RPW, EF, false, false, true>(v, len, wave, lane, nwaves, res_c, codes + base, minmax + 2 * c, nullptr, s_red, blockIdx.x < keep);
+        } else {
+            average_rows_ahead<RPW, EF, false>(xs, k_local, inv_k, res_c, base, len, wave, lane, v);
+            minmax_encode_chunk<RPW, EF, false>(v, len, wave, lane, nwaves, res_c, codes + base, minmax + 2 * c, nullptr, s_red, blockIdx.x < keep);
+        }
+        return;
+    }
     for (int j = 0; j < k_local; ++j) {
         const float* xj = static_cast<const float*>(xs.p[j]) + base;
 #pragma unroll
@@ -164,7 +264,7 @@ k_reduce_compress_minmax(PtrTable xs, int k_local, float inv_k, float* __restric
 }
 
 // The same intra-node stage in front of the 1-bit sign codec.
-template <int RPW, bool EF>
+template <int RPW, bool EF, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_reduce_compress_sign(PtrTable xs, int k_local, float inv_k, float* __restrict__ residual, size_t n, uint32_t chunk,
                        uint32_t* __restrict__ bits, float* __restrict__ scale, ChunkOrder order)
@@ -176,6 +276,19 @@ k_reduce_compress_sign(PtrTable xs, int k_local, float inv_k, float* __restrict_
     const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
 
     f4 v[RPW];
+    if constexpr (SHORT) {
+        float* res_c = EF ? residual + base : nullptr;
+        if (chunk_full<RPW>(len, nwaves)) {
+            average_rows_ahead<RPW, EF, true>(xs, k_local, inv_k, res_c, base, len, wave, lane, v);
+            sign_encode_chunk<RPW, EF, false, true>(v, len, chunk, wave, lane, nwaves, res_c, bits + (base >> 5), scale + c, nullptr, s_q);
+        } else {
+            average_rows_ahead<RPW, EF, false>(xs, k_local, inv_k, res_c, base, len, wave, lane, v);
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) clear_absent(v[i], (wave * RPW + i) * kRow + lane * 4, len);
+            sign_encode_chunk<RPW, EF, false>(v, len, chunk, wave, lane, nwaves, res_c, bits + (base >> 5), scale + c, nullptr, s_q);
+        }
+        return;
+    }
     for (int j = 0; j < k_local; ++j) {
         const float* xj = static_cast<const float*>(xs.p[j]) + base;
 #pragma unroll
@@ -240,7 +353,7 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
         return BAGUA_ERR_ALIGNMENT;
     const FlattenPlanView pv = plan_view(workspace, T);
     const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw_worker(rows, BAGUA_RPW_COMPRESS);
+    const int rpw = pick_rpw_gather(rows, bucket_numel, BAGUA_RPW_COMPRESS);
     dim3 grid(static_cast<unsigned>(num_chunks(bucket_numel, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk), t32 = static_cast<uint32_t>(T);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -277,7 +390,7 @@ extern "C" int bagua_flatten_sign_compress_ef(const void* workspace, size_t T, f
         return BAGUA_ERR_ALIGNMENT;
     const FlattenPlanView pv = plan_view(workspace, T);
     const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw_worker(rows, BAGUA_RPW_SIGN);
+    const int rpw = pick_rpw_gather(rows, bucket_numel, BAGUA_RPW_SIGN);
     const int waves = (rows + rpw - 1) / rpw;
     dim3 grid(static_cast<unsigned>(num_chunks(bucket_numel, chunk))), block(64 * waves);
     const size_t lds = waves > 1 ? static_cast<size_t>(rows) * kWave * sizeof(float) : 0;
@@ -315,21 +428,18 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     if (!aligned16(residual) || !aligned16(codes) || !aligned4(minmax)) return BAGUA_ERR_ALIGNMENT;
     PtrTable xt{};
     for (int j = 0; j < k_local; ++j) xt.p[j] = x[j];
-    const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw_worker(rows, BAGUA_RPW_COMPRESS);
-    dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
+    const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk)));
     const float inv_k = 1.0f / static_cast<float>(k_local);
-    const uint32_t ch = static_cast<uint32_t>(chunk);
+    const uint32_t ch = static_cast<uint32_t>(chunk), keep = keep_chunks(n, chunk);
+    const ChunkOrder order = chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk),
-                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
-    } else {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false>), grid, block, 0, s, xt, k_local,
-                                                   inv_k, residual, n, ch, codes, minmax, keep_chunks(n, chunk),
-                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
-    }
+    average_shape(n, chunk, [&](auto rpw, auto is_short) {
+        constexpr int RPW = decltype(rpw)::value;
+        constexpr bool SHORT = decltype(is_short)::value;
+        const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));
+        if (residual) hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
+        else hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
+    });
     return launch_status();
 }
 
@@ -353,22 +463,18 @@ extern "C" int bagua_reduce_compress_sign_ef(const float* const* x, int k_local,
     if (!aligned16(residual) || !aligned16(bits) || !aligned4(scale)) return BAGUA_ERR_ALIGNMENT;
     PtrTable xt{};
     for (int j = 0; j < k_local; ++j) xt.p[j] = x[j];
-    const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw_worker(rows, BAGUA_RPW_SIGN);
-    const int waves = (rows + rpw - 1) / rpw;
-    dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * waves);
-    const size_t lds = waves > 1 ? static_cast<size_t>(rows) * kWave * sizeof(float) : 0;
+    const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk)));
     const float inv_k = 1.0f / static_cast<float>(k_local);
     const uint32_t ch = static_cast<uint32_t>(chunk);
+    const ChunkOrder order = chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, true>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale,
-                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
-    } else {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_reduce_compress_sign<RPW, false>), grid, block, lds, s, xt, k_local,
-                                                   inv_k, residual, n, ch, bits, scale,
-                                                   chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local))))
-    }
+    average_shape(n, chunk, [&](auto rpw, auto is_short) {
+        constexpr int RPW = decltype(rpw)::value;
+        constexpr bool SHORT = decltype(is_short)::value;
+        const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));
+        const size_t lds = block.x > kWave ? chunk / kRow * kWave * sizeof(float) : 0;
+        if (residual) hipLaunchKernelGGL((k_reduce_compress_sign<RPW, true, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
+        else hipLaunchKernelGGL((k_reduce_compress_sign<RPW, false, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
+    });
     return launch_status();
 }
