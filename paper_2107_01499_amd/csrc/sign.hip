@@ -65,6 +65,45 @@ __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, 
     sign_encode_chunk<RPW, EF, false, FULL>(v, len, chunk, wave, lane, nwaves, residual, bits, scale_c, nullptr, s_q);
 }
 
+// The chunk that is cut short, without tests (see row_at).  With -> without, us per launch: C = 4096, 64 K 2.9 -> 2.7, 1 M 4.6 -> 3.9, with the
+// momentum 5.2 -> 4.2, 3 M 10.4 -> 9.8; five buckets, C = 2048, 1 M 5.2 -> 4.0; above 6 M +-0.  (One row per wave: -0.1 .. 0 us.)
+template <int RPW, bool EF, int MOM>
+__device__ __forceinline__ void sign_compress_cut(const float* __restrict__ x, float* __restrict__ residual, int len, uint32_t chunk,
+                                                  uint32_t* __restrict__ bits, float* __restrict__ scale_c, const float* __restrict__ mom,
+                                                  float beta1, float omb1, float* s_q)
+{
+    const int wave = wave_index(), lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+    f4 v[RPW], m[RPW], d[RPW];
+    RowAt at[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        at[i] = row_at<false>((wave * RPW + i) * kRow, len, lane);
+        v[i] = load_at<false>(x, at[i]);
+        if (MOM != kMomNone) m[i] = load_at<false, true>(mom, at[i]);
+        if (EF) d[i] = load_at<false>(residual, at[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        v[i] = settle<false>(v[i], at[i]);
+        if (MOM != kMomNone) {
+            const f4 mi = settle<false>(m[i], at[i]);
+            v[i].x = beta1 * mi.x + omb1 * v[i].x;
+            v[i].y = beta1 * mi.y + omb1 * v[i].y;
+            v[i].z = beta1 * mi.z + omb1 * v[i].z;
+            v[i].w = beta1 * mi.w + omb1 * v[i].w;
+        }
+        if (EF) {
+            const f4 e = settle<false>(d[i], at[i]);
+            v[i].x = v[i].x + e.x;
+            v[i].y = v[i].y + e.y;
+            v[i].z = v[i].z + e.z;
+            v[i].w = v[i].w + e.w;
+        }
+        clear_absent(v[i], (wave * RPW + i) * kRow + lane * 4, len);
+    }
+    sign_encode_chunk<RPW, EF, false, false>(v, len, chunk, wave, lane, nwaves, residual, bits, scale_c, nullptr, s_q);
+}
+
 template <int RPW, bool EF, int MOM, bool SHORT>
 __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x, float* __restrict__ residual, size_t n,
                                                     uint32_t chunk, uint32_t* __restrict__ bits,
@@ -78,6 +117,8 @@ __device__ __forceinline__ void sign_compress_chunk(const float* __restrict__ x,
     uint32_t* bits_c = bits + (base >> 5);
     if (SHORT && chunk_full<RPW>(len, blockDim.x >> 6))
         sign_compress_rows<RPW, EF, MOM, true>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q, 0, 1);
+    else if (SHORT && RPW > 1 && len < static_cast<int>(chunk) && base + len >= 4)
+        sign_compress_cut<RPW, EF, MOM>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q);
     else sign_compress_rows<RPW, EF, MOM, false>(x + base, res_c, len, chunk, bits_c, scale + c, mom_c, beta1, omb1, s_q, pace, keep);
 }
 

@@ -149,3 +149,63 @@ def test_encode_of_one_peer(bg, oracle, n, C):
     c.check(cw[0], "codes")
     m.check(mw[0], "minmax")
     h.check(hat[0], "hat")
+
+
+def worker_side(bg, oracle, n, C, k_local, ef):
+    """Every worker-side call on the same values: compress, momentum, intra-node average and gather, both codecs."""
+    xs, mom, res = [vals(n, n + j) for j in range(k_local)], vals(n, n + 40), vals(n, n + 41, 1e-5)
+    xg, mg = [torch.from_numpy(x).cuda() for x in xs], torch.from_numpy(mom).cuda()
+    ws = torch.empty(bg.bagua_flatten_workspace_bytes(2, n), dtype=torch.uint8, device="cuda")
+    cut = n // 3
+    bg.bagua_flatten_plan([xg[0][:cut], xg[0][cut:]], [0, cut], n, ws)
+    nc = bg.num_chunks(n, C)
+    minmax = [(lambda r, c, m: bg.bagua_compress_minmax_u8(xg[0], r, C, c, m), lambda r: oracle.compress_minmax_u8(xs[0], r, C)),
+              (lambda r, c, m: bg.bagua_reduce_compress_minmax_u8(xg, r, C, c, m), lambda r: oracle.reduce_compress_minmax_u8(xs, r, C)),
+              (lambda r, c, m: bg.bagua_flatten_compress_minmax_u8(ws, 2, r, n, C, c, m), lambda r: oracle.compress_minmax_u8(xs[0], r, C))]
+    sign = [(lambda r, c, m: bg.bagua_sign_compress_ef(xg[0], r, C, c, m), lambda r: oracle.sign_compress_ef(xs[0], r, C)),
+            (lambda r, c, m: bg.bagua_momentum_sign_compress_ef(xg[0], mg, 0.9, r, C, c, m),
+             lambda r: oracle.momentum_sign_compress_ef(xs[0], mom, 0.9, r, C)),
+            (lambda r, c, m: bg.bagua_reduce_compress_sign_ef(xg, r, C, c, m), lambda r: oracle.reduce_compress_sign(xs, r, C)),
+            (lambda r, c, m: bg.bagua_flatten_sign_compress_ef(ws, 2, r, n, C, c, m), lambda r: oracle.sign_compress_ef(xs[0], r, C))]
+    for i, (run, want) in enumerate(minmax + sign):
+        what = "call %d n=%d C=%d" % (i, n, C)
+        r, ro = Guarded(res), res.copy() if ef else None
+        codes = Guarded(np.zeros(n, np.uint8) if i < 3 else np.zeros((n + 31) // 32, np.int32))
+        meta = Guarded(np.zeros(2 * nc if i < 3 else nc, np.float32))
+        run(r.t if ef else None, codes.t, meta.t)
+        cw, mw = want(ro)
+        codes.check(cw, "codes " + what)
+        meta.check(mw, "meta " + what)
+        if ef:
+            r.check(ro, "residual " + what)
+
+
+@pytest.mark.parametrize("cuts", groups(CUTS, 10), ids=lambda c: "%d-%d" % c[0])
+@pytest.mark.parametrize("k_local", [1, 3, 9])
+def test_worker_side(bg, oracle, cuts, k_local):
+    for i, (C, n) in enumerate(cuts):
+        worker_side(bg, oracle, n, C, k_local, ef=i % 3 != 0)
+
+
+@pytest.mark.parametrize("n,C,k_local", [((1 << 20) - 1, 4096, 2), (1 << 20, 768, 5), ((1 << 20) + 1, 4096, 5), ((1 << 20) - 3, 8192, 9),
+                                         ((1 << 20) + 3, 16384, 2), (1 << 21, 4096, 1), ((1 << 21) + 1, 1024, 1), ((1 << 25) - 5, 4096, 1)])
+def test_worker_side_either_side_of_its_lines(bg, oracle, n, C, k_local):
+    worker_side(bg, oracle, n, C, k_local, ef=True)
+
+
+@pytest.mark.parametrize("C", [1024, 4096])
+def test_compressions_batched(bg, oracle, C):
+    ns = [1, 3, 4, 5, C - 1, C + 1, 3 * C + 257, 70001]
+    xs, res = [vals(n, n) for n in ns], [vals(n, n + 1, 1e-5) for n in ns]
+    ws = torch.empty(bg.bagua_batch_workspace_bytes(len(ns), 0), dtype=torch.uint8, device="cuda")
+    for call, width, dtype, per, want in ((bg.bagua_compress_minmax_u8_batched, lambda n: n, np.uint8, 2, oracle.compress_minmax_u8),
+                                          (bg.bagua_sign_compress_ef_batched, lambda n: (n + 31) // 32, np.int32, 1, oracle.sign_compress_ef)):
+        r, codes = [Guarded(v) for v in res], [Guarded(np.zeros(width(n), dtype)) for n in ns]
+        meta = [Guarded(np.zeros(per * bg.num_chunks(n, C), np.float32)) for n in ns]
+        call([torch.from_numpy(x).cuda() for x in xs], [g.t for g in r], C, [g.t for g in codes], [g.t for g in meta], ws)
+        for b, n in enumerate(ns):
+            ro = res[b].copy()
+            cw, mw = want(xs[b], ro, C)
+            codes[b].check(cw, "codes n=%d" % n)
+            meta[b].check(mw, "meta n=%d" % n)
+            r[b].check(ro, "residual n=%d" % n)
