@@ -15,10 +15,12 @@ namespace bagua {
 
 // Rows per wave of the gathers: one up to 2^21 elements of chunks up to 4096, because a wave walks through the tensor table row after row.  Two -> one,
 // us per launch: MinMax, C = 4096, 64 K 4.3 -> 4.1, 1 M 5.8 -> 5.0, 2 M 7.4 -> 6.6, 4 M 11.2 -> 12.3; C = 1024, 64 K 4.2 -> 3.7, 1 M 5.6 -> 4.8, 2 M 7.2
-// -> 6.2; sign codec, C = 4096, 64 K 4.3 -> 4.0, 1 M 5.9 -> 4.7, 2 M 7.1 -> 5.8, 4 M 10.2 -> 11.0.
+// -> 6.2; sign codec, C = 4096, 64 K 4.3 -> 4.0, 1 M 5.9 -> 4.7, 2 M 7.1 -> 5.8, 4 M 10.2 -> 11.0.  Workgroups that do not fill a CU's 32 waves up to
+// 2^20: C = 3072, MinMax, 1 M 5.6 -> 5.0, 1.6 M 6.4 -> 6.7, sign codec, 1 M 5.7 -> 4.8, 1.6 M 6.4 -> 6.2 but 0.5 % of a round of 12 x 1.6 M more.
 inline int pick_rpw_gather(int rows, size_t n, int preferred)
 {
-    return rows <= kMaxWaves && n <= (static_cast<size_t>(1) << 21) ? 1 : pick_rpw_worker(rows, preferred);
+    const size_t most = static_cast<size_t>(1) << (kWavesPerCu % rows == 0 ? 21 : 20);
+    return rows <= kMaxWaves && n <= most ? 1 : pick_rpw_worker(rows, preferred);
 }
 
 template <int RPW, bool EF, bool WB>
