@@ -77,9 +77,14 @@ inline void batch_fill_lut(uint64_t* table, size_t B, size_t entry_words)
 // buckets of 25.6 M elements in all (17 batched calls): 868 -> 838 us; 4 workers x 5 buckets of 1 M: 99 -> 69 us.  The
 // limit keeps the launch below the 4 KiB of kernel arguments: 58 buckets of a compression, 21 of a server step with
 // eight workers.  The kernels read it through the scalar cache as they read a table in memory.
-constexpr int kInlineWords = 480;
+// A launch's arguments are copied by the host, 0.5 us per KB, and read by the kernel line by line, so a table of up to
+// kShortWords words (7 buckets of a compression, 2 of a server step with eight workers) travels in an argument of its own
+// size.  Whole rounds, the long argument -> the short one: 17 calls over 2
+// buckets of 32 K elements 72.3 -> 68.4 us, 5 calls over 5 buckets of 0.2 M 28.5 -> 26.6 us.
+constexpr int kShortWords = 64, kInlineWords = 480;
+template <int WORDS>
 struct BatchInline {
-    uint64_t w[kInlineWords];
+    uint64_t w[WORDS];
     uint32_t B;
     uint32_t entry_words;
     uint32_t shift;
@@ -130,14 +135,19 @@ int batch_launch(const std::vector<uint64_t>& table, size_t B, size_t entry_word
                  const LAUNCH& launch)
 {
     const BatchView bv = batch_view(workspace, B, entry_words, table[B]);
-    if (table.size() <= kInlineWords) {
-        BatchInline t;
+    auto inlined = [&](auto& t) {
         std::copy(table.begin(), table.end(), t.w);
-        std::fill(t.w + table.size(), t.w + kInlineWords, 0);
         t.B = bv.B;
         t.entry_words = bv.entry_words;
         t.shift = bv.shift;
         launch(t);
+    };
+    if (table.size() <= kShortWords) {
+        BatchInline<kShortWords> t{};
+        inlined(t);
+    } else if (table.size() <= kInlineWords) {
+        BatchInline<kInlineWords> t{};
+        inlined(t);
     } else {
         if (batch_upload(table.data(), table.size(), static_cast<uint64_t*>(workspace), stream) != BAGUA_OK) return BAGUA_ERR_LAUNCH;
         launch(bv);
