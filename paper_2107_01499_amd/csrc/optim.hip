@@ -142,9 +142,44 @@ k_sgd_topk_sparse(const uint16_t* __restrict__ idx, const float* __restrict__ va
     if (i < n) param[i] = param[i] - lr * val[e];
 }
 
+// The entries of a sparse chunk, into its dense copy in LDS.  EARLY: one per thread is requested before anything else, so that the scatter
+// waits for these two loads alone, and not for the index, then for the value, behind everything that the kernel reads.
+template <bool EARLY>
+struct SparseEntries {
+    const uint16_t* idx;
+    const float* val;
+    uint32_t keep, q = 0xFFFFu;
+    float a = 0.0f;
+    __device__ __forceinline__ SparseEntries(const uint16_t* __restrict__ idx_c, const float* __restrict__ val_c, uint32_t kept)
+        : idx(idx_c), val(val_c), keep(kept)
+    {
+        if (EARLY && threadIdx.x < keep) {
+            q = idx[threadIdx.x];
+            a = val[threadIdx.x];
+        }
+    }
+    __device__ __forceinline__ void scatter(uint32_t chunk, float* dense)   // unused slots are 0xFFFF, beyond any chunk
+    {
+        if (EARLY && q < chunk) dense[q] = a;
+        for (uint32_t s = threadIdx.x + (EARLY ? blockDim.x : 0); s < keep; s += blockDim.x) {
+            const uint32_t at = idx[s];
+            if (at < chunk) dense[at] = val[s];
+        }
+    }
+};
+// Late -> early, us of the step (four sets of buffers in turn): SGD, C = 4096, keep = 128, 64 K 2.7 -> 2.5, 1 M 4.1 -> 4.0, 3 M 7.9 -> 9.0, 4 M 11.0 ->
+// 12.2, 8 M +-0, 12 M 33.8 -> 32.4, 25.7 M 69.0 -> 66.7, 100 M 265 -> 256; C = 1024, keep = 32, 25.7 M 72.9 -> 66.6; C = 16384, 25.7 M 76.9 -> 75.9, 100 M
+// 282 -> 295; Adam, C = 4096, 25.7 M 106.3 -> 103.6, C = 8192, keep = 1024, 25.7 M 108.7 -> 106.5, 100 M 418 -> 429.  From 2 M to 5 M, where the state
+// fits the caches, all waves at once lose what the longer chain of loads spreads.
+inline bool entries_early(size_t n, size_t chunk)
+{
+    if (n <= (static_cast<size_t>(5) << 20)) return n <= (static_cast<size_t>(1) << 20);
+    return chunk <= 4096 || n <= (static_cast<size_t>(1) << 26);
+}
+
 // General case: the chunk's decoded gradient is built in LDS (+0 everywhere, then the kept entries), and every
 // element is updated as in k_decompress_sgd.  One workgroup per chunk, RPW rows per wave.
-template <int RPW, bool MOM, bool WD>
+template <int RPW, bool MOM, bool WD, bool EARLY>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk,
                       uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float lr, float mu, float wd)
@@ -155,7 +190,8 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    // parameters (and momentum) do not depend on the decode: request them first
+    SparseEntries<EARLY> entries(idx + c * keep, val + c * keep, keep);
+    // parameters (and momentum) do not depend on the decode: request them next
     f4 p[RPW], m[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -176,10 +212,7 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
-    for (uint32_t s = threadIdx.x; s < keep; s += blockDim.x) {
-        const uint32_t q = idx[c * keep + s];
-        if (q != 0xFFFFu && q < chunk) s_g[q] = val[c * keep + s];
-    }
+    entries.scatter(chunk, s_g);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -212,7 +245,7 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
 
 // Adam-type update after a top-K round: the chunk's decoded tensor is built in LDS as above, then every element is
 // updated as in k_decompress_adam.
-template <int RPW, bool FROZEN, bool WD>
+template <int RPW, bool FROZEN, bool WD, bool EARLY>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk,
                        uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float* __restrict__ vbuf,
@@ -224,7 +257,8 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    // parameters and optimizer state do not depend on the decode: request them first
+    SparseEntries<EARLY> entries(idx + c * keep, val + c * keep, keep);
+    // parameters and optimizer state do not depend on the decode: request them next
     f4 p[RPW], m[RPW], v[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -247,10 +281,7 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
     for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
-    for (uint32_t s = threadIdx.x; s < keep; s += blockDim.x) {
-        const uint32_t q = idx[c * keep + s];
-        if (q != 0xFFFFu && q < chunk) s_g[q] = val[c * keep + s];
-    }
+    entries.scatter(chunk, s_g);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -373,6 +404,10 @@ extern "C" int bagua_decompress_adam_step(int codec, const void* codes, const fl
     return launch_status();
 }
 
+#define BAGUA_DISPATCH_EARLY(stmt)                                              \
+    if (entries_early(n, chunk)) { constexpr bool EARLY = true; stmt; }         \
+    else { constexpr bool EARLY = false; stmt; }
+
 extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* val, size_t n, size_t chunk, size_t keep,
                                               float* param, float* momentum_buf, float lr, float momentum,
                                               float weight_decay, void* stream)
@@ -404,8 +439,8 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const size_t lds = chunk * sizeof(float);
 #define BAGUA_TS(MOMv, WDv)                                                                                      \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_decompress_sgd_topk<RPW, MOMv, WDv>), grid, block, lds, s, idx, \
-                                               val, n, ch, kp, param, momentum_buf, lr, momentum, weight_decay))
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(hipLaunchKernelGGL((k_decompress_sgd_topk<RPW, MOMv, WDv, EARLY>), grid, block, lds, s, idx, \
+                                               val, n, ch, kp, param, momentum_buf, lr, momentum, weight_decay)))
     if (mom && wd) { BAGUA_TS(true, true) }
     else if (mom) { BAGUA_TS(true, false) }
     else if (wd) { BAGUA_TS(false, true) }
@@ -441,9 +476,9 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const size_t lds = chunk * sizeof(float);
 #define BAGUA_TA(FRv, WDv)                                                                                         \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_decompress_adam_topk<RPW, FRv, WDv>), grid, block, lds, s, idx,  \
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(hipLaunchKernelGGL((k_decompress_adam_topk<RPW, FRv, WDv, EARLY>), grid, block, lds, s, idx,  \
                                                val, n, ch, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps,     \
-                                               weight_decay))
+                                               weight_decay)))
     if (frozen && wd) { BAGUA_TA(true, true) }
     else if (frozen) { BAGUA_TA(true, false) }
     else if (wd) { BAGUA_TA(false, true) }

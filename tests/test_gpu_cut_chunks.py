@@ -209,3 +209,23 @@ def test_compressions_batched(bg, oracle, C):
             codes[b].check(cw, "codes n=%d" % n)
             meta[b].check(mw, "meta n=%d" % n)
             r[b].check(ro, "residual n=%d" % n)
+
+
+# keep below, at and above the threads of a workgroup; a chunk cut short; either side of the lines between early and late entries
+@pytest.mark.parametrize("n,C,keep", [(3, 256, 1), (5001, 1024, 7), (70001, 1024, 256), (70001, 1024, 257), (40001, 2048, 2048), (300001, 16384, 1500),
+                                      (1 << 20, 4096, 128), ((1 << 20) + 1, 4096, 600), ((5 << 20) + 3, 4096, 513), ((1 << 26) + 5, 8192, 3)])
+@pytest.mark.parametrize("opt", ["sgd", "adam"])
+def test_optimizer_steps_after_topk(bg, oracle, n, C, keep, opt):
+    idx, val = oracle.compress_topk(vals(n, n), None, C, keep)
+    param, m, v = vals(n, 1, 0.02), vals(n, 2), np.square(vals(n, 3)) + np.float32(1e-8)
+    gp, gm, gv = Guarded(param), Guarded(m), Guarded(v)
+    gi, gx = torch.from_numpy(idx.view(np.int16)).cuda(), torch.from_numpy(val).cuda()
+    if opt == "sgd":
+        bg.bagua_decompress_sgd_step_topk(gi, gx, n, C, keep, gp.t, gm.t, 1e-3, momentum=0.9, weight_decay=1e-4)
+        oracle.decompress_sgd_step_topk(idx, val, n, C, keep, param, m, 1e-3, 0.9, 1e-4)
+    else:
+        bg.bagua_decompress_adam_step_topk(gi, gx, n, C, keep, gp.t, gm.t, gv.t, 1e-4)
+        oracle.decompress_adam_step_topk(idx, val, n, C, keep, param, m, v, 1e-4)
+        gv.check(v, "v")
+    gp.check(param, "param")
+    gm.check(m, "m")
