@@ -16,7 +16,7 @@ int batch_upload(const uint64_t* host, size_t words, uint64_t* dst, hipStream_t 
         const uint32_t count = static_cast<uint32_t>(std::min<size_t>(kUploadWords, words - w0));
         for (uint32_t i = 0; i < count; ++i) blob.w[i] = host[w0 + i];
         for (uint32_t i = count; i < kUploadWords; ++i) blob.w[i] = 0;
-        hipLaunchKernelGGL(k_upload_words, dim3(1), dim3(kUploadWords), 0, stream, blob, count, dst + w0);
+        launch_kernel(k_upload_words, dim3(1), dim3(kUploadWords), 0, stream, blob, count, dst + w0);
     }
     return launch_status();
 }

@@ -589,6 +589,18 @@ inline int pick_rpw_topk(int rows, size_t chunks)
     if (is_short) { constexpr bool SHORT = true; stmt; } \
     else { constexpr bool SHORT = false; stmt; }
 
+// A launch without the detour of <<< >>> over the runtime's call stack, 0.25 of 2.7 us of host time.
+template <typename T>
+struct SameType {
+    using type = T;
+};
+template <typename... P>
+inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, typename SameType<P>::type... args)
+{
+    void* at[] = {const_cast<void*>(static_cast<const void*>(&args))...};
+    (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, at, lds, stream);   // launch_status() tells
+}
+
 inline int launch_status()
 {
     return hipGetLastError() == hipSuccess ? BAGUA_OK : BAGUA_ERR_LAUNCH;

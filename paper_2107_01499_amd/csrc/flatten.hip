@@ -345,7 +345,7 @@ extern "C" int bagua_bucket_flatten_run(const void* workspace, size_t T, float* 
     if (T > 0xfffffff0u || num_tiles(bucket_numel) > kMaxGrid / kTileWaves) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned16(workspace) || !aligned16(bucket)) return BAGUA_ERR_ALIGNMENT;
     const FlattenPlanView pv = plan_view(workspace, T);
-    hipLaunchKernelGGL(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
+    launch_kernel(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
                        dim3(static_cast<unsigned>(num_tiles(bucket_numel) * kTileWaves)), dim3(kWave), 0,
                        static_cast<hipStream_t>(stream), pv.desc, pv.tile_first, static_cast<uint32_t>(T), bucket, bucket_numel);
     return launch_status();
@@ -396,7 +396,7 @@ extern "C" int bagua_bucket_flatten_batched_run(const void* const* plans, const 
     hipStream_t s = static_cast<hipStream_t>(stream);
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
-        hipLaunchKernelGGL((keep_bucket(total * kTile) ? k_flatten_batched<true, TABLE> : k_flatten_batched<false, TABLE>),
+        launch_kernel((keep_bucket(total * kTile) ? k_flatten_batched<true, TABLE> : k_flatten_batched<false, TABLE>),
                            dim3(static_cast<unsigned>(total * kTileWaves)), dim3(kWave), 0, s, tab);
     });
 }
@@ -412,10 +412,10 @@ extern "C" int bagua_decompress_unflatten(int codec, const void* codes, const fl
     dim3 grid(static_cast<unsigned>((num_tiles(n) + kDecodeTiles - 1) / kDecodeTiles)), block(256);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (codec == BAGUA_CODEC_MINMAX_U8)
-        hipLaunchKernelGGL((k_decompress_unflatten<0>), grid, block, 0, s, pv.desc, pv.tile_first, static_cast<uint32_t>(T),
+        launch_kernel((k_decompress_unflatten<0>), grid, block, 0, s, pv.desc, pv.tile_first, static_cast<uint32_t>(T),
                            codes, meta, n, static_cast<uint32_t>(chunk));
     else
-        hipLaunchKernelGGL((k_decompress_unflatten<1>), grid, block, 0, s, pv.desc, pv.tile_first, static_cast<uint32_t>(T),
+        launch_kernel((k_decompress_unflatten<1>), grid, block, 0, s, pv.desc, pv.tile_first, static_cast<uint32_t>(T),
                            codes, meta, n, static_cast<uint32_t>(chunk));
     return launch_status();
 }
@@ -516,12 +516,12 @@ extern "C" int bagua_bucket_flatten_static(const void* const* src, const size_t*
         const uint32_t count = static_cast<uint32_t>(std::min<size_t>(kDescPerLaunch, T - t0));
         for (uint32_t i = 0; i < count; ++i)
             batch.d[i] = TensorDesc{static_cast<const float*>(src[t0 + i]), numel[t0 + i], dst_offset[t0 + i]};
-        hipLaunchKernelGGL(k_table_desc, dim3(1), dim3(kDescPerLaunch), 0, s, batch, count, desc + t0);
+        launch_kernel(k_table_desc, dim3(1), dim3(kDescPerLaunch), 0, s, batch, count, desc + t0);
     }
     const size_t tiles = num_tiles(bucket_numel);
-    hipLaunchKernelGGL(k_table_tiles, dim3(static_cast<unsigned>((tiles + 1 + 255) / 256)), dim3(256), 0, s, desc,
+    launch_kernel(k_table_tiles, dim3(static_cast<unsigned>((tiles + 1 + 255) / 256)), dim3(256), 0, s, desc,
                        static_cast<uint32_t>(T), tile_first, tiles);
-    hipLaunchKernelGGL(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
+    launch_kernel(keep_bucket(bucket_numel) ? k_flatten<true> : k_flatten<false>,
                        dim3(static_cast<unsigned>(tiles * kTileWaves)), dim3(kWave), 0, s, desc, tile_first,
                        static_cast<uint32_t>(T), bucket, bucket_numel);
     return launch_status();
@@ -534,7 +534,7 @@ extern "C" int bagua_bucket_unflatten_run(const void* workspace, size_t T, const
     if (T > 0xfffffff0u || num_tiles(bucket_numel) > kMaxGrid / kTileWaves) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned16(workspace) || !aligned16(bucket)) return BAGUA_ERR_ALIGNMENT;
     const FlattenPlanView pv = plan_view(workspace, T);
-    hipLaunchKernelGGL(k_unflatten, dim3(static_cast<unsigned>(num_tiles(bucket_numel) * kTileWaves)), dim3(kWave), 0,
+    launch_kernel(k_unflatten, dim3(static_cast<unsigned>(num_tiles(bucket_numel) * kTileWaves)), dim3(kWave), 0,
                        static_cast<hipStream_t>(stream), pv.desc, pv.tile_first, static_cast<uint32_t>(T), bucket, bucket_numel);
     return launch_status();
 }

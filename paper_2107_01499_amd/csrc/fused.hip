@@ -364,7 +364,7 @@ extern "C" int bagua_flatten_compress_minmax_u8(const void* workspace, size_t T,
     // 132 -> 134 us; from 7 M on kept is faster or equal at any chunk length.  (A flat bucket's compression gains from 2 M on.)
     const uint32_t keep = bucket_numel < (static_cast<size_t>(1) << 22) ? 0 : keep_chunks(bucket_numel, chunk);
 #define BAGUA_FC(EFv, WBv)                                                                                       \
-    BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
+    BAGUA_DISPATCH_RPW_WORKER(rpw, launch_kernel((k_flatten_compress_minmax<RPW, EFv, WBv>), grid, block, 0, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, codes,  \
                                                minmax, bucket_out, keep,                   \
                                                chunk_order(grid.x, chunk, order_pays_gather_minmax(bucket_numel, chunk))))
@@ -399,7 +399,7 @@ extern "C" int bagua_flatten_sign_compress_ef(const void* workspace, size_t T, f
     const uint32_t ch = static_cast<uint32_t>(chunk), t32 = static_cast<uint32_t>(T);
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define BAGUA_FS(EFv, WBv)                                                                                       \
-    BAGUA_DISPATCH_RPW_WORKER(rpw, hipLaunchKernelGGL((k_flatten_sign_compress<RPW, EFv, WBv>), grid, block, lds, s,    \
+    BAGUA_DISPATCH_RPW_WORKER(rpw, launch_kernel((k_flatten_sign_compress<RPW, EFv, WBv>), grid, block, lds, s,    \
                                                pv.desc, pv.tile_first, t32, residual, bucket_numel, ch, bits,   \
                                                scale, bucket_out, chunk_order(grid.x, chunk)))
     if (residual && bucket_out) { BAGUA_FS(true, true) }
@@ -439,8 +439,8 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
         constexpr int RPW = decltype(rpw)::value;
         constexpr bool SHORT = decltype(is_short)::value;
         const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));
-        if (residual) hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, true, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
-        else hipLaunchKernelGGL((k_reduce_compress_minmax<RPW, false, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
+        if (residual) launch_kernel((k_reduce_compress_minmax<RPW, true, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
+        else launch_kernel((k_reduce_compress_minmax<RPW, false, SHORT>), grid, block, 0, s, xt, k_local, inv_k, residual, n, ch, codes, minmax, keep, order);
     });
     return launch_status();
 }
@@ -475,8 +475,8 @@ extern "C" int bagua_reduce_compress_sign_ef(const float* const* x, int k_local,
         constexpr bool SHORT = decltype(is_short)::value;
         const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));
         const size_t lds = block.x > kWave ? chunk / kRow * kWave * sizeof(float) : 0;
-        if (residual) hipLaunchKernelGGL((k_reduce_compress_sign<RPW, true, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
-        else hipLaunchKernelGGL((k_reduce_compress_sign<RPW, false, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
+        if (residual) launch_kernel((k_reduce_compress_sign<RPW, true, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
+        else launch_kernel((k_reduce_compress_sign<RPW, false, SHORT>), grid, block, lds, s, xt, k_local, inv_k, residual, n, ch, bits, scale, order);
     });
     return launch_status();
 }

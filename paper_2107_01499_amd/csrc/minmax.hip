@@ -428,10 +428,10 @@ int launch_compress_minmax(const float* x, float* residual, size_t n, size_t chu
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
+        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), launch_kernel((k_compress_minmax<RPW, true, SHORT>), grid, block, 0,
                                                                                  stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk, order_pays(n, chunk)))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
+        BAGUA_DISPATCH_RPW_WORKER(rpw, BAGUA_DISPATCH_SHORT(short_launch(n), launch_kernel((k_compress_minmax<RPW, false, SHORT>), grid, block, 0,
                                                                                  stream, x, residual, n, ch, codes, minmax, pace_for(n), keep_chunks(n, chunk), chunk_order(grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
@@ -451,7 +451,7 @@ int launch_drr_minmax(const void* const* codes_in, const float* const* meta_in, 
     drr_minmax_shape(n, n, chunk, k, [&](auto rpw, auto form, dim3 block) {
         constexpr int RPW = decltype(rpw)::value, FORM = decltype(form)::value;
 #define BAGUA_DRR(EFv, OUTv)                                                                                     \
-    hipLaunchKernelGGL((k_drr_minmax<RPW, EFv, OUTv, FORM>), grid, block, 0, stream, ct, mt, k, inv_k, eps, n, ch, \
+    launch_kernel((k_drr_minmax<RPW, EFv, OUTv, FORM>), grid, block, 0, stream, ct, mt, k, inv_k, eps, n, ch, \
                        codes_out, minmax_out, out, keep_server_codes(n))
         if (eps && out) BAGUA_DRR(true, true);
         else if (eps) BAGUA_DRR(true, false);
@@ -476,7 +476,7 @@ int launch_drr_minmax_batched(const std::vector<uint64_t>& table, void* workspac
         drr_minmax_shape(n, least, chunk, k, [&](auto rpw, auto form, dim3 block) {
             constexpr int RPW = decltype(rpw)::value, FORM = decltype(form)::value;
 #define BAGUA_DRR(EFv, OUTv)                                                                                              \
-    hipLaunchKernelGGL((k_drr_minmax_batched<RPW, EFv, OUTv, FORM, TABLE>), grid, block, 0, stream, tab, k, inv_k, ch, \
+    launch_kernel((k_drr_minmax_batched<RPW, EFv, OUTv, FORM, TABLE>), grid, block, 0, stream, tab, k, inv_k, ch, \
                        keep_server_codes(n))
             if (ef && with_out) BAGUA_DRR(true, true);
             else if (ef) BAGUA_DRR(true, false);
@@ -492,7 +492,7 @@ int launch_decompress_minmax(const uint8_t* codes, const float* minmax, size_t n
 {
     const size_t rows = (n + kRow - 1) / kRow;
     dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), block(kWave * kRowWaves);
-    hipLaunchKernelGGL(k_decompress_minmax, grid, block, 0, stream, codes, minmax, n,
+    launch_kernel(k_decompress_minmax, grid, block, 0, stream, codes, minmax, n,
                        static_cast<uint32_t>(chunk), out);
     return launch_status();
 }
@@ -565,10 +565,10 @@ extern "C" int bagua_compress_minmax_u8_batched(const float* const* x, float* co
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, launch_kernel(
                                         (k_compress_minmax_batched<RPW, true, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         } else {
-            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_SHORT(groups > 0 || is_short, launch_kernel(
                                         (k_compress_minmax_batched<RPW, false, SHORT, TABLE>), grid, block, lds, s, tab, ch, pace_for(total * chunk), keep, chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         }
     });

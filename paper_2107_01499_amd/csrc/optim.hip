@@ -349,7 +349,7 @@ extern "C" int bagua_decompress_sgd_step(int codec, const void* codes, const flo
     const ChunkOrder order = n <= (static_cast<size_t>(1) << 24) ? row_order(grid.x, rpc) : ChunkOrder{0, 0};
     const bool mom = momentum_buf != nullptr, wd = weight_decay != 0.0f;
 #define BAGUA_SGD(CODEC, MOMv, WDv)                                                                          \
-    hipLaunchKernelGGL((k_decompress_sgd<CODEC, MOMv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, \
+    launch_kernel((k_decompress_sgd<CODEC, MOMv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, \
                        momentum_buf, lr, momentum, weight_decay, order)
 #define BAGUA_SGD_CODEC(CODEC)                       \
     if (mom && wd) BAGUA_SGD(CODEC, true, true);     \
@@ -390,7 +390,7 @@ extern "C" int bagua_decompress_adam_step(int codec, const void* codes, const fl
     const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
     const bool frozen = variance_frozen != 0, wd = weight_decay != 0.0f;
 #define BAGUA_ADAM(CODEC, FRv, WDv)                                                                            \
-    hipLaunchKernelGGL((k_decompress_adam<CODEC, FRv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, m, \
+    launch_kernel((k_decompress_adam<CODEC, FRv, WDv>), grid, block, 0, s, codes, meta, n, rpc, param, m, \
                        v, lr, beta1, omb1, beta2, omb2, eps, weight_decay, order)
 #define BAGUA_ADAM_CODEC(CODEC)                        \
     if (frozen && wd) BAGUA_ADAM(CODEC, true, true);   \
@@ -430,7 +430,7 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
     // lr * (+0) must be +0 for the sparse form to equal the dense update: lr finite with a clear sign bit
     if (!mom && !wd && std::isfinite(lr) && !std::signbit(lr)) {
         const size_t entries = nc * keep;
-        hipLaunchKernelGGL(k_sgd_topk_sparse, dim3(static_cast<unsigned>((entries + 255) / 256)), dim3(256), 0, s, idx, val,
+        launch_kernel(k_sgd_topk_sparse, dim3(static_cast<unsigned>((entries + 255) / 256)), dim3(256), 0, s, idx, val,
                            entries, ch, kp, n, param, lr);
         return launch_status();
     }
@@ -439,7 +439,7 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const size_t lds = chunk * sizeof(float);
 #define BAGUA_TS(MOMv, WDv)                                                                                      \
-    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(hipLaunchKernelGGL((k_decompress_sgd_topk<RPW, MOMv, WDv, EARLY>), grid, block, lds, s, idx, \
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(launch_kernel((k_decompress_sgd_topk<RPW, MOMv, WDv, EARLY>), grid, block, lds, s, idx, \
                                                val, n, ch, kp, param, momentum_buf, lr, momentum, weight_decay)))
     if (mom && wd) { BAGUA_TS(true, true) }
     else if (mom) { BAGUA_TS(true, false) }
@@ -476,7 +476,7 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
     dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
     const size_t lds = chunk * sizeof(float);
 #define BAGUA_TA(FRv, WDv)                                                                                         \
-    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(hipLaunchKernelGGL((k_decompress_adam_topk<RPW, FRv, WDv, EARLY>), grid, block, lds, s, idx,  \
+    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(launch_kernel((k_decompress_adam_topk<RPW, FRv, WDv, EARLY>), grid, block, lds, s, idx,  \
                                                val, n, ch, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps,     \
                                                weight_decay)))
     if (frozen && wd) { BAGUA_TA(true, true) }

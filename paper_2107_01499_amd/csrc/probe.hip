@@ -76,7 +76,7 @@ extern "C" int bagua_probe_read(const float* x, size_t n, float* tile_sums, void
     if (!aligned16(x) || !aligned4(tile_sums)) return BAGUA_ERR_ALIGNMENT;
     const size_t tiles = (n + kProbeTile - 1) / kProbeTile;
     if (tiles > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_probe_read, dim3(static_cast<unsigned>(tiles)), dim3(256), 0,
+    launch_kernel(k_probe_read, dim3(static_cast<unsigned>(tiles)), dim3(256), 0,
                        static_cast<hipStream_t>(stream), x, n, tile_sums);
     return launch_status();
 }
@@ -114,8 +114,8 @@ extern "C" int bagua_probe_streams(const float* const* in, float* const* out, ui
     const int pace = pace_for(n);
 #define BAGUA_PROBE(NR, NW, NB)                                                                                    \
     if (nr == NR && nw == NW && nb == NB) {                                                                        \
-        if (pw == 1) hipLaunchKernelGGL((k_probe_streams<NR, NW, NB, 1>), grid, block, 0, s, it, ot, bt, seq, n, pace); \
-        else hipLaunchKernelGGL((k_probe_streams<NR, NW, NB, kRowWaves>), grid, block, 0, s, it, ot, bt, seq, n, pace); \
+        if (pw == 1) launch_kernel((k_probe_streams<NR, NW, NB, 1>), grid, block, 0, s, it, ot, bt, seq, n, pace); \
+        else launch_kernel((k_probe_streams<NR, NW, NB, kRowWaves>), grid, block, 0, s, it, ot, bt, seq, n, pace); \
         return launch_status();                                                                                    \
     }
     BAGUA_PROBE(1, 1, 0) BAGUA_PROBE(2, 1, 0) BAGUA_PROBE(2, 1, 1) BAGUA_PROBE(2, 2, 1) BAGUA_PROBE(4, 4, 0) BAGUA_PROBE(8, 8, 0)

@@ -387,11 +387,11 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
     const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (lp_encode_short(n)) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, true, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     } else if (elements <= (static_cast<size_t>(1) << 27)) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, true, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, true, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     } else {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_lp_encode<RPW, false, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, false, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     }
 }
 
@@ -407,7 +407,7 @@ static void launch_fp_k(const PtrTable& in, const MutPtrTable& out, size_t n, fl
 {
     const dim3 grid(static_cast<unsigned>(ring_fp_groups(K, n)));
     const size_t lds = K >= 2 && ring_fp_long(K, n) ? lds_for_residency(ring_fp_waves(K)) : 0;   // one replica is a copy
-    hipLaunchKernelGGL((k_ring_avg_fp<K>), grid, dim3(kWave), lds, s, in, out, n, third);
+    launch_kernel((k_ring_avg_fp<K>), grid, dim3(kWave), lds, s, in, out, n, third);
 }
 
 static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, size_t n, hipStream_t stream)
@@ -426,7 +426,7 @@ static int launch_ring_fp(const float* const* x_in, float* const* x_out, int k, 
         BAGUA_FP_CASE(13) BAGUA_FP_CASE(14) BAGUA_FP_CASE(15) BAGUA_FP_CASE(16)
 #undef BAGUA_FP_CASE
         default:
-            hipLaunchKernelGGL(k_ring_avg_fp_any, dim3(static_cast<unsigned>(ring_fp_groups(k, n))), dim3(kWave * kRowWaves), 0, stream, in,
+            launch_kernel(k_ring_avg_fp_any, dim3(static_cast<unsigned>(ring_fp_groups(k, n))), dim3(kWave * kRowWaves), 0, stream, in,
                                out, k, n, third);
     }
     return launch_status();
@@ -450,7 +450,7 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
     const int keep = keep_codes_of_round(K * n);
     const ChunkOrder order = chunk_order(grid.x, chunk);
 #define BAGUA_RING_KEEP(KEEPv, FULLv, WIDEv)                                                                                  \
-    hipLaunchKernelGGL((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third, order)
+    launch_kernel((k_ring_avg_lp<K, BAGUA_RPW_LP, KEEPv, FULLv, WIDEv>), grid, block, 0, s, in, out, hat, cd, mm, n, chunk, third, order)
 #define BAGUA_RING(FULLv, WIDEv)                   \
     {                                              \
         if (keep) BAGUA_RING_KEEP(1, FULLv, WIDEv); \
@@ -462,7 +462,7 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
     }
     if (!wide) BAGUA_RING(false, false)
     if constexpr (K < 8) BAGUA_RING(false, true)
-    hipLaunchKernelGGL((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep, order);
+    launch_kernel((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep, order);
 #undef BAGUA_RING_KEEP
 #undef BAGUA_RING
 }
@@ -488,8 +488,8 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
     if (ring_lp_two_launches(k, n, chunk)) {
         const size_t nrows = (n + kRow - 1) / kRow;
         const dim3 all(static_cast<unsigned>(nc), k), mix(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), k);
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_publish<RPW>), all, block, 0, stream, in, hat, cd, mm, n, ch))
-        hipLaunchKernelGGL(k_ring_mix, mix, dim3(kWave * kRowWaves), 0, stream, in, out, hat, k, n, third,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_ring_publish<RPW>), all, block, 0, stream, in, hat, cd, mm, n, ch))
+        launch_kernel(k_ring_mix, mix, dim3(kWave * kRowWaves), 0, stream, in, out, hat, k, n, third,
                            row_order(mix.x, static_cast<uint32_t>(rows)));
         return launch_status();
     }
@@ -502,7 +502,7 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
 #undef BAGUA_LP_CASE
         }
     }
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
+    BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
                                                third, keep_codes_of_round(k * n), chunk_order(nc, chunk)))
     return launch_status();
 }
@@ -608,7 +608,7 @@ extern "C" int bagua_decentralized_avg_peers(const float* const* x_in, float* co
         jobs.out_b[nj] = matched ? x_out[p] : nullptr;
         ++nj;
     }
-    hipLaunchKernelGGL(k_peer_avg_fp, dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves), nj), dim3(kWave * kRowWaves), 0,
+    launch_kernel(k_peer_avg_fp, dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves), nj), dim3(kWave * kRowWaves), 0,
                        static_cast<hipStream_t>(stream), jobs, n);
     return launch_status();
 }
@@ -660,7 +660,7 @@ extern "C" int bagua_centralized_avg_fp(const float* const* x, int k, size_t n, 
     if ((rows + kRowWaves - 1) / kRowWaves > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     PtrTable xt{};
     for (int j = 0; j < k; ++j) xt.p[j] = x[j];
-    hipLaunchKernelGGL(k_centralized_avg_fp, dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), dim3(kWave * kRowWaves), 0,
+    launch_kernel(k_centralized_avg_fp, dim3(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), dim3(kWave * kRowWaves), 0,
                        static_cast<hipStream_t>(stream), xt, k, 1.0f / static_cast<float>(k), n, out);
     return launch_status();
 }
@@ -832,19 +832,19 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
             pairs.codes[0][npairs + j] = singles.codes[0][j];
             pairs.minmax[0][npairs + j] = singles.minmax[0][j];
         }
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true, true>), dim3(grid.x, npairs + nsingles), block, 0, s, pairs, npairs, n, ch,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_peer_avg_lp<RPW, true, true>), dim3(grid.x, npairs + nsingles), block, 0, s, pairs, npairs, n, ch,
                                                    keep_codes_of_round(k * n), order))
         nsingles = 0;
     } else if (npairs) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, true, false>), dim3(grid.x, npairs), block, gossip_pairs_lds(chunk, npairs * n), s, pairs, npairs,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_peer_avg_lp<RPW, true, false>), dim3(grid.x, npairs), block, gossip_pairs_lds(chunk, npairs * n), s, pairs, npairs,
                                                    n, ch, keep_codes_of_round(k * n), order))
     }
     if (nsingles) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_peer_avg_lp<RPW, false, false>), dim3(grid.x, nsingles), block, 0, s, singles, 0, n, ch,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_peer_avg_lp<RPW, false, false>), dim3(grid.x, nsingles), block, 0, s, singles, 0, n, ch,
                                                    keep_codes_of_round(k * n), order))
     }
     if (nmix) {                                         // all public copies are advanced by now
-        hipLaunchKernelGGL(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), nmix),
+        launch_kernel(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), nmix),
                            dim3(kWave * kRowWaves), 0, s, mix, n);
     }
     return launch_status();
@@ -944,7 +944,7 @@ extern "C" int bagua_lp_apply_mix(const float* x, const float* xhat_own, float* 
     const ChunkOrder order = n <= (static_cast<size_t>(1) << 25) ? row_order(grid.x, rpc) : ChunkOrder{0, 0};
     const float third = 1.0f / 3.0f;
 #define BAGUA_MIX(L, R, S)                                                                                            \
-    hipLaunchKernelGGL((k_lp_apply_mix<L, R, S>), grid, block, 0, s, x, xhat_own, xhat_left, xhat_right, codes_left, \
+    launch_kernel((k_lp_apply_mix<L, R, S>), grid, block, 0, s, x, xhat_own, xhat_left, xhat_right, codes_left, \
                        minmax_left, codes_right, minmax_right, n, rpc, third, x_out, order)
     const bool al = codes_left != nullptr, ar = codes_right != nullptr;
     if (same) { if (al) BAGUA_MIX(true, false, true); else BAGUA_MIX(false, false, true); }

@@ -415,10 +415,10 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     const SignGeometry g = sign_geometry(n, chunk, BAGUA_RPW_SIGN, true);
     const uint32_t ch = static_cast<uint32_t>(chunk);
     if (residual) {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, true, kMomNone, SHORT>), g.grid, g.block,
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), launch_kernel((k_sign_compress<RPW, true, kMomNone, SHORT>), g.grid, g.block,
                                                      g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     } else {
-        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), hipLaunchKernelGGL((k_sign_compress<RPW, false, kMomNone, SHORT>), g.grid, g.block,
+        BAGUA_DISPATCH_RPW_WORKER(g.rpw, BAGUA_DISPATCH_SHORT(short_launch(n), launch_kernel((k_sign_compress<RPW, false, kMomNone, SHORT>), g.grid, g.block,
                                                      g.lds, stream, x, residual, n, ch, bits, scale, nullptr, 0.0f, 0.0f, pace_for(n), 0u, chunk_order(g.grid.x, chunk, order_pays(n, chunk)))))
     }
     return launch_status();
@@ -436,7 +436,7 @@ int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, in
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
 #define BAGUA_DRR(EFv, OUTv)                                                                                      \
-    BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_drr_sign<RPW, EFv, OUTv>), g.grid, g.block, g.lds, stream, bt, \
+    BAGUA_DISPATCH_RPW(g.rpw, launch_kernel((k_drr_sign<RPW, EFv, OUTv>), g.grid, g.block, g.lds, stream, bt, \
                                                  st, k, inv_k, eps, n, ch, bits_out, scale_out, out))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
@@ -456,7 +456,7 @@ int launch_drr_sign_batched(const std::vector<uint64_t>& table, void* workspace,
     return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
 #define BAGUA_DRR(EFv, OUTv)                                                                                       \
-    BAGUA_DISPATCH_RPW(g.rpw, hipLaunchKernelGGL((k_drr_sign_batched<RPW, EFv, OUTv, TABLE>), g.grid, g.block, g.lds, stream, \
+    BAGUA_DISPATCH_RPW(g.rpw, launch_kernel((k_drr_sign_batched<RPW, EFv, OUTv, TABLE>), g.grid, g.block, g.lds, stream, \
                                                  tab, k, inv_k, ch))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
@@ -471,7 +471,7 @@ int launch_decompress_sign(const uint32_t* bits, const float* scale, size_t n, s
 {
     const size_t rows = (n + kRow - 1) / kRow;
     dim3 grid(static_cast<unsigned>((rows + kRowWaves - 1) / kRowWaves)), block(kWave * kRowWaves);
-    hipLaunchKernelGGL(k_decompress_sign, grid, block, 0, stream, bits, scale, n, static_cast<uint32_t>(chunk), out);
+    launch_kernel(k_decompress_sign, grid, block, 0, stream, bits, scale, n, static_cast<uint32_t>(chunk), out);
     return launch_status();
 }
 
@@ -514,7 +514,7 @@ extern "C" int bagua_momentum_sign_compress_ef(const float* g, const float* m, f
     const float omb1 = 1.0f - beta1;
     const ChunkOrder order = chunk_order(geo.grid.x, chunk, order_pays(n, chunk));
 #define BAGUA_MOM(RPWv, EFv, MOMv, SHORTv)                                                                                      \
-    hipLaunchKernelGGL((k_sign_compress<RPWv, EFv, MOMv, SHORTv>), geo.grid, geo.block, geo.lds, s, g, residual, n, ch, bits, scale, \
+    launch_kernel((k_sign_compress<RPWv, EFv, MOMv, SHORTv>), geo.grid, geo.block, geo.lds, s, g, residual, n, ch, bits, scale, \
                        m, beta1, omb1, pace_for(n), mom_keep(chunk), order)
     if (mom_streams(n, geo.rpw, geo.block.x / kWave)) {
         if (residual) BAGUA_MOM(1, true, kMomStream, false);
@@ -574,10 +574,10 @@ extern "C" int bagua_sign_compress_ef_batched(const float* const* x, float* cons
     return batch_launch(table, B, ew, workspace, s, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
         if (ef) {
-            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), launch_kernel(
                                           (k_sign_compress_batched<RPW, true, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         } else {
-            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), hipLaunchKernelGGL(
+            BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_SHORT(groups > 0 || short_launch(total * chunk, true), launch_kernel(
                                           (k_sign_compress_batched<RPW, false, SHORT, TABLE>), g.grid, g.block, g.lds, s, tab, ch, pace_for(total * chunk), chunk_order(total, chunk, order_pays(total * chunk, chunk)))))
         }
     });

@@ -516,10 +516,10 @@ extern "C" int bagua_compress_topk_ef(const float* x, float* residual, size_t n,
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (residual) {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, true>), grid, block, 0, s, x, residual, n, ch, kp,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_compress_topk<RPW, true>), grid, block, 0, s, x, residual, n, ch, kp,
                                                    idx, val, chunk_order(grid.x, chunk)))
     } else {
-        BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_compress_topk<RPW, false>), grid, block, 0, s, x, residual, n, ch, kp,
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_compress_topk<RPW, false>), grid, block, 0, s, x, residual, n, ch, kp,
                                                    idx, val, chunk_order(grid.x, chunk)))
     }
     return launch_status();
@@ -564,7 +564,7 @@ extern "C" int bagua_decompress_reduce_recompress_topk(const uint16_t* const* id
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define BAGUA_DRR(EFv, OUTv)                                                                                      \
-    BAGUA_DISPATCH_RPW(rpw, hipLaunchKernelGGL((k_drr_topk<RPW, EFv, OUTv>), grid, block, lds, s, it, vt, k, inv_k, \
+    BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_drr_topk<RPW, EFv, OUTv>), grid, block, lds, s, it, vt, k, inv_k, \
                                                kp, server_residual, n, ch, idx_out, val_out, out_fp32))
     if (server_residual && out_fp32) { BAGUA_DRR(true, true) }
     else if (server_residual) { BAGUA_DRR(true, false) }
@@ -588,7 +588,7 @@ extern "C" int bagua_decompress_topk(const uint16_t* idx, const float* val, size
     }
     if (num_chunks(n, chunk) > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned2(idx) || !aligned4(val) || !aligned16(out)) return BAGUA_ERR_ALIGNMENT;
-    hipLaunchKernelGGL(k_decompress_topk, dim3(static_cast<unsigned>(num_chunks(n, chunk))), dim3(256),
+    launch_kernel(k_decompress_topk, dim3(static_cast<unsigned>(num_chunks(n, chunk))), dim3(256),
                        chunk * sizeof(float), static_cast<hipStream_t>(stream), idx, val, n, static_cast<uint32_t>(chunk),
                        static_cast<uint32_t>(keep), out);
     return launch_status();
