@@ -158,40 +158,75 @@ struct SparseEntries {
             a = val[threadIdx.x];
         }
     }
-    __device__ __forceinline__ void scatter(uint32_t chunk, float* dense)   // unused slots are 0xFFFF, beyond any chunk
+    // Those that lie in [from, from + size) of the chunk (unused slots are 0xFFFF, beyond any chunk).
+    __device__ __forceinline__ void scatter(uint32_t from, uint32_t size, float* dense)
     {
-        if (EARLY && q < chunk) dense[q] = a;
-        for (uint32_t s = threadIdx.x + (EARLY ? blockDim.x : 0); s < keep; s += blockDim.x) {
-            const uint32_t at = idx[s];
-            if (at < chunk) dense[at] = val[s];
+        if (EARLY && q - from < size) dense[q - from] = a;
+        for (uint32_t s = threadIdx.x + (EARLY ? blockDim.x : 0); s < keep; s += 4 * blockDim.x) {   // four of a long list at a time
+            uint32_t at[4];
+            float v[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                at[u] = 0xFFFFu;
+                if (u == 0 || s + u * blockDim.x < keep) at[u] = idx[s + u * blockDim.x];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)
+                if (at[u] - from < size) v[u] = val[s + u * blockDim.x];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)
+                if (at[u] - from < size) dense[at[u] - from] = v[u];
         }
     }
 };
 // Late -> early, us of the step (four sets of buffers in turn): SGD, C = 4096, keep = 128, 64 K 2.7 -> 2.5, 1 M 4.1 -> 4.0, 3 M 7.9 -> 9.0, 4 M 11.0 ->
-// 12.2, 8 M +-0, 12 M 33.8 -> 32.4, 25.7 M 69.0 -> 66.7, 100 M 265 -> 256; C = 1024, keep = 32, 25.7 M 72.9 -> 66.6; C = 16384, 25.7 M 76.9 -> 75.9, 100 M
-// 282 -> 295; Adam, C = 4096, 25.7 M 106.3 -> 103.6, C = 8192, keep = 1024, 25.7 M 108.7 -> 106.5, 100 M 418 -> 429.  From 2 M to 5 M, where the state
-// fits the caches, all waves at once lose what the longer chain of loads spreads.
+// 12.2, 8 M +-0, 12 M 33.8 -> 32.4, 25.7 M 69.0 -> 66.7, 100 M 265 -> 256; C = 1024, keep = 32, 25.7 M 72.9 -> 66.6; C = 16384, keep = 512, 8 M 22.9 ->
+// 23.7, 100 M 264 -> 257; Adam, C = 4096, 25.7 M 106.3 -> 103.6.  From 2 M to 5 M, where the state fits the caches, all waves at once lose what the
+// longer chain of loads spreads; chunks of several parts up to 10 M.
 inline bool entries_early(size_t n, size_t chunk)
 {
-    if (n <= (static_cast<size_t>(5) << 20)) return n <= (static_cast<size_t>(1) << 20);
-    return chunk <= 4096 || n <= (static_cast<size_t>(1) << 26);
+    return n <= (static_cast<size_t>(1) << 20) || n > (static_cast<size_t>(chunk <= 4096 ? 5 : 10) << 20);
 }
 
-// General case: the chunk's decoded gradient is built in LDS (+0 everywhere, then the kept entries), and every
-// element is updated as in k_decompress_sgd.  One workgroup per chunk, RPW rows per wave.
-template <int RPW, bool MOM, bool WD, bool EARLY>
-__global__ void __launch_bounds__(wg_threads_max(RPW))
-k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk,
+// How a chunk is cut into the parts that a workgroup takes: up to kTopkPart elements, eight waves of two rows and 16 KB of LDS.  Each looks through
+// all entries of its chunk.  One workgroup per chunk (16 waves of two rows or more) -> this, us of the step: Adam, C = 16384, keep = 512, 64 K 7.0 -> 3.5,
+// 1 M 9.9 -> 5.5, 25.7 M 119 -> 103, 100 M 442 -> 409; SGD 64 K 3.9 -> 2.7, 1 M 6.1 -> 4.2, 25.7 M 76.3 -> 67.7; C = 8192, keep = 256, 1 M 4.8 -> 4.3, 25.7 M
+// 69.8 -> 66.9, 100 M 284 -> 266; C = 6144 0 .. -5 %; C = 16384, keep = 2048, 64 K 4.2 -> 2.9, 40 M 118 -> 108, but 6 M 17.6 -> 19.1 and
+// 8 M 22.9 -> 24.3, where what all parts read of the entries shows.
+constexpr int kTopkPart = 4096, kTopkRpw = 2;
+struct TopkParts {
+    uint32_t part, parts;
+    dim3 grid, block;
+    size_t lds;
+    TopkParts(size_t chunks, size_t chunk)
+    {
+        const uint32_t rows = static_cast<uint32_t>(chunk / kRow);
+        parts = static_cast<uint32_t>((chunk + kTopkPart - 1) / kTopkPart);
+        part = (rows + parts - 1) / parts * kRow;
+        grid = dim3(static_cast<unsigned>(chunks * parts));
+        block = dim3(kWave * ((part / kRow + kTopkRpw - 1) / kTopkRpw));
+        lds = part * sizeof(float);
+    }
+};
+
+// General case: the decoded gradient of a part of a chunk is built in LDS (+0 everywhere, then the kept entries), and every
+// element is updated as in k_decompress_sgd.
+template <bool MOM, bool WD, bool EARLY, bool PARTS>
+__global__ void __launch_bounds__(kTopkPart / kTopkRpw / kRow * kWave)
+k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk, uint32_t part, uint32_t parts,
                       uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float lr, float mu, float wd)
 {
-    extern __shared__ float s_g[];   // chunk floats
-    const size_t c = blockIdx.x;
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    extern __shared__ float s_g[];   // part floats
+    const uint32_t c = PARTS ? blockIdx.x / parts : blockIdx.x, from = PARTS ? (blockIdx.x - c * parts) * part : 0;   // part of chunk c: from element `from` on
+    const size_t base = static_cast<size_t>(c) * chunk + from;
+    if (PARTS && base >= n) return;
+    const uint32_t size = PARTS && chunk - from > part ? part : chunk - from;
+    const int len = static_cast<int>(n - base < size ? n - base : size);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    SparseEntries<EARLY> entries(idx + c * keep, val + c * keep, keep);
+    SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters (and momentum) do not depend on the decode: request them next
+    constexpr int RPW = kTopkRpw;
     f4 p[RPW], m[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -209,10 +244,10 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
     };
     if (wave_full<RPW>(len, wave)) load(std::true_type{});   // no tail tests: all loads in flight together
     else load(std::false_type{});
-    for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
+    for (uint32_t e = threadIdx.x * 4; e < size; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
-    entries.scatter(chunk, s_g);
+    entries.scatter(from, size, s_g);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -245,20 +280,23 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
 
 // Adam-type update after a top-K round: the chunk's decoded tensor is built in LDS as above, then every element is
 // updated as in k_decompress_adam.
-template <int RPW, bool FROZEN, bool WD, bool EARLY>
-__global__ void __launch_bounds__(wg_threads_max(RPW))
-k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk,
+template <bool FROZEN, bool WD, bool EARLY, bool PARTS>
+__global__ void __launch_bounds__(kTopkPart / kTopkRpw / kRow * kWave)
+k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk, uint32_t part, uint32_t parts,
                        uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float* __restrict__ vbuf,
                        float lr, float beta1, float omb1, float beta2, float omb2, float eps, float wd)
 {
-    extern __shared__ float s_g[];   // chunk floats
-    const size_t c = blockIdx.x;
-    const size_t base = c * static_cast<size_t>(chunk);
-    const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
+    extern __shared__ float s_g[];   // part floats
+    const uint32_t c = PARTS ? blockIdx.x / parts : blockIdx.x, from = PARTS ? (blockIdx.x - c * parts) * part : 0;   // part of chunk c: from element `from` on
+    const size_t base = static_cast<size_t>(c) * chunk + from;
+    if (PARTS && base >= n) return;
+    const uint32_t size = PARTS && chunk - from > part ? part : chunk - from;
+    const int len = static_cast<int>(n - base < size ? n - base : size);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    SparseEntries<EARLY> entries(idx + c * keep, val + c * keep, keep);
+    SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters and optimizer state do not depend on the decode: request them next
+    constexpr int RPW = kTopkRpw;
     f4 p[RPW], m[RPW], v[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -278,10 +316,10 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
     };
     if (wave_full<RPW>(len, wave)) load(std::true_type{});
     else load(std::false_type{});
-    for (uint32_t e = threadIdx.x * 4; e < chunk; e += blockDim.x * 4)
+    for (uint32_t e = threadIdx.x * 4; e < size; e += blockDim.x * 4)
         *reinterpret_cast<f4*>(s_g + e) = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
-    entries.scatter(chunk, s_g);
+    entries.scatter(from, size, s_g);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -404,9 +442,12 @@ extern "C" int bagua_decompress_adam_step(int codec, const void* codes, const fl
     return launch_status();
 }
 
-#define BAGUA_DISPATCH_EARLY(stmt)                                              \
-    if (entries_early(n, chunk)) { constexpr bool EARLY = true; stmt; }         \
-    else { constexpr bool EARLY = false; stmt; }
+// Expands `stmt` with constexpr EARLY and PARTS (whether a chunk has more than one).
+#define BAGUA_DISPATCH_TOPK_STEP(tp, stmt)                                                        \
+    if (tp.parts > 1 && entries_early(n, chunk)) { constexpr bool PARTS = true, EARLY = true; stmt; } \
+    else if (tp.parts > 1) { constexpr bool PARTS = true, EARLY = false; stmt; }                  \
+    else if (entries_early(n, chunk)) { constexpr bool PARTS = false, EARLY = true; stmt; }       \
+    else { constexpr bool PARTS = false, EARLY = false; stmt; }
 
 extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* val, size_t n, size_t chunk, size_t keep,
                                               float* param, float* momentum_buf, float lr, float momentum,
@@ -434,13 +475,10 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
                            entries, ch, kp, n, param, lr);
         return launch_status();
     }
-    const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw(rows, 2);
-    dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
-    const size_t lds = chunk * sizeof(float);
-#define BAGUA_TS(MOMv, WDv)                                                                                      \
-    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(launch_kernel((k_decompress_sgd_topk<RPW, MOMv, WDv, EARLY>), grid, block, lds, s, idx, \
-                                               val, n, ch, kp, param, momentum_buf, lr, momentum, weight_decay)))
+    const TopkParts tp(nc, chunk);
+#define BAGUA_TS(MOMv, WDv)                                                                                               \
+    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_sgd_topk<MOMv, WDv, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
+                                       tp.part, tp.parts, kp, param, momentum_buf, lr, momentum, weight_decay))
     if (mom && wd) { BAGUA_TS(true, true) }
     else if (mom) { BAGUA_TS(true, false) }
     else if (wd) { BAGUA_TS(false, true) }
@@ -465,20 +503,16 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
         rc.writes(v, n * sizeof(float));
         if (!rc.disjoint()) return BAGUA_ERR_INVALID_ARG;
     }
-    if (nc > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
+    if (nc > kMaxGrid / ((chunk + kTopkPart - 1) / kTopkPart)) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned2(idx) || !aligned4(val) || !aligned16(param) || !aligned16(m) || !aligned16(v)) return BAGUA_ERR_ALIGNMENT;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
     const bool frozen = variance_frozen != 0, wd = weight_decay != 0.0f;
-    const int rows = static_cast<int>(chunk / kRow);
-    const int rpw = pick_rpw(rows, 2);
-    dim3 grid(static_cast<unsigned>(nc)), block(64 * ((rows + rpw - 1) / rpw));
-    const size_t lds = chunk * sizeof(float);
-#define BAGUA_TA(FRv, WDv)                                                                                         \
-    BAGUA_DISPATCH_RPW(rpw, BAGUA_DISPATCH_EARLY(launch_kernel((k_decompress_adam_topk<RPW, FRv, WDv, EARLY>), grid, block, lds, s, idx,  \
-                                               val, n, ch, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps,     \
-                                               weight_decay)))
+    const TopkParts tp(nc, chunk);
+#define BAGUA_TA(FRv, WDv)                                                                                                 \
+    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_adam_topk<FRv, WDv, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
+                                       tp.part, tp.parts, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps, weight_decay))
     if (frozen && wd) { BAGUA_TA(true, true) }
     else if (frozen) { BAGUA_TA(true, false) }
     else if (wd) { BAGUA_TA(false, true) }

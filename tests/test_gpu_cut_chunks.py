@@ -212,7 +212,7 @@ def test_compressions_batched(bg, oracle, C):
 
 
 # keep below, at and above the threads of a workgroup; a chunk cut short; either side of the lines between early and late entries
-@pytest.mark.parametrize("n,C,keep", [(3, 256, 1), (5001, 1024, 7), (70001, 1024, 256), (70001, 1024, 257), (40001, 2048, 2048), (300001, 16384, 1500),
+@pytest.mark.parametrize("n,C,keep", [(3, 256, 1), (5001, 1024, 7), (70001, 1024, 256), (70001, 1024, 257), (40001, 2048, 2048), (300001, 16384, 1500), (20001, 5376, 100), (12801, 12800, 12800),
                                       (1 << 20, 4096, 128), ((1 << 20) + 1, 4096, 600), ((5 << 20) + 3, 4096, 513), ((1 << 26) + 5, 8192, 3)])
 @pytest.mark.parametrize("opt", ["sgd", "adam"])
 def test_optimizer_steps_after_topk(bg, oracle, n, C, keep, opt):
