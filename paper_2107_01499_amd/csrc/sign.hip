@@ -5,6 +5,8 @@
 // Lane l of a wave owns elements 4l..4l+3 of every 256-element row, so the group of four that the
 // fixed |v| summation order is defined on is exactly one lane's 128-bit load, accumulator m mod 64
 // is lane m mod 64, and the final xor butterfly is a reduction over the wave.
+#include <type_traits>
+
 #include "batch.hpp"
 #include "launchers.hpp"
 #include "sign_device.hpp"
@@ -176,7 +178,7 @@ struct SignEntrySrc {   // pointers in a batch entry: [eps, bits_out, scale_out,
     __device__ __forceinline__ const float* meta(int j) const { return table_ptr<const float>(e[5 + k + j]); }
 };
 
-template <int RPW, bool EF, bool OUT, typename SRC>
+template <int RPW, bool EF, bool OUT, bool REST, typename SRC>
 __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t n,
                                                uint32_t chunk, uint32_t* __restrict__ bits_out,
                                                float* __restrict__ scale_out, float* __restrict__ out, size_t c,
@@ -239,32 +241,34 @@ __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_
                 }
             }
         };
+        // As many workers' words as there are left, up to NJ, are requested together.  Those of k mod NJ one after the other -> together, us of
+        // the step: k = 2, C = 2048, 16 M 25.3 -> 24.2, 134 M 173 -> 170; k = 4, 1 M 4.1 -> 4.0, 16 M 28.3 -> 24.9, 134 M 203 -> 183; k = 7, 65 K 4.1 -> 3.8,
+        // 8 M 18.4 -> 16.2, 33 M 61.7 -> 49.7, 134 M 255 -> 196; k = 5, C = 4096, 33 M 57.1 -> 49.2, C = 16384, 134 M 298 -> 257; k = 12, C = 8192, 134 M 298 ->
+        // 255; k = 3, C = 1024, 4 M 7.7 -> 8.3, 8 M 15.2 -> 14.8.  (Where k is a multiple of NJ the bodies of the rest would cost 1-2 %: REST.)
+        auto group = [&](auto count, int j, bool first) {
+            constexpr int N = decltype(count)::value;
+            uint32_t w[N][RPW];
+#pragma unroll
+            for (int u = 0; u < N; ++u) fetch(j + u, w[u]);
+#pragma unroll
+            for (int u = 0; u < N; ++u) decode(j + u, w[u], first && u == 0);
+        };
         int j = 0;
-        if (k >= NJ) {
-            uint32_t w[NJ][RPW];
-#pragma unroll
-            for (int u = 0; u < NJ; ++u) fetch(u, w[u]);
-            decode(0, w[0], true);
-#pragma unroll
-            for (int u = 1; u < NJ; ++u) decode(u, w[u], false);
-            j = NJ;
-        } else {
-            uint32_t w[RPW];
-            fetch(0, w);
-            decode(0, w, true);
-            j = 1;
+        if (!REST || k >= NJ) {
+            group(std::integral_constant<int, NJ>{}, 0, true);
+            for (j = NJ; j + NJ <= k; j += NJ) group(std::integral_constant<int, NJ>{}, j, false);
         }
-        for (; j + NJ <= k; j += NJ) {
-            uint32_t w[NJ][RPW];
-#pragma unroll
-            for (int u = 0; u < NJ; ++u) fetch(j + u, w[u]);
-#pragma unroll
-            for (int u = 0; u < NJ; ++u) decode(j + u, w[u], false);
-        }
-        for (; j < k; ++j) {
-            uint32_t w[RPW];
-            fetch(j, w);
-            decode(j, w, false);
+        if constexpr (REST) {
+            switch (k - j) {
+                case 1: group(std::integral_constant<int, 1>{}, j, j == 0); break;
+                case 2: group(std::integral_constant<int, 2>{}, j, j == 0); break;
+                case 3: group(std::integral_constant<int, 3>{}, j, j == 0); break;
+                case 4: group(std::integral_constant<int, 4>{}, j, j == 0); break;
+                case 5: group(std::integral_constant<int, 5>{}, j, j == 0); break;
+                case 6: group(std::integral_constant<int, 6>{}, j, j == 0); break;
+                case 7: group(std::integral_constant<int, 7>{}, j, j == 0); break;
+                default: break;
+            }
         }
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
@@ -345,18 +349,18 @@ __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_
                                     bits_out + (base >> 5), scale_out + c, OUT ? out + base : nullptr, s_q);
 }
 
-template <int RPW, bool EF, bool OUT>
+template <int RPW, bool EF, bool OUT, bool REST>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_sign(PtrTable bits_in, PtrTable scale_in, int k, float inv_k, float* __restrict__ eps, size_t n,
            uint32_t chunk, uint32_t* __restrict__ bits_out, float* __restrict__ scale_out,
            float* __restrict__ out)
 {
     extern __shared__ float s_q[];
-    drr_sign_chunk<RPW, EF, OUT>(SignTableSrc{bits_in, scale_in}, k, inv_k, eps, n, chunk, bits_out, scale_out, out,
+    drr_sign_chunk<RPW, EF, OUT, REST>(SignTableSrc{bits_in, scale_in}, k, inv_k, eps, n, chunk, bits_out, scale_out, out,
                                  blockIdx.x, s_q);
 }
 
-template <int RPW, bool EF, bool OUT, typename TABLE>
+template <int RPW, bool EF, bool OUT, bool REST, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_sign_batched(TABLE table, int k, float inv_k, uint32_t chunk)
 {
@@ -364,7 +368,7 @@ k_drr_sign_batched(TABLE table, int k, float inv_k, uint32_t chunk)
     const BatchView bv = table.view();
     const uint32_t b = batch_find(bv, blockIdx.x);
     const uint64_t* e = bv.entries + static_cast<size_t>(b) * bv.entry_words;
-    drr_sign_chunk<RPW, EF, OUT>(SignEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
+    drr_sign_chunk<RPW, EF, OUT, REST>(SignEntrySrc{e, k}, k, inv_k, table_ptr<float>(e[0]), e[4], chunk,
                                  table_ptr<uint32_t>(e[1]), table_ptr<float>(e[2]),
                                  table_ptr<float>(e[3]), blockIdx.x - bv.first_unit[b], s_q);
 }
@@ -424,6 +428,11 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     return launch_status();
 }
 
+// Expands `stmt` with a constexpr REST: whether k workers are not whole groups.
+#define BAGUA_DISPATCH_REST(k, stmt)                                              \
+    if ((k) % BAGUA_DRR_SIGN_NJ != 0) { constexpr bool REST = true; stmt; }       \
+    else { constexpr bool REST = false; stmt; }
+
 int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, int k, float* eps, size_t n,
                     size_t chunk, uint32_t* bits_out, float* scale_out, float* out, hipStream_t stream)
 {
@@ -436,8 +445,8 @@ int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, in
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
 #define BAGUA_DRR(EFv, OUTv)                                                                                      \
-    BAGUA_DISPATCH_RPW(g.rpw, launch_kernel((k_drr_sign<RPW, EFv, OUTv>), g.grid, g.block, g.lds, stream, bt, \
-                                                 st, k, inv_k, eps, n, ch, bits_out, scale_out, out))
+    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(k, launch_kernel((k_drr_sign<RPW, EFv, OUTv, REST>), g.grid, g.block, g.lds, stream, bt, \
+                                                 st, k, inv_k, eps, n, ch, bits_out, scale_out, out)))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
     else if (out) { BAGUA_DRR(false, true) }
@@ -456,8 +465,8 @@ int launch_drr_sign_batched(const std::vector<uint64_t>& table, void* workspace,
     return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
 #define BAGUA_DRR(EFv, OUTv)                                                                                       \
-    BAGUA_DISPATCH_RPW(g.rpw, launch_kernel((k_drr_sign_batched<RPW, EFv, OUTv, TABLE>), g.grid, g.block, g.lds, stream, \
-                                                 tab, k, inv_k, ch))
+    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(k, launch_kernel((k_drr_sign_batched<RPW, EFv, OUTv, REST, TABLE>), g.grid, g.block, g.lds, stream, \
+                                                 tab, k, inv_k, ch)))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }
         else if (with_out) { BAGUA_DRR(false, true) }

@@ -134,7 +134,7 @@ def test_rounds_in_low_precision(bg, oracle, cuts, k, peer):
     (5, 4096, 5 * 24 * 1024, None), (5, 4096, 5 * 24 * 1024 + 1, None), (8, 1536, 8 * 24 * 1024 - 3, None), (4, 4096, 65537, None),
     (32, 8192, 100001, None), (6, 16384, 6 * 80 * 1024 - 1, None), (6, 16384, 6 * 80 * 1024 + 1, None), (6, 6400, 120003, None),
     (2, 4096, (1 << 21) + 1, [1, 0]), (3, 4096, (1 << 21) + 1, [1, 0, 2]), (3, 2048, (1 << 23) + 5, [1, 0, 2]), (3, 16384, 1 << 21, [0, 2, 1]),
-    (3, 4096, 300001, [0, 1, 2])])
+    (3, 4096, 300001, [0, 1, 2]), (3, 16384, 1 << 18, None), (3, 16384, (1 << 18) + 1, None), (4, 16384, 21 << 20, None), (4, 12800, (20 << 20) + 1, None)])
 def test_rounds_in_low_precision_either_side_of_their_lines(bg, oracle, k, C, n, peer):
     ring_low_precision(bg, oracle, k, n, C, peer)
 
@@ -229,3 +229,46 @@ def test_optimizer_steps_after_topk(bg, oracle, n, C, keep, opt):
         gv.check(v, "v")
     gp.check(param, "param")
     gm.check(m, "m")
+
+
+def server_sign(bg, oracle, k, n, C, ef, out):
+    enc = [oracle.sign_compress_ef(vals(n, 3 * j + n), None, C) for j in range(k)]
+    eps, nw = vals(n, n, 1e-5), (n + 31) // 32
+    ci, mi = [torch.from_numpy(b.view(np.int32)).cuda() for b, _ in enc], [torch.from_numpy(s).cuda() for _, s in enc]
+    e, co = Guarded(eps), Guarded(np.zeros(nw, np.int32))
+    mo, o = Guarded(np.zeros(bg.num_chunks(n, C), np.float32)), Guarded(np.zeros(n, np.float32))
+    bg.bagua_decompress_reduce_recompress(1, ci, mi, e.t if ef else None, n, C, co.t, mo.t, o.t if out else None)
+    eps_o = eps.copy() if ef else None
+    cw, mw, ow = oracle.drr_sign([b for b, _ in enc], [s for _, s in enc], eps_o, n, C)
+    what = "k=%d n=%d C=%d" % (k, n, C)
+    co.check(cw, "bits " + what)
+    mo.check(mw, "scale " + what)
+    if ef:
+        e.check(eps_o, "eps " + what)
+    if out:
+        o.check(ow, "out " + what)
+
+
+@pytest.mark.parametrize("k", list(range(1, 18)) + [23, 31, 32])   # whole groups of eight workers and every rest
+def test_server_step_sign(bg, oracle, k):
+    for i, (n, C) in enumerate([(1, 256), (300, 256), (5000, 2048), (12289, 4096), (70001, 8192), (70001, 16384), (9001, 1536)]):
+        server_sign(bg, oracle, k, n, C, ef=i % 3 != 0, out=i % 2 == 0)
+
+
+@pytest.mark.parametrize("k", [3, 7, 8])
+def test_server_step_sign_batched(bg, oracle, k):
+    C, ns = 2048, [1, 2048, 2049, 70001, 300]
+    enc = [[oracle.sign_compress_ef(vals(n, 3 * j + n), None, C) for j in range(k)] for n in ns]
+    eps = [vals(n, n, 1e-5) for n in ns]
+    e, co = [Guarded(v) for v in eps], [Guarded(np.zeros((n + 31) // 32, np.int32)) for n in ns]
+    mo, o = [Guarded(np.zeros(bg.num_chunks(n, C), np.float32)) for n in ns], [Guarded(np.zeros(n, np.float32)) for n in ns]
+    ws = torch.empty(bg.bagua_batch_workspace_bytes(len(ns), k), dtype=torch.uint8, device="cuda")
+    bg.bagua_decompress_reduce_recompress_batched(
+        1, [[torch.from_numpy(b.view(np.int32)).cuda() for b, _ in w] for w in enc], [[torch.from_numpy(s).cuda() for _, s in w] for w in enc],
+        [g.t for g in e], ns, C, [g.t for g in co], [g.t for g in mo], [g.t for g in o], ws)
+    for b, n in enumerate(ns):
+        cw, mw, ow = oracle.drr_sign([w for w, _ in enc[b]], [s for _, s in enc[b]], eps[b], n, C)
+        co[b].check(cw, "bits %d" % b)
+        mo[b].check(mw, "scale %d" % b)
+        e[b].check(eps[b], "eps %d" % b)
+        o[b].check(ow, "out %d" % b)
