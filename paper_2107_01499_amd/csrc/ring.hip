@@ -75,7 +75,7 @@ k_ring_avg_fp_any(PtrTable xin, MutPtrTable xout, int k, size_t n, float third)
 //   FULL: no tail tests, so that a wave's loads are in flight together; a chunk that is cut short takes the loop over
 //         the peers below instead.
 //   WIDE: chunks above 4096 elements, more than eight waves.
-template <int RPW>
+template <int RPW, bool FULL>
 __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const MutPtrTable& xout, const MutPtrTable& xhat,
                                                   const MutPtrTable& codes, const MutPtrTable& minmax, int k, size_t base, size_t c,
                                                   int len, float third, int keep, float (*s_red)[2 * kMaxWaves]);
@@ -94,7 +94,7 @@ k_ring_avg_lp(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable code
 
     if constexpr (FULL) {
         if (!chunk_full<RPW>(len, nwaves)) {
-            ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, K, base, c, len, third, KEEP, s_red);
+            ring_lp_chunk_any<RPW, false>(xin, xout, xhat, codes, minmax, K, base, c, len, third, KEEP, s_red);
             return;
         }
     }
@@ -242,7 +242,7 @@ __device__ __forceinline__ void ring_mix(const f4 (&left)[RPW], const f4 (&mid)[
 // 32 rows it is 1-10 % slower than the unrolled kernel (8 peers x 109 M: 3.03 against 2.84 ms), except for chunks whose
 // last wave has one row only (see launch_lp_k).  Requesting the next peer's rows ahead was slower in every launch of
 // more than one workgroup per CU.
-template <int RPW>
+template <int RPW, bool FULL>
 __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const MutPtrTable& xout, const MutPtrTable& xhat,
                                                   const MutPtrTable& codes, const MutPtrTable& minmax, int k, size_t base, size_t c,
                                                   int len, float third, int keep, float (*s_red)[2 * kMaxWaves])
@@ -255,8 +255,9 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
     f4 left[RPW], mid[RPW], own[RPW];   // public copies of peers i - 2 and i - 1, and what the latter adds to its mix
     f4 x[RPW], h[RPW];
     for (int i = 0; i < k; ++i) {
-        lp_load<RPW>(x_of(i), hat_of(i), len, wave, lane, x, h);
-        lp_publish<RPW>(x, h, hat_of(i), static_cast<uint8_t*>(codes.p[i]) + base, static_cast<float*>(minmax.p[i]) + 2 * c, len,
+        if constexpr (FULL) lp_load_at<RPW, true, false>(x_of(i), hat_of(i), len, wave, lane, x, h);
+        else lp_load<RPW>(x_of(i), hat_of(i), len, wave, lane, x, h);
+        lp_publish<RPW, FULL>(x, h, hat_of(i), static_cast<uint8_t*>(codes.p[i]) + base, static_cast<float*>(minmax.p[i]) + 2 * c, len,
                         wave, lane, nwaves, s_red[i & 1], keep);
         if (i >= 2) ring_mix<RPW>(left, mid, h, own, third, out_of(i - 1), len, wave, lane);
         copy_rows<RPW>(left, mid);
@@ -277,7 +278,15 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
     ring_mix<RPW>(mid, h, right, x, third, out_of(0), len, wave, lane);
 }
 
-template <int RPW>
+// FOLD: complete chunks without tail tests on their loads.  In the shortest and the longest launches of chunks of more than 32 rows; with -> without,
+// us: C = 16384, K = 3, 64 K 15.4 -> 12.9, 1 M +-0, 33 M 365 -> 353, 134 M 1476 -> 1412; K = 2, 64 K 11.6 -> 10.0, 1 M 19.8 -> 20.6, 8 M 67.8 -> 70.3, 33 M
+// 248 -> 250, 134 M 1040 -> 1014; C = 12288, K = 5, 1 M 32.2 -> 34.1, 16 M 296 -> 288, 134 M 2321 -> 2249.
+static bool ring_lp_any_fold(int k, size_t n)
+{
+    return n <= (static_cast<size_t>(1) << 18) || k * n >= (static_cast<size_t>(5) << 24);
+}
+
+template <int RPW, bool FOLD>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable codes, MutPtrTable minmax, int k, size_t n,
                   uint32_t chunk, float third, int keep, ChunkOrder order)
@@ -286,7 +295,8 @@ k_ring_avg_lp_any(PtrTable xin, MutPtrTable xout, MutPtrTable xhat, MutPtrTable 
     const size_t c = order(blockIdx.x);
     const size_t base = c * static_cast<size_t>(chunk);
     const int len = static_cast<int>((n - base < chunk) ? (n - base) : chunk);
-    ring_lp_chunk_any<RPW>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
+    if (FOLD && chunk_full<RPW>(len, blockDim.x >> 6)) ring_lp_chunk_any<RPW, true>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
+    else ring_lp_chunk_any<RPW, false>(xin, xout, xhat, codes, minmax, k, base, c, len, third, keep, s_red);
 }
 
 // Load and publish of a chunk in a launch short enough that its latency counts: neither a complete chunk nor one that is cut short has
@@ -462,7 +472,7 @@ static void launch_lp_k(const PtrTable& in, const MutPtrTable& out, const MutPtr
     }
     if (!wide) BAGUA_RING(false, false)
     if constexpr (K < 8) BAGUA_RING(false, true)
-    launch_kernel((k_ring_avg_lp_any<BAGUA_RPW_LP>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep, order);
+    launch_kernel((k_ring_avg_lp_any<BAGUA_RPW_LP, false>), grid, block, 0, s, in, out, hat, cd, mm, K, n, chunk, third, keep, order);
 #undef BAGUA_RING_KEEP
 #undef BAGUA_RING
 }
@@ -502,8 +512,13 @@ static int launch_ring_lp(const float* const* x_in, float* const* x_out, float* 
 #undef BAGUA_LP_CASE
         }
     }
-    BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_ring_avg_lp_any<RPW>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch,
-                                               third, keep_codes_of_round(k * n), chunk_order(nc, chunk)))
+#define BAGUA_RING_ANY(RPWv, FOLDv)                                                                                    \
+    launch_kernel((k_ring_avg_lp_any<RPWv, FOLDv>), grid, block, 0, stream, in, out, hat, cd, mm, k, n, ch, third, \
+                  keep_codes_of_round(k * n), chunk_order(nc, chunk))
+    if (rpw == 2) BAGUA_RING_ANY(2, false);
+    else if (ring_lp_any_fold(k, n)) BAGUA_RING_ANY(4, true);
+    else BAGUA_RING_ANY(4, false);
+#undef BAGUA_RING_ANY
     return launch_status();
 }
 
