@@ -332,8 +332,8 @@ inline bool drr_minmax_fold(size_t elements, size_t chunk, int k)
 // at a time -> this, us of one launch (from a graph, four sets of buffers in turn):
 //   k = 4, C = 4096: 64 K 4.2 -> 3.3, 1 M 6.3 -> 4.4, 2 M 7.8 -> 6.2, 4 M 11.2 -> 11.0;   k = 8, C = 2048: 64 K 5.0 -> 3.4, 1 M 9.1 -> 5.4, 2 M
 //   10.9 -> 7.8, 4 M 14.8 -> 14.6;   k = 16, C = 8192: 64 K 7.4 -> 6.3, 1 M 14.2 -> 8.5, 2 M 16.5 -> 10.5, 4 M 20.9 -> 20.7;
-//   outside: k = 16, C = 8192, 8 M 40.0 -> 41.4; k = 8, C = 3072, 6 M 20.9 -> 23.3; k = 8, C = 2048, 16 M 48.8 -> 49.8.  C = 16384 needs four rows:
-//   k = 8, 64 K 6.7 -> 6.9, 1 M 9.4 -> 8.0 (with half as many elements), 3 M 13.6 -> 14.2.
+//   outside: k = 16, C = 8192, 8 M 40.0 -> 41.4; k = 8, C = 3072, 6 M 20.9 -> 23.3; k = 8, C = 2048, 16 M 48.8 -> 49.8.  Chunks above 8192 take
+//   four rows either way: C = 16384, k = 8, 64 K 6.7 -> 6.9, 400 K 9.0 -> 7.9, 1 M 10.7 -> 8.8, 2 M 11.6 -> 9.6, 3 M 13.6 -> 14.2; k = 16, 2 M 17.7 -> 13.3.
 //   C = 1536, k = 5: 12 M 35.2 -> 31.8, 33 M 82.4 -> 73.7, 67 M 155.4 -> 150.9, 134 M 310.8 -> 324.7; C = 2560, k = 8: 12 M 43.0 -> 38.6, 67 M
 //   189.0 -> 182.1, 134 M 377.8 -> 396.5.
 inline bool drr_minmax_ahead(size_t n, size_t chunk, size_t least)
@@ -341,11 +341,15 @@ inline bool drr_minmax_ahead(size_t n, size_t chunk, size_t least)
     const size_t rows = chunk / kRow;
     if (least < 4) return false;   // row_at
     if (rows % 2 != 0) return rows <= 12 && n <= (static_cast<size_t>(1) << 20);
-    return chunk <= 8192 && n <= (static_cast<size_t>(1) << (rows % 4 == 2 ? 26 : 22));
+    if (chunk > 8192) return rows % 4 == 0 && n > (static_cast<size_t>(1) << 18) && n <= (static_cast<size_t>(1) << 21);
+    return n <= (static_cast<size_t>(1) << (rows % 4 == 2 ? 26 : 22));
 }
 // Rows per wave then: one in the shortest launches of chunks up to 3072 (two -> one: k = 16, C = 1536, 64 K 6.7 -> 5.6, 512 K 10.7 -> 9.9; k = 8,
 // C = 2048, 1 M 5.7 -> 5.4, 2 M 7.8 -> 7.9), which is also how an odd number of rows fills its waves.
-inline int drr_minmax_ahead_rpw(size_t n, size_t chunk) { return chunk <= 12 * kRow && n <= (static_cast<size_t>(1) << 20) ? 1 : 2; }
+inline int drr_minmax_ahead_rpw(size_t n, size_t chunk)
+{
+    return chunk > 8192 ? 4 : chunk <= 12 * kRow && n <= (static_cast<size_t>(1) << 20) ? 1 : 2;
+}
 
 // The body of its own for the chunk cut short, which a workgroup otherwise spends 8 us on at the very end: up to 2^26 elements.  k = 8, C = 2048, 5 M
 // 20.9 -> 16.8 us, 9 M 31.2 -> 29.6; k = 16, C = 8192, 5 M 30.7 -> 23.5, 9 M 46.1 -> 41.9, 20 M 86.4 -> 84.7; five buckets of 1.8 M, k = 8, C =
@@ -364,7 +368,8 @@ inline void drr_minmax_shape(size_t n, size_t least, size_t chunk, int k, const 
     const int rpw = ahead ? drr_minmax_ahead_rpw(n, chunk) : pick_rpw(rows, BAGUA_RPW_DRR);
     const dim3 block(kWave * ((rows + rpw - 1) / rpw));
     if (ahead && rpw == 1) launch(Const<1>{}, Const<kDrrAhead>{}, block);
-    else if (ahead) launch(Const<2>{}, Const<kDrrAhead>{}, block);
+    else if (ahead && rpw == 2) launch(Const<2>{}, Const<kDrrAhead>{}, block);
+    else if (ahead) launch(Const<4>{}, Const<kDrrAhead>{}, block);
     else if (rpw == 2) launch(Const<2>{}, Const<kDrrTests>{}, block);
     else if (fold && drr_minmax_cut(n)) launch(Const<4>{}, Const<kDrrFoldCut>{}, block);
     else if (fold) launch(Const<4>{}, Const<kDrrFold>{}, block);
