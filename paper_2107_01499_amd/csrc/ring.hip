@@ -320,12 +320,16 @@ __device__ __forceinline__ void lp_encode_folded(const float* x_c, float* hat_c,
 // memory in every launch, and each peer waits for its statistics).  One launch -> two, us (from graphs, four sets of buffers in turn):
 //   K = 8: C = 4096, 64 K elements per peer 13.3 -> 7.1, 256 K 19.1 -> 12.9, 1 M 27.3 -> 43.6; C = 8192, 64 K 17.1 -> 7.7, 256 K 27.7 -> 14.0, 1 M 35.5 -> 44.4;
 //   K = 16: C = 4096, 64 K 32.0 -> 9.0, 256 K 37.3 -> 22.8, 1 M 51.8 -> 79.9; C = 8192, 64 K 47.4 -> 9.0, 256 K 55.7 -> 23.8, 1 M 70.7 -> 80.9;
-//   C = 16384: K = 5, 64 K 25.6 -> 8.4, 1 M 38.8 -> 30.2, 2 M 46.5 -> 54.1; K = 16, 64 K 90.0 -> 12.1, 1 M 107.6 -> 82.7, 2 M 127.1 -> 168.9.
-// Fewer peers gain less than a second launch costs the host (K = 4, C = 2048, 64 K 7.3 -> 5.6, K = 3 6.2 -> 5.5).
+//   C = 16384: K = 2, 64 K 10.0 -> 6.9, 1 M 19.7 -> 13.7, 1.25 M 20.8 -> 15.8; K = 3, 64 K 13.0 -> 7.4, 1 M 26.5 -> 18.1; K = 5, 64 K 25.6 -> 8.4, 1 M 39.3 -> 29.7,
+//   2 M 46.5 -> 54.1; K = 8, 1 M 57.9 -> 42.4; K = 16, 64 K 90.0 -> 12.1, 1 M 107.6 -> 82.7, 2 M 127.1 -> 168.9;   C = 8192: K = 3, 64 K 8.0 -> 6.1, K = 4, 200 K
+//   12.4 -> 9.1, K = 8, 400 K 30.0 -> 20.0;   C = 12288, K = 4, 1 M 26.9 -> 25.4, 1.25 M 29.0 -> 29.3.
+// With chunks up to 4096 elements fewer peers gain less than a second launch costs the host (K = 4, C = 2048, 64 K 7.3 -> 5.6, K = 3 6.2 -> 5.5).
 static bool ring_lp_two_launches(int k, size_t n, size_t chunk)
 {
-    const size_t per = chunk <= 4096 ? 24 * 1024 : chunk <= 8192 ? 48 * 1024 : 80 * 1024;
-    return k >= 5 && n >= 4 && n <= static_cast<size_t>(k) * per;   // n >= 4: row_at
+    if (n < 4) return false;   // row_at
+    if (chunk > 8192) return k >= 2 && n <= 5 * (static_cast<size_t>(1) << 18);
+    if (chunk > 4096) return k >= 3 && n <= std::min<size_t>(static_cast<size_t>(k) << 16, 3 << 18);
+    return k >= 5 && n <= static_cast<size_t>(k) * 24 * 1024;
 }
 
 template <int RPW>
@@ -708,6 +712,10 @@ struct PeerLpJobs {
 // 8.1, 2 M +-0, 8 M 47.9 -> 48.5; C = 16384, 2 M 17.0 -> 15.3, 4 M 27.7 -> 29.4.
 inline bool gossip_short(size_t n, int singles) { return n >= 4 && n <= (static_cast<size_t>(1) << (singles ? 23 : 21)); }
 
+// Chunks above 8192 elements in two launches, as in the ring, where all workers together have little to do.  A pair at a time -> this, us: one pair,
+// C = 16384, 64 K 9.5 -> 6.7, 200 K 9.2 -> 7.6, 700 K +-0; three pairs and a single 64 K 10.5 -> 7.6, 200 K 12.5 -> 12.8; eight pairs 64 K 11.8 -> 11.4.
+inline bool gossip_wide_short(size_t chunk, int k, size_t n) { return chunk > 8192 && n >= 4 && k * n <= (static_cast<size_t>(1) << 19); }
+
 template <int RPW, bool PAIR, bool SHORT>
 __global__ void __launch_bounds__(wg_threads_max(RPW), RPW <= 2 ? 8 : 1)
 k_peer_avg_lp(PeerLpJobs jobs, int npairs, size_t n, uint32_t chunk, int keep, ChunkOrder order)
@@ -838,6 +846,24 @@ extern "C" int bagua_decentralized_avg_peers_lp(const float* const* x_in, float*
                 jobs.minmax[sd][j] = minmax[side[sd]];
             }
         }
+    }
+    if (nmix == 0 && gossip_wide_short(chunk, k, n)) {
+        PtrTable in{};
+        MutPtrTable hat{}, cd{}, mm{};
+        PeerMixJobs all{};
+        for (int i = 0; i < k; ++i) {
+            in.p[i] = x_in[i];
+            hat.p[i] = xhat[i];
+            cd.p[i] = codes[i];
+            mm.p[i] = minmax[i];
+            all.x[i] = x_in[i];
+            all.hat_own[i] = xhat[i];
+            all.hat_peer[i] = xhat[peer[i]];
+            all.out[i] = x_out[i];
+        }
+        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_ring_publish<RPW>), dim3(grid.x, k), block, 0, s, in, hat, cd, mm, n, ch))
+        launch_kernel(k_peer_mix_lp, dim3(static_cast<unsigned>((nrows + kRowWaves - 1) / kRowWaves), k), dim3(kWave * kRowWaves), 0, s, all, n);
+        return launch_status();
     }
     if (npairs && gossip_short(n, nsingles)) {
         for (int j = 0; j < nsingles; ++j) {

@@ -73,6 +73,7 @@ def test_server_step_minmax(bg, oracle, cuts, k):
     (3, 2048, 1 << 20), (3, 2048, (1 << 20) + 1), (2, 768, (1 << 20) + 1),                         # one row per wave, two, an odd number
     (2, 4096, (1 << 22) - 77), (2, 4096, 1 << 22), (2, 4096, (1 << 22) + 77),                      # ahead, behind
     (5, 1536, (1 << 22) + 1541), (2, 8192, (1 << 22) + 5), (2, 16384, (1 << 20) + 3), (5, 2048, (1 << 25) + 2047),
+    (3, 16384, 1 << 18), (3, 16384, (1 << 18) + 5), (2, 12288, (1 << 21) - 1), (2, 16384, (1 << 21) + 1), (2, 9216, 500001),
     (2, 16384, (1 << 26) + 1), (2, 1536, (1 << 26) + 2),                                           # the last with a body for the cut
 ])
 def test_server_step_minmax_either_side_of_its_lines(bg, oracle, k, C, n):
@@ -134,7 +135,8 @@ def test_rounds_in_low_precision(bg, oracle, cuts, k, peer):
     (5, 4096, 5 * 24 * 1024, None), (5, 4096, 5 * 24 * 1024 + 1, None), (8, 1536, 8 * 24 * 1024 - 3, None), (4, 4096, 65537, None),
     (32, 8192, 100001, None), (6, 16384, 6 * 80 * 1024 - 1, None), (6, 16384, 6 * 80 * 1024 + 1, None), (6, 6400, 120003, None),
     (2, 4096, (1 << 21) + 1, [1, 0]), (3, 4096, (1 << 21) + 1, [1, 0, 2]), (3, 2048, (1 << 23) + 5, [1, 0, 2]), (3, 16384, 1 << 21, [0, 2, 1]),
-    (3, 4096, 300001, [0, 1, 2]), (3, 16384, 1 << 18, None), (3, 16384, (1 << 18) + 1, None), (4, 16384, 21 << 20, None), (4, 12800, (20 << 20) + 1, None)])
+    (3, 4096, 300001, [0, 1, 2]), (2, 16384, 5 << 18, None), (2, 16384, (5 << 18) + 1, None), (3, 8192, (3 << 16) + 1, None), (16, 8192, 3 << 18, None),
+    (2, 16384, 1 << 18, [1, 0]), (2, 16384, (1 << 18) + 1, [1, 0]), (7, 12544, 70001, [1, 0, 2, 4, 3, 6, 5]), (3, 16384, 3, [1, 0, 2]), (3, 16384, 1 << 18, None), (3, 16384, (1 << 18) + 1, None), (4, 16384, 21 << 20, None), (4, 12800, (20 << 20) + 1, None)])
 def test_rounds_in_low_precision_either_side_of_their_lines(bg, oracle, k, C, n, peer):
     ring_low_precision(bg, oracle, k, n, C, peer)
 
