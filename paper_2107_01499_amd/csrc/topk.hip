@@ -146,7 +146,8 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_
 // Encode the chunk held in v (absent elements must be +0.0f).  idx_c/val_c point at the chunk's `keep` output slots,
 // residual/out at the chunk's first element (nullptr = not wanted).
 // smem: kTopkLdsWords words of LDS, the first kHistWords of them cleared (no barrier needed in between).
-template <int RPW>
+// JOINT: how the kept entries are stored, see the end.
+template <int RPW, bool JOINT = false>
 __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, uint32_t keep, int wave, int lane, int nwaves,
                                                   float* __restrict__ residual, uint16_t* __restrict__ idx_c,
                                                   float* __restrict__ val_c, float* __restrict__ out, uint32_t* smem)
@@ -296,17 +297,32 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
         }
         const float el[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
         float res[4], dec[4];
+        uint32_t left = 0;   // which of the lane's four are kept and still to be stored
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const bool sel = dist[i][e] < bound;
             const float stored = el[e] + 0.0f;  // -0 is stored as +0
-            if (sel) {
+            if (JOINT) {
+                left |= sel ? 1u << e : 0u;
+            } else if (sel) {
                 idx_c[mine] = static_cast<uint16_t>(off + lane * 4 + e);
                 val_c[mine] = stored;
                 ++mine;
             }
             res[e] = sel ? 0.0f : el[e];
             dec[e] = sel ? stored : 0.0f;
+        }
+        // A store takes the memory pipeline as long for one lane as for 64, and few lanes keep more than one of their four: all store their
+        // first one together, then those that have another.
+        if (JOINT) {
+            while (__ballot(left != 0)) {
+                if (left != 0) {
+                    idx_c[mine] = static_cast<uint16_t>(off + lane * 4 + __builtin_ctz(left));
+                    val_c[mine] = (left & 1u) ? dec[0] : (left & 2u) ? dec[1] : (left & 4u) ? dec[2] : dec[3];
+                    ++mine;
+                    left &= left - 1;
+                }
+            }
         }
         if (residual) store_row(residual + off, lane, remain, f4{res[0], res[1], res[2], res[3]});
         if (out) store_row(out + off, lane, remain, f4{dec[0], dec[1], dec[2], dec[3]});
@@ -318,7 +334,12 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
 }
 
 // ------------------------------------------------------------------------------------------ worker side
-template <int RPW, bool EF>
+// Long launches of chunks up to 1536 elements, where the many small workgroups wait for their stores.  One element of the lane at a time -> joint, us:
+// C = 1024, keep = 32, 2 M 6.8 -> 7.1, 8 M +-0, 25.7 M 52.8 -> 51.1, 60 M 116.4 -> 113.7, 134 M 259.0 -> 252.1, keep = 128, 134 M 286.3 -> 278.4, keep = 10, 134 M
+// 255.4 -> 251.2; C = 1536, keep = 192, 60 M 118.5 -> 114.3; C = 768, 134 M 250.4 -> 244.1.  Longer chunks +0.2 us in short launches, -0.5 .. +0.4 % in long ones.
+static bool topk_stores_joint(size_t n, size_t chunk) { return chunk <= 1536 && n > (static_cast<size_t>(1) << 23); }
+
+template <int RPW, bool EF, bool JOINT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_t n, uint32_t chunk, uint32_t keep,
                 uint16_t* __restrict__ idx, float* __restrict__ val, ChunkOrder order)
@@ -359,7 +380,7 @@ k_compress_topk(const float* __restrict__ x, float* __restrict__ residual, size_
             v[i].w = v[i].w + d[i].w;
         }
     }
-    topk_encode_chunk<RPW>(v, len, keep, wave, lane, nwaves, EF ? residual + base : nullptr, idx + c * keep,
+    topk_encode_chunk<RPW, JOINT>(v, len, keep, wave, lane, nwaves, EF ? residual + base : nullptr, idx + c * keep,
                            val + c * keep, nullptr, smem);
 }
 
@@ -515,13 +536,17 @@ extern "C" int bagua_compress_topk_ef(const float* x, float* residual, size_t n,
     dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (residual) {
-        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_compress_topk<RPW, true>), grid, block, 0, s, x, residual, n, ch, kp,
-                                                   idx, val, chunk_order(grid.x, chunk)))
+#define BAGUA_TOPK(RPWv, EFv, JOINTv)                                                                                \
+    launch_kernel((k_compress_topk<RPWv, EFv, JOINTv>), grid, block, 0, s, x, residual, n, ch, kp, idx, val, chunk_order(grid.x, chunk))
+    if (topk_stores_joint(n, chunk)) {
+        if (residual) BAGUA_TOPK(2, true, true);
+        else BAGUA_TOPK(2, false, true);
+    } else if (residual) {
+        BAGUA_DISPATCH_RPW(rpw, BAGUA_TOPK(RPW, true, false))
     } else {
-        BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_compress_topk<RPW, false>), grid, block, 0, s, x, residual, n, ch, kp,
-                                                   idx, val, chunk_order(grid.x, chunk)))
+        BAGUA_DISPATCH_RPW(rpw, BAGUA_TOPK(RPW, false, false))
     }
+#undef BAGUA_TOPK
     return launch_status();
 }
 
