@@ -432,10 +432,12 @@ __device__ __forceinline__ void store_codes_row(uint8_t* __restrict__ row, int l
 }
 
 // A row of a chunk that may be cut short, read without a test: every lane makes one access and the lane on the edge the last one
-// that lies inside the chunk, so that what it gets begins `skip` elements before its own; settle() shifts it.  What a lane
-// beyond the end holds means nothing.  With the tests of load_row a wave waits for one row, and in load_codes_row for one byte, before it
-// asks for the next, and the one chunk that is cut short decides how long a short launch takes.  The access and settle() are two steps
-// because the compiler moves a load whose result is used under a condition behind the condition.  The buffer must hold four elements.
+// that ends inside the chunk, so that what it gets begins `skip` elements before its own; settle() shifts it.  What a lane
+// beyond the end holds means nothing (in a chunk of fewer than four elements all of them reach back into the chunk before it, and
+// settle() drops what they find there).  With the tests of load_row a wave waits for one row, and in load_codes_row for one byte,
+// before it asks for the next, and the one chunk that is cut short decides how long a short launch takes.  The access and settle()
+// are two steps because the compiler moves a load whose result is used under a condition behind the condition.  The buffer must hold
+// four elements.
 struct RowAt {
     int at, skip;   // in elements; at: from the beginning of the chunk
 };
