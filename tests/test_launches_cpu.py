@@ -1,0 +1,24 @@
+"""The launches that entry points make, recorded on the host by a stand-in for the runtime (no GPU code, no GPU needed), with
+the settings of the build that csrc/common.hpp admits."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def check(name, tmp_path, flags):
+    obj, exe = str(tmp_path / "check.o"), str(tmp_path / "check")
+    subprocess.run([HIPCC, "--cuda-host-only", "-x", "hip", "-O1", "-fPIC", "-I" + os.path.join(ROOT, "paper_2107_01499_amd", "csrc"),
+                    "-I" + os.path.join(ROOT, "include"), "-c", os.path.join(ROOT, "tests", "host", name + "_launches_check.hip"), "-o", obj] + flags, check=True)
+    subprocess.run([os.environ.get("CXX", "g++"), obj, "-o", exe], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    assert res.stdout.startswith("OK ")
+
+
+@pytest.mark.parametrize("rows", [2, 4])
+def test_topk_compression(tmp_path, rows):
+    check("topk", tmp_path, ["-DBAGUA_RPW_TOPK=%d" % rows])
