@@ -193,26 +193,36 @@ inline bool entries_early(size_t n, size_t chunk)
 // 1 M 9.9 -> 5.5, 25.7 M 119 -> 103, 100 M 442 -> 409; SGD 64 K 3.9 -> 2.7, 1 M 6.1 -> 4.2, 25.7 M 76.3 -> 67.7; C = 8192, keep = 256, 1 M 4.8 -> 4.3, 25.7 M
 // 69.8 -> 66.9, 100 M 284 -> 266; C = 6144 0 .. -5 %; C = 16384, keep = 2048, 64 K 4.2 -> 2.9, 40 M 118 -> 108, but 6 M 17.6 -> 19.1 and
 // 8 M 22.9 -> 24.3, where what all parts read of the entries shows.
-constexpr int kTopkPart = 4096, kTopkRpw = 2;
+constexpr int kTopkPart = 4096;
+// A launch of more parts than a grid holds takes whole chunks: up to MOST elements, 16 waves of two or of four rows.
+constexpr int kTopkWhole = 8192, kTopkWholeLong = 16384;
+constexpr int topk_step_rpw(int most) { return most <= kTopkWhole ? 2 : 4; }
+constexpr int topk_step_threads(int most) { return most / topk_step_rpw(most) / kRow * kWave; }
 struct TopkParts {
-    uint32_t part, parts;
+    uint32_t most, part, parts;   // most: elements that the kernel's workgroup can take
     dim3 grid, block;
     size_t lds;
     TopkParts(size_t chunks, size_t chunk)
     {
         const uint32_t rows = static_cast<uint32_t>(chunk / kRow);
         parts = static_cast<uint32_t>((chunk + kTopkPart - 1) / kTopkPart);
+        most = kTopkPart;
+        if (parts > 1 && chunks > kMaxGrid / parts) {
+            parts = 1;
+            most = chunk <= kTopkWhole ? kTopkWhole : kTopkWholeLong;
+        }
         part = (rows + parts - 1) / parts * kRow;
+        const uint32_t rpw = static_cast<uint32_t>(topk_step_rpw(most));
         grid = dim3(static_cast<unsigned>(chunks * parts));
-        block = dim3(kWave * ((part / kRow + kTopkRpw - 1) / kTopkRpw));
+        block = dim3(kWave * ((part / kRow + rpw - 1) / rpw));
         lds = part * sizeof(float);
     }
 };
 
 // General case: the decoded gradient of a part of a chunk is built in LDS (+0 everywhere, then the kept entries), and every
 // element is updated as in k_decompress_sgd.
-template <bool MOM, bool WD, bool EARLY, bool PARTS>
-__global__ void __launch_bounds__(kTopkPart / kTopkRpw / kRow * kWave)
+template <bool MOM, bool WD, int MOST, bool EARLY, bool PARTS>
+__global__ void __launch_bounds__(topk_step_threads(MOST))
 k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk, uint32_t part, uint32_t parts,
                       uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float lr, float mu, float wd)
 {
@@ -226,7 +236,7 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
 
     SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters (and momentum) do not depend on the decode: request them next
-    constexpr int RPW = kTopkRpw;
+    constexpr int RPW = topk_step_rpw(MOST);
     f4 p[RPW], m[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -280,8 +290,8 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
 
 // Adam-type update after a top-K round: the chunk's decoded tensor is built in LDS as above, then every element is
 // updated as in k_decompress_adam.
-template <bool FROZEN, bool WD, bool EARLY, bool PARTS>
-__global__ void __launch_bounds__(kTopkPart / kTopkRpw / kRow * kWave)
+template <bool FROZEN, bool WD, int MOST, bool EARLY, bool PARTS>
+__global__ void __launch_bounds__(topk_step_threads(MOST))
 k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict__ val, size_t n, uint32_t chunk, uint32_t part, uint32_t parts,
                        uint32_t keep, float* __restrict__ param, float* __restrict__ mbuf, float* __restrict__ vbuf,
                        float lr, float beta1, float omb1, float beta2, float omb2, float eps, float wd)
@@ -296,7 +306,7 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
 
     SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters and optimizer state do not depend on the decode: request them next
-    constexpr int RPW = kTopkRpw;
+    constexpr int RPW = topk_step_rpw(MOST);
     f4 p[RPW], m[RPW], v[RPW];
     auto load = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
@@ -442,12 +452,17 @@ extern "C" int bagua_decompress_adam_step(int codec, const void* codes, const fl
     return launch_status();
 }
 
-// Expands `stmt` with constexpr EARLY and PARTS (whether a chunk has more than one).
-#define BAGUA_DISPATCH_TOPK_STEP(tp, stmt)                                                        \
-    if (tp.parts > 1 && entries_early(n, chunk)) { constexpr bool PARTS = true, EARLY = true; stmt; } \
-    else if (tp.parts > 1) { constexpr bool PARTS = true, EARLY = false; stmt; }                  \
-    else if (entries_early(n, chunk)) { constexpr bool PARTS = false, EARLY = true; stmt; }       \
-    else { constexpr bool PARTS = false, EARLY = false; stmt; }
+// Expands `stmt` with constexpr MOST, EARLY and PARTS (whether a chunk has more than one).
+#define BAGUA_DISPATCH_TOPK_STEP(tp, stmt)                                                                                 \
+    if (tp.most == kTopkWholeLong) { constexpr int MOST = kTopkWholeLong; constexpr bool PARTS = false, EARLY = false; stmt; } \
+    else if (tp.most == kTopkWhole) { constexpr int MOST = kTopkWhole; constexpr bool PARTS = false, EARLY = false; stmt; }    \
+    else {                                                                                                                 \
+        constexpr int MOST = kTopkPart;                                                                                    \
+        if (tp.parts > 1 && entries_early(n, chunk)) { constexpr bool PARTS = true, EARLY = true; stmt; }                  \
+        else if (tp.parts > 1) { constexpr bool PARTS = true, EARLY = false; stmt; }                                       \
+        else if (entries_early(n, chunk)) { constexpr bool PARTS = false, EARLY = true; stmt; }                            \
+        else { constexpr bool PARTS = false, EARLY = false; stmt; }                                                        \
+    }
 
 extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* val, size_t n, size_t chunk, size_t keep,
                                               float* param, float* momentum_buf, float lr, float momentum,
@@ -477,7 +492,7 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
     }
     const TopkParts tp(nc, chunk);
 #define BAGUA_TS(MOMv, WDv)                                                                                               \
-    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_sgd_topk<MOMv, WDv, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
+    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_sgd_topk<MOMv, WDv, MOST, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
                                        tp.part, tp.parts, kp, param, momentum_buf, lr, momentum, weight_decay))
     if (mom && wd) { BAGUA_TS(true, true) }
     else if (mom) { BAGUA_TS(true, false) }
@@ -503,7 +518,7 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
         rc.writes(v, n * sizeof(float));
         if (!rc.disjoint()) return BAGUA_ERR_INVALID_ARG;
     }
-    if (nc > kMaxGrid / ((chunk + kTopkPart - 1) / kTopkPart)) return BAGUA_ERR_UNSUPPORTED;
+    if (nc > kMaxGrid) return BAGUA_ERR_UNSUPPORTED;
     if (!aligned2(idx) || !aligned4(val) || !aligned16(param) || !aligned16(m) || !aligned16(v)) return BAGUA_ERR_ALIGNMENT;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
@@ -511,7 +526,7 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
     const bool frozen = variance_frozen != 0, wd = weight_decay != 0.0f;
     const TopkParts tp(nc, chunk);
 #define BAGUA_TA(FRv, WDv)                                                                                                 \
-    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_adam_topk<FRv, WDv, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
+    BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_adam_topk<FRv, WDv, MOST, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
                                        tp.part, tp.parts, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps, weight_decay))
     if (frozen && wd) { BAGUA_TA(true, true) }
     else if (frozen) { BAGUA_TA(true, false) }

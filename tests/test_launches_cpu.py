@@ -22,3 +22,7 @@ def check(name, tmp_path, flags):
 @pytest.mark.parametrize("rows", [2, 4])
 def test_topk_compression(tmp_path, rows):
     check("topk", tmp_path, ["-DBAGUA_RPW_TOPK=%d" % rows])
+
+
+def test_optimizer_steps_after_topk(tmp_path):
+    check("optim", tmp_path, [])
