@@ -253,23 +253,7 @@ __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_
 #pragma unroll
             for (int u = 0; u < N; ++u) decode(j + u, w[u], first && u == 0);
         };
-        int j = 0;
-        if (!REST || k >= NJ) {
-            group(std::integral_constant<int, NJ>{}, 0, true);
-            for (j = NJ; j + NJ <= k; j += NJ) group(std::integral_constant<int, NJ>{}, j, false);
-        }
-        if constexpr (REST) {
-            switch (k - j) {
-                case 1: group(std::integral_constant<int, 1>{}, j, j == 0); break;
-                case 2: group(std::integral_constant<int, 2>{}, j, j == 0); break;
-                case 3: group(std::integral_constant<int, 3>{}, j, j == 0); break;
-                case 4: group(std::integral_constant<int, 4>{}, j, j == 0); break;
-                case 5: group(std::integral_constant<int, 5>{}, j, j == 0); break;
-                case 6: group(std::integral_constant<int, 6>{}, j, j == 0); break;
-                case 7: group(std::integral_constant<int, 7>{}, j, j == 0); break;
-                default: break;
-            }
-        }
+        for_worker_groups<NJ, REST>(k, group);
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             v[i].x = v[i].x * inv_k;

@@ -1,11 +1,42 @@
 // Statistics + encoding of one chunk held in registers (1-bit sign codec): the fixed-order |v| sum, the nibble
 // gather into 32-bit sign words, and the error-state / decoded-value stores.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 
 #pragma clang fp contract(off)
 
 namespace bagua {
+
+// The workers of a server step in ascending order, in groups of NJ and then those that are left together: group(how many, the first one,
+// whether it is worker 0), the count as a type.  REST: k is not a multiple of NJ.  More than seven that are left (NJ above 8) come one by one.
+template <int NJ, bool REST, typename GROUP>
+__host__ __device__ __forceinline__ void for_worker_groups(int k, const GROUP& group)
+{
+    static_assert(NJ >= 1, "a group of workers");
+    int j = 0;
+    if (!REST || k >= NJ) {
+        group(std::integral_constant<int, NJ>{}, 0, true);
+        for (j = NJ; j + NJ <= k; j += NJ) group(std::integral_constant<int, NJ>{}, j, false);
+    }
+    if constexpr (REST) {
+        switch (k - j) {
+            case 1: group(std::integral_constant<int, 1>{}, j, j == 0); break;
+            case 2: group(std::integral_constant<int, 2>{}, j, j == 0); break;
+            case 3: group(std::integral_constant<int, 3>{}, j, j == 0); break;
+            case 4: group(std::integral_constant<int, 4>{}, j, j == 0); break;
+            case 5: group(std::integral_constant<int, 5>{}, j, j == 0); break;
+            case 6: group(std::integral_constant<int, 6>{}, j, j == 0); break;
+            case 7: group(std::integral_constant<int, 7>{}, j, j == 0); break;
+            default:
+                if constexpr (NJ > 8) {
+                    for (; j < k; ++j) group(std::integral_constant<int, 1>{}, j, j == 0);
+                }
+                break;
+        }
+    }
+}
 
 // Sum of |v| over the chunk in the fixed order (see bagua_sign_compress_ef in the header).
 // s_q: LDS, rows*64 floats, used only when the chunk is spread over several waves.
