@@ -144,7 +144,11 @@ k_sgd_topk_sparse(const uint16_t* __restrict__ idx, const float* __restrict__ va
 
 // The entries of a sparse chunk, into its dense copy in LDS.  EARLY: one per thread is requested before anything else, so that the scatter
 // waits for these two loads alone, and not for the index, then for the value, behind everything that the kernel reads.
-template <bool EARLY>
+// U: how many of a long list a thread requests at a time.  SINGLE: a list that gives no thread more than one is taken without looking for more,
+// us of the step, SGD with late entries: C = 256, keep = 32, 1.1 M 4.80 -> 4.57, 4 M 13.8 -> 13.3; C = 2048, keep = 256, 2 M 6.27 -> 6.08, 4.9 M 15.5 -> 15.1;
+// C = 1024, keep = 512 (no such list) 2 M 7.05 -> 6.87.  Adam loses by it from 3 M to 4 M (C = 4096, 4 M 16.4 -> 16.9, C = 7168, 3 M 13.3 -> 15.5), where a
+// longer chain of loads spreads the waves.
+template <bool EARLY, int U, bool SINGLE>
 struct SparseEntries {
     const uint16_t* idx;
     const float* val;
@@ -162,19 +166,26 @@ struct SparseEntries {
     __device__ __forceinline__ void scatter(uint32_t from, uint32_t size, float* dense)
     {
         if (EARLY && q - from < size) dense[q - from] = a;
-        for (uint32_t s = threadIdx.x + (EARLY ? blockDim.x : 0); s < keep; s += 4 * blockDim.x) {   // four of a long list at a time
-            uint32_t at[4];
-            float v[4];
+        if (!EARLY && (U == 1 || (SINGLE && keep <= blockDim.x))) {
+            for (uint32_t s = threadIdx.x; s < keep; s += blockDim.x) {
+                const uint32_t at = idx[s];
+                if (at - from < size) dense[at - from] = val[s];
+            }
+            return;
+        }
+        for (uint32_t s = threadIdx.x + (EARLY ? blockDim.x : 0); s < keep; s += U * blockDim.x) {
+            uint32_t at[U];
+            float v[U];
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) {
+            for (uint32_t u = 0; u < U; ++u) {
                 at[u] = 0xFFFFu;
                 if (u == 0 || s + u * blockDim.x < keep) at[u] = idx[s + u * blockDim.x];
             }
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u)
+            for (uint32_t u = 0; u < U; ++u)
                 if (at[u] - from < size) v[u] = val[s + u * blockDim.x];
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u)
+            for (uint32_t u = 0; u < U; ++u)
                 if (at[u] - from < size) dense[at[u] - from] = v[u];
         }
     }
@@ -191,23 +202,37 @@ inline bool entries_early(size_t n, size_t chunk)
 // How a chunk is cut into the parts that a workgroup takes: up to kTopkPart elements, eight waves of two rows and 16 KB of LDS.  Each looks through
 // all entries of its chunk.  One workgroup per chunk (16 waves of two rows or more) -> this, us of the step: Adam, C = 16384, keep = 512, 64 K 7.0 -> 3.5,
 // 1 M 9.9 -> 5.5, 25.7 M 119 -> 103, 100 M 442 -> 409; SGD 64 K 3.9 -> 2.7, 1 M 6.1 -> 4.2, 25.7 M 76.3 -> 67.7; C = 8192, keep = 256, 1 M 4.8 -> 4.3, 25.7 M
-// 69.8 -> 66.9, 100 M 284 -> 266; C = 6144 0 .. -5 %; C = 16384, keep = 2048, 64 K 4.2 -> 2.9, 40 M 118 -> 108, but 6 M 17.6 -> 19.1 and
-// 8 M 22.9 -> 24.3, where what all parts read of the entries shows.
+// 69.8 -> 66.9, 100 M 284 -> 266; C = 6144 0 .. -5 %; C = 16384, keep = 2048, 64 K 4.2 -> 2.9, 40 M 118 -> 108.  Where that loses: topk_step_whole().
 constexpr int kTopkPart = 4096;
-// A launch of more parts than a grid holds takes whole chunks: up to MOST elements, 16 waves of two or of four rows.
+// A whole chunk by one workgroup: up to MOST elements, 16 waves of two or of four rows, late entries.  So many parts that no grid holds them are taken so
+// as well.
 constexpr int kTopkWhole = 8192, kTopkWholeLong = 16384;
 constexpr int topk_step_rpw(int most) { return most <= kTopkWhole ? 2 : 4; }
 constexpr int topk_step_threads(int most) { return most / topk_step_rpw(most) / kRow * kWave; }
+// Where the whole chunks all run at once and their parts, of which a CU holds no more elements, need a second, nearly empty go; up to 8192 elements also as
+// long as there is a CU for every chunk and the entries come late.  Parts -> whole, us of the step: C = 8192, keep = 256, Adam 1.1 M 7.6 -> 6.7, 1.5 M 8.4 ->
+// 7.4, 2 M 8.8 -> 8.7, 2.5 M 11.7 -> 13.6, SGD 1.1 M 4.9 -> 4.8; C = 9216 (three chunks on a CU), keep = 288, SGD 3.6 M 10.2 -> 10.4, 4.1 M 13.5 -> 11.8, 6 M 18.8
+// -> 16.9, 6.8 M 21.6 -> 22.1, Adam 4.1 M 20.5 -> 18.8, 4.6 M 22.6 -> 25.2, 6 M 28.7 -> 27.4; C = 12288 (two), keep = 1536, SGD 4.6 M 15.8 -> 13.6, 6 M 19.5 -> 16.9, 6.8 M
+// 21.5 -> 22.1, Adam 4.6 M 23.6 -> 21.3, 6 M 28.7 -> 26.7; C = 16384, keep = 2048, SGD 4.6 M 16.3 -> 16.6, 5.2 M 18.0 -> 17.4, 6 M 19.8 -> 17.6, 8 M 24.5 -> 22.6, 8.5 M
+// 27.1 -> 27.8, Adam 5.2 M 26.2 -> 28.4, 6 M 29.3 -> 28.3, 8 M 37.1 -> 35.8, 8.5 M 40.7 -> 45; keep = 8192, of which every part reads all, SGD 4.6 M 20.6 -> 17.0, 8 M
+// 29.3 -> 24.3, Adam 4.6 M 27.4 -> 27.4, 6 M 33.2 -> 27.5.
+inline bool topk_step_whole(size_t chunks, size_t chunk, size_t keep)
+{
+    if (chunk <= kTopkWhole) return chunks * chunk > (static_cast<size_t>(1) << 20) && chunks <= kCus;
+    if (chunk <= 9 * 4 * kRow) return chunks > 5 * kCus / 3 && chunks <= 3 * kCus;
+    const size_t least = chunk <= 3 * kTopkPart ? 4 * kCus / 3 : keep > chunk / 4 ? 9 * kCus / 8 : 11 * kCus / 8;
+    return chunks > least && chunks <= 2 * kCus;
+}
 struct TopkParts {
     uint32_t most, part, parts;   // most: elements that the kernel's workgroup can take
     dim3 grid, block;
     size_t lds;
-    TopkParts(size_t chunks, size_t chunk)
+    TopkParts(size_t chunks, size_t chunk, size_t keep)
     {
         const uint32_t rows = static_cast<uint32_t>(chunk / kRow);
         parts = static_cast<uint32_t>((chunk + kTopkPart - 1) / kTopkPart);
         most = kTopkPart;
-        if (parts > 1 && chunks > kMaxGrid / parts) {
+        if (parts > 1 && (chunks > kMaxGrid / parts || topk_step_whole(chunks, chunk, keep))) {
             parts = 1;
             most = chunk <= kTopkWhole ? kTopkWhole : kTopkWholeLong;
         }
@@ -234,7 +259,7 @@ k_decompress_sgd_topk(const uint16_t* __restrict__ idx, const float* __restrict_
     const int len = static_cast<int>(n - base < size ? n - base : size);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
+    SparseEntries<EARLY, 4, MOST != kTopkWholeLong> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters (and momentum) do not depend on the decode: request them next
     constexpr int RPW = topk_step_rpw(MOST);
     f4 p[RPW], m[RPW];
@@ -304,7 +329,7 @@ k_decompress_adam_topk(const uint16_t* __restrict__ idx, const float* __restrict
     const int len = static_cast<int>(n - base < size ? n - base : size);
     const int wave = wave_index(), lane = threadIdx.x & 63;
 
-    SparseEntries<EARLY> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
+    SparseEntries<EARLY, (MOST == kTopkPart ? 4 : 1), false> entries(idx + static_cast<size_t>(c) * keep, val + static_cast<size_t>(c) * keep, keep);
     // parameters and optimizer state do not depend on the decode: request them next
     constexpr int RPW = topk_step_rpw(MOST);
     f4 p[RPW], m[RPW], v[RPW];
@@ -490,7 +515,7 @@ extern "C" int bagua_decompress_sgd_step_topk(const uint16_t* idx, const float* 
                            entries, ch, kp, n, param, lr);
         return launch_status();
     }
-    const TopkParts tp(nc, chunk);
+    const TopkParts tp(nc, chunk, keep);
 #define BAGUA_TS(MOMv, WDv)                                                                                               \
     BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_sgd_topk<MOMv, WDv, MOST, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
                                        tp.part, tp.parts, kp, param, momentum_buf, lr, momentum, weight_decay))
@@ -524,7 +549,7 @@ extern "C" int bagua_decompress_adam_step_topk(const uint16_t* idx, const float*
     const uint32_t ch = static_cast<uint32_t>(chunk), kp = static_cast<uint32_t>(keep);
     const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
     const bool frozen = variance_frozen != 0, wd = weight_decay != 0.0f;
-    const TopkParts tp(nc, chunk);
+    const TopkParts tp(nc, chunk, keep);
 #define BAGUA_TA(FRv, WDv)                                                                                                 \
     BAGUA_DISPATCH_TOPK_STEP(tp, launch_kernel((k_decompress_adam_topk<FRv, WDv, MOST, EARLY, PARTS>), tp.grid, tp.block, tp.lds, s, idx, val, n, ch, \
                                        tp.part, tp.parts, kp, param, m, v, lr, beta1, omb1, beta2, omb2, eps, weight_decay))

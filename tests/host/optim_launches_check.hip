@@ -31,8 +31,23 @@ static void covers(size_t chunks, size_t chunk, int status, const char* what)
     EXPECT(waves <= static_cast<size_t>(takes<kTopkPart>(l.kernel) ? topk_step_threads(kTopkPart) : 1024) / kWave, "%s chunk %zu chunks %zu", what, chunk, chunks);
 }
 
+// Chunks whole or in parts, on either side of each line (a launch of chunks up to 8192 elements that has a CU for every chunk and late entries; one go
+// of longer chunks where the parts need two).
+static void whole()
+{
+    EXPECT(topk_step_whole(256, 8192, 1) && !topk_step_whole(257, 8192, 1) && topk_step_whole(129, 8192, 1) && !topk_step_whole(128, 8192, 1), "8192");
+    EXPECT(topk_step_whole(256, 4352, 4352) && !topk_step_whole(240, 4352, 1), "4352");
+    for (const size_t chunk : {8448, 9216}) EXPECT(!topk_step_whole(426, chunk, 1) && topk_step_whole(427, chunk, 1) && topk_step_whole(768, chunk, 1) && !topk_step_whole(769, chunk, 1), "three on a CU");
+    for (const size_t chunk : {9472, 12288}) EXPECT(!topk_step_whole(341, chunk, 1) && topk_step_whole(342, chunk, chunk) && topk_step_whole(512, chunk, 1) && !topk_step_whole(513, chunk, 1), "two on a CU");
+    for (const size_t chunk : {12544, 16384}) {
+        EXPECT(!topk_step_whole(352, chunk, chunk / 4) && topk_step_whole(353, chunk, chunk / 4) && topk_step_whole(512, chunk, 1) && !topk_step_whole(513, chunk, 1), "two on a CU");
+        EXPECT(!topk_step_whole(288, chunk, chunk / 4 + 1) && topk_step_whole(289, chunk, chunk / 4 + 1), "long lists");
+    }
+}
+
 int main()
 {
+    whole();
     for (size_t chunk = 256; chunk <= 16384; chunk += 256) {
         std::vector<size_t> counts = {1, 100, 400, 600, 1000, 3000, size_t{1} << 20, kMaxGrid};
         for (const size_t parts : {2, 3, 4}) counts.insert(counts.end(), {kMaxGrid / parts, kMaxGrid / parts + 1});

@@ -213,21 +213,38 @@ def test_compressions_batched(bg, oracle, C):
             r[b].check(ro, "residual n=%d" % n)
 
 
-# keep below, at and above the threads of a workgroup; a chunk cut short; either side of the lines between early and late entries
+# keep below, at and above the threads of a workgroup; a chunk cut short; early and late entries; chunks in parts and whole
 @pytest.mark.parametrize("n,C,keep", [(3, 256, 1), (5001, 1024, 7), (70001, 1024, 256), (70001, 1024, 257), (40001, 2048, 2048), (300001, 16384, 1500), (20001, 5376, 100), (12801, 12800, 12800),
-                                      (1 << 20, 4096, 128), ((1 << 20) + 1, 4096, 600), ((5 << 20) + 3, 4096, 513), ((1 << 26) + 5, 8192, 3)])
+                                      (1 << 20, 4096, 128), ((1 << 20) + 1, 4096, 600), ((5 << 20) + 3, 4096, 513), ((1 << 26) + 5, 8192, 3),
+                                      ((1 << 20) + 1, 8192, 1500), (1 << 21, 8192, 1024), ((1 << 21) + 1, 8192, 300), ((1 << 20) + 1, 16384, 1500), (10 << 20, 8192, 513), ((10 << 20) + 1, 8192, 300),
+                                      (352 * 16384, 16384, 600), (352 * 16384 + 1, 16384, 600), (288 * 14336 + 7, 14336, 3585), (512 * 16384 - 255, 16384, 1025), (512 * 16384 + 1, 16384, 1025),
+                                      (426 * 9216, 9216, 300), (768 * 9216 - 1, 9216, 577), (341 * 12288 + 4, 12288, 100)])
 @pytest.mark.parametrize("opt", ["sgd", "adam"])
 def test_optimizer_steps_after_topk(bg, oracle, n, C, keep, opt):
+    optimizer_step_after_topk(bg, oracle, n, C, keep, opt, momentum=True, weight_decay=1e-4 if opt == "sgd" else 0.0, lr=1e-3 if opt == "sgd" else 1e-4)
+
+
+# The other forms of the step: late entries in parts, whole chunks of two and of four rows per wave
+@pytest.mark.parametrize("n,C,keep", [((1 << 21) + 1, 8192, 300), ((1 << 20) + 1, 8192, 300), (353 * 16384, 16384, 600)])
+@pytest.mark.parametrize("form", [("sgd", True, 0.0, 1e-3), ("sgd", False, 1e-4, 1e-3), ("sgd", False, 0.0, -1e-3), ("adam", False, 1e-2, 1e-4), ("adam", True, 0.0, 1e-4),
+                                  ("adam", True, 1e-2, 1e-4)], ids=["mom", "wd", "neither", "adam-wd", "frozen", "frozen-wd"])
+def test_forms_of_the_optimizer_step_after_topk(bg, oracle, n, C, keep, form):
+    opt, flag, wd, lr = form
+    optimizer_step_after_topk(bg, oracle, n, C, keep, opt, momentum=flag, weight_decay=wd, lr=lr, frozen=opt == "adam" and flag)
+
+
+def optimizer_step_after_topk(bg, oracle, n, C, keep, opt, momentum, weight_decay, lr, frozen=False):
     idx, val = oracle.compress_topk(vals(n, n), None, C, keep)
     param, m, v = vals(n, 1, 0.02), vals(n, 2), np.square(vals(n, 3)) + np.float32(1e-8)
     gp, gm, gv = Guarded(param), Guarded(m), Guarded(v)
     gi, gx = torch.from_numpy(idx.view(np.int16)).cuda(), torch.from_numpy(val).cuda()
     if opt == "sgd":
-        bg.bagua_decompress_sgd_step_topk(gi, gx, n, C, keep, gp.t, gm.t, 1e-3, momentum=0.9, weight_decay=1e-4)
-        oracle.decompress_sgd_step_topk(idx, val, n, C, keep, param, m, 1e-3, 0.9, 1e-4)
+        mu = 0.9 if momentum else 0.0
+        bg.bagua_decompress_sgd_step_topk(gi, gx, n, C, keep, gp.t, gm.t if momentum else None, lr, momentum=mu, weight_decay=weight_decay)
+        oracle.decompress_sgd_step_topk(idx, val, n, C, keep, param, m if momentum else None, lr, mu, weight_decay)
     else:
-        bg.bagua_decompress_adam_step_topk(gi, gx, n, C, keep, gp.t, gm.t, gv.t, 1e-4)
-        oracle.decompress_adam_step_topk(idx, val, n, C, keep, param, m, v, 1e-4)
+        bg.bagua_decompress_adam_step_topk(gi, gx, n, C, keep, gp.t, gm.t, gv.t, lr, weight_decay=weight_decay, variance_frozen=frozen)
+        oracle.decompress_adam_step_topk(idx, val, n, C, keep, param, m, v, lr, weight_decay=weight_decay, variance_frozen=frozen)
         gv.check(v, "v")
     gp.check(param, "param")
     gm.check(m, "m")
