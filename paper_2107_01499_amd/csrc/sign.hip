@@ -178,7 +178,7 @@ struct SignEntrySrc {   // pointers in a batch entry: [eps, bits_out, scale_out,
     __device__ __forceinline__ const float* meta(int j) const { return table_ptr<const float>(e[5 + k + j]); }
 };
 
-template <int RPW, bool EF, bool OUT, bool REST, typename SRC>
+template <int RPW, bool EF, bool OUT, int REST, typename SRC>
 __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_k, float* __restrict__ eps, size_t n,
                                                uint32_t chunk, uint32_t* __restrict__ bits_out,
                                                float* __restrict__ scale_out, float* __restrict__ out, size_t c,
@@ -241,10 +241,10 @@ __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_
                 }
             }
         };
-        // As many workers' words as there are left, up to NJ, are requested together.  Those of k mod NJ one after the other -> together, us of
-        // the step: k = 2, C = 2048, 16 M 25.3 -> 24.2, 134 M 173 -> 170; k = 4, 1 M 4.1 -> 4.0, 16 M 28.3 -> 24.9, 134 M 203 -> 183; k = 7, 65 K 4.1 -> 3.8,
+        // As many workers' words as there are left, up to NJ, are requested together, unless sign_rest() says otherwise.  Those of k mod NJ one after
+        // the other -> together, us of the step: k = 2, C = 2048, 16 M 25.3 -> 24.2, 134 M 173 -> 170; k = 4, 1 M 4.1 -> 4.0, 16 M 28.3 -> 24.9, 134 M 203 -> 183; k = 7, 65 K 4.1 -> 3.8,
         // 8 M 18.4 -> 16.2, 33 M 61.7 -> 49.7, 134 M 255 -> 196; k = 5, C = 4096, 33 M 57.1 -> 49.2, C = 16384, 134 M 298 -> 257; k = 12, C = 8192, 134 M 298 ->
-        // 255; k = 3, C = 1024, 4 M 7.7 -> 8.3, 8 M 15.2 -> 14.8.  (Where k is a multiple of NJ the bodies of the rest would cost 1-2 %: REST.)
+        // 255; k = 3, C = 1024, 8 M 15.2 -> 14.8.  (Where k is a multiple of NJ the bodies of the rest would cost 1-2 %.)
         auto group = [&](auto count, int j, bool first) {
             constexpr int N = decltype(count)::value;
             uint32_t w[N][RPW];
@@ -333,7 +333,7 @@ __device__ __forceinline__ void drr_sign_chunk(const SRC& src, int k, float inv_
                                     bits_out + (base >> 5), scale_out + c, OUT ? out + base : nullptr, s_q);
 }
 
-template <int RPW, bool EF, bool OUT, bool REST>
+template <int RPW, bool EF, bool OUT, int REST>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_sign(PtrTable bits_in, PtrTable scale_in, int k, float inv_k, float* __restrict__ eps, size_t n,
            uint32_t chunk, uint32_t* __restrict__ bits_out, float* __restrict__ scale_out,
@@ -344,7 +344,7 @@ k_drr_sign(PtrTable bits_in, PtrTable scale_in, int k, float inv_k, float* __res
                                  blockIdx.x, s_q);
 }
 
-template <int RPW, bool EF, bool OUT, bool REST, typename TABLE>
+template <int RPW, bool EF, bool OUT, int REST, typename TABLE>
 __global__ void __launch_bounds__(wg_threads_max(RPW))
 k_drr_sign_batched(TABLE table, int k, float inv_k, uint32_t chunk)
 {
@@ -412,10 +412,30 @@ int launch_sign_compress(const float* x, float* residual, size_t n, size_t chunk
     return launch_status();
 }
 
-// Expands `stmt` with a constexpr REST: whether k workers are not whole groups.
-#define BAGUA_DISPATCH_REST(k, stmt)                                              \
-    if ((k) % BAGUA_DRR_SIGN_NJ != 0) { constexpr bool REST = true; stmt; }       \
-    else { constexpr bool REST = false; stmt; }
+// How the workers beyond the last group of NJ are taken.  One by one where the launch is one go that more than half fills the chip: there the waves that
+// request everything together only meet in the memory, and the longer chain of loads spreads them.  Together -> one by one, us of the step: C = 512, k =
+// 3, 2.4 M 6.8 -> 5.9, 3 M 7.7 -> 6.5, 4 M 9.2 -> 8.2, 4.3 M 9.9 -> 10.0; C = 1024, k = 2, 3.9 M 8.3 -> 7.5, k = 5, 4 M 9.2 -> 8.0, k = 7, 3.5 M 9.0 -> 8.5, k = 11, 4 M
+// 10.9 -> 10.2; from 1536 elements on later and for less than six: C = 2048, k = 3, 2.5 M 5.5 -> 5.6, 3 M 6.7 -> 6.1, 3.5 M 7.7 -> 6.9, 4 M 8.2 -> 8.1, k = 7, 3.9 M 9.2 ->
+// 9.6; C = 4096, k = 2, 3.5 M 7.5 -> 6.4, k = 5, 2.7 M 7.2 -> 7.5, 3.9 M 8.5 -> 8.3, k = 7, 3.9 M 8.8 -> 9.1; C = 8192 nothing.  A single worker has nothing to be taken
+// together with, and half the code is 2 to 5 % less time (C = 256, 3 M 8.3 -> 8.0).
+static int sign_rest(int k, size_t groups, size_t waves)
+{
+    const int left = k % BAGUA_DRR_SIGN_NJ;
+    if (left == 0) return kRestNone;
+    if (k == 1 || BAGUA_DRR_SIGN_NJ > 8) return kRestOneByOne;
+    const size_t at_once = kCus * (kWavesPerCu / waves) * waves, all = groups * waves;
+    if (waves > 8 || all > at_once) return kRestTogether;
+    if (waves <= 2) return all > at_once / 2 ? kRestOneByOne : kRestTogether;
+    return left < 6 && all > at_once / 16 * 11 ? kRestOneByOne : kRestTogether;
+}
+
+// Expands `stmt` with a constexpr REST equal to the runtime value.
+#define BAGUA_DISPATCH_REST(rest, stmt)                                                                                                          \
+    switch (rest) {                                                                                                                              \
+        case kRestNone: { constexpr int REST = kRestNone; stmt; } break;                                                                         \
+        case kRestTogether: { constexpr int REST = BAGUA_DRR_SIGN_NJ <= 8 ? kRestTogether : kRestOneByOne; stmt; } break;   /* as sign_rest() */ \
+        default: { constexpr int REST = kRestOneByOne; stmt; } break;                                                                            \
+    }
 
 int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, int k, float* eps, size_t n,
                     size_t chunk, uint32_t* bits_out, float* scale_out, float* out, hipStream_t stream)
@@ -426,10 +446,11 @@ int launch_drr_sign(const void* const* bits_in, const float* const* scale_in, in
         st.p[j] = scale_in[j];
     }
     const SignGeometry g = sign_geometry(n, chunk, BAGUA_RPW_DRR_SIGN, false);
+    const int rest = sign_rest(k, g.grid.x, g.block.x / kWave);
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
 #define BAGUA_DRR(EFv, OUTv)                                                                                      \
-    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(k, launch_kernel((k_drr_sign<RPW, EFv, OUTv, REST>), g.grid, g.block, g.lds, stream, bt, \
+    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(rest, launch_kernel((k_drr_sign<RPW, EFv, OUTv, REST>), g.grid, g.block, g.lds, stream, bt, \
                                                  st, k, inv_k, eps, n, ch, bits_out, scale_out, out)))
     if (eps && out) { BAGUA_DRR(true, true) }
     else if (eps) { BAGUA_DRR(true, false) }
@@ -446,10 +467,11 @@ int launch_drr_sign_batched(const std::vector<uint64_t>& table, void* workspace,
     g.grid = dim3(static_cast<unsigned>(table[B]));
     const float inv_k = 1.0f / static_cast<float>(k);
     const uint32_t ch = static_cast<uint32_t>(chunk);
+    const int rest = sign_rest(k, g.grid.x, g.block.x / kWave);
     return batch_launch(table, B, 5 + 2 * static_cast<size_t>(k), workspace, stream, [&](const auto& tab) {
         using TABLE = std::decay_t<decltype(tab)>;
 #define BAGUA_DRR(EFv, OUTv)                                                                                       \
-    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(k, launch_kernel((k_drr_sign_batched<RPW, EFv, OUTv, REST, TABLE>), g.grid, g.block, g.lds, stream, \
+    BAGUA_DISPATCH_RPW(g.rpw, BAGUA_DISPATCH_REST(rest, launch_kernel((k_drr_sign_batched<RPW, EFv, OUTv, REST, TABLE>), g.grid, g.block, g.lds, stream, \
                                                  tab, k, inv_k, ch)))
         if (ef && with_out) { BAGUA_DRR(true, true) }
         else if (ef) { BAGUA_DRR(true, false) }

@@ -9,18 +9,24 @@
 
 namespace bagua {
 
-// The workers of a server step in ascending order, in groups of NJ and then those that are left together: group(how many, the first one,
-// whether it is worker 0), the count as a type.  REST: k is not a multiple of NJ.  More than seven that are left (NJ above 8) come one by one.
-template <int NJ, bool REST, typename GROUP>
+// What comes after the last whole group of workers in a server step: nothing, up to seven of them together, or all one by one.
+enum SignRest { kRestNone, kRestTogether, kRestOneByOne };
+
+// The workers of a server step in ascending order, in groups of NJ and then the rest: group(how many, the first one, whether it is
+// worker 0), the count as a type.
+template <int NJ, int REST, typename GROUP>
 __host__ __device__ __forceinline__ void for_worker_groups(int k, const GROUP& group)
 {
-    static_assert(NJ >= 1, "a group of workers");
+    static_assert(NJ >= 1 && (REST != kRestTogether || NJ <= 8), "no body for so many workers together");
     int j = 0;
-    if (!REST || k >= NJ) {
+    if (REST == kRestNone || k >= NJ) {
         group(std::integral_constant<int, NJ>{}, 0, true);
         for (j = NJ; j + NJ <= k; j += NJ) group(std::integral_constant<int, NJ>{}, j, false);
+    } else if (REST == kRestOneByOne) {
+        group(std::integral_constant<int, 1>{}, 0, true);
+        j = 1;
     }
-    if constexpr (REST) {
+    if constexpr (REST == kRestTogether) {
         switch (k - j) {
             case 1: group(std::integral_constant<int, 1>{}, j, j == 0); break;
             case 2: group(std::integral_constant<int, 2>{}, j, j == 0); break;
@@ -29,12 +35,11 @@ __host__ __device__ __forceinline__ void for_worker_groups(int k, const GROUP& g
             case 5: group(std::integral_constant<int, 5>{}, j, j == 0); break;
             case 6: group(std::integral_constant<int, 6>{}, j, j == 0); break;
             case 7: group(std::integral_constant<int, 7>{}, j, j == 0); break;
-            default:
-                if constexpr (NJ > 8) {
-                    for (; j < k; ++j) group(std::integral_constant<int, 1>{}, j, j == 0);
-                }
-                break;
+            default: break;
         }
+    }
+    if constexpr (REST == kRestOneByOne) {
+        for (; j < k; ++j) group(std::integral_constant<int, 1>{}, j, false);
     }
 }
 

@@ -7,22 +7,27 @@ using namespace bagua;
 static bool g_failed = false;
 static long g_checked = 0;
 
+template <int NJ, int REST>
+static void groups(int k)
+{
+    int next = 0;
+    for_worker_groups<NJ, REST>(k, [&](auto count, int j, bool first) {
+        ++g_checked;
+        if (j != next || first != (j == 0)) g_failed = true;
+        next = j + decltype(count)::value;
+    });
+    if (next != k) {
+        std::printf("groups of %d, rest %d: %d of %d workers\n", NJ, REST, next, k);
+        g_failed = true;
+    }
+}
 template <int NJ>
 static void groups()
 {
     for (int k = 1; k <= 32; ++k) {
-        int next = 0;
-        auto group = [&](auto count, int j, bool first) {
-            ++g_checked;
-            if (j != next || first != (j == 0)) g_failed = true;
-            next = j + decltype(count)::value;
-        };
-        if (k % NJ != 0) for_worker_groups<NJ, true>(k, group);
-        else for_worker_groups<NJ, false>(k, group);
-        if (next != k) {
-            std::printf("groups of %d: %d of %d workers\n", NJ, next, k);
-            g_failed = true;
-        }
+        groups<NJ, kRestOneByOne>(k);
+        if (k % NJ == 0) groups<NJ, kRestNone>(k);
+        if constexpr (NJ <= 8) groups<NJ, kRestTogether>(k);
     }
 }
 

@@ -274,6 +274,13 @@ def test_server_step_sign(bg, oracle, k):
         server_sign(bg, oracle, k, n, C, ef=i % 3 != 0, out=i % 2 == 0)
 
 
+# Either side of the launches whose rest of workers comes one by one, and one worker.
+@pytest.mark.parametrize("k,C,n", [(1, 2048, 5000), (3, 512, 1 << 21), (3, 512, (1 << 21) + 512), (9, 1024, (1 << 22) - 5), (14, 1024, 1 << 22), (2, 1024, (1 << 22) + 1),
+                                   (5, 4096, 2880000), (5, 4096, 2885632), (6, 4096, 3 << 20), (11, 3072, 3 << 20), (2, 4096, (1 << 22) + 4096)])
+def test_server_step_sign_either_side_of_its_lines(bg, oracle, k, C, n):
+    server_sign(bg, oracle, k, n, C, ef=True, out=k % 2 == 0)
+
+
 @pytest.mark.parametrize("k", [3, 7, 8])
 def test_server_step_sign_batched(bg, oracle, k):
     C, ns = 2048, [1, 2048, 2049, 70001, 300]
