@@ -392,7 +392,7 @@ inline bool lp_encode_short(size_t n) { return n >= 4 && n <= (static_cast<size_
 // `elements`: of all peers that are encoded before the first mix.  READ_AGAIN pays up to 2^27 of them; without -> with it,
 // encode + mix of one peer: 6.5 M 50.0 -> 46.6 us, 25.6 M 174 -> 158 us, 50 M 332 -> 315 us, 134 M 949 -> 936 us, 300 M 2169 ->
 // 2185 us; 8 workers that all choose one way: 8 x 4 M 173 -> 163 us, 8 x 16 M 633 -> 624 us, 8 x 25 M 959 -> 960 us, 8 x 50 M
-// 1888 -> 1963 us.
+// 1888 -> 1963 us, 32 x 5 M 852 -> 881 us, 32 x 8 M 1307 -> 1361 us (without tail tests as well, for which there is no form that streams).
 static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk, uint8_t* codes, float* minmax, size_t elements,
                              hipStream_t stream)
 {
@@ -400,9 +400,10 @@ static void launch_lp_encode(const float* x, float* xhat, size_t n, size_t chunk
     const int rpw = pick_rpw(rows, BAGUA_RPW_LP);
     const dim3 grid(static_cast<unsigned>(num_chunks(n, chunk))), block(64 * ((rows + rpw - 1) / rpw));
     const uint32_t ch = static_cast<uint32_t>(chunk);
-    if (lp_encode_short(n)) {
+    const bool again = elements <= (static_cast<size_t>(1) << 27);
+    if (again && lp_encode_short(n)) {
         BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, true, true>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
-    } else if (elements <= (static_cast<size_t>(1) << 27)) {
+    } else if (again) {
         BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, true, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))
     } else {
         BAGUA_DISPATCH_RPW(rpw, launch_kernel((k_lp_encode<RPW, false, false>), grid, block, 0, stream, x, xhat, n, ch, codes, minmax))

@@ -1,0 +1,44 @@
+// Host-only check of the rules by which the low-precision rounds choose their kernels.
+#include "fake_runtime.hpp"
+#include "ring.hip"
+
+static bool encodes(const void* kernel, bool again, bool is_short)
+{
+    if (again && is_short) return kernel == stub(k_lp_encode<2, true, true>) || kernel == stub(k_lp_encode<4, true, true>);
+    if (again) return kernel == stub(k_lp_encode<2, true, false>) || kernel == stub(k_lp_encode<4, true, false>);
+    return !is_short && (kernel == stub(k_lp_encode<2, false, false>) || kernel == stub(k_lp_encode<4, false, false>));
+}
+
+// Workers that all choose one way: each is encoded before the first mix, which reads the copies again as long as they are 2^27 elements in all.
+static void one_way()
+{
+    const size_t line = size_t{1} << 27, line_short = size_t{1} << 23;
+    const float* x[BAGUA_MAX_WORKERS];
+    float *out[BAGUA_MAX_WORKERS], *hat[BAGUA_MAX_WORKERS], *minmax[BAGUA_MAX_WORKERS];
+    uint8_t* codes[BAGUA_MAX_WORKERS];
+    int peer[BAGUA_MAX_WORKERS];
+    for (int i = 0; i < BAGUA_MAX_WORKERS; ++i) {
+        x[i] = far_apart<const float>(1 + i);
+        out[i] = far_apart<float>(101 + i);
+        hat[i] = far_apart<float>(201 + i);
+        codes[i] = far_apart<uint8_t>(301 + i);
+        minmax[i] = far_apart<float>(401 + i);
+    }
+    for (const int k : {3, 16, 17, 32})
+        for (const size_t n : {size_t{3}, size_t{4}, line / 32, line / 32 + 1, line_short, line_short + 1, line / 3 + 1})
+            for (const size_t chunk : {1024, 4096, 16384}) {
+                for (int i = 0; i < k; ++i) peer[i] = (i + 1) % k;
+                g_launches.clear();
+                const int status = bagua_decentralized_avg_peers_lp(x, out, hat, codes, minmax, peer, k, n, chunk, nullptr);
+                EXPECT(status == BAGUA_OK && g_launches.size() == static_cast<size_t>(k) + 1, "k %d n %zu", k, n);
+                const bool again = k * n <= line, is_short = n >= 4 && n <= line_short;
+                for (int i = 0; i < k && i < static_cast<int>(g_launches.size()); ++i)
+                    EXPECT(encodes(g_launches[i].kernel, again, again && is_short), "k %d n %zu chunk %zu", k, n, chunk);
+            }
+}
+
+int main()
+{
+    one_way();
+    return finish();
+}

@@ -30,3 +30,7 @@ def test_optimizer_steps_after_topk(tmp_path):
 
 def test_every_worker_of_a_sign_server_step_is_in_a_group(tmp_path):
     check("sign_groups", tmp_path, [])
+
+
+def test_rounds_in_low_precision(tmp_path):
+    check("ring_launches", tmp_path, [])
