@@ -324,12 +324,16 @@ __device__ __forceinline__ void lp_encode_folded(const float* x_c, float* hat_c,
 //   2 M 46.5 -> 54.1; K = 8, 1 M 57.9 -> 42.4; K = 16, 64 K 90.0 -> 12.1, 1 M 107.6 -> 82.7, 2 M 127.1 -> 168.9;   C = 8192: K = 3, 64 K 8.0 -> 6.1, K = 4, 200 K
 //   12.4 -> 9.1, K = 8, 400 K 30.0 -> 20.0;   C = 12288, K = 4, 1 M 26.9 -> 25.4, 1.25 M 29.0 -> 29.3.
 // With chunks up to 4096 elements fewer peers gain less than a second launch costs the host (K = 4, C = 2048, 64 K 7.3 -> 5.6, K = 3 6.2 -> 5.5).
+// One workgroup for all peers takes 2 to 3.5 us a peer, longer chunks more, at nearly any length; two launches take what the bytes take, so that the line
+// does not rise with the peers for good.  K = 32: C = 1024, 393 K 70.2 -> 51.5, 500 K 73.6 -> 76.9, 786 K 80.6 -> 105.8; C = 2048, 500 K 79.2 -> 79.2, 600 K 80.8
+// -> 85.0; C = 3072, 590 K 80.9 -> 79.2; C = 4096, 590 K 91.9 -> 78.5, 786 K 98.7 -> 105.9; C = 4352, 600 K 95.5 -> 85.6, 786 K 102.4 -> 106.2; C = 6144, 786 K 110.4 ->
+// 106.8; K = 24: C = 1024, 500 K 56.6 -> 59.1; C = 4352, 786 K 79.3 -> 79.6.
 static bool ring_lp_two_launches(int k, size_t n, size_t chunk)
 {
     if (n < 4) return false;   // row_at
     if (chunk > 8192) return k >= 2 && n <= 5 * (static_cast<size_t>(1) << 18);
-    if (chunk > 4096) return k >= 3 && n <= std::min<size_t>(static_cast<size_t>(k) << 16, 3 << 18);
-    return k >= 5 && n <= static_cast<size_t>(k) * 24 * 1024;
+    if (chunk > 4096) return k >= 3 && n <= std::min<size_t>(static_cast<size_t>(k) << 16, k > 24 && chunk < 6144 ? 5 << 17 : 3 << 18);
+    return k >= 5 && n <= static_cast<size_t>(std::min(k, chunk > 2048 ? 24 : 16)) * 24 * 1024;
 }
 
 template <int RPW>

@@ -37,8 +37,23 @@ static void one_way()
             }
 }
 
+// Where a ring goes through its peers in one launch again: a peer more costs that launch 2 to 3.5 us whatever the size, the two launches its bytes.
+static void two_launches()
+{
+    const size_t quarter = 24 * 1024;
+    for (const size_t chunk : {256, 1024, 2048, 2304, 4096}) {
+        const size_t line = (chunk > 2048 ? 24 : 16) * quarter;
+        EXPECT(!ring_lp_two_launches(4, 4, chunk) && ring_lp_two_launches(5, 5 * quarter, chunk) && !ring_lp_two_launches(5, 5 * quarter + 1, chunk), "chunk %zu", chunk);
+        for (const int k : {24, 25, 32}) EXPECT(ring_lp_two_launches(k, line, chunk) && !ring_lp_two_launches(k, line + 1, chunk), "k %d chunk %zu", k, chunk);
+    }
+    EXPECT(ring_lp_two_launches(25, 5 << 17, 4352) && !ring_lp_two_launches(32, (5 << 17) + 1, 5888) && ring_lp_two_launches(32, 3 << 18, 6144), "chunks above 4096");
+    EXPECT(ring_lp_two_launches(24, 3 << 18, 4352) && !ring_lp_two_launches(24, (3 << 18) + 1, 4352) && ring_lp_two_launches(32, 5 << 18, 16384), "chunks above 4096");
+    for (const size_t chunk : {1024, 8192, 16384}) EXPECT(!ring_lp_two_launches(32, 3, chunk) && ring_lp_two_launches(32, 4, chunk), "chunk %zu", chunk);
+}
+
 int main()
 {
+    two_launches();
     one_way();
     return finish();
 }

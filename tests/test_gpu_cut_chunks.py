@@ -132,7 +132,7 @@ def test_rounds_in_low_precision(bg, oracle, cuts, k, peer):
 
 
 @pytest.mark.parametrize("k,C,n,peer", [
-    (5, 4096, 5 * 24 * 1024, None), (5, 4096, 5 * 24 * 1024 + 1, None), (8, 1536, 8 * 24 * 1024 - 3, None), (4, 4096, 65537, None),
+    (25, 4096, 24 * 24 * 1024, None), (25, 4096, 24 * 24 * 1024 + 1, None), (17, 1024, 16 * 24 * 1024 + 1, None), (25, 4352, (5 << 17) + 1, None), (5, 4096, 5 * 24 * 1024, None), (5, 4096, 5 * 24 * 1024 + 1, None), (8, 1536, 8 * 24 * 1024 - 3, None), (4, 4096, 65537, None),
     (32, 8192, 100001, None), (6, 16384, 6 * 80 * 1024 - 1, None), (6, 16384, 6 * 80 * 1024 + 1, None), (6, 6400, 120003, None),
     (2, 4096, (1 << 21) + 1, [1, 0]), (3, 4096, (1 << 21) + 1, [1, 0, 2]), (3, 2048, (1 << 23) + 5, [1, 0, 2]), (3, 16384, 1 << 21, [0, 2, 1]),
     (3, 4096, 300001, [0, 1, 2]), (2, 16384, 5 << 18, None), (2, 16384, (5 << 18) + 1, None), (3, 8192, (3 << 16) + 1, None), (16, 8192, 3 << 18, None),
