@@ -17,10 +17,11 @@ namespace bagua {
 // us per launch: MinMax, C = 4096, 64 K 4.3 -> 4.1, 1 M 5.8 -> 5.0, 2 M 7.4 -> 6.6, 4 M 11.2 -> 12.3; C = 1024, 64 K 4.2 -> 3.7, 1 M 5.6 -> 4.8, 2 M 7.2
 // -> 6.2; sign codec, C = 4096, 64 K 4.3 -> 4.0, 1 M 5.9 -> 4.7, 2 M 7.1 -> 5.8, 4 M 10.2 -> 11.0.  Workgroups that do not fill a CU's 32 waves up to
 // 2^20: C = 3072, MinMax, 1 M 5.6 -> 5.0, 1.6 M 6.4 -> 6.7, sign codec, 1 M 5.7 -> 4.8, 1.6 M 6.4 -> 6.2 but 0.5 % of a round of 12 x 1.6 M more.
+// A build that prefers four rows gets them at any size.
 inline int pick_rpw_gather(int rows, size_t n, int preferred)
 {
     const size_t most = static_cast<size_t>(1) << (kWavesPerCu % rows == 0 ? 21 : 20);
-    return rows <= kMaxWaves && n <= most ? 1 : pick_rpw_worker(rows, preferred);
+    return preferred == 2 && rows <= kMaxWaves && n <= most ? 1 : pick_rpw_worker(rows, preferred);
 }
 
 template <int RPW, bool EF, bool WB>
@@ -182,13 +183,14 @@ __device__ __forceinline__ void average_rows_ahead(const PtrTable& xs, int k_loc
 // 7.4 -> 5.2), 256 K 8.5 -> 5.8, 1 M 10.2 -> 8.7, 2 M 14.7 -> 16.0; 4 workers, C = 8192, 1 M 7.9 -> 7.2, 2 M 9.9 -> 12.7; sign codec, 4 workers, C =
 // 2048, 64 K 3.3 -> 2.9, 256 K 4.6 -> 3.5, 1 M 5.9 -> 5.5, 2 M 9.2 -> 9.4.  C = 16384 (four rows per wave, 128 registers): 64 K 12.8 -> 16.5.
 inline bool short_average(size_t n, size_t chunk) { return n >= 4 && n <= (static_cast<size_t>(1) << 20) && chunk <= 8192; }
-// launch(rows per wave, whether it is a short launch), both as types.  Short chunks take one row per wave then.
+// launch(rows per wave, whether it is a short launch), both as types.  Short chunks take one row per wave then.  There is no short form for a build
+// that prefers four rows.
 template <typename F>
-inline void average_shape(size_t n, size_t chunk, const F& launch)
+inline void average_shape(size_t n, size_t chunk, int preferred, const F& launch)
 {
     const int rows = static_cast<int>(chunk / kRow);
-    if (!short_average(n, chunk)) {
-        BAGUA_DISPATCH_RPW_WORKER(pick_rpw_worker(rows, 2), (launch(std::integral_constant<int, RPW>{}, std::false_type{})))
+    if (preferred != 2 || !short_average(n, chunk)) {
+        BAGUA_DISPATCH_RPW_WORKER(pick_rpw_worker(rows, preferred), (launch(std::integral_constant<int, RPW>{}, std::false_type{})))
     } else if (rows <= kMaxWaves) {
         launch(std::integral_constant<int, 1>{}, std::true_type{});
     } else {
@@ -435,7 +437,7 @@ extern "C" int bagua_reduce_compress_minmax_u8(const float* const* x, int k_loca
     const uint32_t ch = static_cast<uint32_t>(chunk), keep = keep_chunks(n, chunk);
     const ChunkOrder order = chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    average_shape(n, chunk, [&](auto rpw, auto is_short) {
+    average_shape(n, chunk, BAGUA_RPW_COMPRESS, [&](auto rpw, auto is_short) {
         constexpr int RPW = decltype(rpw)::value;
         constexpr bool SHORT = decltype(is_short)::value;
         const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));
@@ -470,7 +472,7 @@ extern "C" int bagua_reduce_compress_sign_ef(const float* const* x, int k_local,
     const uint32_t ch = static_cast<uint32_t>(chunk);
     const ChunkOrder order = chunk_order(grid.x, chunk, order_pays_average(n, chunk, k_local));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    average_shape(n, chunk, [&](auto rpw, auto is_short) {
+    average_shape(n, chunk, BAGUA_RPW_SIGN, [&](auto rpw, auto is_short) {
         constexpr int RPW = decltype(rpw)::value;
         constexpr bool SHORT = decltype(is_short)::value;
         const dim3 block(kWave * ((chunk / kRow + RPW - 1) / RPW));

@@ -34,3 +34,8 @@ def test_every_worker_of_a_sign_server_step_is_in_a_group(tmp_path):
 
 def test_rounds_in_low_precision(tmp_path):
     check("ring_launches", tmp_path, [])
+
+
+@pytest.mark.parametrize("rows", [2, 4])
+def test_averages_and_gathers(tmp_path, rows):
+    check("fused_launches", tmp_path, ["-DBAGUA_RPW_COMPRESS=%d" % rows, "-DBAGUA_RPW_SIGN=%d" % rows])
