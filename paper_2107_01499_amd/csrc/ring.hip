@@ -278,12 +278,13 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
     ring_mix<RPW>(mid, h, right, x, third, out_of(0), len, wave, lane);
 }
 
-// FOLD: complete chunks without tail tests on their loads.  In the shortest and the longest launches of chunks of more than 32 rows; with -> without,
-// us: C = 16384, K = 3, 64 K 15.4 -> 12.9, 1 M +-0, 33 M 365 -> 353, 134 M 1476 -> 1412; K = 2, 64 K 11.6 -> 10.0, 1 M 19.8 -> 20.6, 8 M 67.8 -> 70.3, 33 M
-// 248 -> 250, 134 M 1040 -> 1014; C = 12288, K = 5, 1 M 32.2 -> 34.1, 16 M 296 -> 288, 134 M 2321 -> 2249.
+// FOLD: complete chunks without tail tests on their loads.  In the longest launches of chunks of more than 32 rows, and in the shortest of a ring of one
+// (two peers and more take two launches there); without -> with, us: C = 16384, K = 3, 33 M 365 -> 353, 134 M 1476 -> 1412; K = 2, 8 M 67.8 -> 70.3, 33 M
+// 248 -> 250, 134 M 1040 -> 1014; C = 12288, K = 5, 16 M 296 -> 288, 134 M 2321 -> 2249; K = 1, C = 16384, 64 K 6.7 -> 6.2, 256 K 7.1 -> 6.4, 1 M +-0, C = 8448, 64 K
+// 4.7 -> 4.8.
 static bool ring_lp_any_fold(int k, size_t n)
 {
-    return n <= (static_cast<size_t>(1) << 18) || k * n >= (static_cast<size_t>(5) << 24);
+    return (k == 1 && n <= (static_cast<size_t>(1) << 18)) || k * n >= (static_cast<size_t>(5) << 24);
 }
 
 template <int RPW, bool FOLD>

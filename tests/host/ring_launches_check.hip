@@ -51,8 +51,35 @@ static void two_launches()
     for (const size_t chunk : {1024, 8192, 16384}) EXPECT(!ring_lp_two_launches(32, 3, chunk) && ring_lp_two_launches(32, 4, chunk), "chunk %zu", chunk);
 }
 
+// The one kernel for chunks of more than 32 rows: without tail tests where that pays.
+static void folded()
+{
+    const float* x[3];
+    float *out[3], *hat[3], *minmax[3];
+    uint8_t* codes[3];
+    for (int i = 0; i < 3; ++i) {
+        x[i] = far_apart<const float>(1 + i);
+        out[i] = far_apart<float>(11 + i);
+        hat[i] = far_apart<float>(21 + i);
+        codes[i] = far_apart<uint8_t>(31 + i);
+        minmax[i] = far_apart<float>(41 + i);
+    }
+    const size_t line = size_t{1} << 18, long_line = size_t{5} << 24;
+    for (const int k : {1, 2, 3})
+        for (const size_t n : {size_t{3}, size_t{4}, line, line + 1, 5 * line, 5 * line + 1, long_line / 3, long_line / 3 + 1, long_line}) {
+            g_launches.clear();
+            const int status = bagua_decentralized_avg(BAGUA_AVG_LP_MINMAX_U8, x, out, hat, codes, minmax, k, n, 16384, nullptr);
+            const bool two = k > 1 && n >= 4 && n <= 5 * line;
+            EXPECT(status == BAGUA_OK && g_launches.size() == (two ? 2u : 1u), "k %d n %zu", k, n);
+            if (two || g_launches.empty()) continue;
+            const bool fold = (k == 1 && n <= line) || k * n >= long_line;
+            EXPECT(g_launches[0].kernel == (fold ? stub(k_ring_avg_lp_any<4, true>) : stub(k_ring_avg_lp_any<4, false>)), "k %d n %zu", k, n);
+        }
+}
+
 int main()
 {
+    folded();
     two_launches();
     one_way();
     return finish();

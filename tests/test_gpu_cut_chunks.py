@@ -136,7 +136,7 @@ def test_rounds_in_low_precision(bg, oracle, cuts, k, peer):
     (32, 8192, 100001, None), (6, 16384, 6 * 80 * 1024 - 1, None), (6, 16384, 6 * 80 * 1024 + 1, None), (6, 6400, 120003, None),
     (2, 4096, (1 << 21) + 1, [1, 0]), (3, 4096, (1 << 21) + 1, [1, 0, 2]), (3, 2048, (1 << 23) + 5, [1, 0, 2]), (3, 16384, 1 << 21, [0, 2, 1]),
     (3, 4096, 300001, [0, 1, 2]), (2, 16384, 5 << 18, None), (2, 16384, (5 << 18) + 1, None), (3, 8192, (3 << 16) + 1, None), (16, 8192, 3 << 18, None),
-    (2, 16384, 1 << 18, [1, 0]), (2, 16384, (1 << 18) + 1, [1, 0]), (7, 12544, 70001, [1, 0, 2, 4, 3, 6, 5]), (3, 16384, 3, [1, 0, 2]), (3, 16384, 1 << 18, None), (3, 16384, (1 << 18) + 1, None), (4, 16384, 21 << 20, None), (4, 12800, (20 << 20) + 1, None)])
+    (2, 16384, 1 << 18, [1, 0]), (2, 16384, (1 << 18) + 1, [1, 0]), (7, 12544, 70001, [1, 0, 2, 4, 3, 6, 5]), (3, 16384, 3, [1, 0, 2]), (3, 16384, 1 << 18, None), (3, 16384, (1 << 18) + 1, None), (1, 16384, 1 << 18, None), (1, 16384, (1 << 18) + 1, None), (1, 12800, 70001, None), (3, 16384, 2, None), (4, 16384, 21 << 20, None), (4, 12800, (20 << 20) + 1, None)])
 def test_rounds_in_low_precision_either_side_of_their_lines(bg, oracle, k, C, n, peer):
     ring_low_precision(bg, oracle, k, n, C, peer)
 
