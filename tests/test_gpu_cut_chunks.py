@@ -301,12 +301,13 @@ def test_server_step_sign_batched(bg, oracle, k):
 
 
 @pytest.mark.parametrize("n,C,keep", [((1 << 23) + 77, 1024, 32), ((1 << 23) + 1, 1536, 1), ((1 << 23) + 255, 768, 768), ((1 << 23) + 3, 256, 100), (1 << 23, 1024, 9)])
-def test_topk_compression_either_side_of_its_joint_stores(bg, oracle, n, C, keep):
+@pytest.mark.parametrize("ef", [True, False])
+def test_topk_compression_either_side_of_its_joint_stores(bg, oracle, n, C, keep, ef):
     x, res = vals(n, n), vals(n, n + 1)
     r, slots = Guarded(res), bg.num_chunks(n, C) * keep
     idx, val = Guarded(np.zeros(slots, np.int16)), Guarded(np.zeros(slots, np.float32))
-    bg.bagua_compress_topk_ef(torch.from_numpy(x).cuda(), r.t, C, keep, idx.t, val.t)
-    iw, vw = oracle.compress_topk(x, res, C, keep)
+    bg.bagua_compress_topk_ef(torch.from_numpy(x).cuda(), r.t if ef else None, C, keep, idx.t, val.t)
+    iw, vw = oracle.compress_topk(x, res if ef else None, C, keep)
     idx.check(iw.view(np.int16), "idx")
     val.check(vw, "val")
     r.check(res, "residual")
