@@ -3,6 +3,7 @@ ordinary one it does what the general path does."""
 import importlib.util
 import inspect
 import os
+import sysconfig
 
 import pytest
 import torch
@@ -66,6 +67,32 @@ def test_what_is_not_ordinary_is_declined_and_refused_as_before(bg):
         bg.bagua_decentralized_avg(bg.AVG_FP, [x, x], [r])
     with pytest.raises(AttributeError):
         bg.bagua_compress_minmax_u8(None, r, 256, c, m)
+
+
+def test_an_extension_for_another_python_or_torch_is_not_loaded(bg):
+    """The extension holds the layouts of torch's and Python's types, so its name has both versions in it."""
+    from paper_2107_01499_amd import build
+    path = build.native_path()
+    assert bg.binding._native.__spec__.origin == path and os.path.exists(path)
+    name = os.path.basename(path)
+    assert torch.__version__ in name and sysconfig.get_config_var("SOABI") in name
+    assert build.native_path(torch_version="0.0.0") != path and not os.path.exists(build.native_path(torch_version="0.0.0"))
+
+
+def test_without_the_extension_the_general_path_makes_the_calls(bg):
+    with pytest.warns(RuntimeWarning, match="host extension is not there"):
+        none = bg.binding._load_native(os.path.join(ROOT, "there-is-none.so"))
+    assert none.bagua_compress_minmax_u8(None, None, 256, None, None, None) is False
+
+
+def test_where_the_extension_cannot_be_built_there_is_none(bg, tmp_path, monkeypatch):
+    from paper_2107_01499_amd import build
+    old = build.native_path(str(tmp_path))
+    open(old, "w").close()
+    monkeypatch.setattr(build, "CXX", str(tmp_path / "no-compiler"))
+    with pytest.warns(RuntimeWarning, match="no-compiler is missing"):
+        assert build.build_native(libdir=str(tmp_path)) is None
+    assert not os.path.exists(old)
 
 
 def _cases():
