@@ -19,7 +19,7 @@ ceiling.  `roofline` is the kernel with the largest share of the timed GPU time;
 kernel of every block.  `cpu_baseline` times the CPU oracle on a bounded sample (>= 1 GiB of fp32 input where the
 configuration is that large) of every block on the host cores; `parity` compares the HIP path with the oracle's
 outputs on those same samples, all primitives, word for word.  Inputs are generated on the GPU before the timed
-region and stay resident in HBM.  Prints ONE JSON line.
+region and stay resident in HBM.  Prints ONE JSON line; the complete result goes to --details or to stderr.
 
 --workload W runs one block only (resnet50, bert_large, bert_base_ring, onebit, single_bucket_x32); --layout chooses
 how a worker's buckets are launched: flat (default: back to back in one allocation, one launch per worker; every bucket
@@ -93,6 +93,7 @@ def parse_args():
     ap.add_argument("--fused-flatten", action="store_true",
                     help="replace flatten + compress_minmax by the fused bagua_flatten_compress_minmax_u8")
     ap.add_argument("--per-bucket-launch", action="store_true", help="same as --layout per_bucket")
+    ap.add_argument("--details", metavar="FILE", help="where to write the complete result (default: one line on stderr)")
     ap.add_argument("--verify-all", action="store_true",
                     help="no timing: compare EVERY element of configs[2], configs[3] (5 rounds) and configs[4] with the oracle")
     return ap.parse_args()
@@ -1257,7 +1258,28 @@ def main():
         par = dict(total.c)
         par["sample"] = "every primitive of every block on its oracle sample (see blocks[*].parity), HIP path against the oracle"
         result["parity"] = par
-    print(json.dumps(result))
+    details = json.dumps(result)
+    if args.details:
+        with open(args.details, "w") as f:
+            f.write(details + "\n")
+    else:
+        print("bench: details " + details, file=sys.stderr, flush=True)
+    print(json.dumps(headline(result)))
+
+
+def headline(result):
+    """The result line: what was measured and how, each primitive's time and share of the HBM peak.  Everything else is in
+    the details, which are too long for what keeps a run's output."""
+    line = {k: result[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                                   "vs_baseline", "dtype", "data")}
+    line["config"] = {"workload": result["config"]["workload"]}
+    line["per_primitive"] = {p: {"ms": v["ms"], "frac_of_peak": v["frac_of_peak"]} for p, v in result["per_primitive"].items()}
+    line["roofline"] = {k: result["roofline"][k] for k in ("bound", "kernel", "config") if k in result["roofline"]}
+    line["copy_kernel_GBps"] = result["copy_kernel_GBps"]
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = {k: result["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+        line["parity"] = {k: v for k, v in result["parity"].items() if k != "sample"}
+    return line
 
 
 if __name__ == "__main__":
