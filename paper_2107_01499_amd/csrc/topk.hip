@@ -334,11 +334,12 @@ __device__ __forceinline__ void topk_encode_chunk(const f4 (&v)[RPW], int len, u
 }
 
 // ------------------------------------------------------------------------------------------ worker side
-// Long launches of chunks up to 1536 elements, where the many small workgroups wait for their stores.  One element of the lane at a time -> joint, us:
+// Long launches of chunks of 512 to 1536 elements, where the many small workgroups wait for their stores.  One element of the lane at a time -> joint, us:
 // C = 1024, keep = 32, 2 M 6.8 -> 7.1, 8 M +-0, 25.7 M 52.8 -> 51.1, 60 M 116.4 -> 113.7, 134 M 259.0 -> 252.1, keep = 128, 134 M 286.3 -> 278.4, keep = 10, 134 M
 // 255.4 -> 251.2; C = 1536, keep = 192, 60 M 118.5 -> 114.3; C = 768, 134 M 250.4 -> 244.1.  Longer chunks +0.2 us in short launches, -0.5 .. +0.4 % in long ones.
+// C = 256, a single wave of one row, loses: keep = 32, 25 M 56.7 -> 58.8, 60 M 130.6 -> 134.3, keep = 2, 10 M 23.4 -> 24.4.
 // Only two rows per wave are built that way: a build with another BAGUA_RPW_TOPK stores one element at a time throughout.
-static bool topk_stores_joint(size_t n, size_t chunk, int rpw) { return rpw == 2 && chunk <= 1536 && n > (static_cast<size_t>(1) << 23); }
+static bool topk_stores_joint(size_t n, size_t chunk, int rpw) { return rpw == 2 && chunk > kRow && chunk <= 1536 && n > (static_cast<size_t>(1) << 23); }
 
 template <int RPW, bool EF, bool JOINT>
 __global__ void __launch_bounds__(wg_threads_max(RPW))

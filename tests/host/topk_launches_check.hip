@@ -23,5 +23,8 @@ int main()
                 EXPECT(l.grid.x == num_chunks(n, chunk) && waves <= kMaxWaves && waves * rpw >= rows && (waves - 1) * rpw < rows,
                        "chunk %zu n %zu: %zu waves of %zu rows", chunk, n, waves, rpw);
             }
+    const size_t line = size_t{1} << 23;
+    for (const size_t chunk : {512, 1024, 1536}) EXPECT(topk_stores_joint(line + 1, chunk, 2) && !topk_stores_joint(line, chunk, 2) && !topk_stores_joint(line + 1, chunk, 4), "chunk %zu", chunk);
+    for (const size_t chunk : {256, 1792, 4096}) EXPECT(!topk_stores_joint(8 * line, chunk, 2), "chunk %zu", chunk);
     return finish();
 }
