@@ -49,7 +49,7 @@ __device__ __forceinline__ void compress_minmax_rows(const float* __restrict__ x
 }
 
 // The chunk that is cut short, without tests (see row_at).  With -> without, us per launch: C = 4096, 64 K 3.1 -> 3.0, 1 M 4.8 -> 4.1, 3 M 8.4 -> 8.1;
-// C = 16384, 1 M 7.0 -> 6.0; five buckets, 1 M 4.9 -> 4.6; above 6 M +-0.  (One row per wave gains nothing.)
+// C = 16384, 1 M 7.0 -> 6.0; five buckets, 1 M 4.9 -> 4.6; above 6 M +-0.  (Chunks that are held in one row per wave gain nothing by it.)
 template <int RPW, bool EF>
 __device__ __forceinline__ void compress_minmax_cut(const float* __restrict__ x, float* __restrict__ residual, int len, uint8_t* __restrict__ codes,
                                                     float* __restrict__ minmax_c, float* s_red, int keep)
@@ -328,8 +328,9 @@ inline bool drr_minmax_fold(size_t elements, size_t chunk, int k)
     return chunk > 4096 || k <= 4 || elements < (static_cast<size_t>(1) << 25);
 }
 // Whether the workers' codes are requested ahead: up to 2^22 elements of chunks up to 8192, where the launch is too short to be bound by HBM
-// (14 bytes an element with k = 4), and, of chunks that four rows per wave do not divide, up to 2^26.  Four rows per wave and one worker
-// at a time -> this, us of one launch (from a graph, four sets of buffers in turn):
+// (14 bytes an element with k = 4), and up to 2^26 where four rows per wave leave a wave with two; an odd number of rows fills its waves
+// with one row each only, up to 2^20 elements and 11 rows.  Four rows per wave and one worker at a time -> this, us of one launch (from a
+// graph, four sets of buffers in turn):
 //   k = 4, C = 4096: 64 K 4.2 -> 3.3, 1 M 6.3 -> 4.4, 2 M 7.8 -> 6.2, 4 M 11.2 -> 11.0;   k = 8, C = 2048: 64 K 5.0 -> 3.4, 1 M 9.1 -> 5.4, 2 M
 //   10.9 -> 7.8, 4 M 14.8 -> 14.6;   k = 16, C = 8192: 64 K 7.4 -> 6.3, 1 M 14.2 -> 8.5, 2 M 16.5 -> 10.5, 4 M 20.9 -> 20.7;
 //   outside: k = 16, C = 8192, 8 M 40.0 -> 41.4; k = 8, C = 3072, 6 M 20.9 -> 23.3; k = 8, C = 2048, 16 M 48.8 -> 49.8.  Chunks above 8192 take

@@ -5,7 +5,8 @@
 // contiguity, dtype, size of every tensor) and launches.  It answers True when it has made the call, raises BaguaError when the
 // entry point refused it, and answers False, having done nothing, whenever anything about an argument is out of the ordinary:
 // binding.py's general path then decides, and words the error.  A round of short launches is bound by this path: a call
-// took 5.2 .. 6.4 us of host time (up to 20 us with a ring's forty tensors), of which the launch itself needs 2.5.
+// took 5.2 .. 6.4 us of host time (20 with the forty tensors of a ring of eight, 32 with a ring of sixteen), of which the launch itself
+// needs 2.5.
 #include <Python.h>
 
 #include <stddef.h>
@@ -489,7 +490,16 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t given)
         PyErr_SetString(PyExc_TypeError, "bind(library, error, raw_stream, device)");
         return nullptr;
     }
-#define X(name)                                                                                         {                                                                                                       PyObject* at = PyDict_GetItemString(a[0], #name);                                                   void* p = at ? PyLong_AsVoidPtr(at) : nullptr;                                                      if (!p) {                                                                                               if (!PyErr_Occurred()) PyErr_SetString(PyExc_KeyError, #name);                                      return nullptr;                                                                                 }                                                                                                   f_##name = reinterpret_cast<decltype(&name)>(p);                                                }
+#define X(name)                                                            \
+    {                                                                      \
+        PyObject* at = PyDict_GetItemString(a[0], #name);                  \
+        void* p = at ? PyLong_AsVoidPtr(at) : nullptr;                     \
+        if (!p) {                                                          \
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_KeyError, #name); \
+            return nullptr;                                                \
+        }                                                                  \
+        f_##name = reinterpret_cast<decltype(&name)>(p);                   \
+    }
     BAGUA_NATIVE(X)
 #undef X
     PyObject** keep[3] = {&g_error, &g_raw_stream, &g_device};

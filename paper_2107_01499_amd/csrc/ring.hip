@@ -279,7 +279,7 @@ __device__ __forceinline__ void ring_lp_chunk_any(const PtrTable& xin, const Mut
 }
 
 // FOLD: complete chunks without tail tests on their loads.  In the longest launches of chunks of more than 32 rows, and in the shortest of a ring of one
-// (two peers and more take two launches there); without -> with, us: C = 16384, K = 3, 33 M 365 -> 353, 134 M 1476 -> 1412; K = 2, 8 M 67.8 -> 70.3, 33 M
+// (two peers and more take two launches there); with the tests -> without, us: C = 16384, K = 3, 33 M 365 -> 353, 134 M 1476 -> 1412; K = 2, 8 M 67.8 -> 70.3, 33 M
 // 248 -> 250, 134 M 1040 -> 1014; C = 12288, K = 5, 16 M 296 -> 288, 134 M 2321 -> 2249; K = 1, C = 16384, 64 K 6.7 -> 6.2, 256 K 7.1 -> 6.4, 1 M +-0, C = 8448, 64 K
 // 4.7 -> 4.8.
 static bool ring_lp_any_fold(int k, size_t n)

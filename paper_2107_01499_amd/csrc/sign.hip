@@ -68,7 +68,7 @@ __device__ __forceinline__ void sign_compress_rows(const float* __restrict__ x, 
 }
 
 // The chunk that is cut short, without tests (see row_at).  With -> without, us per launch: C = 4096, 64 K 2.9 -> 2.7, 1 M 4.6 -> 3.9, with the
-// momentum 5.2 -> 4.2, 3 M 10.4 -> 9.8; five buckets, C = 2048, 1 M 5.2 -> 4.0; above 6 M +-0.  (One row per wave: -0.1 .. 0 us.)
+// momentum 5.2 -> 4.2, 3 M 10.4 -> 9.8; five buckets, C = 2048, 1 M 5.2 -> 4.0; above 6 M +-0.  (Chunks that are held in one row per wave: -0.1 .. 0 us.)
 template <int RPW, bool EF, int MOM>
 __device__ __forceinline__ void sign_compress_cut(const float* __restrict__ x, float* __restrict__ residual, int len, uint32_t chunk,
                                                   uint32_t* __restrict__ bits, float* __restrict__ scale_c, const float* __restrict__ mom,
